@@ -66,7 +66,7 @@ def draw(rng):
                 "context": _log_int(rng, 64, 2000), "temperature": rng.choice([0.7, 1.0])}
     if kind == "prefill":
         shape = rng.choice(["draft_110m", "draft_paper_115m", "llama7b", "llama7b"])
-        rows = _log_int(rng, 16, 2047)
+        rows = _log_int(rng, 16, 2047 if shape == "llama7b" else 1472)
         layers = 4 if shape == "llama7b" else synth.SHAPES[shape].n_layers
         return {"kind": kind, "shape": shape, "layers": layers, "rows": rows, "image_rows": min(576, rows // 2) if shape == "llama7b" else 0}
     return {"kind": kind, "shape": "llama7b", "layers": 4, "n_seqs": rng.randint(1, 8), "tokens": rng.randint(1, 8), "context": _log_int(rng, 64, 2048)}
