@@ -155,7 +155,9 @@ int32_t spd_kv_export(spd_model *model, int32_t layer, int32_t seq, int32_t pos0
  * e.g. [V_1..V_m ; E[X_1..X_n]] for the target, Section 2.2 Eq. 1) to sequence
  * `seq` starting at its current KV length, appending their K, V.  If
  * last_logits != NULL it receives the float32 logits [vocab] of the last row.
- * Runs the same kernels as a batched verify step, 40 rows per pass. */
+ * Long runs go through kernels of their own, up to 2048 rows per pass over the weights (the workspace
+ * holds the activations of one such pass, or of max_positions rows if that is less); short ones run as
+ * passes of a batched verify step. */
 int32_t spd_prefill(spd_model *model, int32_t seq, const float *embeds, int32_t n_rows,
                     float *last_logits, void *stream);
 

@@ -136,6 +136,44 @@ struct QkvAttnArgs {
 bool qkv_attention_supported(int K, int H, int dh, int rows, int n_seqs, int M);
 hipError_t launch_qkv_attention(const QkvAttnArgs &a, hipStream_t stream);
 
+// ---- prefill: many rows of one sequence per pass (prefill.hip) ----------------------
+constexpr int kPrefillRows = 2048;   // rows per pass at most
+// Runs of at least this many rows take these kernels, shorter ones the batched verify path (64 rows per pass).  Measured
+// (us per call, context 0, batched path / these kernels): four 7B layers, 64 rows 957 / 1402, 96 rows 1577 / 1456; the
+// 12-layer draft, 32 rows 865 / 1017, 48 rows 1234 / 1043; the 4-layer draft, 40 rows 361 / 453, 48 rows 466 / 453.
+// At d = 4096 a pass of up to 64 rows is a weight stream, which the batched kernels are made for.
+inline int prefill_min_rows(int d_model) { return d_model >= 2048 ? 73 : 45; }
+hipError_t launch_prefill_rows(const void *embed_bf16, const int32_t *tokens, const float *embeds, int rows, int d, int vocab,
+                               const float *gain, float *h, void *X, float *ssq, int ssq_ld, hipStream_t stream);
+struct PrefillGemmArgs {
+    const void *W;            // packed weights [N, K]
+    const void *X;            // activations in the prefill layout (ceil(rows / 16) row tiles)
+    int N, K, rows;
+    float *Y;                 // STORE: Y = s * acc; RESIDUAL: Y += acc
+    int ldy;
+    const float *ssq_in;      // [rows][ssq_ld]: ssq_parts partial sums of squares per row (NULL: s = 1)
+    int ssq_ld, ssq_parts;
+    float eps;
+    const float *gain_next;   // RESIDUAL: gain of the following norm; then Xnext and ssq_out are written too
+    void *Xnext;
+    float *ssq_out;           // prefill_ssq_parts(N / 16, rows) parts per row
+    void *Xout;               // SWIGLU: activations of N / 2 columns
+};
+int prefill_ssq_parts(int n_tiles, int rows);
+hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream_t stream);
+struct PrefillAttnArgs {
+    const float *qkv;         // [rows, 3 * H * dh] before RoPE
+    const float *rope;
+    void *k_cache, *v_cache;  // this layer and sequence, layouts as in AttnArgs
+    void *xout;               // attention output in the prefill layout, K = H * dh
+    int rows, H, dh, max_positions, v_stride;
+    const int32_t *d_len;     // KV length in device memory, or NULL: `len`
+    int32_t *d_error;
+    int len;
+};
+// RoPE + append of the rows' keys and values, then attention of the rows over everything cached (two kernels)
+hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t stream);
+
 // ---- sampling ---------------------------------------------------------------------
 struct AcceptArgs {
     const float *target, *draft;

@@ -2,6 +2,7 @@
 // one decoder forward (verify step / draft step / prefill) out of the HIP kernels.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -50,7 +51,10 @@ struct Layout {                    // byte offsets inside the three buffers
     size_t kv_layer_stride, kv_k_bytes, kv_v_bytes, kv_total;
     int v_stride;
     // workspace
-    size_t h, qkv, xn, xo, xf, rope, logits, ssq_a, ssq_b, d_lens, d_error, qa_count, qa_abort, part, arrive, zero, ws_total;
+    size_t h, qkv, xn, xo, xf, rope, logits, ssq_a, ssq_b, d_lens, d_error, qa_count, qa_abort, part, arrive, zero;
+    size_t ph, pqkv, pxn, pxo, pxf, pssq_a, pssq_b;      // prefill passes of up to prefill_rows rows
+    int prefill_rows, pssq_ld;
+    size_t ws_total;
 };
 
 int32_t check_shape(const spd_model_config &c) {
@@ -114,6 +118,17 @@ void make_layout(const spd_model_config &c, Layout &L) {
     L.part = take(pb);
     L.arrive = take((size_t)kBatchMaxTileGroups * 4);
     L.zero = take(1024);
+    // prefill: activations of one pass, row tiles of 16 rows, whole workgroup tiles of 128 rows
+    L.prefill_rows = std::min((int)kPrefillRows, c.max_positions);
+    L.pssq_ld = (d / 16 + 3) / 4;
+    const size_t pr = align_up((size_t)L.prefill_rows, 16);
+    L.ph = take(pr * d * 4);
+    L.pqkv = take(pr * 3 * HD * 4);
+    L.pxn = take(pr * KSd * 64 * kTerms);
+    L.pxo = take(pr * KShd * 64 * kTerms);
+    L.pxf = take(pr * KSf * 64 * kTerms);
+    L.pssq_a = take(pr * L.pssq_ld * 4);
+    L.pssq_b = take(pr * L.pssq_ld * 4);
     L.ws_total = off;
 }
 
@@ -528,6 +543,66 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
     return SPD_OK;
 }
 
+// One prefill pass: M rows (at most L.prefill_rows) of sequence `seq` through all layers; last_logits (may be NULL)
+// receives the logits of the last one.
+int32_t prefill_pass(spd_model *m, int32_t seq, const float *embeds, const int32_t *tokens, int M, float *last_logits, hipStream_t st) {
+    const spd_model_config &c = m->cfg;
+    const Layout &L = m->L;
+    const int d = c.d_model, HD = c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
+    float *h = (float *)(m->ws + L.ph), *qkv = (float *)(m->ws + L.pqkv);
+    float *ssq_a = (float *)(m->ws + L.pssq_a), *ssq_b = (float *)(m->ws + L.pssq_b);
+    void *xn = m->ws + L.pxn, *xo = m->ws + L.pxo, *xf = m->ws + L.pxf;
+    const int parts = prefill_ssq_parts(d / 16, M);
+    auto gain_of = [&](size_t off) { return (const float *)(m->packed + off); };
+    PROF_TRY(PK_EMBED, launch_prefill_rows(m->packed + L.embed, tokens, embeds, M, d, V, gain_of(L.attn_norm[0]), h, xn, ssq_b, L.pssq_ld, st));
+    PrefillAttnArgs at{};
+    at.qkv = qkv; at.rope = (const float *)(m->ws + L.rope); at.xout = xo;
+    at.rows = M; at.H = c.n_heads; at.dh = c.head_dim; at.max_positions = c.max_positions; at.v_stride = L.v_stride;
+    at.len = m->lens[seq];
+    if (m->dev_lens) {
+        at.d_len = (const int32_t *)(m->ws + L.d_lens) + seq;
+        at.d_error = (int32_t *)(m->ws + L.d_error);
+    }
+    for (int l = 0; l < c.n_layers; ++l) {
+        char *kv_l = m->kv + (size_t)l * L.kv_layer_stride;
+        at.k_cache = kv_l + (size_t)seq * c.n_heads * c.max_positions * c.head_dim * 2;
+        at.v_cache = kv_l + align_up(L.kv_k_bytes, 256) + (size_t)seq * c.n_heads * c.head_dim * L.v_stride * 2;
+        PrefillGemmArgs g{};
+        g.rows = M; g.ssq_ld = L.pssq_ld; g.eps = c.rms_eps;
+        g.W = m->packed + L.wqkv[l]; g.X = xn; g.N = 3 * HD; g.K = d; g.Y = qkv; g.ldy = 3 * HD;
+        g.ssq_in = ssq_b; g.ssq_parts = l == 0 ? 1 : parts;
+        PROF_TRY(PK_QKV, launch_prefill_gemm(g, EPI_STORE, st));
+        PROF_TRY(PK_ATTENTION, launch_prefill_attention(at, st));
+        g = PrefillGemmArgs{};
+        g.rows = M; g.ssq_ld = L.pssq_ld;
+        g.W = m->packed + L.wo[l]; g.X = xo; g.N = d; g.K = HD; g.Y = h; g.ldy = d;
+        g.gain_next = gain_of(L.mlp_norm[l]); g.Xnext = xn; g.ssq_out = ssq_a;
+        PROF_TRY(PK_O, launch_prefill_gemm(g, EPI_RESIDUAL, st));
+        g = PrefillGemmArgs{};
+        g.rows = M; g.ssq_ld = L.pssq_ld; g.eps = c.rms_eps;
+        g.W = m->packed + L.wgu[l]; g.X = xn; g.N = 2 * F; g.K = d; g.Xout = xf;
+        g.ssq_in = ssq_a; g.ssq_parts = parts;
+        PROF_TRY(PK_GATE_UP, launch_prefill_gemm(g, EPI_SWIGLU, st));
+        g = PrefillGemmArgs{};
+        g.rows = M; g.ssq_ld = L.pssq_ld;
+        g.W = m->packed + L.wdown[l]; g.X = xf; g.N = d; g.K = F; g.Y = h; g.ldy = d;
+        if (l + 1 < c.n_layers) { g.gain_next = gain_of(L.attn_norm[l + 1]); g.Xnext = xn; g.ssq_out = ssq_b; }
+        PROF_TRY(PK_DOWN, launch_prefill_gemm(g, EPI_RESIDUAL, st));
+    }
+    if (last_logits) {
+        // the last row alone goes through the LM head: its final-norm operand in the one-row-group layout
+        float *h1 = (float *)(m->ws + L.h), *ssq1 = (float *)(m->ws + L.ssq_b);
+        HIP_TRY(launch_input_rows(nullptr, nullptr, 1, 1, h + (size_t)(M - 1) * d, 1, d, V, gain_of(L.final_norm), h1, m->ws + L.xn, ssq1, st));
+        GemmArgs g{};
+        g.W = m->packed + L.lm_head; g.X = m->ws + L.xn; g.N = V; g.K = d; g.rows = 1; g.Y = last_logits; g.ldy = V;
+        g.ssq_in = ssq1; g.ssq_in_parts = 1; g.eps = c.rms_eps;
+        PROF_KERNEL(PK_LM_HEAD, launch_gemm(g, EPI_STORE, m->t_lm, st));
+    }
+    if (m->dev_lens) HIP_TRY(launch_lens_add((int32_t *)(m->ws + L.d_lens) + seq, 1, M, st));
+    m->lens[seq] = std::min(m->lens[seq] + M, c.max_positions);
+    return SPD_OK;
+}
+
 int32_t prefill_common(spd_model *m, int32_t seq, const float *embeds, const int32_t *tokens, int32_t n_rows,
                        float *last_logits, hipStream_t st) {
     if (!m || (!embeds && !tokens)) return fail(SPD_ERR_INVALID_ARG, "NULL argument to spd_prefill");
@@ -536,7 +611,20 @@ int32_t prefill_common(spd_model *m, int32_t seq, const float *embeds, const int
     if (m->lens[seq] + n_rows > m->cfg.max_positions)
         return fail(SPD_ERR_CAPACITY, "KV cache overflow in prefill: %d + %d > %d", m->lens[seq], n_rows, m->cfg.max_positions);
     float *scratch = (float *)(m->ws + m->L.logits);
-    // rows per pass over the weights: 64 through the batched projection kernel (measured 0.108 ms per row at the 7B
+    // passes through the prefill kernels, unless a kernel family was asked for (batch_kernel = 1 or 2)
+    if (!m->t_qkv.no_batch && !m->t_qkv.force_batch) {
+        const int min_rows = prefill_min_rows(m->cfg.d_model);
+        while (n_rows >= min_rows) {
+            const int M = std::min(n_rows, m->L.prefill_rows);
+            const int32_t rc = prefill_pass(m, seq, embeds, tokens, M, M == n_rows ? last_logits : nullptr, st);
+            if (rc) return rc;
+            n_rows -= M;
+            if (embeds) embeds += (size_t)M * m->cfg.d_model;
+            else tokens += M;
+        }
+        if (n_rows == 0) return SPD_OK;
+    }
+    // what is left -- rows per pass over the weights: 64 through the batched projection kernel (measured 0.108 ms per row at the 7B
     // shape against 0.128 for passes of 40), 40 (8 row groups) through the K-splitting kernel otherwise
     const bool batched = m->L.part != 0 && !m->t_qkv.no_batch;
     const int pass_rows = batched ? SPD_MAX_ROWS : 8 * kGroupRows;

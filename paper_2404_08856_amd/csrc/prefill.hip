@@ -1,0 +1,561 @@
+// Prefill: long runs of new rows of ONE sequence (the prompt) through the decoder, up to kPrefillRows rows per
+// pass over the weights.  With hundreds of rows the projections are bound by the matrix cores, not by the
+// weight stream, so everything here is organised around them:
+//
+//  * Operand layouts.  Weights: the packed 1 KiB blocks of common.h, unchanged (A operand).  Activations X[R, K]:
+//    three bf16 terms per value as everywhere, but each term is a matrix-core operand of its own -- 16 rows fill
+//    the 16 columns of the B operand -- and the three products go into the same accumulator: no column of a tile
+//    is unused and no sum over term columns is needed.  Block (row tile rt of 16 rows, K-step s, term t) is the
+//    1 KiB at index (rt * KS + s) * 3 + t, lane l = r + 16 g holding X[16 rt + r][32 s + 8 g .. + 7].
+//  * prefill_gemm_kernel: tiled GEMM, both operands through LDS.  Bound by the matrix cores: the 7B QKV projection of
+//    2047 rows runs at 1.31 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.28).
+//  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
+//    the pass's own rows).
+// Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
+// four 7B layers, 2047 rows 9.06 ms (was 41.1), 640 rows 3.24 (10.2); 12-layer draft, 1472 rows 2.17 ms (47.1).
+#include "gemm_core.h"
+#include "launch.h"
+
+namespace spd {
+
+// element offset (bf16 units) of X[row][k] term t in the layout above
+__device__ __forceinline__ size_t ppack_index(int row, int k, int KS, int t) {
+    return (((size_t)(row >> 4) * KS + (k >> 5)) * kTerms + t) * 512 + packed_elem_index(row & 15, k & 31);
+}
+
+// four consecutive values (k % 4 == 0) of one row into the packed layout, 8 bytes per term
+__device__ __forceinline__ void ppack_store4(uint16_t *X, int row, int k, int KS, const float (&y)[4]) {
+    union { uint2 v; uint16_t h[4]; } term[kTerms];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint16_t t3[kTerms];
+        split3(y[e], t3);
+#pragma unroll
+        for (int t = 0; t < kTerms; ++t) term[t].h[e] = t3[t];
+    }
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t) *reinterpret_cast<uint2 *>(X + ppack_index(row, k, KS, t)) = term[t].v;
+}
+
+// 1 KiB from memory (16 bytes per lane) to LDS (lane-linear from `dst`, wave-uniform), without registers; counts on
+// vmcnt.  As inline assembly because the compiler makes every LDS read wait for ALL outstanding LDS-direct loads it
+// knows of (vmcnt(0)), which would undo the pipelining: the waits are written out in the loops below.  M0 carries the
+// LDS address; nothing else in these kernels uses it.
+__device__ __forceinline__ unsigned lds_addr(const void *p) { return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void *)p; }
+__device__ __forceinline__ void lds_dma16(const void *base_uniform, unsigned lane_offset, unsigned dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_offset), "s"(base_uniform) : "memory");
+}
+__device__ __forceinline__ void lds_dma16(const void *src, unsigned dst) {     // any address per lane
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");
+}
+
+// ---------------------------------------------------------------------------------
+// input rows: h, packed (h * gain) and the row's sum of squares (one part)
+// ---------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void prefill_rows_kernel(const uint16_t *__restrict__ E, const int32_t *__restrict__ tokens,
+                                                           const float *__restrict__ embeds, int d, int vocab,
+                                                           const float *__restrict__ gain, float *__restrict__ h,
+                                                           uint16_t *__restrict__ X, float *__restrict__ ssq, int ssq_ld) {
+    const int row = blockIdx.x, KS = d / 32;
+    const uint16_t *src_tok = nullptr;
+    if (tokens) src_tok = E + (size_t)min(max(tokens[row], 0), vocab - 1) * d;      // never read outside the table
+    const float *src_row = embeds ? embeds + (size_t)row * d : nullptr;
+    float ss = 0.f;
+#pragma unroll 4
+    for (int k = threadIdx.x * 4; k < d; k += 256 * 4) {
+        float4 v;
+        if (src_tok) {
+            const uint2 p = *reinterpret_cast<const uint2 *>(src_tok + k);
+            v = float4{bf16_lo(p.x), bf16_hi(p.x), bf16_lo(p.y), bf16_hi(p.y)};
+        } else {
+            v = *reinterpret_cast<const float4 *>(src_row + k);
+        }
+        *reinterpret_cast<float4 *>(h + (size_t)row * d + k) = v;
+        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        const float4 g = *reinterpret_cast<const float4 *>(gain + k);
+        const float y[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
+        ppack_store4(X, row, k, KS, y);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    __shared__ float part[4];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    if (threadIdx.x == 0) ssq[(size_t)row * ssq_ld] = (part[0] + part[1]) + (part[2] + part[3]);
+}
+
+hipError_t launch_prefill_rows(const void *embed_bf16, const int32_t *tokens, const float *embeds, int rows, int d, int vocab,
+                               const float *gain, float *h, void *X, float *ssq, int ssq_ld, hipStream_t stream) {
+    if ((!tokens) == (!embeds) || rows < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(prefill_rows_kernel, dim3(rows), dim3(256), 0, stream, (const uint16_t *)embed_bf16, tokens, embeds, d, vocab,
+                       gain, h, (uint16_t *)X, ssq, ssq_ld);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------
+// GEMM
+// ---------------------------------------------------------------------------------
+struct PrefillGemmKernelArgs {
+    const uint4 *W;           // packed weights, n_tiles x KS blocks
+    const uint4 *X;           // packed activations, n_rt x KS x 3 blocks
+    int KS, n_tiles, n_rt, rows;
+    int n_blk, r_blk;         // workgroups along the features / the rows
+    float *Y;
+    int ldy;
+    const float *ssq_in;      // [rows][ssq_ld], ssq_parts valid: partial sums of squares, or NULL
+    int ssq_ld, ssq_parts;
+    float inv_d, eps;
+    const float *gain_next;   // RESIDUAL: gain of the following norm, or NULL: no Xnext, no ssq_out
+    uint16_t *Xnext;
+    float *ssq_out;           // RESIDUAL: [rows][ssq_ld], one part per NW tiles
+    uint16_t *Xout;           // SWIGLU
+    int KS_out;
+};
+
+constexpr int kPgBuf = 3;     // LDS stages: one being multiplied, two on their way
+constexpr int kPgChunk = 8;   // K-steps summed before they are added to the running sum
+
+// WN x WR waves; a wave owns NW weight tiles (16 features each) and NX row tiles (16 rows each).  One K-step of
+// both operands (WN * NW + 3 * WR * NX blocks of 1 KiB) is one LDS stage, brought in by LDS-direct loads two stages
+// ahead; all blocks are in operand order already, so the fragment reads are lane-linear and conflict-free.
+// Accumulation: the three terms of a K-step go smallest first into a chunk accumulator that is added to the
+// running sum every kPgChunk K-steps.  The terms below the first are 2^-8 and 2^-16 of it, so adding them into
+// a short partial sum instead of the running one keeps the rounding at the level of separate accumulators per
+// term without their registers.
+template <int WN, int WR, int NW, int NX, int EPI>
+__global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGemmKernelArgs a) {
+    constexpr int WAVES = WN * WR, TN = WN * NW, TR = WR * NX, BLK = TN + kTerms * TR, PB = BLK / WAVES;
+    static_assert(BLK % WAVES == 0, "equal loads per wave: the waits count them");
+    static_assert(NW % 2 == 0, "the SwiGLU epilogue takes tiles in pairs");
+    __shared__ uint4 S[kPgBuf][BLK][64];
+    __shared__ float inv_s[TR * 16];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int KS = a.KS;
+
+    // Workgroup -> tile.  Workgroups go round robin over the 8 XCDs; each XCD takes a contiguous run of an order that
+    // walks 8 row blocks for one feature block before the next, so that the ~32 workgroups an XCD runs together
+    // share 8 row blocks and 4 feature blocks in its L2.
+    int nb, rb;
+    {
+        const int total = a.n_blk * a.r_blk, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+        const int base = total >> 3, extra = total & 7;
+        const int lin = xcd * base + min(xcd, extra) + slot;
+        const int band = 8 * a.n_blk, b0 = lin / band, in = lin - b0 * band;
+        const int rows_in = min(8, a.r_blk - 8 * b0);
+        nb = in / rows_in;
+        rb = 8 * b0 + in - nb * rows_in;
+    }
+    const int t0 = nb * TN, rt0 = rb * TR;
+
+    const uint4 *src[PB];                                 // wave-uniform: block w + i * WAVES of stage 0
+    int step[PB];
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+        const int b = w + i * WAVES;
+        if (b < TN) {
+            src[i] = a.W + (size_t)min(t0 + b, a.n_tiles - 1) * KS * 64;      // beyond the matrix: a valid tile, result dropped
+            step[i] = 64;
+        } else {
+            const int x = b - TN;
+            src[i] = a.X + ((size_t)min(rt0 + x / kTerms, a.n_rt - 1) * KS * kTerms + x % kTerms) * 64;
+            step[i] = 64 * kTerms;
+        }
+    }
+    const unsigned lds0 = lds_addr(&S[0][0][0]);
+    auto issue = [&](int s, int buf) __attribute__((always_inline)) {
+        const int ss = s < KS ? s : KS - 1;               // past the end: a harmless re-read
+#pragma unroll
+        for (int i = 0; i < PB; ++i) lds_dma16(src[i] + (size_t)ss * step[i], 16u * lane, lds0 + (unsigned)((buf * BLK + w + i * WAVES) * 1024));
+    };
+    issue(0, 0);
+    issue(1, 1);
+
+    const int wn = w % WN, wr = w / WN;
+    f32x4_t part[NW][NX], sum[NW][NX];
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+#pragma unroll
+        for (int j = 0; j < NX; ++j) { part[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+
+    int buf = 0, nbuf = 2;
+    for (int s = 0; s < KS; ++s) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PB) : "memory");     // this wave's share of stage s has landed
+        __builtin_amdgcn_s_barrier();                                  // ... and everyone's; stage s - 1 is no longer read
+        asm volatile("" ::: "memory");
+        issue(s + 2, nbuf);
+        uint4 wf[NW];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) wf[i] = S[buf][wn * NW + i][lane];
+#pragma unroll
+        for (int t = kTerms - 1; t >= 0; --t)
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                const uint4 xf = S[buf][TN + (wr * NX + j) * kTerms + t][lane];
+#pragma unroll
+                for (int i = 0; i < NW; ++i) part[i][j] = mfma_bf16(wf[i], xf, part[i][j]);
+            }
+        if (s % kPgChunk == kPgChunk - 1) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int j = 0; j < NX; ++j) { sum[i][j] += part[i][j]; part[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+        }
+        buf = buf + 1 == kPgBuf ? 0 : buf + 1;
+        nbuf = nbuf + 1 == kPgBuf ? 0 : nbuf + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // no load to LDS may outlive the workgroup
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+#pragma unroll
+        for (int j = 0; j < NX; ++j) sum[i][j] += part[i][j];
+
+    // 1 / rms of the workgroup's rows, 4 threads per row, fixed order
+    if (a.ssq_in) {
+        for (int i = threadIdx.x; i < TR * 64; i += WAVES * 64) {
+            const int row = min(rt0 * 16 + i / 4, a.rows - 1), q = i & 3;
+            float ss = 0.f;
+            for (int p = q; p < a.ssq_parts; p += 4) ss += a.ssq_in[(size_t)row * a.ssq_ld + p];
+            ss += __shfl_xor(ss, 1);
+            ss += __shfl_xor(ss, 2);
+            if (q == 0) inv_s[i / 4] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
+        }
+        __syncthreads();
+    }
+
+    // D[feature 4 g + v][row r] of tile (i, j): a lane holds 4 consecutive features of one row
+    const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+        const int lrow = (wr * NX + j) * 16 + r, row = rt0 * 16 + lrow;
+        const bool row_ok = row < a.rows;
+        const float inv = a.ssq_in ? inv_s[lrow] : 1.0f;
+        if (EPI == EPI_SWIGLU) {
+            // rows 0..7 of a tile are gate features (g = 0, 1), rows 8..15 the matching up features (g = 2, 3): of a pair
+            // of tiles the lower half-wave finishes the first, the upper half the second
+#pragma unroll
+            for (int i = 0; i < NW; i += 2) {
+                const int t = t0 + wn * NW + i + (g >> 1);
+                float y[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float p = sum[i][j][v] * inv, q = sum[i + 1][j][v] * inv;
+                    const float got = __shfl_xor(g < 2 ? q : p, 32);
+                    const float gate = g < 2 ? p : got, up = g < 2 ? got : q;
+                    y[v] = gate / (1.0f + expf(-gate)) * up;
+                }
+                if (row_ok && t < a.n_tiles) ppack_store4(a.Xout, row, t * 8 + 4 * (g & 1), a.KS_out, y);
+            }
+        } else {
+            float sq = 0.f;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                const int t = t0 + wn * NW + i, col = t * 16 + 4 * g;
+                if (!(row_ok && t < a.n_tiles)) continue;
+                float4 *dst = reinterpret_cast<float4 *>(a.Y + (size_t)row * a.ldy + col);
+                if (EPI == EPI_STORE) {
+                    *dst = float4{sum[i][j][0] * inv, sum[i][j][1] * inv, sum[i][j][2] * inv, sum[i][j][3] * inv};
+                } else {
+                    float4 h = *dst;
+                    h.x += sum[i][j][0]; h.y += sum[i][j][1]; h.z += sum[i][j][2]; h.w += sum[i][j][3];
+                    *dst = h;
+                    if (a.gain_next) {
+                        const float4 gn = *reinterpret_cast<const float4 *>(a.gain_next + col);
+                        const float y[4] = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
+                        ppack_store4(a.Xnext, row, col, a.n_tiles / 2, y);
+                        sq += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
+                    }
+                }
+            }
+            if (EPI == EPI_RESIDUAL && a.gain_next) {
+                sq += __shfl_xor(sq, 16);
+                sq += __shfl_xor(sq, 32);
+                const int p = nb * WN + wn;
+                if (g == 0 && row_ok && p * NW < a.n_tiles) a.ssq_out[(size_t)row * a.ssq_ld + p] = sq;
+            }
+        }
+    }
+}
+
+template <int WN, int WR, int NW, int NX>
+static hipError_t launch_pg(PrefillGemmKernelArgs &k, int epilogue, hipStream_t stream) {
+    k.n_blk = (k.n_tiles + WN * NW - 1) / (WN * NW);
+    k.r_blk = (k.n_rt + WR * NX - 1) / (WR * NX);
+    const dim3 grid(k.n_blk * k.r_blk), block(WN * WR * 64);
+    switch (epilogue) {
+        case EPI_STORE: hipLaunchKernelGGL((prefill_gemm_kernel<WN, WR, NW, NX, EPI_STORE>), grid, block, 0, stream, k); break;
+        case EPI_RESIDUAL: hipLaunchKernelGGL((prefill_gemm_kernel<WN, WR, NW, NX, EPI_RESIDUAL>), grid, block, 0, stream, k); break;
+        case EPI_SWIGLU: hipLaunchKernelGGL((prefill_gemm_kernel<WN, WR, NW, NX, EPI_SWIGLU>), grid, block, 0, stream, k); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// Workgroup shape of a projection: large = 256 features x 128 rows, one 8-wave workgroup per CU; small = 128 x 64, two
+// 4-wave workgroups per CU (a quarter of the work each, so a large workgroup stands for four small ones).  The large
+// shape moves less through LDS per product; the small one wastes less of the last round and of ragged edges.  Large
+// where its rounds cost no more than the small one's (7B, 2047 rows, gate|up: 6 large rounds against 11 small ones:
+// 921 us small, 946 large by the rate of whole rounds; 640 rows, O: 80 large workgroups leave two thirds of the CUs idle).
+static bool prefill_large(int n_tiles, int rows) {
+    const int large = ((n_tiles + 15) / 16) * ((rows + 127) / 128), small = ((n_tiles + 7) / 8) * ((rows + 63) / 64);
+    const int rounds_large = (large + 255) / 256, rounds_small = (small + 511) / 512;
+    return rounds_large * 2 <= rounds_small;
+}
+int prefill_ssq_parts(int n_tiles, int rows) { return prefill_large(n_tiles, rows) ? (n_tiles + 7) / 8 : (n_tiles + 3) / 4; }
+
+hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream_t stream) {
+    if (a.N % 16 != 0 || a.rows < 1 || a.rows > kPrefillRows) return hipErrorInvalidValue;
+    if (epilogue == EPI_RESIDUAL && a.gain_next && a.N % 32 != 0) return hipErrorInvalidValue;
+    PrefillGemmKernelArgs k;
+    k.W = (const uint4 *)a.W; k.X = (const uint4 *)a.X;
+    k.KS = (a.K + 31) / 32; k.n_tiles = a.N / 16; k.n_rt = (a.rows + 15) / 16; k.rows = a.rows;
+    k.Y = a.Y; k.ldy = a.ldy;
+    k.ssq_in = a.ssq_in; k.ssq_ld = a.ssq_ld; k.ssq_parts = a.ssq_parts;
+    k.inv_d = 1.0f / (float)a.K; k.eps = a.eps;
+    k.gain_next = a.gain_next; k.Xnext = (uint16_t *)a.Xnext; k.ssq_out = a.ssq_out;
+    k.Xout = (uint16_t *)a.Xout; k.KS_out = (a.N / 2 + 31) / 32;
+    if (prefill_large(k.n_tiles, a.rows)) return launch_pg<2, 4, 8, 2>(k, epilogue, stream);
+    return launch_pg<2, 2, 4, 2>(k, epilogue, stream);
+}
+
+// ---------------------------------------------------------------------------------
+// RoPE on the new keys, append of K and V
+// ---------------------------------------------------------------------------------
+// KV length before the call, clamped so that `rows` more positions fit (only device-resident lengths can need it)
+__device__ __forceinline__ int first_position(const PrefillAttnArgs &a, bool report) {
+    int P0 = a.d_len ? *a.d_len : a.len;
+    if (P0 < 0 || P0 + a.rows > a.max_positions) {
+        if (report && a.d_error) *a.d_error = 1;
+        P0 = max(0, min(P0, a.max_positions - a.rows));
+    }
+    return P0;
+}
+
+// one workgroup per (aligned unit of 32 positions, head)
+template <int DH>
+__global__ __launch_bounds__(256) void prefill_append_kernel(PrefillAttnArgs a) {
+    constexpr int HALF = DH / 2;
+    const int P0 = first_position(a, threadIdx.x == 0);
+    const int hh = blockIdx.x, unit = P0 / 32 + blockIdx.y;
+    const size_t HD = (size_t)a.H * DH;
+    uint16_t *Kc = (uint16_t *)a.k_cache + (size_t)hh * a.max_positions * DH;
+    uint16_t *Vt = (uint16_t *)a.v_cache + (size_t)hh * DH * a.v_stride + (size_t)unit * DH * 32;
+    __shared__ uint16_t vs[DH][40];               // V transposed: [dim][position in the unit], rows of 80 bytes
+    if (32 * unit >= P0 + a.rows) return;
+    for (int idx = threadIdx.x; idx < 32 * (HALF / 4); idx += 256) {
+        const int i = idx / (HALF / 4), j = 4 * (idx % (HALF / 4)), pos = 32 * unit + i, row = pos - P0;
+        if (row < 0 || row >= a.rows) continue;
+        const float *src = a.qkv + (size_t)row * 3 * HD + HD + (size_t)hh * DH + j;
+        const float4 k1 = *reinterpret_cast<const float4 *>(src), k2 = *reinterpret_cast<const float4 *>(src + HALF);
+        const float4 v1 = *reinterpret_cast<const float4 *>(src + HD), v2 = *reinterpret_cast<const float4 *>(src + HD + HALF);
+        const float4 cs0 = *reinterpret_cast<const float4 *>(a.rope + ((size_t)pos * HALF + j) * 2);
+        const float4 cs1 = *reinterpret_cast<const float4 *>(a.rope + ((size_t)pos * HALF + j) * 2 + 4);
+        const float c[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, s[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
+        const float ka[4] = {k1.x, k1.y, k1.z, k1.w}, kb[4] = {k2.x, k2.y, k2.z, k2.w};
+        const float va[4] = {v1.x, v1.y, v1.z, v1.w}, vb[4] = {v2.x, v2.y, v2.z, v2.w};
+        union { uint2 u; uint16_t h[4]; } o1, o2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            o1.h[e] = f32_to_bf16_bits(ka[e] * c[e] - kb[e] * s[e]);
+            o2.h[e] = f32_to_bf16_bits(kb[e] * c[e] + ka[e] * s[e]);
+            vs[j + e][i] = f32_to_bf16_bits(va[e]);
+            vs[j + e + HALF][i] = f32_to_bf16_bits(vb[e]);
+        }
+        *reinterpret_cast<uint2 *>(Kc + (size_t)pos * DH + j) = o1.u;
+        *reinterpret_cast<uint2 *>(Kc + (size_t)pos * DH + j + HALF) = o2.u;
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < DH * 4; idx += 256) {       // 8 positions of one dimension: 16 bytes
+        const int dim = idx >> 2, p8 = 8 * (idx & 3), row = 32 * unit + p8 - P0;
+        uint16_t *dst = Vt + (size_t)dim * 32 + p8;
+        if (row >= 0 && row + 8 <= a.rows) {
+            *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(&vs[dim][p8]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (row + e >= 0 && row + e < a.rows) dst[e] = vs[dim][p8 + e];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------
+// attention
+// ---------------------------------------------------------------------------------
+// One workgroup of 4 waves per (head, 64 queries), 16 queries per wave.  Units of 32 keys (K and V: DH / 16 KiB) pass
+// through LDS, already in operand order, two units ahead; every wave multiplies its queries with them:
+//   S[key, query] = K q^T (A = 16 keys x 32 dims, B = q, three terms smallest first into one accumulator),
+//   online softmax (a lane's column is one query), O[dim, query] += V^T p (B = p in three terms).
+// The rows of the two score tiles of a unit stand for keys 8 (i / 4) + 4 ab + i % 4, so a lane ends up with the
+// probabilities of 8 consecutive keys, which is its slot of the second product's B operand.
+// Heavy query blocks (late positions) are launched first; the head index is fastest, so with a head count that is a
+// multiple of 8 a head's workgroups share an XCD and its L2.
+constexpr int kPaBuf = 3;
+
+// bf16 pairs with an infinite or NaN value replaced by 0
+__device__ __forceinline__ uint32_t finite_pair(uint32_t p) {
+    if ((p & 0x7f80u) == 0x7f80u) p &= 0xffff0000u;
+    if ((p & 0x7f800000u) == 0x7f800000u) p &= 0x0000ffffu;
+    return p;
+}
+
+template <int DH>
+__global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnArgs a) {
+    constexpr int HALF = DH / 2, NC = DH / 32, NDT = DH / 16, BLK = 2 * NC + NDT, PB = BLK / 4;
+    __shared__ uint4 S[kPaBuf][BLK][64];
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int hh = blockIdx.x, qt = gridDim.y - 1 - blockIdx.y;
+    const int P0 = first_position(a, false);
+    const size_t HD = (size_t)a.H * DH;
+    const uint16_t *Kc = (const uint16_t *)a.k_cache + (size_t)hh * a.max_positions * DH;
+    const uint16_t *Vt = (const uint16_t *)a.v_cache + (size_t)hh * DH * a.v_stride;
+    const int k_end = P0 + a.rows - 1;                           // last valid position
+    const int n_units = min(P0 + qt * 64 + 63, k_end) / 32 + 1;  // units any query of this workgroup sees
+
+    // this wave's share of a unit: blocks w, w + 4, ...; 0 .. 2 NC - 1: K (tile ab, chunk c), then V (dim tile)
+    const unsigned lds0 = lds_addr(&S[0][0][0]);
+    auto issue = [&](int u, int buf) __attribute__((always_inline)) {
+        const int uu = min(u, n_units - 1);                      // past the end: a harmless re-read
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+            const int b = w + 4 * i;
+            const uint16_t *src;
+            if (b < 2 * NC) {
+                const int key = min(32 * uu + 8 * (r >> 2) + 4 * (b / NC) + (r & 3), k_end);
+                src = Kc + (size_t)key * DH + 32 * (b % NC) + 8 * g;
+            } else {
+                src = Vt + ((size_t)uu * DH + 16 * (b - 2 * NC) + r) * 32 + 8 * g;
+            }
+            lds_dma16(src, lds0 + (unsigned)((buf * BLK + b) * 1024));
+        }
+    };
+    const int row = qt * 64 + w * 16 + r;                        // this lane's query
+    // q: RoPE, scale, three terms, as B operand blocks (chunk c: dims 32 c + 8 g .. + 7 of query r)
+    uint4 q[NC][kTerms];
+    {
+        const float scale = 1.0f / sqrtf((float)DH);
+        const int rr = min(row, a.rows - 1), pos = P0 + rr;
+        const float *src = a.qkv + (size_t)rr * 3 * HD + (size_t)hh * DH + 8 * g;
+#pragma unroll
+        for (int c = 0; c < NC / 2; ++c) {
+            union { uint4 v; uint16_t h[8]; } t1[kTerms], t2[kTerms];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float x1 = src[32 * c + e], x2 = src[32 * c + HALF + e];
+                const float2 cs = *reinterpret_cast<const float2 *>(a.rope + ((size_t)pos * HALF + 32 * c + 8 * g + e) * 2);
+                uint16_t s1[kTerms], s2[kTerms];
+                split3((x1 * cs.x - x2 * cs.y) * scale, s1);
+                split3((x2 * cs.x + x1 * cs.y) * scale, s2);
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t) { t1[t].h[e] = s1[t]; t2[t].h[e] = s2[t]; }
+            }
+#pragma unroll
+            for (int t = 0; t < kTerms; ++t) { q[c][t] = t1[t].v; q[c + NC / 2][t] = t2[t].v; }
+        }
+    }
+    issue(0, 0);
+    issue(1, 1);
+
+    const int q_pos = P0 + row, w_first = P0 + qt * 64 + w * 16, w_last = min(w_first + 15, k_end);
+    const bool wave_has_rows = w_first <= k_end;
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x4_t acc[NDT];
+#pragma unroll
+    for (int i = 0; i < NDT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    int buf = 0, nbuf = 2;
+    for (int u = 0; u < n_units; ++u) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PB) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(u + 2, nbuf);
+        if (wave_has_rows && 32 * u <= w_last) {                 // wave-uniform
+            const bool diagonal = 32 * u + 31 > w_first;         // some key is hidden from some query of the wave
+            f32x4_t sc[2];
+#pragma unroll
+            for (int ab = 0; ab < 2; ++ab) {
+                sc[ab] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                uint4 kf[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) kf[c] = S[buf][ab * NC + c][lane];
+#pragma unroll
+                for (int t = kTerms - 1; t >= 0; --t)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) sc[ab] = mfma_bf16(kf[c], q[c][t], sc[ab]);
+            }
+            if (diagonal) {
+#pragma unroll
+                for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (32 * u + 8 * g + 4 * ab + v > q_pos) sc[ab][v] = -INFINITY;
+            }
+            float mx = -INFINITY;
+#pragma unroll
+            for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) mx = fmaxf(mx, sc[ab][v]);
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m_run, mx);                // finite from the first unit on: key 0 is visible to all
+            const float rescale = exp_neg(fmaxf(m_run, -3.0e38f) - m_new);
+            float lsum = 0.f;
+            union { uint4 v; uint16_t h[8]; } pb[kTerms];
+#pragma unroll
+            for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float x = sc[ab][v] - m_new;
+                    const float p = x == -INFINITY ? 0.f : (x != x ? x : exp_neg(x));    // hidden: 0; NaN stays NaN
+                    lsum += p;
+                    uint16_t t3[kTerms];
+                    split3(p, t3);
+#pragma unroll
+                    for (int t = 0; t < kTerms; ++t) pb[t].h[4 * ab + v] = t3[t];
+                }
+            l_run = l_run * rescale + lsum;                      // this lane's keys only: added up over the lane groups at the end
+            m_run = m_new;
+#pragma unroll
+            for (int i = 0; i < NDT; ++i) {
+                uint4 vf = S[buf][2 * NC + i][lane];
+                if (diagonal) {                                  // a hidden key's V must not leak through 0 * inf
+                    vf.x = finite_pair(vf.x); vf.y = finite_pair(vf.y); vf.z = finite_pair(vf.z); vf.w = finite_pair(vf.w);
+                }
+                f32x4_t o = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int t = kTerms - 1; t >= 0; --t) o = mfma_bf16(vf, pb[t].v, o);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][v] = acc[i][v] * rescale + o[v];
+            }
+        }
+        buf = buf + 1 == kPaBuf ? 0 : buf + 1;
+        nbuf = nbuf + 1 == kPaBuf ? 0 : nbuf + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+    if (row < a.rows) {
+#pragma unroll
+        for (int i = 0; i < NDT; ++i) {
+            const float y[4] = {acc[i][0] / l_run, acc[i][1] / l_run, acc[i][2] / l_run, acc[i][3] / l_run};
+            ppack_store4((uint16_t *)a.xout, row, hh * DH + 16 * i + 4 * g, (int)(HD / 32), y);
+        }
+    }
+}
+
+hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t stream) {
+    if (a.rows < 1 || a.rows > a.max_positions || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
+    const dim3 g1(a.H, (a.rows + 31) / 32 + 1), g2(a.H, (a.rows + 63) / 64);
+    if (a.dh == 128) {
+        hipLaunchKernelGGL(prefill_append_kernel<128>, g1, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(prefill_attention_kernel<128>, g2, dim3(256), 0, stream, a);
+    } else if (a.dh == 64) {
+        hipLaunchKernelGGL(prefill_append_kernel<64>, g1, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(prefill_attention_kernel<64>, g2, dim3(256), 0, stream, a);
+    } else {
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace spd
