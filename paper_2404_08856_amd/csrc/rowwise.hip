@@ -109,24 +109,48 @@ hipError_t launch_block_commit(const CommitArgs &a, hipStream_t stream) {
 // ---- KV cache read-out (inspection: tests, the benchmark's CPU baseline) -------------------
 // K[pos][head][d] and V[pos][head][d] of one (layer, sequence) as float32, from the cache's own layouts:
 // K bf16 [head][pos][dh], V bf16 [head][v_stride / 32][dh][32].
-__global__ void kv_export_kernel(const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Vt, int H, int dh, int max_positions,
-                                 int pos0, int n, float *__restrict__ k_out, float *__restrict__ v_out) {
-    const size_t total = (size_t)n * H * dh;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int d = (int)(i % dh), h = (int)((i / dh) % H), p = (int)(i / ((size_t)dh * H));
-        const int pos = pos0 + p;
-        k_out[i] = bf16_bits_to_f32(Kc[((size_t)h * max_positions + pos) * dh + d]);
-        v_out[i] = bf16_bits_to_f32(Vt[(((size_t)h * ((max_positions + 31) / 32) + (pos >> 5)) * dh + d) * 32 + (pos & 31)]);
+// One workgroup per (aligned unit of 32 positions, head): K rows 8 values per thread, the unit's V tile transposed
+// through LDS, so that every access is whole lines (element by element through the transposed cache: 47 us for 2047
+// positions of the 7B shape).
+__global__ __launch_bounds__(256) void kv_export_kernel(const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Vt, int H, int dh, int max_positions,
+                                                        int pos0, int n, float *__restrict__ k_out, float *__restrict__ v_out) {
+    __shared__ uint16_t tile[128][34];                      // [dim][position in the unit], 17 words a row: no bank conflicts
+    const int h = blockIdx.x, unit = pos0 / 32 + blockIdx.y, d8 = dh / 8;
+    const size_t ld = (size_t)H * dh;
+    const uint16_t *vt = Vt + ((size_t)h * ((max_positions + 31) / 32) + unit) * dh * 32;
+    for (int i = threadIdx.x; i < dh * 4; i += 256) {       // 8 positions of one dimension
+        const uint4 q = reinterpret_cast<const uint4 *>(vt)[i];
+        uint32_t *dst = reinterpret_cast<uint32_t *>(&tile[i >> 2][8 * (i & 3)]);
+        dst[0] = q.x; dst[1] = q.y; dst[2] = q.z; dst[3] = q.w;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 32 * d8; i += 256) {      // 8 dimensions of one position
+        const int p = i / d8, d = 8 * (i % d8), pos = 32 * unit + p;
+        if (pos < pos0 || pos >= pos0 + n) continue;
+        const size_t o = (size_t)(pos - pos0) * ld + (size_t)h * dh + d;
+        const uint4 k = *reinterpret_cast<const uint4 *>(Kc + ((size_t)h * max_positions + pos) * dh + d);
+        float4 a = {bf16_lo(k.x), bf16_hi(k.x), bf16_lo(k.y), bf16_hi(k.y)}, b = {bf16_lo(k.z), bf16_hi(k.z), bf16_lo(k.w), bf16_hi(k.w)};
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = bf16_bits_to_f32(tile[d + e][p]);
+        if ((((uintptr_t)k_out | (uintptr_t)v_out) & 15) == 0) {
+            *reinterpret_cast<float4 *>(k_out + o) = a;
+            *reinterpret_cast<float4 *>(k_out + o + 4) = b;
+            *reinterpret_cast<float4 *>(v_out + o) = float4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<float4 *>(v_out + o + 4) = float4{v[4], v[5], v[6], v[7]};
+        } else {                                            // outputs aligned to single floats only
+            const float k8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { k_out[o + e] = k8[e]; v_out[o + e] = v[e]; }
+        }
     }
 }
 
 hipError_t launch_kv_export(const void *k_cache, const void *v_cache, int H, int dh, int max_positions, int pos0, int n,
                             float *k_out, float *v_out, hipStream_t stream) {
-    if (n < 1 || pos0 < 0 || pos0 + n > max_positions) return hipErrorInvalidValue;
-    const size_t total = (size_t)n * H * dh;
-    unsigned grid = (unsigned)((total + 255) / 256);
-    if (grid > 4096) grid = 4096;
-    hipLaunchKernelGGL(kv_export_kernel, dim3(grid), dim3(256), 0, stream, (const uint16_t *)k_cache, (const uint16_t *)v_cache, H, dh,
+    if (n < 1 || pos0 < 0 || pos0 + n > max_positions || (dh != 64 && dh != 128)) return hipErrorInvalidValue;
+    const int units = (pos0 + n - 1) / 32 - pos0 / 32 + 1;
+    hipLaunchKernelGGL(kv_export_kernel, dim3(H, units), dim3(256), 0, stream, (const uint16_t *)k_cache, (const uint16_t *)v_cache, H, dh,
                        max_positions, pos0, n, k_out, v_out);
     return hipGetLastError();
 }
