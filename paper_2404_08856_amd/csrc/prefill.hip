@@ -12,7 +12,7 @@
 //  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
 //    the pass's own rows).
 // Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
-// four 7B layers, 2047 rows 9.06 ms (was 41.1), 640 rows 3.24 (10.2); 12-layer draft, 1472 rows 2.17 ms (47.1).
+// four 7B layers, 2047 rows 8.6 ms (was 41.1), 640 rows 3.12 (10.2); 12-layer draft, 1472 rows 1.85 ms (47.1).
 #include "gemm_core.h"
 #include "launch.h"
 
@@ -25,16 +25,11 @@ __device__ __forceinline__ size_t ppack_index(int row, int k, int KS, int t) {
 
 // four consecutive values (k % 4 == 0) of one row into the packed layout, 8 bytes per term
 __device__ __forceinline__ void ppack_store4(uint16_t *X, int row, int k, int KS, const float (&y)[4]) {
-    union { uint2 v; uint16_t h[4]; } term[kTerms];
+    uint32_t lo[kTerms], hi[kTerms];
+    split3_pair(y[0], y[1], lo);
+    split3_pair(y[2], y[3], hi);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        uint16_t t3[kTerms];
-        split3(y[e], t3);
-#pragma unroll
-        for (int t = 0; t < kTerms; ++t) term[t].h[e] = t3[t];
-    }
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t) *reinterpret_cast<uint2 *>(X + ppack_index(row, k, KS, t)) = term[t].v;
+    for (int t = 0; t < kTerms; ++t) *reinterpret_cast<uint2 *>(X + ppack_index(row, k, KS, t)) = uint2{lo[t], hi[t]};
 }
 
 // 1 KiB from memory (16 bytes per lane) to LDS (lane-linear from `dst`, wave-uniform), without registers; counts on
@@ -113,19 +108,18 @@ struct PrefillGemmKernelArgs {
 };
 
 constexpr int kPgBuf = 3;     // LDS stages: one being multiplied, two on their way
-constexpr int kPgChunk = 8;   // K-steps summed before they are added to the running sum
 
 // WN x WR waves; a wave owns NW weight tiles (16 features each) and NX row tiles (16 rows each).  One K-step of
 // both operands (WN * NW + 3 * WR * NX blocks of 1 KiB) is one LDS stage, brought in by LDS-direct loads two stages
 // ahead; all blocks are in operand order already, so the fragment reads are lane-linear and conflict-free.
-// Accumulation: the three terms of a K-step go smallest first into a chunk accumulator that is added to the
-// running sum every kPgChunk K-steps.  The terms below the first are 2^-8 and 2^-16 of it, so adding them into
-// a short partial sum instead of the running one keeps the rounding at the level of separate accumulators per
-// term without their registers.
+// Accumulation: partial sums over 4 or 8 K-steps are added to a running sum, so no long chain rounds at the size of
+// the result.  The second and third terms (2^-8 and 2^-16 of the first) have an accumulator of their own where the
+// registers allow it (NW * NX <= 8); otherwise they go into the short partial sum ahead of the first term.
 template <int WN, int WR, int NW, int NX, int EPI>
 __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGemmKernelArgs a) {
     constexpr int WAVES = WN * WR, TN = WN * NW, TR = WR * NX, BLK = TN + kTerms * TR, PB = BLK / WAVES;
     static_assert(BLK % WAVES == 0, "equal loads per wave: the waits count them");
+    constexpr bool OWN_REST = NW * NX <= 8;
     static_assert(NW % 2 == 0, "the SwiGLU epilogue takes tiles in pairs");
     __shared__ uint4 S[kPgBuf][BLK][64];
     __shared__ float inv_s[TR * 16];
@@ -172,35 +166,55 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
     issue(1, 1);
 
     const int wn = w % WN, wr = w / WN;
-    f32x4_t part[NW][NX], sum[NW][NX];
+    f32x4_t part[NW][NX], sum[NW][NX], rest[OWN_REST ? NW : 1][NX];
 #pragma unroll
     for (int i = 0; i < NW; ++i)
 #pragma unroll
-        for (int j = 0; j < NX; ++j) { part[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
-
-    int buf = 0, nbuf = 2;
-    for (int s = 0; s < KS; ++s) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PB) : "memory");     // this wave's share of stage s has landed
-        __builtin_amdgcn_s_barrier();                                  // ... and everyone's; stage s - 1 is no longer read
-        asm volatile("" ::: "memory");
-        issue(s + 2, nbuf);
-        uint4 wf[NW];
+        for (int j = 0; j < NX; ++j) {
+            part[i][j] = sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (OWN_REST) rest[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    const int chunk = KS <= 64 ? 4 : 8;                   // K-steps per partial sum
+    int left = chunk;
+    uint4 wf[NW], xf[kTerms][NX];
+    auto fetch = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NW; ++i) wf[i] = S[buf][wn * NW + i][lane];
 #pragma unroll
         for (int t = kTerms - 1; t >= 0; --t)
 #pragma unroll
-            for (int j = 0; j < NX; ++j) {
-                const uint4 xf = S[buf][TN + (wr * NX + j) * kTerms + t][lane];
+            for (int j = 0; j < NX; ++j) xf[t][j] = S[buf][TN + (wr * NX + j) * kTerms + t][lane];
+    };
+    auto multiply = [&] __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < NW; ++i) part[i][j] = mfma_bf16(wf[i], xf, part[i][j]);
-            }
-        if (s % kPgChunk == kPgChunk - 1) {
+        for (int t = kTerms - 1; t >= 0; --t)
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+#pragma unroll
+                for (int i = 0; i < NW; ++i) {
+                    if (OWN_REST && t > 0) rest[i][j] = mfma_bf16(wf[i], xf[t][j], rest[i][j]);
+                    else part[i][j] = mfma_bf16(wf[i], xf[t][j], part[i][j]);
+                }
+        if (--left == 0) {
+            left = chunk;
 #pragma unroll
             for (int i = 0; i < NW; ++i)
 #pragma unroll
                 for (int j = 0; j < NX; ++j) { sum[i][j] += part[i][j]; part[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
         }
+    };
+    // stage s has landed for everyone, nobody reads stage s - 1 any more: refill its buffer with stage s + 2
+    int buf = 0, nbuf = kPgBuf - 1;
+    auto arrive = [&](int s) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kPgBuf - 2) * PB) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(s + kPgBuf - 1, nbuf);
+    };
+    for (int s = 0; s < KS; ++s) {
+        arrive(s);
+        fetch(buf);
+        multiply();
         buf = buf + 1 == kPgBuf ? 0 : buf + 1;
         nbuf = nbuf + 1 == kPgBuf ? 0 : nbuf + 1;
     }
@@ -208,7 +222,10 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
 #pragma unroll
     for (int i = 0; i < NW; ++i)
 #pragma unroll
-        for (int j = 0; j < NX; ++j) sum[i][j] += part[i][j];
+        for (int j = 0; j < NX; ++j) {
+            if (OWN_REST) part[i][j] += rest[i][j];
+            sum[i][j] += part[i][j];
+        }
 
     // 1 / rms of the workgroup's rows, 4 threads per row, fixed order
     if (a.ssq_in) {
@@ -381,14 +398,18 @@ __global__ __launch_bounds__(256) void prefill_append_kernel(PrefillAttnArgs a) 
 // ---------------------------------------------------------------------------------
 // attention
 // ---------------------------------------------------------------------------------
-// One workgroup of 4 waves per (head, 64 queries), 16 queries per wave.  Units of 32 keys (K and V: DH / 16 KiB) pass
-// through LDS, already in operand order, two units ahead; every wave multiplies its queries with them:
+// One workgroup of 4 waves per (head, 64 queries), 16 queries per wave.  Units of 32 keys (K and V: DH / 16 KiB each)
+// pass through LDS, already in operand order, two units ahead; every wave multiplies its queries with them:
 //   S[key, query] = K q^T (A = 16 keys x 32 dims, B = q, three terms smallest first into one accumulator),
 //   online softmax (a lane's column is one query), O[dim, query] += V^T p (B = p in three terms).
 // The rows of the two score tiles of a unit stand for keys 8 (i / 4) + 4 ab + i % 4, so a lane ends up with the
 // probabilities of 8 consecutive keys, which is its slot of the second product's B operand.
 // Heavy query blocks (late positions) are launched first; the head index is fastest, so with a head count that is a
 // multiple of 8 a head's workgroups share an XCD and its L2.
+// Bound by the vector instructions of the softmax and the three-term split next to as many matrix-core cycles: no
+// branches per key, packed conversions and register swaps instead of LDS for the maximum took the 7B shape at 2047
+// rows from 133 to 114 us per layer, the 12-layer draft at 1472 rows from 58 to 34.  A second set of 4 waves on every other
+// unit of the same queries (merged at the end) was no faster where workgroups are few (31 us) and slower at 2047 rows (157).
 constexpr int kPaBuf = 3;
 
 // bf16 pairs with an infinite or NaN value replaced by 0
@@ -396,6 +417,17 @@ __device__ __forceinline__ uint32_t finite_pair(uint32_t p) {
     if ((p & 0x7f80u) == 0x7f80u) p &= 0xffff0000u;
     if ((p & 0x7f800000u) == 0x7f800000u) p &= 0x0000ffffu;
     return p;
+}
+
+constexpr float kHidden = -1.0e30f;    // score of a hidden key: finite, so that differences stay finite, and exp gives exactly 0
+
+// exp(x) for x <= 0 like exp_neg, but NaN stays NaN and very negative arguments give exactly 0
+__device__ __forceinline__ float exp_score(float x) {
+    const float c1 = 1.44269502162933349609375f, c2 = 1.925963033500011e-8f;   // log2(e) = c1 + c2
+    const float t = x * c1;
+    const float lo = __builtin_fmaf(x, c1, -t) + x * c2;
+    const float p = __builtin_amdgcn_exp2f(t);
+    return __builtin_fmaf(p, lo * 0.693147180559945f, p);
 }
 
 template <int DH>
@@ -420,7 +452,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
         for (int i = 0; i < PB; ++i) {
             const int b = w + 4 * i;
             const uint16_t *src;
-            if (b < 2 * NC) {
+            if (i < NC / 2) {                                    // b < 2 NC
                 const int key = min(32 * uu + 8 * (r >> 2) + 4 * (b / NC) + (r & 3), k_end);
                 src = Kc + (size_t)key * DH + 32 * (b % NC) + 8 * g;
             } else {
@@ -429,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
             lds_dma16(src, lds0 + (unsigned)((buf * BLK + b) * 1024));
         }
     };
-    const int row = qt * 64 + w * 16 + r;                        // this lane's query
+    const int row = qt * 64 + w * 16 + r;                       // this lane's query
     // q: RoPE, scale, three terms, as B operand blocks (chunk c: dims 32 c + 8 g .. + 7 of query r)
     uint4 q[NC][kTerms];
     {
@@ -438,16 +470,22 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
         const float *src = a.qkv + (size_t)rr * 3 * HD + (size_t)hh * DH + 8 * g;
 #pragma unroll
         for (int c = 0; c < NC / 2; ++c) {
-            union { uint4 v; uint16_t h[8]; } t1[kTerms], t2[kTerms];
+            union { uint4 v; uint32_t h[4]; } t1[kTerms], t2[kTerms];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float x1 = src[32 * c + e], x2 = src[32 * c + HALF + e];
-                const float2 cs = *reinterpret_cast<const float2 *>(a.rope + ((size_t)pos * HALF + 32 * c + 8 * g + e) * 2);
-                uint16_t s1[kTerms], s2[kTerms];
-                split3((x1 * cs.x - x2 * cs.y) * scale, s1);
-                split3((x2 * cs.x + x1 * cs.y) * scale, s2);
+            for (int e = 0; e < 8; e += 2) {
+                float y1[2], y2[2];
 #pragma unroll
-                for (int t = 0; t < kTerms; ++t) { t1[t].h[e] = s1[t]; t2[t].h[e] = s2[t]; }
+                for (int f = 0; f < 2; ++f) {
+                    const float x1 = src[32 * c + e + f], x2 = src[32 * c + HALF + e + f];
+                    const float2 cs = *reinterpret_cast<const float2 *>(a.rope + ((size_t)pos * HALF + 32 * c + 8 * g + e + f) * 2);
+                    y1[f] = (x1 * cs.x - x2 * cs.y) * scale;
+                    y2[f] = (x2 * cs.x + x1 * cs.y) * scale;
+                }
+                uint32_t s1[kTerms], s2[kTerms];
+                split3_pair(y1[0], y1[1], s1);
+                split3_pair(y2[0], y2[1], s2);
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t) { t1[t].h[e / 2] = s1[t]; t2[t].h[e / 2] = s2[t]; }
             }
 #pragma unroll
             for (int t = 0; t < kTerms; ++t) { q[c][t] = t1[t].v; q[c + NC / 2][t] = t2[t].v; }
@@ -458,7 +496,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
 
     const int q_pos = P0 + row, w_first = P0 + qt * 64 + w * 16, w_last = min(w_first + 15, k_end);
     const bool wave_has_rows = w_first <= k_end;
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = kHidden, l_run = 0.f;
     f32x4_t acc[NDT];
 #pragma unroll
     for (int i = 0; i < NDT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -487,45 +525,45 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
 #pragma unroll
                 for (int ab = 0; ab < 2; ++ab)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (32 * u + 8 * g + 4 * ab + v > q_pos) sc[ab][v] = -INFINITY;
+                    for (int v = 0; v < 4; ++v) sc[ab][v] = 32 * u + 8 * g + 4 * ab + v > q_pos ? kHidden : sc[ab][v];
             }
-            float mx = -INFINITY;
-#pragma unroll
-            for (int ab = 0; ab < 2; ++ab)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) mx = fmaxf(mx, sc[ab][v]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m_run, mx);                // finite from the first unit on: key 0 is visible to all
-            const float rescale = exp_neg(fmaxf(m_run, -3.0e38f) - m_new);
-            float lsum = 0.f;
-            union { uint4 v; uint16_t h[8]; } pb[kTerms];
-#pragma unroll
-            for (int ab = 0; ab < 2; ++ab)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float x = sc[ab][v] - m_new;
-                    const float p = x == -INFINITY ? 0.f : (x != x ? x : exp_neg(x));    // hidden: 0; NaN stays NaN
-                    lsum += p;
-                    uint16_t t3[kTerms];
-                    split3(p, t3);
-#pragma unroll
-                    for (int t = 0; t < kTerms; ++t) pb[t].h[4 * ab + v] = t3[t];
-                }
-            l_run = l_run * rescale + lsum;                      // this lane's keys only: added up over the lane groups at the end
+            float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])), fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
+            mx = max_over_rows(mx);
+            const float m_new = fmaxf(m_run, mx);
+            const float rescale = exp_score(m_run - m_new);      // first unit (key 0 is visible to every query): exp(-1e30) = 0
             m_run = m_new;
+            float p[8], lsum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                p[e] = exp_score(sc[e >> 2][e & 3] - m_new);
+                lsum += p[e];
+            }
+            l_run = l_run * rescale + lsum;                      // this lane's keys only: added up over the lane groups at the end
+            union { uint4 v; uint32_t h[4]; } pb[kTerms];
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                uint32_t t3[kTerms];
+                split3_pair(p[e], p[e + 1], t3);
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t) pb[t].h[e / 2] = t3[t];
+            }
+            uint4 vf[NDT];
+#pragma unroll
+            for (int i = 0; i < NDT; ++i) vf[i] = S[buf][2 * NC + i][lane];
+            if (diagonal) {                                      // a hidden key's V must not leak through 0 * inf
+#pragma unroll
+                for (int i = 0; i < NDT; ++i) {
+                    vf[i].x = finite_pair(vf[i].x); vf[i].y = finite_pair(vf[i].y);
+                    vf[i].z = finite_pair(vf[i].z); vf[i].w = finite_pair(vf[i].w);
+                }
+            }
 #pragma unroll
             for (int i = 0; i < NDT; ++i) {
-                uint4 vf = S[buf][2 * NC + i][lane];
-                if (diagonal) {                                  // a hidden key's V must not leak through 0 * inf
-                    vf.x = finite_pair(vf.x); vf.y = finite_pair(vf.y); vf.z = finite_pair(vf.z); vf.w = finite_pair(vf.w);
-                }
                 f32x4_t o = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int t = kTerms - 1; t >= 0; --t) o = mfma_bf16(vf, pb[t].v, o);
+                for (int t = kTerms - 1; t >= 0; --t) o = mfma_bf16(vf[i], pb[t].v, o);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][v] = acc[i][v] * rescale + o[v];
+                for (int v = 0; v < 4; ++v) acc[i][v] = __builtin_fmaf(acc[i][v], rescale, o[v]);
             }
         }
         buf = buf + 1 == kPaBuf ? 0 : buf + 1;
@@ -546,14 +584,13 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
 hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t stream) {
     if (a.rows < 1 || a.rows > a.max_positions || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
     const dim3 g1(a.H, (a.rows + 31) / 32 + 1), g2(a.H, (a.rows + 63) / 64);
+    if (a.dh != 128 && a.dh != 64) return hipErrorInvalidValue;
     if (a.dh == 128) {
         hipLaunchKernelGGL(prefill_append_kernel<128>, g1, dim3(256), 0, stream, a);
         hipLaunchKernelGGL(prefill_attention_kernel<128>, g2, dim3(256), 0, stream, a);
-    } else if (a.dh == 64) {
+    } else {
         hipLaunchKernelGGL(prefill_append_kernel<64>, g1, dim3(256), 0, stream, a);
         hipLaunchKernelGGL(prefill_attention_kernel<64>, g2, dim3(256), 0, stream, a);
-    } else {
-        return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
