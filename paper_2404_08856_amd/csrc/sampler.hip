@@ -154,37 +154,58 @@ __device__ __forceinline__ void load_row(const float *__restrict__ row, int V, f
     }
 }
 
-// softmax statistics from a row held in registers (same definition as row_stats)
-__device__ void row_stats_regs(const float4 (&v)[kRowVec], int V, float inv_temp, RowStats *out_shared) {
+// quad (group of 4 entries) of the row that register slot i of this thread holds.  WAVE_MAJOR: every wave owns a contiguous
+// run of 64 * NV quads, so that the order of the entries is wave, slot, lane (what the inverse-CDF search wants);
+// otherwise slot, thread.  Both are one contiguous KiB per wave and load.
+template <int NV, bool WAVE_MAJOR>
+__device__ __forceinline__ int quad_of(int i) {
+    return WAVE_MAJOR ? (int)(threadIdx.x >> 6) * (64 * NV) + 64 * i + (int)(threadIdx.x & 63) : i * kSampThreads + (int)threadIdx.x;
+}
+
+// softmax statistics from a row held in registers (same definition as row_stats; the argmax only where it is used)
+template <bool WAVE_MAJOR>
+__device__ void row_stats_regs(const float4 (&v)[kRowVec], bool greedy, float inv_temp, RowStats *out_shared) {
     __shared__ float s_mx[kSampThreads / 64];
     __shared__ int s_arg[kSampThreads / 64];
     __shared__ float s_sum[kSampThreads / 64];
+    static_assert(kSampThreads / 64 == 16, "the cross-wave steps below combine 16 partials in 16 lanes");
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     float mx = -INFINITY;
     int arg = 0x7fffffff;
+    if (greedy) {
 #pragma unroll
-    for (int i = 0; i < kRowVec; ++i) {                       // ascending x within the thread
-        const int x0 = 4 * (i * kSampThreads + (int)threadIdx.x);
-        const float e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+        for (int i = 0; i < kRowVec; ++i) {                   // ascending x within the thread
+            const int x0 = 4 * quad_of<kRowVec, WAVE_MAJOR>(i);
+            const float e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (e[j] > mx) { mx = e[j]; arg = x0 + j; }
-    }
+            for (int j = 0; j < 4; ++j)
+                if (e[j] > mx) { mx = e[j]; arg = x0 + j; }
+        }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        float om = __shfl_xor(mx, off);
-        int oa = __shfl_xor(arg, off);
-        if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-    }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) { s_mx[w] = mx; s_arg[w] = arg; }
-    __syncthreads();
-    static_assert(kSampThreads / 64 == 16, "the cross-wave steps below combine 16 partials in 16 lanes");
-    mx = s_mx[lane & 15]; arg = s_arg[lane & 15];             // 16 wave results, combined by every 16-lane group
+        for (int off = 32; off > 0; off >>= 1) {
+            float om = __shfl_xor(mx, off);
+            int oa = __shfl_xor(arg, off);
+            if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+        }
+        if (lane == 0) { s_mx[w] = mx; s_arg[w] = arg; }
+        __syncthreads();
+        mx = s_mx[lane & 15]; arg = s_arg[lane & 15];         // 16 wave results, combined by every 16-lane group
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) {
-        float om = __shfl_xor(mx, off);
-        int oa = __shfl_xor(arg, off);
-        if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+        for (int off = 8; off > 0; off >>= 1) {
+            float om = __shfl_xor(mx, off);
+            int oa = __shfl_xor(arg, off);
+            if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kRowVec; ++i) mx = fmaxf(mx, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        if (lane == 0) s_mx[w] = mx;
+        __syncthreads();
+        mx = s_mx[lane & 15];
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     }
     float sum = 0.f;
 #pragma unroll
@@ -205,94 +226,111 @@ __device__ void row_stats_regs(const float4 (&v)[kRowVec], int V, float inv_temp
     __syncthreads();
 }
 
-// Inverse-CDF draw (same definition as sample_inverse_cdf) from weights given per register
-// slot: wf(i, j, x) = fixed-point weight of entry x = 4 (i * 1024 + t) + j.  The running sum
-// over x is: all of slice i' < i, then the threads before t in slice i, then entries before j.
-template <class WF>
-__device__ int sample_inverse_cdf_regs(WF wf, int V, float u, unsigned long long *tmp, int *result) {
-    // tmp: kRowVec * 17 u64 of shared memory
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    // per slice: the sum of the thread's 4 weights, and its inclusive scan over the wave
-    unsigned long long part[kRowVec], incl[kRowVec];
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
 #pragma unroll
-    for (int i = 0; i < kRowVec; ++i) {
-        const int x0 = 4 * (i * kSampThreads + (int)threadIdx.x);
-        unsigned long long p = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) p += (x0 + j < V) ? wf(i, j, x0 + j) : 0ull;
-        part[i] = p;
-        incl[i] = p;
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned lo = __shfl_xor((unsigned)v, off), hi = __shfl_xor((unsigned)(v >> 32), off);
+        v += ((unsigned long long)hi << 32) | lo;
     }
-#pragma unroll
-    for (int i = 0; i < kRowVec; ++i) {
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            unsigned long long t = shfl_up_u64(incl[i], off);
-            if (lane >= off) incl[i] += t;
-        }
-    }
-    __syncthreads();                                          // tmp may still be in use by a previous call
-    if (lane == 63) {
-#pragma unroll
-        for (int i = 0; i < kRowVec; ++i) tmp[i * 17 + w] = incl[i];
-    }
-    __syncthreads();
-    // exclusive scan of the kRowVec x 16 wave totals (slices in order, waves in order) by wave 0:
-    // two neighbouring entries per lane, integer sums, so the order of combination does not matter
-    static_assert(kRowVec * (kSampThreads / 64) == 128, "one wave, two entries per lane");
-    if (w == 0) {
-        const int n0 = 2 * lane, n1 = 2 * lane + 1;
-        const int a0 = (n0 >> 4) * 17 + (n0 & 15), a1 = (n1 >> 4) * 17 + (n1 & 15);
-        const unsigned long long v0 = tmp[a0], v1 = tmp[a1];
-        unsigned long long inc = v0 + v1;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            unsigned long long t = shfl_up_u64(inc, off);
-            if (lane >= off) inc += t;
-        }
-        const unsigned long long excl = inc - v0 - v1;
-        tmp[a0] = excl;
-        tmp[a1] = excl + v0;
-        if (lane == 63) { tmp[16] = inc; *result = -1; }      // slot 16 of slice 0 is free: the grand total
-    }
-    __syncthreads();
-    const unsigned long long S = tmp[16];
-    if (S != 0) {
-        const unsigned long long thr = threshold_of(u, S);
-#pragma unroll
-        for (int i = 0; i < kRowVec; ++i) {
-            const unsigned long long excl = tmp[i * 17 + w] + incl[i] - part[i];
-            if (excl <= thr && thr < excl + part[i]) {        // exactly one (thread, slice)
-                const int x0 = 4 * (i * kSampThreads + (int)threadIdx.x);
-                unsigned long long run = excl;
-                int found = -1;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (x0 + j < V) run += wf(i, j, x0 + j);
-                    if (found < 0 && run > thr) found = x0 + j;
-                }
-                *result = found;
-            }
-        }
-    }
-    __syncthreads();
-    return *result;
+    return v;
 }
+
+// Inverse-CDF draw (same definition as sample_inverse_cdf) over a row, or one slice of it, whose values r >= 0 sit in
+// registers in wave-major order (entries outside the slice are 0): a wave's total needs one reduction, whatever the
+// number of slots; the slots are only looked at by the one wave the threshold falls into.
+template <int NV>
+struct SliceSampler {
+    unsigned long long part[NV];        // fixed-point sum of each slot's 4 entries
+    unsigned long long before;          // total of the waves before this one (valid after total())
+
+    __device__ __forceinline__ void weigh(const float4 (&r)[NV]) {
+        float top = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) top = fmaxf(top, fmaxf(fmaxf(r[i].x, r[i].y), fmaxf(r[i].z, r[i].w)));
+        if (__any(top >= 1.0f)) {       // weights of 2^32 and more: the general conversion
+#pragma unroll
+            for (int i = 0; i < NV; ++i) part[i] = fixed_weight(r[i].x) + fixed_weight(r[i].y) + fixed_weight(r[i].z) + fixed_weight(r[i].w);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+                part[i] = (unsigned long long)__float2uint_rz(r[i].x * 4294967296.0f) + __float2uint_rz(r[i].y * 4294967296.0f) +
+                          __float2uint_rz(r[i].z * 4294967296.0f) + __float2uint_rz(r[i].w * 4294967296.0f);
+        }
+    }
+    // total of the slice; all threads of the workgroup call it and get it.  tmp: 17 u64 of shared memory
+    __device__ __forceinline__ unsigned long long total(unsigned long long *tmp) {
+        unsigned long long v = 0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v += part[i];
+        v = wave_sum_u64(v);
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        __syncthreads();                // tmp may still be in use by a previous call
+        if (lane == 0) tmp[w] = v;
+        __syncthreads();
+        unsigned long long all = 0;
+        before = 0;
+#pragma unroll
+        for (int i = 0; i < kSampThreads / 64; ++i) {
+            const unsigned long long t = tmp[i];
+            before = i == w ? all : before;
+            all += t;
+        }
+        mine = v;
+        return all;
+    }
+    // the entry (4 * quad + j, quad relative to the slice) whose running sum first exceeds thr < total(); written by
+    // one thread to *result: the caller synchronises
+    __device__ __forceinline__ void find(const float4 (&r)[NV], unsigned long long thr, int first_quad, int *result) const {
+        if (!(before <= thr && thr < before + mine)) return;  // wave-uniform
+        const int lane = threadIdx.x & 63;
+        unsigned long long run = before;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const unsigned long long t = wave_sum_u64(part[i]);
+            if (run <= thr && thr < run + t) {                // exactly one slot
+                unsigned long long incl = part[i];
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const unsigned long long o = shfl_up_u64(incl, off);
+                    if (lane >= off) incl += o;
+                }
+                unsigned long long c = run + incl - part[i];
+                if (c <= thr && thr < run + incl) {           // exactly one lane
+                    const int x0 = 4 * (first_quad + quad_of<NV, true>(i));
+                    const float e[4] = {r[i].x, r[i].y, r[i].z, r[i].w};
+                    int found = -1;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        c += fixed_weight(e[j]);
+                        if (found < 0 && c > thr) found = x0 + j;
+                    }
+                    *result = found;
+                }
+            }
+            run += t;
+        }
+    }
+
+  private:
+    unsigned long long mine;            // this wave's total
+};
 
 __global__ __launch_bounds__(kSampThreads) void accept_stats_kernel(AcceptArgs a) {
     // one workgroup per logits row: target rows first, then draft rows
     const int n_t = a.n_seqs * (a.gamma + 1);
     const int r = blockIdx.x;
     const bool is_t = r < n_t;
-    if (is_t && (a.flags & 1u)) return;
-    if (!is_t && (a.flags & 2u)) return;
+    if (a.flags & (is_t ? 1u : 2u)) {                         // probabilities: no statistics (but the slices' ticket starts at 0)
+        if (threadIdx.x == 0) reinterpret_cast<RowStats *>(a.stats)[r].pad = 0;
+        return;
+    }
     const float *row = is_t ? a.target + (size_t)r * a.vocab : a.draft + (size_t)(r - n_t) * a.vocab;
     const float inv_temp = a.temperature > 0.f ? 1.0f / a.temperature : 1.0f;
     __shared__ RowStats st;
     if (row_fits_registers(row, a.vocab)) {
         float4 v[kRowVec];
         load_row(row, a.vocab, -INFINITY, v);
-        row_stats_regs(v, a.vocab, inv_temp, &st);
+        row_stats_regs<false>(v, !(a.temperature > 0.f), inv_temp, &st);
     } else {
         row_stats(row, a.vocab, inv_temp, &st);
     }
@@ -315,92 +353,213 @@ struct RowProb {
     }
 };
 
+constexpr int kMaxGamma = 63;
+
+// Statistics of a sequence's rows and its accept tests.  Everything that does not depend on anything else is loaded
+// first, then the drafted tokens' entries: two dependent round trips in all, and later readers find the statistics in LDS.
+struct SeqRows {
+    RowStats t[kMaxGamma + 1], d[kMaxGamma];
+    int acc[kMaxGamma + 1];
+};
+struct SeqView {
+    const AcceptArgs &a;
+    SeqRows &rows;
+    int seq, t_mode, d_mode;
+    float inv_temp;
+    __device__ __forceinline__ SeqView(const AcceptArgs &a_, SeqRows &rows_, int seq_) : a(a_), rows(rows_), seq(seq_) {
+        inv_temp = a.temperature > 0.f ? 1.0f / a.temperature : 1.0f;
+        t_mode = (a.flags & 1u) ? 0 : (a.temperature > 0.f ? 1 : 2);
+        d_mode = (a.flags & 2u) ? 0 : (a.temperature > 0.f ? 1 : 2);
+    }
+    __device__ __forceinline__ RowStats *stats_t(int j) const { return reinterpret_cast<RowStats *>(a.stats) + seq * (a.gamma + 1) + j; }
+    __device__ __forceinline__ RowStats *stats_d(int j) const {
+        return reinterpret_cast<RowStats *>(a.stats) + a.n_seqs * (a.gamma + 1) + seq * a.gamma + j;
+    }
+    __device__ __forceinline__ const float *t_ptr(int j) const { return a.target + ((size_t)seq * (a.gamma + 1) + j) * a.vocab; }
+    __device__ __forceinline__ const float *d_ptr(int j) const { return a.draft + ((size_t)seq * a.gamma + j) * a.vocab; }
+    __device__ __forceinline__ RowProb prob(const float *row, const RowStats &st, int mode) const {
+        RowProb p;
+        p.row = row; p.st = st; p.inv_temp = inv_temp; p.mode = mode; p.inv_sum = 1.0f / st.sum;
+        return p;
+    }
+    __device__ __forceinline__ RowProb t_row(int j) const { return prob(t_ptr(j), rows.t[j], t_mode); }
+    __device__ __forceinline__ RowProb d_row(int j) const { return prob(d_ptr(j), rows.d[j], d_mode); }
+    // accept tests: u_j * D_j(d_j) < T_j(d_j), one float32 multiply and one compare; number of leading accepts.
+    // All threads of the workgroup call it.
+    __device__ __forceinline__ int accepted(bool write_prob) const {
+        const int G = a.gamma, j = threadIdx.x;
+        if (j <= G) {
+            RowStats st = {0.f, 1.f, 0, 0}, sd = {0.f, 1.f, 0, 0};
+            if (t_mode != 0) st = *stats_t(j);
+            if (j < G) {
+                int d = a.draft_tokens[(size_t)seq * a.token_stride + j];
+                if (d_mode != 0) sd = *stats_d(j);
+                const float u = a.u[seq * (G + 1) + j];
+                d = min(max(d, 0), a.vocab - 1);                                    // never index outside the row
+                const float Tx = prob(t_ptr(j), st, t_mode)(d), Dx = prob(d_ptr(j), sd, d_mode)(d);
+                rows.acc[j] = (__fmul_rn(u, Dx) < Tx) ? 1 : 0;
+                if (write_prob && a.accept_prob)
+                    a.accept_prob[seq * G + j] = (Dx == 0.f) ? (Tx > 0.f ? 1.0f : 0.0f) : fminf(1.0f, Tx / Dx);
+                rows.d[j] = sd;
+            }
+            rows.t[j] = st;
+        }
+        __syncthreads();
+        int k = 0;
+        while (k < G && rows.acc[k]) ++k;
+        return k;
+    }
+};
+
+// The general draw, out of line: where it is a rare fallback its registers are nobody else's business.
+__device__ __noinline__ int sample_row_slowly(RowProb T, int V, float u, unsigned long long *tmp, int *result) {
+    return sample_inverse_cdf(T, V, u, tmp, result);
+}
+
+// Any vocabulary size and alignment: one workgroup per sequence walks the rows from memory.
 __global__ __launch_bounds__(kSampThreads) void accept_decide_kernel(AcceptArgs a) {
     const int seq = blockIdx.x, G = a.gamma, V = a.vocab;
-    const int n_t = a.n_seqs * (G + 1);
-    const RowStats *stats = reinterpret_cast<const RowStats *>(a.stats);
-    const float inv_temp = a.temperature > 0.f ? 1.0f / a.temperature : 1.0f;
-    const int t_mode = (a.flags & 1u) ? 0 : (a.temperature > 0.f ? 1 : 2);
-    const int d_mode = (a.flags & 2u) ? 0 : (a.temperature > 0.f ? 1 : 2);
-    __shared__ int s_acc[64];
-    __shared__ int s_k;
-    __shared__ unsigned long long tmp[kRowVec * 17];
+    __shared__ SeqRows rows;
+    __shared__ unsigned long long tmp[17];
     __shared__ int result;
-
-    auto t_row = [&](int j) {
-        RowProb p;
-        p.row = a.target + ((size_t)seq * (G + 1) + j) * V;
-        p.st = t_mode == 0 ? RowStats{0.f, 1.f, 0, 0} : stats[seq * (G + 1) + j];
-        p.inv_temp = inv_temp; p.mode = t_mode; p.inv_sum = 1.0f / p.st.sum;
-        return p;
-    };
-    auto d_row = [&](int j) {
-        RowProb p;
-        p.row = a.draft + ((size_t)seq * G + j) * V;
-        p.st = d_mode == 0 ? RowStats{0.f, 1.f, 0, 0} : stats[n_t + seq * G + j];
-        p.inv_temp = inv_temp; p.mode = d_mode; p.inv_sum = 1.0f / p.st.sum;
-        return p;
-    };
-
-    // accept tests: u_j * D_j(d_j) < T_j(d_j), one float32 multiply and one compare
-    if ((int)threadIdx.x < G) {
-        int j = threadIdx.x;
-        int d = min(max(a.draft_tokens[(size_t)seq * a.token_stride + j], 0), V - 1);   // never index outside the row
-        float Tx = t_row(j)(d), Dx = d_row(j)(d);
-        float u = a.u[seq * (G + 1) + j];
-        s_acc[j] = (__fmul_rn(u, Dx) < Tx) ? 1 : 0;
-        if (a.accept_prob) {
-            float ap = (Dx == 0.f) ? (Tx > 0.f ? 1.0f : 0.0f) : fminf(1.0f, Tx / Dx);
-            a.accept_prob[seq * G + j] = ap;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int k = 0;
-        while (k < G && s_acc[k]) ++k;
-        s_k = k;
-    }
-    __syncthreads();
-    const int k = s_k;
-
-    int y;
+    const SeqView q(a, rows, seq);
     const float u_last = a.u[seq * (G + 1) + G];
-    const RowProb T = t_row(k < G ? k : G);
-    if (row_fits_registers(T.row, V) && (k == G || row_fits_registers(d_row(k).row, V))) {
-        // rows once through registers; padding entries give probability 0 in every mode
-        // (the distribution to draw from, as float32 probabilities, replaces the row in its registers)
-        float4 tv[kRowVec];
-        load_row(T.row, V, T.mode == 0 ? 0.f : -INFINITY, tv);
-        if (k < G) {
-            const RowProb D = d_row(k);
-            const int n4 = V >> 2;
-            const float fill = D.mode == 0 ? 0.f : -INFINITY;
-#pragma unroll
-            for (int i = 0; i < kRowVec; ++i) {               // the draft row passes through 4 registers at a time
-                const int q = i * kSampThreads + (int)threadIdx.x;
-                const int x0 = 4 * q;
-                const float4 dq = q < n4 ? reinterpret_cast<const float4 *>(D.row)[q] : float4{fill, fill, fill, fill};
-                tv[i].x = fmaxf(0.0f, __fsub_rn(T.of(tv[i].x, x0), D.of(dq.x, x0)));
-                tv[i].y = fmaxf(0.0f, __fsub_rn(T.of(tv[i].y, x0 + 1), D.of(dq.y, x0 + 1)));
-                tv[i].z = fmaxf(0.0f, __fsub_rn(T.of(tv[i].z, x0 + 2), D.of(dq.z, x0 + 2)));
-                tv[i].w = fmaxf(0.0f, __fsub_rn(T.of(tv[i].w, x0 + 3), D.of(dq.w, x0 + 3)));
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < kRowVec; ++i) {
-                const int x0 = 4 * (i * kSampThreads + (int)threadIdx.x);
-                tv[i] = float4{T.of(tv[i].x, x0), T.of(tv[i].y, x0 + 1), T.of(tv[i].z, x0 + 2), T.of(tv[i].w, x0 + 3)};
-            }
-        }
-        auto elem = [](const float4 &q, int j) { return j == 0 ? q.x : (j == 1 ? q.y : (j == 2 ? q.z : q.w)); };
-        y = sample_inverse_cdf_regs([&](int i, int j, int) { return fixed_weight(elem(tv[i], j)); }, V, u_last, tmp, &result);
-        if (y < 0 && k < G) y = sample_inverse_cdf(T, V, u_last, tmp, &result);   // residual mass truncates to zero: rare
-    } else if (k < G) {
-        const RowProb D = d_row(k);
+    const int k = q.accepted(true);
+    const RowProb T = q.t_row(k);
+    int y = -1;
+    if (k < G) {
+        const RowProb D = q.d_row(k);
         y = sample_inverse_cdf([&](int x) { return fmaxf(0.0f, __fsub_rn(T(x), D(x))); }, V, u_last, tmp, &result);
-        if (y < 0) y = sample_inverse_cdf(T, V, u_last, tmp, &result);
+    }
+    if (y < 0) y = sample_inverse_cdf(T, V, u_last, tmp, &result);    // bonus row, or the residual mass truncates to zero
+    if (threadIdx.x == 0) {
+        a.n_accepted[seq] = k;
+        a.next_token[seq] = y < 0 ? 0 : y;
+    }
+}
+
+// Rows that fit the registers (see row_fits_registers): NS workgroups per sequence, each with a slice of the row to
+// draw from, read once.  Every slice adds up its fixed-point weights, publishes the total and takes a ticket; the last
+// one to arrive finds the slice the threshold falls into, reads that slice again and searches it.  The totals are
+// integers: the result does not depend on the number of slices.
+// Totals and ticket live in the words of the row statistics nobody else uses at a temperature above 0 (argmax and
+// padding): the ticket in the padding of the first target row, which the statistics kernel clears, slice total i
+// behind row i + 1 of the 2 gamma rows that follow -- so NS <= 2 gamma.
+// EARLY: with few sequences the slices of ALL their rows are requested before the accept tests, which takes the
+// round trip of the rows out of the chain.
+// Bound by a chain of dependent round trips (statistics and tokens, drafted entries, total, ticket, totals, the hit slice),
+// no longer by one CU's vector instructions: 10.8 us for one sequence (one workgroup: 14.4), 12.9 for 64 (18.9).
+constexpr int kEarlyGamma = 7;
+template <int NS, bool EARLY>
+__global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(AcceptArgs a) {
+    constexpr int NV = kRowVec / NS;
+    const int seq = blockIdx.x / NS, slice = blockIdx.x % NS, G = a.gamma, V = a.vocab;
+    __shared__ SeqRows rows;
+    __shared__ unsigned long long tmp[17];
+    __shared__ int result;
+    __shared__ int is_last;
+    const SeqView q(a, rows, seq);
+    const float u_last = a.u[seq * (G + 1) + G];
+    const int n4 = V >> 2, per = (n4 + NS - 1) / NS;          // quads of a slice
+    float4 t[NV], d[NV];
+    auto load = [&](const float *row, int sl, float4 (&v)[NV]) __attribute__((always_inline)) {
+        const int q0 = sl * per, q1 = min(n4, q0 + per);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int qi = q0 + quad_of<NV, true>(i);
+            v[i] = qi < q1 ? reinterpret_cast<const float4 *>(row)[qi] : float4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    int k;
+    if (EARLY) {
+        float4 te[kEarlyGamma + 1][NV], de[kEarlyGamma][NV];
+#pragma unroll
+        for (int j = 0; j <= kEarlyGamma; ++j) {
+            if (j <= G) load(q.t_ptr(j), slice, te[j]);
+            if (j < kEarlyGamma && j < G) load(q.d_ptr(j), slice, de[j]);
+        }
+        k = q.accepted(slice == 0);
+#pragma unroll
+        for (int j = 0; j <= kEarlyGamma; ++j)
+            if (j == k) {
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    t[i] = te[j][i];
+                    if (j < kEarlyGamma) d[i] = de[j][i];
+                }
+            }
     } else {
-        y = sample_inverse_cdf(T, V, u_last, tmp, &result);
+        k = q.accepted(slice == 0);
+        load(q.t_ptr(k), slice, t);
+        if (k < G) load(q.d_ptr(k), slice, d);
+    }
+    const RowProb T = q.t_row(k), D = k < G ? q.d_row(k) : T;
+    // the values of the distribution to draw from: residual max(0, T - D), or the bonus row
+    float4 r[NV];
+    auto values = [&](int sl) __attribute__((always_inline)) {
+        const int q0 = sl * per, q1 = min(n4, q0 + per);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int qi = q0 + quad_of<NV, true>(i), x0 = 4 * qi;
+            r[i] = float4{T.of(t[i].x, x0), T.of(t[i].y, x0 + 1), T.of(t[i].z, x0 + 2), T.of(t[i].w, x0 + 3)};
+            if (k < G) {
+                r[i].x = fmaxf(0.0f, __fsub_rn(r[i].x, D.of(d[i].x, x0)));
+                r[i].y = fmaxf(0.0f, __fsub_rn(r[i].y, D.of(d[i].y, x0 + 1)));
+                r[i].z = fmaxf(0.0f, __fsub_rn(r[i].z, D.of(d[i].z, x0 + 2)));
+                r[i].w = fmaxf(0.0f, __fsub_rn(r[i].w, D.of(d[i].w, x0 + 3)));
+            }
+            if (qi >= q1) r[i] = float4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    SliceSampler<NV> s;
+    unsigned long long S = 0, off = 0, thr = 0;
+    int hit = slice;
+    for (int pass = 0;; ++pass) {                             // pass 1: the last workgroup, on the slice that was hit
+        values(hit);
+        s.weigh(r);
+        const unsigned long long mine = s.total(tmp);
+        if (pass > 0) break;
+        if (NS == 1) {
+            S = mine;
+            thr = threshold_of(u_last, S);
+            break;
+        }
+        // total of slice i: 8 bytes at `argmax` of row i + 1 (the target rows, then the draft rows)
+        auto slot = [&](int i) { return reinterpret_cast<unsigned long long *>(&(i < G ? q.stats_t(i + 1) : q.stats_d(i - G))->argmax); };
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(slot(slice), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const unsigned ticket = __hip_atomic_fetch_add(reinterpret_cast<unsigned *>(&q.stats_t(0)->pad), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            is_last = ticket == NS - 1;
+        }
+        __syncthreads();
+        if (!is_last) return;
+        unsigned long long tot[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) tot[i] = __hip_atomic_load(slot(i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < NS; ++i) S += tot[i];
+        if (S == 0) break;
+        thr = threshold_of(u_last, S);
+        unsigned long long run = 0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            if (run <= thr && thr < run + tot[i]) { hit = i; off = run; }
+            run += tot[i];
+        }
+        if (hit == slice) break;
+        load(T.row, hit, t);
+        if (k < G) load(D.row, hit, d);
+    }
+    int y = -1;
+    if (S != 0) {
+        if (threadIdx.x == 0) result = -1;
+        __syncthreads();
+        s.find(r, thr - off, hit * per, &result);
+        __syncthreads();
+        y = result;
+    } else if (k < G) {
+        y = sample_row_slowly(T, V, u_last, tmp, &result);    // residual mass truncates to zero: rare
     }
     if (threadIdx.x == 0) {
         a.n_accepted[seq] = k;
@@ -419,7 +578,19 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
         int n_rows = a.n_seqs * (2 * a.gamma + 1);
         hipLaunchKernelGGL(accept_stats_kernel, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
     }
-    hipLaunchKernelGGL(accept_decide_kernel, dim3(a.n_seqs), dim3(kSampThreads), 0, stream, a);
+    const bool fits = (a.vocab & 3) == 0 && a.vocab <= kRowVec * kSampThreads * 4 && (((uintptr_t)a.target | (uintptr_t)a.draft) & 15) == 0;
+    // Slices per sequence: as many as there are words for their totals (2 gamma, none without statistics or where the
+    // statistics' argmax is in use) and as run in one round of one workgroup per CU (64 sequences, whole step: 1 slice
+    // 29.3 us, 2 slices 31.3, 4 slices 27.8; 8 slices, two rounds, 49).
+    int ns = need_stats && a.temperature > 0.f ? (a.gamma >= 4 ? 8 : (a.gamma >= 2 ? 4 : 2)) : 1;
+    while (ns > 1 && (long)a.n_seqs * ns > 256) ns /= 2;
+    const dim3 block(kSampThreads);
+    if (!fits) hipLaunchKernelGGL(accept_decide_kernel, dim3(a.n_seqs), block, 0, stream, a);
+    else if (ns == 8 && a.gamma <= kEarlyGamma) hipLaunchKernelGGL((accept_decide_slices_kernel<8, true>), dim3(a.n_seqs * 8), block, 0, stream, a);
+    else if (ns == 8) hipLaunchKernelGGL((accept_decide_slices_kernel<8, false>), dim3(a.n_seqs * 8), block, 0, stream, a);
+    else if (ns == 4) hipLaunchKernelGGL((accept_decide_slices_kernel<4, false>), dim3(a.n_seqs * 4), block, 0, stream, a);
+    else if (ns == 2) hipLaunchKernelGGL((accept_decide_slices_kernel<2, false>), dim3(a.n_seqs * 2), block, 0, stream, a);
+    else hipLaunchKernelGGL((accept_decide_slices_kernel<1, false>), dim3(a.n_seqs), block, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -437,27 +608,37 @@ __global__ __launch_bounds__(kSampThreads) void softmax_sample_kernel(const floa
     float *out = probs_out + (size_t)seq * probs_stride;
     const float u_seq = u[(size_t)seq * u_stride];
     __shared__ RowStats st;
-    __shared__ unsigned long long tmp[kRowVec * 17];
+    __shared__ unsigned long long tmp[17];
     __shared__ int result;
     const float inv_temp = temperature > 0.f ? 1.0f / temperature : 1.0f;
     RowProb p;
     p.row = row; p.inv_temp = inv_temp; p.mode = temperature > 0.f ? 1 : 2;
     int y;
     if (row_fits_registers(row, V) && row_fits_registers(out, V)) {
-        float4 v[kRowVec];
-        load_row(row, V, -INFINITY, v);
-        row_stats_regs(v, V, inv_temp, &st);
-        p.st = st; p.inv_sum = 1.0f / st.sum;
         const int n4 = V >> 2;
+        float4 v[kRowVec];
 #pragma unroll
         for (int i = 0; i < kRowVec; ++i) {
-            const int q = i * kSampThreads + (int)threadIdx.x;
+            const int q = quad_of<kRowVec, true>(i);
+            v[i] = q < n4 ? reinterpret_cast<const float4 *>(row)[q] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        }
+        row_stats_regs<true>(v, p.mode == 2, inv_temp, &st);
+        p.st = st; p.inv_sum = 1.0f / st.sum;
+#pragma unroll
+        for (int i = 0; i < kRowVec; ++i) {
+            const int q = quad_of<kRowVec, true>(i);
             const int x0 = 4 * q;
             v[i] = float4{p.of(v[i].x, x0), p.of(v[i].y, x0 + 1), p.of(v[i].z, x0 + 2), p.of(v[i].w, x0 + 3)};
             if (q < n4) reinterpret_cast<float4 *>(out)[q] = v[i];
         }
-        auto elem = [](const float4 &q, int j) { return j == 0 ? q.x : (j == 1 ? q.y : (j == 2 ? q.z : q.w)); };
-        y = sample_inverse_cdf_regs([&](int i, int j, int) { return fixed_weight(elem(v[i], j)); }, V, u_seq, tmp, &result);
+        SliceSampler<kRowVec> s;
+        s.weigh(v);
+        const unsigned long long S = s.total(tmp);
+        if (threadIdx.x == 0) result = -1;
+        __syncthreads();
+        if (S != 0) s.find(v, threshold_of(u_seq, S), 0, &result);
+        __syncthreads();
+        y = result;
     } else {
         row_stats(row, V, inv_temp, &st);
         p.st = st; p.inv_sum = 1.0f / st.sum;
