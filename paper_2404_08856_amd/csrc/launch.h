@@ -138,11 +138,11 @@ hipError_t launch_qkv_attention(const QkvAttnArgs &a, hipStream_t stream);
 
 // ---- prefill: many rows of one sequence per pass (prefill.hip) ----------------------
 constexpr int kPrefillRows = 2048;   // rows per pass at most
-// Runs of at least this many rows take these kernels, shorter ones the batched verify path (64 rows per pass).  Measured
-// (us per call, context 0, batched path / these kernels): four 7B layers, 64 rows 957 / 1402, 96 rows 1577 / 1456; the
-// 12-layer draft, 32 rows 865 / 1017, 48 rows 1234 / 1043; the 4-layer draft, 40 rows 361 / 453, 48 rows 466 / 453.
-// At d = 4096 a pass of up to 64 rows is a weight stream, which the batched kernels are made for.
-inline int prefill_min_rows(int d_model) { return d_model >= 2048 ? 73 : 45; }
+// Runs of at least this many rows take these kernels, shorter ones the batched verify path.  Measured (us per call,
+// batched path / these kernels, empty cache and 500 cached positions): four 7B layers, 32 rows 677 / 683 and 801 / 749,
+// 40 rows 712 / 699 and 864 / 763; the 12-layer draft, 24 rows 769 / 791 and 948 / 920, 32 rows 867 / 796 and 1110 / 924;
+// the 4-layer draft, 24 rows 294 / 307 and 382 / 368, 32 rows 330 / 309 and 450 / 370.
+inline int prefill_min_rows(int d_model) { return d_model >= 2048 ? 33 : 25; }
 hipError_t launch_prefill_rows(const void *embed_bf16, const int32_t *tokens, const float *embeds, int rows, int d, int vocab,
                                const float *gain, float *h, void *X, float *ssq, int ssq_ld, hipStream_t stream);
 struct PrefillGemmArgs {
@@ -158,7 +158,11 @@ struct PrefillGemmArgs {
     void *Xnext;
     float *ssq_out;           // prefill_ssq_parts(N / 16, rows) parts per row
     void *Xout;               // SWIGLU: activations of N / 2 columns
+    float *partials;          // scratch for the sums of K slices (prefill_partial_bytes), or NULL: K is never sliced
+    unsigned *arrive;         // kPrefillMaxSplit counters, zero between launches
 };
+constexpr int kPrefillMaxSlices = 8, kPrefillMaxSplit = 1024;    // K slices per tile; workgroups of a sliced launch
+size_t prefill_partial_bytes(int N, int max_rows);
 int prefill_ssq_parts(int n_tiles, int rows);
 hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream_t stream);
 struct PrefillAttnArgs {

@@ -52,7 +52,7 @@ struct Layout {                    // byte offsets inside the three buffers
     int v_stride;
     // workspace
     size_t h, qkv, xn, xo, xf, rope, logits, ssq_a, ssq_b, d_lens, d_error, qa_count, qa_abort, part, arrive, zero;
-    size_t ph, pqkv, pxn, pxo, pxf, pssq_a, pssq_b;      // prefill passes of up to prefill_rows rows
+    size_t ph, pqkv, pxn, pxo, pxf, pssq_a, pssq_b, ppart;      // prefill passes of up to prefill_rows rows
     int prefill_rows, pssq_ld;
     size_t ws_total;
 };
@@ -129,6 +129,7 @@ void make_layout(const spd_model_config &c, Layout &L) {
     L.pxf = take(pr * KSf * 64 * kTerms);
     L.pssq_a = take(pr * L.pssq_ld * 4);
     L.pssq_b = take(pr * L.pssq_ld * 4);
+    L.ppart = take(std::max({prefill_partial_bytes(3 * HD, L.prefill_rows), prefill_partial_bytes(d, L.prefill_rows), prefill_partial_bytes(2 * F, L.prefill_rows)}));
     L.ws_total = off;
 }
 
@@ -567,24 +568,23 @@ int32_t prefill_pass(spd_model *m, int32_t seq, const float *embeds, const int32
         char *kv_l = m->kv + (size_t)l * L.kv_layer_stride;
         at.k_cache = kv_l + (size_t)seq * c.n_heads * c.max_positions * c.head_dim * 2;
         at.v_cache = kv_l + align_up(L.kv_k_bytes, 256) + (size_t)seq * c.n_heads * c.head_dim * L.v_stride * 2;
-        PrefillGemmArgs g{};
-        g.rows = M; g.ssq_ld = L.pssq_ld; g.eps = c.rms_eps;
+        PrefillGemmArgs common{};
+        common.rows = M; common.ssq_ld = L.pssq_ld; common.eps = c.rms_eps;
+        common.partials = (float *)(m->ws + L.ppart); common.arrive = (unsigned *)(m->ws + L.arrive);
+        PrefillGemmArgs g = common;
         g.W = m->packed + L.wqkv[l]; g.X = xn; g.N = 3 * HD; g.K = d; g.Y = qkv; g.ldy = 3 * HD;
         g.ssq_in = ssq_b; g.ssq_parts = l == 0 ? 1 : parts;
         PROF_TRY(PK_QKV, launch_prefill_gemm(g, EPI_STORE, st));
         PROF_TRY(PK_ATTENTION, launch_prefill_attention(at, st));
-        g = PrefillGemmArgs{};
-        g.rows = M; g.ssq_ld = L.pssq_ld;
+        g = common;
         g.W = m->packed + L.wo[l]; g.X = xo; g.N = d; g.K = HD; g.Y = h; g.ldy = d;
         g.gain_next = gain_of(L.mlp_norm[l]); g.Xnext = xn; g.ssq_out = ssq_a;
         PROF_TRY(PK_O, launch_prefill_gemm(g, EPI_RESIDUAL, st));
-        g = PrefillGemmArgs{};
-        g.rows = M; g.ssq_ld = L.pssq_ld; g.eps = c.rms_eps;
+        g = common;
         g.W = m->packed + L.wgu[l]; g.X = xn; g.N = 2 * F; g.K = d; g.Xout = xf;
         g.ssq_in = ssq_a; g.ssq_parts = parts;
         PROF_TRY(PK_GATE_UP, launch_prefill_gemm(g, EPI_SWIGLU, st));
-        g = PrefillGemmArgs{};
-        g.rows = M; g.ssq_ld = L.pssq_ld;
+        g = common;
         g.W = m->packed + L.wdown[l]; g.X = xf; g.N = d; g.K = F; g.Y = h; g.ldy = d;
         if (l + 1 < c.n_layers) { g.gain_next = gain_of(L.attn_norm[l + 1]); g.Xnext = xn; g.ssq_out = ssq_b; }
         PROF_TRY(PK_DOWN, launch_prefill_gemm(g, EPI_RESIDUAL, st));

@@ -12,7 +12,9 @@
 //  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
 //    the pass's own rows).
 // Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
-// four 7B layers, 2047 rows 8.6 ms (was 41.1), 640 rows 3.12 (10.2); 12-layer draft, 1472 rows 1.85 ms (47.1).
+// four 7B layers, 2047 rows 8.6 ms (was 41.1), 640 rows 2.85 (10.2); 12-layer draft, 1472 rows 1.75 ms (47.1).
+#include <algorithm>
+
 #include "gemm_core.h"
 #include "launch.h"
 
@@ -105,8 +107,12 @@ struct PrefillGemmKernelArgs {
     float *ssq_out;           // RESIDUAL: [rows][ssq_ld], one part per NW tiles
     uint16_t *Xout;           // SWIGLU
     int KS_out;
+    int J;                    // K slices
+    float *partials;          // J > 1: [tile][slice][TN * TR * 256] sums
+    unsigned *arrive;         // J > 1: one counter per tile, zero between launches
 };
 
+// J > 1: the K range is cut into J slices, one workgroup each.
 constexpr int kPgBuf = 3;     // LDS stages: one being multiplied, two on their way
 
 // WN x WR waves; a wave owns NW weight tiles (16 features each) and NX row tiles (16 rows each).  One K-step of
@@ -125,22 +131,23 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
     __shared__ float inv_s[TR * 16];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int KS = a.KS;
-
     // Workgroup -> tile.  Workgroups go round robin over the 8 XCDs; each XCD takes a contiguous run of an order that
     // walks 8 row blocks for one feature block before the next, so that the ~32 workgroups an XCD runs together
     // share 8 row blocks and 4 feature blocks in its L2.
-    int nb, rb;
+    int nb, rb, slice, tile;
     {
-        const int total = a.n_blk * a.r_blk, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+        const int tiles = a.n_blk * a.r_blk, total = tiles * a.J, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
         const int base = total >> 3, extra = total & 7;
         const int lin = xcd * base + min(xcd, extra) + slot;
-        const int band = 8 * a.n_blk, b0 = lin / band, in = lin - b0 * band;
+        slice = lin / tiles;                              // all tiles of one slice of K before the next
+        tile = lin - slice * tiles;
+        const int band = 8 * a.n_blk, b0 = tile / band, in = tile - b0 * band;
         const int rows_in = min(8, a.r_blk - 8 * b0);
         nb = in / rows_in;
         rb = 8 * b0 + in - nb * rows_in;
     }
     const int t0 = nb * TN, rt0 = rb * TR;
+    const int k0 = (int)((long)a.KS * slice / a.J), KS = (int)((long)a.KS * (slice + 1) / a.J) - k0;    // K-steps k0 .. k0 + KS - 1
 
     const uint4 *src[PB];                                 // wave-uniform: block w + i * WAVES of stage 0
     int step[PB];
@@ -148,11 +155,11 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
     for (int i = 0; i < PB; ++i) {
         const int b = w + i * WAVES;
         if (b < TN) {
-            src[i] = a.W + (size_t)min(t0 + b, a.n_tiles - 1) * KS * 64;      // beyond the matrix: a valid tile, result dropped
+            src[i] = a.W + (size_t)min(t0 + b, a.n_tiles - 1) * a.KS * 64 + (size_t)k0 * 64;      // beyond the matrix: a valid tile, result dropped
             step[i] = 64;
         } else {
             const int x = b - TN;
-            src[i] = a.X + ((size_t)min(rt0 + x / kTerms, a.n_rt - 1) * KS * kTerms + x % kTerms) * 64;
+            src[i] = a.X + (((size_t)min(rt0 + x / kTerms, a.n_rt - 1) * a.KS + k0) * kTerms + x % kTerms) * 64;
             step[i] = 64 * kTerms;
         }
     }
@@ -164,6 +171,18 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
     };
     issue(0, 0);
     issue(1, 1);
+
+    // 1 / rms of the workgroup's rows, 4 threads per row, fixed order; read behind the loop's barriers
+    if (a.ssq_in) {
+        for (int i = threadIdx.x; i < TR * 64; i += WAVES * 64) {
+            const int row = min(rt0 * 16 + i / 4, a.rows - 1), q = i & 3;
+            float ss = 0.f;
+            for (int p = q; p < a.ssq_parts; p += 4) ss += a.ssq_in[(size_t)row * a.ssq_ld + p];
+            ss += __shfl_xor(ss, 1);
+            ss += __shfl_xor(ss, 2);
+            if (q == 0) inv_s[i / 4] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
+        }
+    }
 
     const int wn = w % WN, wr = w / WN;
     f32x4_t part[NW][NX], sum[NW][NX], rest[OWN_REST ? NW : 1][NX];
@@ -227,21 +246,71 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
             sum[i][j] += part[i][j];
         }
 
-    // 1 / rms of the workgroup's rows, 4 threads per row, fixed order
-    if (a.ssq_in) {
-        for (int i = threadIdx.x; i < TR * 64; i += WAVES * 64) {
-            const int row = min(rt0 * 16 + i / 4, a.rows - 1), q = i & 3;
-            float ss = 0.f;
-            for (int p = q; p < a.ssq_parts; p += 4) ss += a.ssq_in[(size_t)row * a.ssq_ld + p];
-            ss += __shfl_xor(ss, 1);
-            ss += __shfl_xor(ss, 2);
-            if (q == 0) inv_s[i / 4] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
+    __syncthreads();                                      // inv_s
+    if (a.J > 1) {
+        // This slice's sums in whole lines (512 contiguous bytes per store), written through to memory; once they are acknowledged take a
+        // ticket.  The last slice of the tile to arrive (nobody waits) adds all of them in slice order and goes on.
+        constexpr size_t kTile = (size_t)TN * TR * 64;    // float4 quads of a tile
+        unsigned long long *mine = reinterpret_cast<unsigned long long *>(a.partials) + ((size_t)tile * a.J + slice) * kTile * 2;
+        auto at = [&](int i, int j, int half) { return (size_t)(((w * NW + i) * NX + j) * 2 + half) * 64 + lane; };
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2_t;
+                const u64x2_t v = __builtin_bit_cast(u64x2_t, sum[i][j]);
+                __hip_atomic_store(mine + at(i, j, 0), v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(mine + at(i, j, 1), v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __shared__ int is_last;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned ticket = __hip_atomic_fetch_add(a.arrive + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            is_last = ticket == (unsigned)(a.J - 1);
+            if (is_last) __hip_atomic_store(a.arrive + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
         }
         __syncthreads();
+        if (!is_last) return;
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int j = 0; j < NX; ++j) sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < a.J; ++s) {
+            const unsigned long long *src = reinterpret_cast<const unsigned long long *>(a.partials) + ((size_t)tile * a.J + s) * kTile * 2;
+            unsigned long long lo[NW][NX], hi[NW][NX];
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    lo[i][j] = __hip_atomic_load(src + at(i, j, 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    hi[i][j] = __hip_atomic_load(src + at(i, j, 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    sum[i][j][0] += __uint_as_float((unsigned)lo[i][j]); sum[i][j][1] += __uint_as_float((unsigned)(lo[i][j] >> 32));
+                    sum[i][j][2] += __uint_as_float((unsigned)hi[i][j]); sum[i][j][3] += __uint_as_float((unsigned)(hi[i][j] >> 32));
+                }
+        }
     }
 
     // D[feature 4 g + v][row r] of tile (i, j): a lane holds 4 consecutive features of one row
     const int r = lane & 15, g = lane >> 4;
+    float4 hold[NW][NX], gn[NW];
+    if (EPI == EPI_RESIDUAL) {                            // all old values on their way together, before any store
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int t = min(t0 + wn * NW + i, a.n_tiles - 1), col = t * 16 + 4 * g;
+            gn[i] = a.gain_next ? *reinterpret_cast<const float4 *>(a.gain_next + col) : float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                const int row = min((rt0 + wr * NX + j) * 16 + r, a.rows - 1);
+                hold[i][j] = *reinterpret_cast<const float4 *>(a.Y + (size_t)row * a.ldy + col);
+            }
+        }
+    }
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
         const int lrow = (wr * NX + j) * 16 + r, row = rt0 * 16 + lrow;
@@ -273,12 +342,11 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                 if (EPI == EPI_STORE) {
                     *dst = float4{sum[i][j][0] * inv, sum[i][j][1] * inv, sum[i][j][2] * inv, sum[i][j][3] * inv};
                 } else {
-                    float4 h = *dst;
+                    float4 h = hold[i][j];
                     h.x += sum[i][j][0]; h.y += sum[i][j][1]; h.z += sum[i][j][2]; h.w += sum[i][j][3];
                     *dst = h;
                     if (a.gain_next) {
-                        const float4 gn = *reinterpret_cast<const float4 *>(a.gain_next + col);
-                        const float y[4] = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
+                        const float y[4] = {h.x * gn[i].x, h.y * gn[i].y, h.z * gn[i].z, h.w * gn[i].w};
                         ppack_store4(a.Xnext, row, col, a.n_tiles / 2, y);
                         sq += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
                     }
@@ -298,7 +366,7 @@ template <int WN, int WR, int NW, int NX>
 static hipError_t launch_pg(PrefillGemmKernelArgs &k, int epilogue, hipStream_t stream) {
     k.n_blk = (k.n_tiles + WN * NW - 1) / (WN * NW);
     k.r_blk = (k.n_rt + WR * NX - 1) / (WR * NX);
-    const dim3 grid(k.n_blk * k.r_blk), block(WN * WR * 64);
+    const dim3 grid(k.n_blk * k.r_blk * k.J), block(WN * WR * 64);
     switch (epilogue) {
         case EPI_STORE: hipLaunchKernelGGL((prefill_gemm_kernel<WN, WR, NW, NX, EPI_STORE>), grid, block, 0, stream, k); break;
         case EPI_RESIDUAL: hipLaunchKernelGGL((prefill_gemm_kernel<WN, WR, NW, NX, EPI_RESIDUAL>), grid, block, 0, stream, k); break;
@@ -318,6 +386,25 @@ static bool prefill_large(int n_tiles, int rows) {
     const int rounds_large = (large + 255) / 256, rounds_small = (small + 511) / 512;
     return rounds_large * 2 <= rounds_small;
 }
+// K slices of the small shape, so that a matrix with few tiles still fills the chip: the smallest estimate, in K-steps of
+// a CU shared by two workgroups (0.67 us; 0.45 where a workgroup has a CU of its own), of rounds x steps, plus the
+// exchange of the partial sums (a few round trips, and 64 KiB per workgroup across the chip through memory).  Four 7B layers, unsliced / sliced:
+// 128 rows 1457 / 1025 us, 320 rows 1922 / 1667, 640 rows 3077 / 2852; the 12-layer draft, 64 rows 1015 / 770, 640 rows
+// 1249 / 1106.
+static int prefill_slices(int tiles, int KS) {
+    auto cost = [&](int J) {
+        const int n = tiles * J, steps = (KS + J - 1) / J;
+        return (n <= 256 ? 0.67f : (float)((n + 511) / 512)) * steps + (J > 1 ? 10.f + 0.02f * n : 0.f);
+    };
+    int best = 1;
+    for (int J = 2; J <= kPrefillMaxSlices && tiles * J <= kPrefillMaxSplit && KS / J >= 4; ++J)
+        if (cost(J) < cost(best)) best = J;
+    return best;
+}
+size_t prefill_partial_bytes(int N, int max_rows) {
+    const long tiles = (long)((N / 16 + 7) / 8) * ((max_rows + 63) / 64);
+    return (size_t)std::min((long)kPrefillMaxSplit, tiles * kPrefillMaxSlices) * 32 * 1024;
+}
 int prefill_ssq_parts(int n_tiles, int rows) { return prefill_large(n_tiles, rows) ? (n_tiles + 7) / 8 : (n_tiles + 3) / 4; }
 
 hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream_t stream) {
@@ -331,7 +418,10 @@ hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream
     k.inv_d = 1.0f / (float)a.K; k.eps = a.eps;
     k.gain_next = a.gain_next; k.Xnext = (uint16_t *)a.Xnext; k.ssq_out = a.ssq_out;
     k.Xout = (uint16_t *)a.Xout; k.KS_out = (a.N / 2 + 31) / 32;
+    k.J = 1;
+    k.partials = a.partials; k.arrive = a.arrive;
     if (prefill_large(k.n_tiles, a.rows)) return launch_pg<2, 4, 8, 2>(k, epilogue, stream);
+    if (a.partials && a.arrive) k.J = prefill_slices(((k.n_tiles + 7) / 8) * ((a.rows + 63) / 64), k.KS);
     return launch_pg<2, 2, 4, 2>(k, epilogue, stream);
 }
 

@@ -1,5 +1,5 @@
 """GPU parity of the prefill passes (many rows of one sequence per pass) against the float64 oracle: row counts around
-the edges of the row tiles, workgroup tiles and key units, a second pass on top of a cached prefix, ragged d_ffn,
+the edges of the row tiles, workgroup tiles, slices of K and key units, a second pass on top of a cached prefix, ragged d_ffn,
 both head sizes, the KV cache it leaves and the decode step that follows."""
 import numpy as np
 import pytest
@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = {
     "dh64_ragged_ffn": synth.ModelShape(2, 256, 4, 64, 688, 1024),        # 43 / 2 K-steps: the last one half empty
     "dh128": synth.ModelShape(2, 512, 4, 128, 1408, 512),
+    "deep_k": synth.ModelShape(2, 128, 32, 64, 2728, 256),                # O and down: one feature tile, K cut into 8 slices
     "heads_wider_than_d": synth.ModelShape(1, 160, 3, 64, 424, 256),      # 10 feature tiles: a workgroup tile is partly empty
 }
 
@@ -27,6 +28,7 @@ def cached(model, layer, n, shape):
 @pytest.mark.parametrize("name,first,second", [
     ("dh64_ragged_ffn", 45, 0), ("dh64_ragged_ffn", 64, 65), ("dh64_ragged_ffn", 127, 128), ("dh64_ragged_ffn", 255, 47),
     ("dh128", 48, 0), ("dh128", 129, 63), ("dh128", 300, 45), ("heads_wider_than_d", 81, 79),
+    ("deep_k", 25, 64), ("deep_k", 129, 47), ("deep_k", 700, 0),
 ])
 def test_prefill_passes_against_oracle(name, first, second):
     from paper_2404_08856_amd import spd
