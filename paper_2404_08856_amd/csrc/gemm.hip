@@ -404,23 +404,21 @@ static hipError_t launch_multi(const GemmKernelArgs &k, int epilogue, int grid, 
 // the epilogue, then clears the counter for the next launch.  Fixed order => bit-reproducible.  The partials
 // cross workgroups (and XCDs, each with its own L2) inside one launch: device-scope stores, acknowledged
 // before the arrival is counted, and device-scope loads.
-constexpr int kBatchWaves = 8, kBatchMaxJ = 8;
+constexpr int kBatchMaxJ = 8;
 constexpr int kBatchCH = 4;      // K-steps per activation chunk: every LDS buffer holds NG * CH KiB
 // chunks the weight ring runs ahead (registers: TT * RDC * CH * 4 for the ring next to TT * NG * 4 accumulators)
 constexpr int batch_ring_chunks(int NG, int TT) { return (TT * NG * 4 + TT * 2 * kBatchCH * 4 <= 144) ? 2 : 1; }
 
-struct BatchPlan { int TT, J, n_tgroups; };
-// TT tiles per wave (accumulators = TT * NG * 4 VGPRs, weight ring = TT * CH blocks in flight per wave and ring
-// chunk); J K-slices (at most 8: the last arriver reads J partials per output) so that there is about one
-// workgroup per CU: the J in range with the shortest longest slice.
-static BatchPlan batch_plan(int n_tiles, int KS, int NG, int tt = 0) {
+struct BatchPlan { int waves, TT, J, n_tgroups; };
+// waves multiplying waves per workgroup (8 or 6), TT tiles per wave (accumulators = TT * NG * 4 VGPRs, weight ring = TT * CH
+// blocks in flight per wave and ring chunk), J K-slices (at most 8: the last arriver reads J partials per output) so that
+// there is about one workgroup per CU: the J in range with the shortest longest slice.
+static BatchPlan batch_plan_for(int n_tiles, int KS, int NG, int waves, int TT) {
     BatchPlan p;
-    // Measured at the 7B shapes: one tile per wave beats two everywhere (40 rows: 5.31 against 5.45 ms per step, 20 rows:
-    // 4.02 against 4.27) -- twice the workgroups, and the larger matrices then need no K slices at all.  Two tiles per
-    // wave remain for matrices with more tile groups than arrival counters.
-    p.TT = tt == 1 || tt == 2 ? tt : 1;
-    p.n_tgroups = (n_tiles + kBatchWaves * p.TT - 1) / (kBatchWaves * p.TT);
-    const int unit = batch_ring_chunks(NG, p.TT) * kBatchCH;
+    p.waves = waves;
+    p.TT = TT;
+    p.n_tgroups = (n_tiles + waves * TT - 1) / (waves * TT);
+    const int unit = batch_ring_chunks(NG, TT) * kBatchCH;
     const int n_units = (KS + unit - 1) / unit;
     int Jmax = 256 / p.n_tgroups;                             // at most one workgroup per CU: a single round
     if (Jmax > kBatchMaxJ) Jmax = kBatchMaxJ;
@@ -432,15 +430,30 @@ static BatchPlan batch_plan(int n_tiles, int KS, int NG, int tt = 0) {
     p.J = J;
     return p;
 }
+// KiB that the busiest CU pulls in: rounds x K-steps of the longest slice x (weight tiles + row groups)
+static long batch_cost(const BatchPlan &p, int KS, int NG) {
+    const int unit = batch_ring_chunks(NG, p.TT) * kBatchCH;
+    const long steps = (long)unit * (((KS + unit - 1) / unit + p.J - 1) / p.J);
+    return (long)((p.n_tgroups * p.J + 255) / 256) * steps * (p.waves * p.TT + NG);
+}
+// A workgroup's time is what its CU pulls through its memory path, so the plan with less to pull for the busiest CU wins:
+// 6 waves where 8 would leave CUs without a tile group (7B gate|up: 172 groups of 8 or 230 of 6; QKV 96 x 2 or 128 x 2).
+// Measured at the 7B shapes: one tile per wave beats two everywhere (40 rows: 5.31 against 5.45 ms per step, 20 rows:
+// 4.02 against 4.27) -- twice the workgroups, and the larger matrices then need no K slices at all.  Two tiles per
+// wave remain for matrices with more tile groups than arrival counters.
+static BatchPlan batch_plan(int n_tiles, int KS, int NG) {
+    const BatchPlan p8 = batch_plan_for(n_tiles, KS, NG, 8, 1), p6 = batch_plan_for(n_tiles, KS, NG, 6, 1);
+    if (p8.n_tgroups > kBatchMaxTileGroups) return batch_plan_for(n_tiles, KS, NG, 8, 2);
+    return p6.n_tgroups <= kBatchMaxTileGroups && batch_cost(p6, KS, NG) < batch_cost(p8, KS, NG) ? p6 : p8;
+}
 size_t gemm_batch_scratch_bytes(int N, int K) {
     const int n_tiles = N / 16, KS = (K + 31) / 32;
     size_t worst = 0;
-    for (int NG : {4, 8, kMaxGroups})
-        for (int tt : {1, 2}) {
-            const BatchPlan p = batch_plan(n_tiles, KS, NG, tt);
-            const size_t b = (size_t)p.J * p.n_tgroups * kBatchWaves * p.TT * NG * 80 * sizeof(float);
-            worst = b > worst ? b : worst;
-        }
+    for (int NG : {4, 8, kMaxGroups}) {
+        const BatchPlan p = batch_plan(n_tiles, KS, NG);
+        const size_t b = (size_t)p.J * p.n_tgroups * p.waves * p.TT * NG * 80 * sizeof(float);
+        worst = b > worst ? b : worst;
+    }
     return worst;
 }
 
@@ -452,9 +465,9 @@ struct BatchArgs { float *partials; unsigned *arrive; int J; const uint4 *zero_b
 constexpr int kBatchLoaders = 2;
 constexpr int batch_buffers(int NG) { return NG <= 8 ? 4 : 3; }
 
-template <int NG, int TT, int EPI>
-__global__ __launch_bounds__((kBatchWaves + kBatchLoaders) * 64) void gemm_batch_kernel(GemmKernelArgs a, BatchArgs b) {
-    constexpr int WAVES = kBatchWaves, LW = kBatchLoaders, CH = kBatchCH, RDC = batch_ring_chunks(NG, TT), NBUF = batch_buffers(NG);
+template <int WAVES, int NG, int TT, int EPI>
+__global__ __launch_bounds__((WAVES + kBatchLoaders) * 64) void gemm_batch_kernel(GemmKernelArgs a, BatchArgs b) {
+    constexpr int LW = kBatchLoaders, CH = kBatchCH, RDC = batch_ring_chunks(NG, TT), NBUF = batch_buffers(NG);
     constexpr int TPG = WAVES * TT;                        // tiles per workgroup
     constexpr int PB = (NG * CH + LW - 1) / LW;            // activation blocks per loader wave and chunk
     static_assert((NBUF - 1) * PB <= 63, "outstanding loads of a loader wave");
@@ -466,6 +479,13 @@ __global__ __launch_bounds__((kBatchWaves + kBatchLoaders) * 64) void gemm_batch
     // K-steps get zero activations), so the loops below have no conditional parts and every wait counts exactly
     const int n_units = (KS + RDC * CH - 1) / (RDC * CH);
     const int c_begin = RDC * (int)(((long)n_units * j) / J), c_end = RDC * (int)(((long)n_units * (j + 1)) / J);
+    // Every workgroup starts its slice at another chunk unit (the workgroups of an XCD spread evenly) and wraps round
+    const int c_len = c_end - c_begin;
+    const int rot = RDC * (int)(((long)(blockIdx.x >> 3) * (c_len / RDC)) / ((gridDim.x + 7) >> 3));
+    auto chunk_at = [&](int c) __attribute__((always_inline)) {       // c: c_begin + position; past the slice: any chunk
+        const int p = c + rot;
+        return p < c_end ? p : (p - c_len < c_end ? p - c_len : c_begin);
+    };
     const int g0 = a.row0 / kGroupRows;
     const int ngv = (a.rows + kGroupRows - 1) / kGroupRows;    // row groups that hold rows of this pass (<= NG)
 
@@ -483,7 +503,7 @@ __global__ __launch_bounds__((kBatchWaves + kBatchLoaders) * 64) void gemm_batch
         // ---- loader waves: chunk c + NBUF - 1 is requested while chunk c is multiplied; their loads wait in
         // their own queues, so the multiplying waves' weight rings are never held up by them ----
         auto issue_chunk = [&](int c) __attribute__((always_inline)) {
-            const int cc = c < c_end ? c : c_begin;           // past the slice: a harmless re-read
+            const int cc = chunk_at(c);
             const int bufi = (c - c_begin) % NBUF;
 #pragma unroll
             for (int r = 0; r < PB; ++r) {
@@ -517,7 +537,7 @@ __global__ __launch_bounds__((kBatchWaves + kBatchLoaders) * 64) void gemm_batch
         }
         uint4 ring[TT][RDC * CH];
         auto refill = [&](int tt, int slot, int k, int c) __attribute__((always_inline)) {   // block (tile, K-step k of chunk c)
-            int s = (c < c_end ? c : c_begin) * CH + k;       // past the slice: a harmless re-read
+            int s = chunk_at(c) * CH + k;
             s = s < KS ? s : KS - 1;
             ring[tt][slot] = load_stream(a.W + ((size_t)tile[tt] * KS + s) * 64 + lane);
         };
@@ -723,13 +743,13 @@ __global__ __launch_bounds__((kBatchWaves + kBatchLoaders) * 64) void gemm_batch
     else finish(std::integral_constant<int, kBatchMaxJ>{}, std::integral_constant<int, 2>{});
 }
 
-template <int NG, int TT>
+template <int WAVES, int NG, int TT>
 static hipError_t launch_batch(const GemmKernelArgs &k, const BatchArgs &b, int epilogue, int grid, hipStream_t stream) {
-    dim3 g(grid), block((kBatchWaves + kBatchLoaders) * 64);
+    dim3 g(grid), block((WAVES + kBatchLoaders) * 64);
     switch (epilogue) {
-        case EPI_STORE: hipLaunchKernelGGL((gemm_batch_kernel<NG, TT, EPI_STORE>), g, block, 0, stream, k, b); break;
-        case EPI_RESIDUAL: hipLaunchKernelGGL((gemm_batch_kernel<NG, TT, EPI_RESIDUAL>), g, block, 0, stream, k, b); break;
-        case EPI_SWIGLU: hipLaunchKernelGGL((gemm_batch_kernel<NG, TT, EPI_SWIGLU>), g, block, 0, stream, k, b); break;
+        case EPI_STORE: hipLaunchKernelGGL((gemm_batch_kernel<WAVES, NG, TT, EPI_STORE>), g, block, 0, stream, k, b); break;
+        case EPI_RESIDUAL: hipLaunchKernelGGL((gemm_batch_kernel<WAVES, NG, TT, EPI_RESIDUAL>), g, block, 0, stream, k, b); break;
+        case EPI_SWIGLU: hipLaunchKernelGGL((gemm_batch_kernel<WAVES, NG, TT, EPI_SWIGLU>), g, block, 0, stream, k, b); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -975,16 +995,15 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
     if (a.batch_partials && a.batch_arrive && a.batch_zero && groups > 2 && !tune.no_batch && (batch_pays || tune.force_batch)) {
         const int NG = groups <= 4 ? 4 : (groups <= 8 ? 8 : kMaxGroups);
         BatchPlan p = batch_plan(k.n_tiles, k.KS, NG);
-        if (p.n_tgroups > kBatchMaxTileGroups) p = batch_plan(k.n_tiles, k.KS, NG, 2);
         if (p.n_tgroups > kBatchMaxTileGroups) return hipErrorInvalidValue;     // more than 256 K output columns
         if (tune.grid_cap > 0 && tune.grid_cap / p.n_tgroups < p.J)          // a cap on the grid means fewer K slices here
             p.J = tune.grid_cap / p.n_tgroups > 0 ? tune.grid_cap / p.n_tgroups : 1;
         BatchArgs b{a.batch_partials, a.batch_arrive, p.J, (const uint4 *)a.batch_zero};
         const int bgrid = p.n_tgroups * p.J;
-#define SPD_BATCH_CASE(NG_, TT_) if (NG == NG_ && p.TT == TT_) return launch_batch<NG_, TT_>(k, b, epilogue, bgrid, stream)
-        SPD_BATCH_CASE(4, 1); SPD_BATCH_CASE(4, 2);
-        SPD_BATCH_CASE(8, 1); SPD_BATCH_CASE(8, 2);
-        SPD_BATCH_CASE(kMaxGroups, 1); SPD_BATCH_CASE(kMaxGroups, 2);
+#define SPD_BATCH_CASE(W_, NG_, TT_) if (p.waves == W_ && NG == NG_ && p.TT == TT_) return launch_batch<W_, NG_, TT_>(k, b, epilogue, bgrid, stream)
+        SPD_BATCH_CASE(8, 4, 1); SPD_BATCH_CASE(6, 4, 1); SPD_BATCH_CASE(8, 4, 2);
+        SPD_BATCH_CASE(8, 8, 1); SPD_BATCH_CASE(6, 8, 1); SPD_BATCH_CASE(8, 8, 2);
+        SPD_BATCH_CASE(8, kMaxGroups, 1); SPD_BATCH_CASE(6, kMaxGroups, 1); SPD_BATCH_CASE(8, kMaxGroups, 2);
 #undef SPD_BATCH_CASE
         return hipErrorInvalidValue;
     }
