@@ -125,10 +125,11 @@ typedef struct {
     int32_t  gemm_grid_cap[SPD_N_PROJECTIONS];       /* upper bound of the grid; 0 = default         */
     int32_t  gemm_general_kernel[SPD_N_PROJECTIONS]; /* 1: never the register-resident variant       */
     int32_t  gemm_ring[SPD_N_PROJECTIONS];           /* general kernel: weight blocks a wave keeps in flight, 8 or 16; 0 = default */
-    int32_t  batch_kernel;           /* calls of more than 10 rows: 0 = the library chooses per projection between the
-                                        tile-splitting batched kernel (one pass over the weights for up to 64 rows) and
-                                        the K-splitting kernels (passes of 40 rows); 1 = always the former, 2 = always
-                                        the latter */
+    int32_t  batch_kernel;           /* calls of more than 5 rows, where no register-resident kernel fits: 0 = the library
+                                        chooses per projection between the tile-splitting batched kernel (one pass over
+                                        the weights for up to 64 rows) and the K-splitting kernels (passes of 40 rows);
+                                        1 = always the former, 2 = always the latter.  Either one also keeps prompts on
+                                        the batched verify path */
     uint32_t wait_spin_limit;        /* polls before a wait between workgroups gives up and raises the flag that
                                         spd_device_status reports (0 = default, 2^22); a tiny value lets a test
                                         drive that error path from the host while every kernel still exits */

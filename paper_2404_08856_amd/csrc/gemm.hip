@@ -449,7 +449,7 @@ static BatchPlan batch_plan(int n_tiles, int KS, int NG) {
 size_t gemm_batch_scratch_bytes(int N, int K) {
     const int n_tiles = N / 16, KS = (K + 31) / 32;
     size_t worst = 0;
-    for (int NG : {4, 8, kMaxGroups}) {
+    for (int NG : {2, 4, 8, kMaxGroups}) {
         const BatchPlan p = batch_plan(n_tiles, KS, NG);
         const size_t b = (size_t)p.J * p.n_tgroups * p.waves * p.TT * NG * 80 * sizeof(float);
         worst = b > worst ? b : worst;
@@ -989,11 +989,12 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
 #undef SPD_GEMM_CASE
     // More than 10 rows with a scratch buffer: the tile-splitting kernel makes one pass over the weights for up to 13
     // row groups (65 rows).  Measured at the 7B shapes against the K-splitting kernel (microseconds per launch), 20 rows:
-    // gate|up 40 / 48, down 28 / 36, LM head 51 / 66, QKV 30 / 29, O 17 / 17; 40 rows: gate|up 51 / 67, down 34 / 52,
-    // LM head 51 / 91, QKV 35 / 40, O 22 / 23; beyond 40 rows the K-splitting kernel needs a second pass.
-    const bool batch_pays = groups > 2;
-    if (a.batch_partials && a.batch_arrive && a.batch_zero && groups > 2 && !tune.no_batch && (batch_pays || tune.force_batch)) {
-        const int NG = groups <= 4 ? 4 : (groups <= 8 ? 8 : kMaxGroups);
+    // gate|up 35 / 48, down 28 / 36, LM head 46 / 66, QKV 23 / 29, O 17 / 17; 40 rows: gate|up 44 / 67, down 34 / 52,
+    // LM head 51 / 91, QKV 28 / 40, O 22 / 23; beyond 40 rows the K-splitting kernel needs a second pass.  Rows 6..10 only
+    // where K is too long for resident activations (7B down: 22.3 / 24.1).
+    const bool batch_pays = groups > 2 || k.KS > 128;
+    if (a.batch_partials && a.batch_arrive && a.batch_zero && groups > 1 && !tune.no_batch && (batch_pays || tune.force_batch)) {
+        const int NG = groups <= 2 ? 2 : groups <= 4 ? 4 : (groups <= 8 ? 8 : kMaxGroups);
         BatchPlan p = batch_plan(k.n_tiles, k.KS, NG);
         if (p.n_tgroups > kBatchMaxTileGroups) return hipErrorInvalidValue;     // more than 256 K output columns
         if (tune.grid_cap > 0 && tune.grid_cap / p.n_tgroups < p.J)          // a cap on the grid means fewer K slices here
@@ -1001,6 +1002,7 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
         BatchArgs b{a.batch_partials, a.batch_arrive, p.J, (const uint4 *)a.batch_zero};
         const int bgrid = p.n_tgroups * p.J;
 #define SPD_BATCH_CASE(W_, NG_, TT_) if (p.waves == W_ && NG == NG_ && p.TT == TT_) return launch_batch<W_, NG_, TT_>(k, b, epilogue, bgrid, stream)
+        SPD_BATCH_CASE(8, 2, 1); SPD_BATCH_CASE(6, 2, 1); SPD_BATCH_CASE(8, 2, 2);
         SPD_BATCH_CASE(8, 4, 1); SPD_BATCH_CASE(6, 4, 1); SPD_BATCH_CASE(8, 4, 2);
         SPD_BATCH_CASE(8, 8, 1); SPD_BATCH_CASE(6, 8, 1); SPD_BATCH_CASE(8, 8, 2);
         SPD_BATCH_CASE(8, kMaxGroups, 1); SPD_BATCH_CASE(6, kMaxGroups, 1); SPD_BATCH_CASE(8, kMaxGroups, 2);

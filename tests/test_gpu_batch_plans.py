@@ -1,0 +1,47 @@
+"""GPU parity of the batched projection kernel's plans: 6 and 8 multiplying waves, one and several K slices with ragged last
+units, two row groups with a long K -- over models whose matrices make the plan come out that way."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decoder as dec
+from paper_2404_08856_amd import synth
+from tests.helpers import check_logits, oracle_cfg, randomize_gains, to_device
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    # QKV 96 tiles (6 waves: 16 groups), gate|up 172, down K = 1376: 43 steps, the last unit ragged
+    "d512": synth.ModelShape(1, 512, 4, 128, 1376, 1040),
+    # LM head 258 tiles of 16: 43 groups of 6 or 33 of 8, the last one partly empty
+    "wide_head": synth.ModelShape(1, 256, 4, 64, 688, 4128),
+    # down: K = 4352 (136 steps) with 256 tiles -- two row groups through the batched kernel at 6..10 rows
+    "long_down": synth.ModelShape(1, 4096, 2, 128, 4352, 512),
+}
+
+
+@pytest.mark.parametrize("name,n_seqs,M", [("d512", 3, 5), ("d512", 8, 5), ("d512", 8, 8), ("wide_head", 2, 6), ("wide_head", 5, 7),
+                                           ("long_down", 1, 6), ("long_down", 2, 5), ("long_down", 7, 1), ("long_down", 3, 4)])
+def test_batched_step_against_oracle(name, n_seqs, M):
+    from paper_2404_08856_amd import spd
+    shape = SHAPES[name]
+    print(f"batch plan {name} {n_seqs}x{M}", flush=True)
+    w = randomize_gains(synth.make_weights(shape, 21))
+    wn = synth.weights_to_numpy(w)
+    cfg = oracle_cfg(shape)
+    model = spd.Model(spd.make_config(shape, n_seqs, 64), to_device(w))
+    caches = []
+    for s in range(n_seqs):
+        ids = synth.text_tokens(9 + 2 * s, shape.vocab, 30 + s)
+        cache = dec.KVCache(cfg, 64)
+        dec.forward_tokens(cfg, wn, cache, ids)
+        model.spd_prefill_tokens(s, torch.from_numpy(ids).cuda())
+        caches.append(cache)
+    vt = np.stack([synth.text_tokens(M, shape.vocab, 60 + s) for s in range(n_seqs)])
+    out = torch.empty((n_seqs, M, shape.vocab), device="cuda")
+    for _ in range(2):                       # the arrival counters are zero again after a launch
+        model.spd_kv_set_len([c.length for c in caches])
+        model.spd_verify_forward(torch.from_numpy(vt).cuda(), out)
+    got = out.cpu().numpy()
+    for s in range(n_seqs):
+        check_logits(got[s], dec.forward_tokens(cfg, wn, caches[s], vt[s]), f"{name} seq {s}")
