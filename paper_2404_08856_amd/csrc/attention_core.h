@@ -93,14 +93,14 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     uint16_t *Kc = (uint16_t *)a.k_cache + pair * a.max_positions * DH;        // [pos][DH]
     uint16_t *Vt = (uint16_t *)a.v_cache + pair * (size_t)DH * VS;             // [VS / 32][DH][32]: see launch.h
 
-    __shared__ float qf[8][DH];
-    __shared__ float kf[8][DH];
+    __shared__ float qf[8][DH + 4];               // rows 4 banks apart: 8 rows are read side by side below
+    __shared__ float kf[8][DH + 4];
     __shared__ float vf[8][DH];
     __shared__ uint16_t qb[QG][NC][64][8];        // q as matrix-core B operand (three bf16 terms), per query group
     __shared__ float pn[8][8];
     __shared__ float part_m[AW + 1][8];
     __shared__ float part_l[AW + 1][8];
-    __shared__ float part_o[AW + 1][8][DW];
+    __shared__ float part_o[AW][8][DW];
 
     // ---- key units of this wave; first iteration's loads go out before anything else --------
     const int n_units = (P + 31) / 32;
@@ -234,7 +234,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 const float m_new = fmaxf(m_run[qg], mx);              // finite: a unit has >= 1 valid key
-                const float rescale = (m_run[qg] == -INFINITY) ? 0.f : expf(m_run[qg] - m_new);
+                const float rescale = (m_run[qg] == -INFINITY) ? 0.f : exp_neg(m_run[qg] - m_new);
                 float lsum = 0.f;
                 uint32_t hv[8];
 #pragma unroll
@@ -277,38 +277,39 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     }
 
     // ---- the M new keys (causal among the new rows), float32 from LDS -----------------------
-    if (w == 0) {                                   // wave 0 owns the fewest key units
-        const int m = lane >> 3, j = lane & 7;
-        float s = -INFINITY;
+    // Two queries per wave on the first four waves: lane = quarter of the dimensions, key j, query.  (One lane per (query,
+    // key) on one wave walked the dimensions in a chain of conflicting reads while every other wave waited.)
+    if (w < 4) {
+        const int part = lane & 3, j = (lane >> 2) & 7, m = 2 * w + (lane >> 5);
+        float s = 0.f;
         if (m < M && j <= m) {
-            s = 0.f;
-            for (int e = 0; e < DH; ++e) s += qf[m][e] * kf[j][e];
+#pragma unroll
+            for (int e = 0; e < DH / 4; e += 4) {
+                const float4 x = *reinterpret_cast<const float4 *>(&qf[m][part * (DH / 4) + e]);
+                const float4 y = *reinterpret_cast<const float4 *>(&kf[j][part * (DH / 4) + e]);
+                s += (x.x * y.x + x.y * y.y) + (x.z * y.z + x.w * y.w);
+            }
         }
+        s += __shfl_xor(s, 1);
+        s += __shfl_xor(s, 2);
+        if (m >= M || j > m) s = -INFINITY;
         float mx = s;
-        mx = fmaxf(mx, __shfl_xor(mx, 1));
-        mx = fmaxf(mx, __shfl_xor(mx, 2));
         mx = fmaxf(mx, __shfl_xor(mx, 4));
+        mx = fmaxf(mx, __shfl_xor(mx, 8));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
         const float p = (mx == -INFINITY) ? 0.f : expf(s - mx);        // rows m >= M: nothing visible
         float l = p;
-        l += __shfl_xor(l, 1);
-        l += __shfl_xor(l, 2);
         l += __shfl_xor(l, 4);
-        pn[m][j] = p;
-        if (j == 0) { part_m[AW][m] = mx; part_l[AW][m] = l; }
-    }
-    __syncthreads();
-    if (w == 0) {                                   // wave 0 owns the fewest key units
-        const int m = lane >> 3, j = lane & 7;
-        for (int dd = j; dd < DW; dd += 8) {
-            float o = 0.f;
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) o += pn[m][jj] * vf[jj][dim0 + dd];
-            part_o[AW][m][dd] = o;
+        l += __shfl_xor(l, 8);
+        l += __shfl_xor(l, 16);
+        if (part == 0) {
+            pn[m][j] = p;
+            if (j == 0) { part_m[AW][m] = mx; part_l[AW][m] = l; }
         }
     }
     __syncthreads();
 
-    // ---- merge the 8 + 1 partials in index order, write the B operand of the O projection ----
+    // ---- merge the AW + 1 partials in index order, write the B operand of the O projection ----
     const int KS = H * DH / 32;
     for (int idx = tid; idx < M * DW; idx += AW * 64) {
         const int m = idx / DW, dd = idx % DW;
@@ -317,11 +318,19 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
         for (int p = 0; p <= AW; ++p) mstar = fmaxf(mstar, part_m[p][m]);
         float num = 0.f, den = 0.f;
 #pragma unroll
-        for (int p = 0; p <= AW; ++p) {
+        for (int p = 0; p < AW; ++p) {
             const float pm = part_m[p][m];
-            const float wg = (pm == -INFINITY) ? 0.f : expf(pm - mstar);
+            const float wg = (pm == -INFINITY) ? 0.f : exp_neg(pm - mstar);
             den += wg * part_l[p][m];
             num += wg * part_o[p][m][dd];
+        }
+        {
+            float o = 0.f;
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) o += pn[m][jj] * vf[jj][dim0 + dd];
+            const float wg = exp_neg(part_m[AW][m] - mstar);           // every query sees itself
+            den += wg * part_l[AW][m];
+            num += wg * o;
         }
         uint16_t t3[kTerms];
         split3(num / den, t3);
