@@ -3,14 +3,45 @@
 
 namespace spd {
 
+constexpr int kXcds = 8;
+
+// The share of a prefetching workgroup (index `id` >= `own` of `all`): of the tiles of its XCD, over all matrices, every n-th
+// for the n prefetching workgroups on that XCD; read and dropped.
+template <int THREADS>
+__device__ __forceinline__ void prefetch_tiles(const WeightPrefetch &pf, int id, int own, int all) {
+    const int xcd = id % kXcds, first = own + (xcd - own % kXcds + kXcds) % kXcds;
+    const int n = (all - first + kXcds - 1) / kXcds;
+    int at = (id - first) / kXcds;                          // position in the run of this XCD's tiles
+    for (int k = 0; k < pf.n; ++k) {
+        const int mine = (pf.m[k].tiles - xcd + kXcds - 1) / kXcds;
+        for (; at < mine; at += n) {
+            const uint4 *src = reinterpret_cast<const uint4 *>((const char *)pf.m[k].w + (size_t)(xcd + kXcds * at) * pf.m[k].tile_bytes);
+            const int quads = pf.m[k].tile_bytes / 16;
+            for (int o = threadIdx.x; o < quads; o += 4 * THREADS) {
+                uint4 v[4];                                 // four loads under way (beyond the tile: its last quad again)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = src[min(o + i * THREADS, quads - 1)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(v[i].x), "v"(v[i].y), "v"(v[i].z), "v"(v[i].w));
+            }
+        }
+        at -= mine;
+    }
+}
+
 template <int DH, int DS, int AW, int QG>
-__global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a) {
+__global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPrefetch pf) {
+    if ((int)blockIdx.z >= a.n_seqs) {
+        const int id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+        prefetch_tiles<AW * 64>(pf, id, gridDim.x * gridDim.y * a.n_seqs, gridDim.x * gridDim.y * gridDim.z);
+        return;
+    }
     // head index fastest: consecutive workgroups go to consecutive XCDs, so with a head count that is
     // a multiple of 8 all slices of one head share an XCD and its L2 holds that head's K once
     attention_core<DH, DS, AW, kUnitsPerIter, false, QG>(a, blockIdx.x, blockIdx.y, blockIdx.z, [] {});
 }
 
-hipError_t launch_attention(const AttnArgs &a, hipStream_t stream) {
+hipError_t launch_attention(const AttnArgs &a, const WeightPrefetch &pf, hipStream_t stream) {
     if (a.M < 1 || a.M > kMaxRows || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
     if (a.Mq < 1 || a.Mq > 8 || a.m0 < 0 || a.m0 + a.Mq > a.M || a.M > a.max_positions) return hipErrorInvalidValue;
     // Workgroups per head (slices of the head dimension).  One sequence: 16 output dimensions per
@@ -25,12 +56,21 @@ hipError_t launch_attention(const AttnArgs &a, hipStream_t stream) {
     if (slices != 1 && slices != 2 && slices != 4 && slices != 8) slices = pairs > 128 ? 1 : (pairs > 64 ? 2 : (pairs > 32 ? 4 : 8));
     if (slices == 1 && a.Mq > kGroupRows) slices = 2;   // two query groups and a whole head do not fit the registers
     // up to 5 queries per sequence: one query group; 6..8: two groups share the cached keys' registers
+    // Prefetching workgroups: whole (head, slice) planes of the grid, at least kPrefetchWgs together, where attention leaves at
+    // least half of the CUs idle.  12-layer draft, one sequence (48 workgroups): attention 5.9 -> 6.2 us, the projections
+    // behind it 18.3 -> 16.0 per layer, draft step 301 -> 285.  4-layer draft, 8 sequences (256 workgroups): attention
+    // 18.7 -> 23.0, projections 25.1 -> 20.6: nothing gained, so not there.  From the O projection's idle CUs instead: O itself
+    // 1 to 3 us slower, no gain.
+    constexpr int kPrefetchWgs = 192;
 #define SPD_ATTN(DH_, DS_, AW_)                                                                                              \
     do {                                                                                                                     \
+        const int plane = a.H * DS_;                                                                                         \
+        const int planes = pf.n > 0 && plane * a.n_seqs <= 128 ? (kPrefetchWgs + plane - 1) / plane : 0;                     \
+        const dim3 grid(a.H, DS_, a.n_seqs + planes);                                                                        \
         if (a.Mq <= kGroupRows)                                                                                              \
-            hipLaunchKernelGGL((attention_kernel<DH_, DS_, AW_, 1>), dim3(a.H, DS_, a.n_seqs), dim3(AW_ * 64), 0, stream, a); \
+            hipLaunchKernelGGL((attention_kernel<DH_, DS_, AW_, 1>), grid, dim3(AW_ * 64), 0, stream, a, pf);                \
         else                                                                                                                 \
-            hipLaunchKernelGGL((attention_kernel<DH_, DS_, 8, 2>), dim3(a.H, DS_, a.n_seqs), dim3(8 * 64), 0, stream, a);    \
+            hipLaunchKernelGGL((attention_kernel<DH_, DS_, 8, 2>), grid, dim3(8 * 64), 0, stream, a, pf);                    \
     } while (0)
     if (a.dh == 128 && slices == 1) {
         SPD_ATTN(128, 1, 8);

@@ -113,7 +113,15 @@ struct AttnArgs {
                              // works on a clamped length: wrong results, but every access stays in bounds)
     SeqLens lens;            // KV length of every sequence before this call
 };
-hipError_t launch_attention(const AttnArgs &a, hipStream_t stream);
+// Weight matrices that the following launches read, to be brought into the L2 caches by workgroups on the CUs that attention
+// leaves idle.  Tile t of a matrix (16 rows, `tile_bytes` contiguous bytes, a multiple of 1024) is read by workgroup t of its
+// projection, and workgroup i of any launch runs on XCD i % 8: so does the workgroup that fetches it.  (Where that does not
+// hold the fetch only misses its purpose.)
+struct WeightPrefetch {
+    struct { const void *w; int tiles, tile_bytes; } m[4];
+    int n;                   // matrices; 0: none
+};
+hipError_t launch_attention(const AttnArgs &a, const WeightPrefetch &pf, hipStream_t stream);
 
 // ---- QKV projection and attention in one kernel (one row group, one sequence, K = 4096, head_dim 128) ----
 // One workgroup per (head, 16 output dimensions) computes the three 16-row tiles of the fused

@@ -488,6 +488,10 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
     at.v_stride = L.v_stride;
     at.slices = m->attn_slices;
 
+    // Small models, few rows: a projection lasts about as long as its first loads take, so the weights of the next ones are
+    // brought into L2 meanwhile.  A layer has to fit the L2s (8 x 4 MiB) next to everything else.
+    const size_t layer_bytes = packed_matrix_bytes(3 * HD, d) + packed_matrix_bytes(d, HD) + packed_matrix_bytes(2 * F, d) + packed_matrix_bytes(d, F);
+    const bool prefetch = rows <= 2 * kGroupRows && layer_bytes <= ((size_t)26 << 20);
     const bool fused = m->fuse_qa && n_seqs == 1 && (rows <= kGroupRows || (rows <= 8 && m->fuse_qa2));   // shapes checked at creation
     for (int l = 0; l < c.n_layers; ++l) {
         // RMSNorm is folded into the projections: the producer of h (input rows / O / down
@@ -511,9 +515,17 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
             g.W = m->packed + L.wqkv[l]; g.X = xn; g.N = 3 * HD; g.K = d; g.rows = rows; g.Y = qkv; g.ldy = 3 * HD;
             g.ssq_in = ssq_b; g.ssq_in_parts = (l == 0) ? 1 : d_tiles; g.eps = c.rms_eps;
             PROF_GEMM(PK_QKV, launch_gemm(g, EPI_STORE, m->t_qkv, st));
+            WeightPrefetch pf{};
+            if (prefetch) {
+                auto add = [&](size_t off, int N, int K) { pf.m[pf.n].w = m->packed + off; pf.m[pf.n].tiles = N / 16; pf.m[pf.n++].tile_bytes = (K + 31) / 32 * 1024; };
+                add(L.wo[l], d, HD);
+                add(L.wgu[l], 2 * F, d);
+                add(L.wdown[l], d, F);
+                if (l + 1 < c.n_layers) add(L.wqkv[l + 1], 3 * HD, d);
+            }
             for (int m0 = 0; m0 < M; m0 += 8) {         // at most 8 queries per sequence and launch
                 at.m0 = m0; at.Mq = std::min(8, M - m0);
-                PROF_TRY(PK_ATTENTION, launch_attention(at, st));
+                PROF_TRY(PK_ATTENTION, launch_attention(at, m0 == 0 ? pf : WeightPrefetch{}, st));
             }
         }
         g = GemmArgs{};
