@@ -1,4 +1,6 @@
 // Stand-alone attention kernel: RoPE + KV-cache append + causal attention (see attention_core.h).
+#include <algorithm>
+
 #include "attention_core.h"
 
 namespace spd {
@@ -29,7 +31,8 @@ __device__ __forceinline__ void prefetch_tiles(const WeightPrefetch &pf, int id,
     }
 }
 
-template <int DH, int DS, int AW, int QG>
+// grid: heads, slices x runs of keys, sequences (and planes of prefetching workgroups behind them)
+template <int DH, int DS, int AW, int QG, int KSP>
 __global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPrefetch pf) {
     if ((int)blockIdx.z >= a.n_seqs) {
         const int id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
@@ -38,8 +41,12 @@ __global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPr
     }
     // head index fastest: consecutive workgroups go to consecutive XCDs, so with a head count that is
     // a multiple of 8 all slices of one head share an XCD and its L2 holds that head's K once
-    attention_core<DH, DS, AW, kUnitsPerIter, false, QG>(a, blockIdx.x, blockIdx.y, blockIdx.z, [] {});
+    attention_core<DH, DS, AW, kUnitsPerIter, false, QG, KSP>(a, blockIdx.x, KSP == 1 ? blockIdx.y : blockIdx.y % DS, KSP == 1 ? 0 : blockIdx.y / DS, blockIdx.z, [] {});
 }
+
+constexpr int kAttnRuns = 4;
+// at most 64 (sequence, head) pairs; a run's result is [8][dh] sums and 16 statistics
+size_t attention_partial_bytes(int dh) { return (size_t)64 * kAttnRuns * (8 * dh + 16) * sizeof(float); }
 
 hipError_t launch_attention(const AttnArgs &a, const WeightPrefetch &pf, hipStream_t stream) {
     if (a.M < 1 || a.M > kMaxRows || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
@@ -68,10 +75,23 @@ hipError_t launch_attention(const AttnArgs &a, const WeightPrefetch &pf, hipStre
         const int planes = pf.n > 0 && plane * a.n_seqs <= 128 ? (kPrefetchWgs + plane - 1) / plane : 0;                     \
         const dim3 grid(a.H, DS_, a.n_seqs + planes);                                                                        \
         if (a.Mq <= kGroupRows)                                                                                              \
-            hipLaunchKernelGGL((attention_kernel<DH_, DS_, AW_, 1>), grid, dim3(AW_ * 64), 0, stream, a, pf);                \
+            hipLaunchKernelGGL((attention_kernel<DH_, DS_, AW_, 1, 1>), grid, dim3(AW_ * 64), 0, stream, a, pf);                \
         else                                                                                                                 \
-            hipLaunchKernelGGL((attention_kernel<DH_, DS_, 8, 2>), grid, dim3(8 * 64), 0, stream, a, pf);                    \
+            hipLaunchKernelGGL((attention_kernel<DH_, DS_, 8, 2, 1>), grid, dim3(8 * 64), 0, stream, a, pf);                    \
     } while (0)
+    // Where 4 slices of a head would all score all keys of a long cache, its keys are cut into 4 runs instead, if they pay for the
+    // exchange of the runs' results (about 4 us, more with more queries).  Per layer, runs / slices, 64 pairs: 4-layer
+    // draft, one query, 512 positions 35.7 / 35.6 us, 1000 38.5 / 40.5, 2000 44.1 / 49.4; five queries, 1000 70.8 / 71.1,
+    // 2000 77.1 / 80.2.  Two runs instead of two slices (65 to 128 pairs) gain 1 us at 1500 positions and lose 3 below 1000.
+    int longest = 0;
+    for (int q = 0; q < a.n_seqs; ++q) longest = std::max(longest, a.lens.len[q]);       // (an upper bound with device lengths)
+    if (a.slices == 0 && a.partials && a.arrive && pairs > 32 && pairs <= 64 && a.Mq <= kGroupRows && a.m0 == 0 && longest >= 512 + 96 * a.Mq) {
+        const dim3 grid(a.H, kAttnRuns, a.n_seqs);
+        if (a.dh == 128) hipLaunchKernelGGL((attention_kernel<128, 1, 8, 1, kAttnRuns>), grid, dim3(8 * 64), 0, stream, a, WeightPrefetch{});
+        else if (a.dh == 64) hipLaunchKernelGGL((attention_kernel<64, 1, kAttnWaves, 1, kAttnRuns>), grid, dim3(kAttnWaves * 64), 0, stream, a, WeightPrefetch{});
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
     if (a.dh == 128 && slices == 1) {
         SPD_ATTN(128, 1, 8);
     } else if (a.dh == 128 && slices == 2) {

@@ -69,8 +69,11 @@ __device__ __forceinline__ uint32_t pack2(uint16_t lo, uint16_t hi) { return (ui
 // before the new rows are read: the place to wait for their producer.
 // QG: query groups of 5 handled by one launch (1: up to 5 new rows per sequence, 2: up to 8; the
 // cached keys are then multiplied with both groups from the same registers).
-template <int DH, int DS, int AW, int UPI, bool DEV, int QG, class ReadyFn>
-__device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, const int ds, const int seq, ReadyFn rows_ready) {
+// KSP > 1: the cached keys are cut into KSP contiguous runs of units, one workgroup (index ks) each.  Every one leaves its
+// unnormalised result in a.partials and takes a ticket; the last of the KSP to arrive (nobody waits) combines them in
+// order.  The new rows belong to run 0.
+template <int DH, int DS, int AW, int UPI, bool DEV, int QG, int KSP, class ReadyFn>
+__device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, const int ds, const int ks, const int seq, ReadyFn rows_ready) {
     constexpr int HALF = DH / 2;
     constexpr int NC = DH / 32;                   // 32-dim chunks of a key row
     constexpr int DW = DH / DS;                   // output dims of this workgroup
@@ -104,7 +107,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
 
     // ---- key units of this wave; first iteration's loads go out before anything else --------
     const int n_units = (P + 31) / 32;
-    const int u_begin = (n_units * w) / AW, u_end = (n_units * (w + 1)) / AW;
+    const int run0 = (n_units * ks) / KSP, run_n = (n_units * (ks + 1)) / KSP - run0;      // this workgroup's run of units
+    const int u_begin = run0 + (run_n * w) / AW, u_end = run0 + (run_n * (w + 1)) / AW;
 
     uint4 kreg[UPI][2][NC], vreg[UPI][NDT];
     auto issue_loads = [&](int u0) {
@@ -132,6 +136,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     issue_loads(u_begin);
     rows_ready();
 
+    const bool own = KSP == 1 || ks == 0;         // the new rows belong to run 0
     // ---- RoPE on q, k of the new rows; bf16 rounding of new k, v; cache append ------------
     {
         const float scale = 1.0f / sqrtf((float)DH);
@@ -144,8 +149,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 const float c = a.rope[((size_t)pos * HALF + j) * 2 + 0];
                 const float s = a.rope[((size_t)pos * HALF + j) * 2 + 1];
                 const float q1 = ldf<DEV>(row + j), q2 = ldf<DEV>(row + j + HALF);
-                const float k1 = ldf<DEV>(row + HD + j), k2 = ldf<DEV>(row + HD + j + HALF);
-                const float v1 = ldf<DEV>(row + 2 * HD + j), v2 = ldf<DEV>(row + 2 * HD + j + HALF);
+                const float k1 = own ? ldf<DEV>(row + HD + j) : 0.f, k2 = own ? ldf<DEV>(row + HD + j + HALF) : 0.f;
+                const float v1 = own ? ldf<DEV>(row + 2 * HD + j) : 0.f, v2 = own ? ldf<DEV>(row + 2 * HD + j + HALF) : 0.f;
                 qa = (q1 * c - q2 * s) * scale;
                 qc = (q2 * c + q1 * s) * scale;
                 const uint16_t kb1 = f32_to_bf16_bits(k1 * c - k2 * s);
@@ -155,7 +160,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 kf[i][j + HALF] = bf16_bits_to_f32(kb2);
                 vf[i][j] = bf16_bits_to_f32(vb1);
                 vf[i][j + HALF] = bf16_bits_to_f32(vb2);
-                if (ds == 0) {                                         // one workgroup of the head appends
+                if (ds == 0 && own) {                                  // one workgroup of the head appends
                     Kc[(size_t)pos * DH + j] = kb1;
                     Kc[(size_t)pos * DH + j + HALF] = kb2;
                     Vt[((size_t)(pos >> 5) * DH + j) * 32 + (pos & 31)] = vb1;
@@ -279,7 +284,9 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     // ---- the M new keys (causal among the new rows), float32 from LDS -----------------------
     // Two queries per wave on the first four waves: lane = quarter of the dimensions, key j, query.  (One lane per (query,
     // key) on one wave walked the dimensions in a chain of conflicting reads while every other wave waited.)
-    if (w < 4) {
+    if (!own) {
+        if (tid < 8) { part_m[AW][tid] = -INFINITY; part_l[AW][tid] = 0.f; }
+    } else if (w < 4) {
         const int part = lane & 3, j = (lane >> 2) & 7, m = 2 * w + (lane >> 5);
         float s = 0.f;
         if (m < M && j <= m) {
@@ -311,6 +318,9 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
 
     // ---- merge the AW + 1 partials in index order, write the B operand of the O projection ----
     const int KS = H * DH / 32;
+    constexpr int kPart = 8 * DW + 16;            // floats of a partial result: [8][DW] sums, 8 maxima, 8 denominators
+    const size_t group = pair * DS + ds;
+    float *mine = KSP > 1 ? a.partials + (group * KSP + ks) * kPart : nullptr;
     for (int idx = tid; idx < M * DW; idx += AW * 64) {
         const int m = idx / DW, dd = idx % DW;
         float mstar = -INFINITY;
@@ -324,7 +334,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
             den += wg * part_l[p][m];
             num += wg * part_o[p][m][dd];
         }
-        {
+        if (own) {
             float o = 0.f;
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) o += pn[m][jj] * vf[jj][dim0 + dd];
@@ -332,11 +342,58 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
             den += wg * part_l[AW][m];
             num += wg * o;
         }
+        if constexpr (KSP > 1) {                                       // (a run without units: maximum -inf, sums 0)
+            float *out = mine + m * DW + dd;
+            __hip_atomic_store(out, num, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (dd == 0) {
+                __hip_atomic_store(mine + 8 * DW + m, mstar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(mine + 8 * DW + 8 + m, den, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            continue;
+        }
         uint16_t t3[kTerms];
         split3(num / den, t3);
         const int row = row_base + m, k = hh * DH + dim0 + dd;
 #pragma unroll
         for (int t = 0; t < kTerms; ++t) ((uint16_t *)a.xout)[xpack_index(row, k, KS, t)] = t3[t];
+    }
+    if (KSP > 1) {
+        __shared__ int is_last;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // the partial result is acknowledged by memory
+        __syncthreads();
+        if (tid == 0) {
+            const unsigned ticket = __hip_atomic_fetch_add(a.arrive + group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            is_last = ticket == (unsigned)(KSP - 1);
+            if (is_last) __hip_atomic_store(a.arrive + group, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+        }
+        __syncthreads();
+        if (!is_last) return;
+        const float *all = a.partials + group * KSP * kPart;
+        for (int idx = tid; idx < M * DW; idx += AW * 64) {
+            const int m = idx / DW, dd = idx % DW;
+            float pm[KSP], pl[KSP], po[KSP];
+#pragma unroll
+            for (int p = 0; p < KSP; ++p) {
+                pm[p] = ldf<true>(all + (size_t)p * kPart + 8 * DW + m);
+                pl[p] = ldf<true>(all + (size_t)p * kPart + 8 * DW + 8 + m);
+                po[p] = ldf<true>(all + (size_t)p * kPart + idx);
+            }
+            float mstar = pm[0];                                       // run 0 holds the query itself: finite
+#pragma unroll
+            for (int p = 1; p < KSP; ++p) mstar = fmaxf(mstar, pm[p]);
+            float num = 0.f, den = 0.f;
+#pragma unroll
+            for (int p = 0; p < KSP; ++p) {
+                const float wg = pm[p] == -INFINITY ? 0.f : exp_neg(pm[p] - mstar);
+                den += wg * pl[p];
+                num += wg * po[p];
+            }
+            uint16_t t3[kTerms];
+            split3(num / den, t3);
+            const int row = row_base + m, k = hh * DH + dim0 + dd;
+#pragma unroll
+            for (int t = 0; t < kTerms; ++t) ((uint16_t *)a.xout)[xpack_index(row, k, KS, t)] = t3[t];
+        }
     }
 }
 

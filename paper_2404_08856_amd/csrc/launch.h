@@ -112,7 +112,10 @@ struct AttnArgs {
     int32_t *d_error;        // set to 1 if a device length does not leave room for M rows (the launch then
                              // works on a clamped length: wrong results, but every access stays in bounds)
     SeqLens lens;            // KV length of every sequence before this call
+    float *partials;         // stand-alone kernel: scratch for results of runs of keys (attention_partial_bytes), or NULL
+    unsigned *arrive;        // counters for them, zero between launches
 };
+size_t attention_partial_bytes(int dh);
 // Weight matrices that the following launches read, to be brought into the L2 caches by workgroups on the CUs that attention
 // leaves idle.  Tile t of a matrix (16 rows, `tile_bytes` contiguous bytes, a multiple of 1024) is read by workgroup t of its
 // projection, and workgroup i of any launch runs on XCD i % 8: so does the workgroup that fetches it.  (Where that does not

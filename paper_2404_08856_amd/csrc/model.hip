@@ -111,7 +111,7 @@ void make_layout(const spd_model_config &c, Layout &L) {
     L.qa_abort = take(4);
     L.ssq_a = take((size_t)(d / 16) * kMaxRows * 4);
     L.ssq_b = take((size_t)(d / 16) * kMaxRows * 4);
-    size_t pb = 0;
+    size_t pb = attention_partial_bytes(c.head_dim);         // (shared: attention and the projections run one after the other)
     for (size_t b : {gemm_batch_scratch_bytes(3 * HD, d), gemm_batch_scratch_bytes(d, HD), gemm_batch_scratch_bytes(2 * F, d),
                      gemm_batch_scratch_bytes(d, F), gemm_batch_scratch_bytes(V, d)})
         pb = b > pb ? b : pb;
@@ -487,6 +487,7 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
     at.n_seqs = n_seqs; at.M = M; at.H = c.n_heads; at.dh = c.head_dim; at.max_positions = c.max_positions;
     at.v_stride = L.v_stride;
     at.slices = m->attn_slices;
+    at.partials = (float *)(m->ws + L.part); at.arrive = (unsigned *)(m->ws + L.arrive);
 
     // Small models, few rows: a projection lasts about as long as its first loads take, so the weights of the next ones are
     // brought into L2 meanwhile.  A layer has to fit the L2s (8 x 4 MiB) next to everything else.

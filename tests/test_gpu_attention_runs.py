@@ -1,0 +1,49 @@
+"""GPU parity of attention over runs of keys (a long cache, 33 to 64 (sequence, head) pairs): lengths on both sides of the rule's
+line, a sequence so short that later runs have no unit, both head sizes, one and five queries, launches repeated on the
+same counters, lengths on the device."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decoder as dec
+from paper_2404_08856_amd import synth
+from tests.helpers import check_logits, oracle_cfg, randomize_gains, to_device
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {"dh128": synth.ModelShape(1, 256, 16, 128, 688, 512), "dh64": synth.ModelShape(1, 256, 13, 64, 688, 512)}
+
+
+@pytest.mark.parametrize("name,lens,M,device_lens", [
+    ("dh128", [1100, 3, 40, 700], 5, False), ("dh128", [607, 1, 600], 1, False), ("dh128", [608, 0, 33], 1, True),
+    ("dh64", [1024, 31, 32, 65], 4, False), ("dh64", [995, 500, 2], 5, True),
+])
+def test_runs_of_keys_against_oracle(name, lens, M, device_lens):
+    from paper_2404_08856_amd import spd
+    shape = SHAPES[name]
+    print(f"attention runs {name} {lens} M {M} device lengths {device_lens}", flush=True)
+    w = randomize_gains(synth.make_weights(shape, 31))
+    wn = synth.weights_to_numpy(w)
+    cfg = oracle_cfg(shape)
+    n = len(lens)
+    model = spd.Model(spd.make_config(shape, n, max(lens) + 3 * M), to_device(w))
+    caches = []
+    for s, length in enumerate(lens):
+        cache = dec.KVCache(cfg, max(lens) + 3 * M)
+        if length:
+            ids = synth.text_tokens(length, shape.vocab, 40 + s)
+            dec.forward_tokens(cfg, wn, cache, ids)
+            model.spd_prefill_tokens(s, torch.from_numpy(ids).cuda())
+        caches.append(cache)
+    if device_lens:
+        model.spd_kv_lens_to_device()
+    out = torch.empty((n, M, shape.vocab), device="cuda")
+    for step in range(2):                    # the second step reads what the first one appended
+        vt = np.stack([synth.text_tokens(M, shape.vocab, 70 + 10 * step + s) for s in range(n)])
+        model.spd_verify_forward(torch.from_numpy(vt).cuda(), out)
+        got = out.cpu().numpy()
+        for s in range(n):
+            check_logits(got[s], dec.forward_tokens(cfg, wn, caches[s], vt[s]), f"{name} step {step} seq {s}")
+    if device_lens:
+        model.spd_kv_lens_from_device()
+    assert model.spd_kv_get_len(n) == [c + 2 * M for c in lens]
