@@ -163,8 +163,9 @@ __device__ __forceinline__ int quad_of(int i) {
 }
 
 // softmax statistics from a row held in registers (same definition as row_stats; the argmax only where it is used)
-template <bool WAVE_MAJOR>
-__device__ void row_stats_regs(const float4 (&v)[kRowVec], bool greedy, float inv_temp, RowStats *out_shared) {
+// KEEP: above temperature 0 the numerators exp((l - max) / temp) take the place of the row's entries.
+template <bool WAVE_MAJOR, bool KEEP, class Row>
+__device__ void row_stats_regs(Row &v, bool greedy, float inv_temp, RowStats *out_shared) {
     __shared__ float s_mx[kSampThreads / 64];
     __shared__ int s_arg[kSampThreads / 64];
     __shared__ float s_sum[kSampThreads / 64];
@@ -210,10 +211,14 @@ __device__ void row_stats_regs(const float4 (&v)[kRowVec], bool greedy, float in
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < kRowVec; ++i) {                       // padding is -inf: exp gives 0
-        sum += softmax_num(v[i].x, mx, inv_temp);
-        sum += softmax_num(v[i].y, mx, inv_temp);
-        sum += softmax_num(v[i].z, mx, inv_temp);
-        sum += softmax_num(v[i].w, mx, inv_temp);
+        const float4 e = {softmax_num(v[i].x, mx, inv_temp), softmax_num(v[i].y, mx, inv_temp),
+                          softmax_num(v[i].z, mx, inv_temp), softmax_num(v[i].w, mx, inv_temp)};
+        sum += e.x;
+        sum += e.y;
+        sum += e.z;
+        sum += e.w;
+        if constexpr (KEEP)
+            if (!greedy) v[i] = e;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
@@ -330,7 +335,7 @@ __global__ __launch_bounds__(kSampThreads) void accept_stats_kernel(AcceptArgs a
     if (row_fits_registers(row, a.vocab)) {
         float4 v[kRowVec];
         load_row(row, a.vocab, -INFINITY, v);
-        row_stats_regs<false>(v, !(a.temperature > 0.f), inv_temp, &st);
+        row_stats_regs<false, false>(v, !(a.temperature > 0.f), inv_temp, &st);
     } else {
         row_stats(row, a.vocab, inv_temp, &st);
     }
@@ -622,13 +627,14 @@ __global__ __launch_bounds__(kSampThreads) void softmax_sample_kernel(const floa
             const int q = quad_of<kRowVec, true>(i);
             v[i] = q < n4 ? reinterpret_cast<const float4 *>(row)[q] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         }
-        row_stats_regs<true>(v, p.mode == 2, inv_temp, &st);
+        row_stats_regs<true, true>(v, p.mode == 2, inv_temp, &st);
         p.st = st; p.inv_sum = 1.0f / st.sum;
 #pragma unroll
         for (int i = 0; i < kRowVec; ++i) {
             const int q = quad_of<kRowVec, true>(i);
             const int x0 = 4 * q;
-            v[i] = float4{p.of(v[i].x, x0), p.of(v[i].y, x0 + 1), p.of(v[i].z, x0 + 2), p.of(v[i].w, x0 + 3)};
+            if (p.mode == 1) v[i] = float4{v[i].x * p.inv_sum, v[i].y * p.inv_sum, v[i].z * p.inv_sum, v[i].w * p.inv_sum};
+            else v[i] = float4{p.of(v[i].x, x0), p.of(v[i].y, x0 + 1), p.of(v[i].z, x0 + 2), p.of(v[i].w, x0 + 3)};
             if (q < n4) reinterpret_cast<float4 *>(out)[q] = v[i];
         }
         SliceSampler<kRowVec> s;
