@@ -947,7 +947,7 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
     k.Xout = (uint16_t *)a.Xout;
     k.KS_out = (a.K_out + 31) / 32;
     const int groups = (a.rows + kGroupRows - 1) / kGroupRows;
-    int waves = tune.waves;
+    int waves = groups > 1 ? tune.waves : tune.waves_few[a.rows > 3];
     if (waves != 4 && waves != 8 && waves != 16) waves = 8;
     if (groups > 1 && waves == 16) waves = 8;            // 16 waves need <= 128 VGPRs: only the 1-group ring fits
     int cap = tune.grid_cap > 0 ? tune.grid_cap : (waves == 4 ? 1024 : (waves == 8 ? 512 : 256));

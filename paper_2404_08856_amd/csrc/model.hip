@@ -150,6 +150,15 @@ GemmTuning default_tuning(int N, int K) {
     else if (tiles >= 1024) t.waves = 4;
     else if (tiles >= 512) t.waves = 8;
     else t.waves = 16;
+    // One row group over a short K: the launch is a chain of latencies, and fewer waves shorten its reduction across waves.
+    // Draft step of the 12-layer shape (d = 768), 4 / 8 / 16 waves for QKV, O and gate|up: 1 sequence 256.1 / 258.6 / 270.1 us,
+    // 3 sequences 294.5 / 295.4 / 306.1, 5 sequences 319.7 / 312.1 / 321.4; its down projection (K = 2048), 4 / 8 waves: 252.9 /
+    // 256.1.  The same order at d = 256, 512, 640, 896 and 2048.  Two row groups (6..10 rows) go best as they are.
+    t.waves_few[0] = t.waves_few[1] = t.waves;
+    if (KS <= 64) {
+        t.waves_few[0] = 4;
+        t.waves_few[1] = (KS == 64 || t.waves == 4) ? 4 : 8;
+    }
     return t;
 }
 
@@ -354,7 +363,7 @@ int32_t spd_model_set_tuning(spd_model *m, const spd_tuning *t) {
     const int Ns[SPD_N_PROJECTIONS] = {3 * HD, d, 2 * F, d, V}, Ks[SPD_N_PROJECTIONS] = {d, HD, d, F, d};
     for (int i = 0; i < SPD_N_PROJECTIONS; ++i) {
         *gt[i] = default_tuning(Ns[i], Ks[i]);
-        if (t->gemm_waves[i]) gt[i]->waves = t->gemm_waves[i];
+        if (t->gemm_waves[i]) gt[i]->waves = gt[i]->waves_few[0] = gt[i]->waves_few[1] = t->gemm_waves[i];
         gt[i]->grid_cap = t->gemm_grid_cap[i];
         if (t->gemm_ring[i]) gt[i]->ring = t->gemm_ring[i];
         gt[i]->no_regb = t->gemm_general_kernel[i] ? 1 : 0;

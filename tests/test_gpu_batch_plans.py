@@ -1,5 +1,6 @@
 """GPU parity of the batched projection kernel's plans: 6 and 8 multiplying waves, one and several K slices with ragged last
-units, two row groups with a long K -- over models whose matrices make the plan come out that way."""
+units, two row groups with a long K; and the wave counts of
+the kernels for one row group over a short K -- over models whose matrices make the plan come out that way."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +12,10 @@ from tests.helpers import check_logits, oracle_cfg, randomize_gains, to_device
 pytestmark = pytest.mark.gpu
 
 SHAPES = {
+    # K = 2048 everywhere: four waves with 16 resident K-steps each at one row group, eight waves at two
+    "k2048": synth.ModelShape(1, 2048, 16, 128, 2048, 1024),
+    # K = 768: waves of 6, 3 or 1.5 K-steps by the number of rows
+    "k768": synth.ModelShape(1, 768, 12, 64, 768, 512),
     # QKV 96 tiles (6 waves: 16 groups), gate|up 172, down K = 1376: 43 steps, the last unit ragged
     "d512": synth.ModelShape(1, 512, 4, 128, 1376, 1040),
     # LM head 258 tiles of 16: 43 groups of 6 or 33 of 8, the last one partly empty
@@ -21,6 +26,8 @@ SHAPES = {
 
 
 @pytest.mark.parametrize("name,n_seqs,M", [("d512", 3, 5), ("d512", 8, 5), ("d512", 8, 8), ("wide_head", 2, 6), ("wide_head", 5, 7),
+                                           ("k2048", 1, 3), ("k2048", 5, 1), ("k2048", 2, 4),
+                                           ("k768", 1, 1), ("k768", 3, 1), ("k768", 4, 1), ("k768", 1, 5), ("k768", 6, 1),
                                            ("long_down", 1, 6), ("long_down", 2, 5), ("long_down", 7, 1), ("long_down", 3, 4)])
 def test_batched_step_against_oracle(name, n_seqs, M):
     from paper_2404_08856_amd import spd
