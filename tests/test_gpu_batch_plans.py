@@ -25,7 +25,7 @@ SHAPES = {
 }
 
 
-@pytest.mark.parametrize("name,n_seqs,M", [("d512", 3, 5), ("d512", 8, 5), ("d512", 8, 8), ("wide_head", 2, 6), ("wide_head", 5, 7),
+@pytest.mark.parametrize("name,n_seqs,M", [("d512", 3, 5), ("d512", 8, 5), ("d512", 8, 8), ("d512", 4, 7), ("d512", 6, 8), ("wide_head", 2, 6), ("wide_head", 5, 7),
                                            ("k2048", 1, 3), ("k2048", 5, 1), ("k2048", 2, 4),
                                            ("k768", 1, 1), ("k768", 3, 1), ("k768", 4, 1), ("k768", 1, 5), ("k768", 6, 1),
                                            ("long_down", 1, 6), ("long_down", 2, 5), ("long_down", 7, 1), ("long_down", 3, 4)])
