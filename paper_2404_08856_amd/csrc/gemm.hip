@@ -391,13 +391,13 @@ static hipError_t launch_multi(const GemmKernelArgs &k, int epilogue, int grid, 
 }
 
 // ---------------------------------------------------------------------------------
-// Batched rows (11..64 rows: several sequences' verify tokens, or a prefill pass)
+// Batched rows (11..64 rows: several sequences' verify tokens or a short prompt; 6..10 rows where K is long)
 // ---------------------------------------------------------------------------------
 // With many row groups the activation operand is as large as a weight tile group (40 rows x K = 4096 x 3
 // terms = 1 MiB), so a kernel whose waves split K re-reads it from L2 for every few tiles and is bound by
-// that traffic, not by HBM.  Here the waves of a workgroup split TILES instead: all 8 waves walk the same
+// that traffic, not by HBM.  Here the waves of a workgroup split TILES instead: all 8 (or 6) waves walk the same
 // K range, each with its own TT tiles, so an activation block is fetched once per workgroup (into LDS, CH
-// K-steps at a time, several chunks ahead) and used by 8 * TT tiles.  No cross-wave reduction is needed.  To keep
+// K-steps at a time, several chunks ahead) and used by 8 (or 6) * TT tiles.  No cross-wave reduction is needed.  To keep
 // enough workgroups for the chip the K range is split ACROSS workgroups (J slices): every workgroup writes
 // its partial tiles to a scratch buffer and counts itself in on its tile group's arrival counter; the one
 // that arrives last (its ticket says so -- nobody ever waits) adds the J partials in slice order and runs
@@ -459,7 +459,7 @@ size_t gemm_batch_scratch_bytes(int N, int K) {
 
 struct BatchArgs { float *partials; unsigned *arrive; int J; const uint4 *zero_block; };
 
-// Two loader waves next to the 8 multiplying waves bring the activation chunks into LDS with LDS-direct loads (no
+// Two loader waves next to the multiplying waves bring the activation chunks into LDS with LDS-direct loads (no
 // registers, asynchronous), NBUF - 1 chunks ahead of the products; a wave can have 63 loads outstanding, which
 // bounds (NBUF - 1) * blocks per loader wave and chunk.
 constexpr int kBatchLoaders = 2;

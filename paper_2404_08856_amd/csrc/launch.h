@@ -61,7 +61,7 @@ struct GemmArgs {
     float *ssq_out;           // [64][N / 16] per-tile sums of squares of h_new
     void *Xout;           // SWIGLU: packed activations with K_out = N / 2 columns
     int K_out;
-    // more than 10 rows: scratch for the partial tiles of the K slices (gemm_batch_scratch_bytes) and the tile
+    // more than 5 rows: scratch for the partial tiles of the K slices (gemm_batch_scratch_bytes) and the tile
     // groups' arrival counters (1024 entries, zero between launches); NULL: the kernels that need neither
     float *batch_partials;
     unsigned *batch_arrive;

@@ -587,7 +587,8 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
     // Slices per sequence: as many as there are words for their totals (2 gamma, none without statistics or where the
     // statistics' argmax is in use) and as run in one round of one workgroup per CU (64 sequences, whole step: 1 slice
     // 29.3 us, 2 slices 31.3, 4 slices 27.8; 8 slices, two rounds, 49).
-    int ns = need_stats && a.temperature > 0.f ? (a.gamma >= 4 ? 8 : (a.gamma >= 2 ? 4 : 2)) : 1;
+    // (the totals are 8-byte words: a workspace aligned to single floats only keeps one slice)
+    int ns = need_stats && a.temperature > 0.f && ((uintptr_t)a.stats & 7) == 0 ? (a.gamma >= 4 ? 8 : (a.gamma >= 2 ? 4 : 2)) : 1;
     while (ns > 1 && (long)a.n_seqs * ns > 256) ns /= 2;
     const dim3 block(kSampThreads);
     if (!fits) hipLaunchKernelGGL(accept_decide_kernel, dim3(a.n_seqs), block, 0, stream, a);
