@@ -133,25 +133,45 @@ __device__ void row_stats(const float *__restrict__ row, int V, float inv_temp, 
 }
 
 // ---------------------------------------------------------------------------------
-// Register-staged fast path: rows of up to 32768 entries (a multiple of 4, 16-byte aligned)
-// are read exactly once, with coalesced 16-byte loads that are all in flight together:
+// Register-staged fast path: rows of up to 32768 entries are read exactly once, with coalesced 16-byte loads that are all in flight together:
 // thread t holds float4 number i * 1024 + t of the row, i < kRowVec.  The generic code above
 // (any vocabulary size) walks the row with dependent loads and is several times slower.
 // ---------------------------------------------------------------------------------
 constexpr int kRowVec = 8;
 
-__device__ __forceinline__ bool row_fits_registers(const float *row, int V) {
-    return (V & 3) == 0 && V <= kRowVec * kSampThreads * 4 && (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+// How a row is read: entry by entry from memory, or once into registers, with or without the alignment.  Rows of no
+// alignment take the registers from 12288 entries on (accept step, one sequence, 32003 entries: 45.3 us from memory, 17 in
+// registers; 9001 entries 16.3 / 18.4).
+enum RowKind { ROW_MEMORY, ROW_ALIGNED, ROW_QUADS };
+__host__ __device__ __forceinline__ RowKind row_kind(const void *row0, const void *row1, int V) {
+    if (V > kRowVec * kSampThreads * 4) return ROW_MEMORY;
+    if ((V & 3) == 0 && (((uintptr_t)row0 | (uintptr_t)row1) & 15) == 0) return ROW_ALIGNED;
+    return V >= 12288 ? ROW_QUADS : ROW_MEMORY;
 }
 
-// entries beyond the row read as `fill`
-__device__ __forceinline__ void load_row(const float *__restrict__ row, int V, float fill, float4 (&v)[kRowVec]) {
-    const int n4 = V >> 2;
-#pragma unroll
-    for (int i = 0; i < kRowVec; ++i) {
-        const int q = i * kSampThreads + (int)threadIdx.x;
-        v[i] = q < n4 ? reinterpret_cast<const float4 *>(row)[q] : float4{fill, fill, fill, fill};
+// Quad q of a row (entries 4 q .. 4 q + 3), `fill` beyond its end.  ALIGNED: the row is 16-byte aligned and a multiple of 4
+// long.  Otherwise it starts at any multiple of 4 bytes and may end with a part of a quad: 16-byte accesses of that
+// alignment, entry by entry at the end (which costs 1 us for one sequence and 4 for 64, so the two are kept apart).
+struct __attribute__((packed, aligned(4))) Quad { float x, y, z, w; };
+template <bool ALIGNED>
+__device__ __forceinline__ float4 load_quad(const float *__restrict__ row, int q, int V, float fill) {
+    if (ALIGNED) return 4 * q < V ? reinterpret_cast<const float4 *>(row)[q] : float4{fill, fill, fill, fill};
+    const int left = V - 4 * q;
+    if (left >= 4) {
+        const Quad v = *reinterpret_cast<const Quad *>(row + 4 * q);
+        return float4{v.x, v.y, v.z, v.w};
     }
+    float4 v = {fill, fill, fill, fill};
+    if (left > 0) v.x = row[4 * q];
+    if (left > 1) v.y = row[4 * q + 1];
+    if (left > 2) v.z = row[4 * q + 2];
+    return v;
+}
+// entries beyond the row read as `fill`
+template <bool ALIGNED>
+__device__ __forceinline__ void load_row(const float *__restrict__ row, int V, float fill, float4 (&v)[kRowVec]) {
+#pragma unroll
+    for (int i = 0; i < kRowVec; ++i) v[i] = load_quad<ALIGNED>(row, i * kSampThreads + (int)threadIdx.x, V, fill);
 }
 
 // quad (group of 4 entries) of the row that register slot i of this thread holds.  WAVE_MAJOR: every wave owns a contiguous
@@ -320,6 +340,7 @@ struct SliceSampler {
     unsigned long long mine;            // this wave's total
 };
 
+template <RowKind KIND>
 __global__ __launch_bounds__(kSampThreads) void accept_stats_kernel(AcceptArgs a) {
     // one workgroup per logits row: target rows first, then draft rows
     const int n_t = a.n_seqs * (a.gamma + 1);
@@ -332,9 +353,9 @@ __global__ __launch_bounds__(kSampThreads) void accept_stats_kernel(AcceptArgs a
     const float *row = is_t ? a.target + (size_t)r * a.vocab : a.draft + (size_t)(r - n_t) * a.vocab;
     const float inv_temp = a.temperature > 0.f ? 1.0f / a.temperature : 1.0f;
     __shared__ RowStats st;
-    if (row_fits_registers(row, a.vocab)) {
+    if constexpr (KIND != ROW_MEMORY) {
         float4 v[kRowVec];
-        load_row(row, a.vocab, -INFINITY, v);
+        load_row<KIND == ROW_ALIGNED>(row, a.vocab, -INFINITY, v);
         row_stats_regs<false, false>(v, !(a.temperature > 0.f), inv_temp, &st);
     } else {
         row_stats(row, a.vocab, inv_temp, &st);
@@ -421,7 +442,7 @@ __device__ __noinline__ int sample_row_slowly(RowProb T, int V, float u, unsigne
     return sample_inverse_cdf(T, V, u, tmp, result);
 }
 
-// Any vocabulary size and alignment: one workgroup per sequence walks the rows from memory.
+// Any vocabulary size: one workgroup per sequence walks the rows from memory.
 __global__ __launch_bounds__(kSampThreads) void accept_decide_kernel(AcceptArgs a) {
     const int seq = blockIdx.x, G = a.gamma, V = a.vocab;
     __shared__ SeqRows rows;
@@ -443,7 +464,7 @@ __global__ __launch_bounds__(kSampThreads) void accept_decide_kernel(AcceptArgs 
     }
 }
 
-// Rows that fit the registers (see row_fits_registers): NS workgroups per sequence, each with a slice of the row to
+// Rows that fit the registers (see row_kind): NS workgroups per sequence, each with a slice of the row to
 // draw from, read once.  Every slice adds up its fixed-point weights, publishes the total and takes a ticket; the last
 // one to arrive finds the slice the threshold falls into, reads that slice again and searches it.  The totals are
 // integers: the result does not depend on the number of slices.
@@ -455,7 +476,7 @@ __global__ __launch_bounds__(kSampThreads) void accept_decide_kernel(AcceptArgs 
 // Bound by a chain of dependent round trips (statistics and tokens, drafted entries, total, ticket, totals, the hit slice),
 // no longer by one CU's vector instructions: 10.8 us for one sequence (one workgroup: 14.4), 12.9 for 64 (18.9).
 constexpr int kEarlyGamma = 7;
-template <int NS, bool EARLY>
+template <int NS, bool EARLY, bool ALIGNED>
 __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(AcceptArgs a) {
     constexpr int NV = kRowVec / NS;
     const int seq = blockIdx.x / NS, slice = blockIdx.x % NS, G = a.gamma, V = a.vocab;
@@ -465,14 +486,15 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
     __shared__ int is_last;
     const SeqView q(a, rows, seq);
     const float u_last = a.u[seq * (G + 1) + G];
-    const int n4 = V >> 2, per = (n4 + NS - 1) / NS;          // quads of a slice
+    const int n4 = (V + 3) >> 2, per = (n4 + NS - 1) / NS;    // quads of the row (the last one may be a part), of a slice
     float4 t[NV], d[NV];
-    auto load = [&](const float *row, int sl, float4 (&v)[NV]) __attribute__((always_inline)) {
+    // (entries beyond the row: probability 0 in every mode; quads beyond the slice are cleared below)
+    auto load = [&](const float *row, int mode, int sl, float4 (&v)[NV]) __attribute__((always_inline)) {
         const int q0 = sl * per, q1 = min(n4, q0 + per);
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int qi = q0 + quad_of<NV, true>(i);
-            v[i] = qi < q1 ? reinterpret_cast<const float4 *>(row)[qi] : float4{0.f, 0.f, 0.f, 0.f};
+            v[i] = load_quad<ALIGNED>(row, qi < q1 ? qi : n4, V, ALIGNED || mode == 0 ? 0.f : -INFINITY);
         }
     };
     int k;
@@ -480,8 +502,8 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
         float4 te[kEarlyGamma + 1][NV], de[kEarlyGamma][NV];
 #pragma unroll
         for (int j = 0; j <= kEarlyGamma; ++j) {
-            if (j <= G) load(q.t_ptr(j), slice, te[j]);
-            if (j < kEarlyGamma && j < G) load(q.d_ptr(j), slice, de[j]);
+            if (j <= G) load(q.t_ptr(j), q.t_mode, slice, te[j]);
+            if (j < kEarlyGamma && j < G) load(q.d_ptr(j), q.d_mode, slice, de[j]);
         }
         k = q.accepted(slice == 0);
 #pragma unroll
@@ -495,8 +517,8 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
             }
     } else {
         k = q.accepted(slice == 0);
-        load(q.t_ptr(k), slice, t);
-        if (k < G) load(q.d_ptr(k), slice, d);
+        load(q.t_ptr(k), q.t_mode, slice, t);
+        if (k < G) load(q.d_ptr(k), q.d_mode, slice, d);
     }
     const RowProb T = q.t_row(k), D = k < G ? q.d_row(k) : T;
     // the values of the distribution to draw from: residual max(0, T - D), or the bonus row
@@ -553,8 +575,8 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
             run += tot[i];
         }
         if (hit == slice) break;
-        load(T.row, hit, t);
-        if (k < G) load(D.row, hit, d);
+        load(T.row, q.t_mode, hit, t);
+        if (k < G) load(D.row, q.d_mode, hit, d);
     }
     int y = -1;
     if (S != 0) {
@@ -578,12 +600,14 @@ size_t accept_workspace_bytes(int n_seqs, int gamma) {
 
 hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
     if (a.gamma < 1 || a.gamma > 63) return hipErrorInvalidValue;
+    const RowKind kind = row_kind(a.target, a.draft, a.vocab);
     const bool need_stats = ((a.flags & 3u) != 3u);
     if (need_stats) {
         int n_rows = a.n_seqs * (2 * a.gamma + 1);
-        hipLaunchKernelGGL(accept_stats_kernel, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
+        if (kind == ROW_ALIGNED) hipLaunchKernelGGL(accept_stats_kernel<ROW_ALIGNED>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
+        else if (kind == ROW_QUADS) hipLaunchKernelGGL(accept_stats_kernel<ROW_QUADS>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
+        else hipLaunchKernelGGL(accept_stats_kernel<ROW_MEMORY>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
     }
-    const bool fits = (a.vocab & 3) == 0 && a.vocab <= kRowVec * kSampThreads * 4 && (((uintptr_t)a.target | (uintptr_t)a.draft) & 15) == 0;
     // Slices per sequence: as many as there are words for their totals (2 gamma, none without statistics or where the
     // statistics' argmax is in use) and as run in one round of one workgroup per CU (64 sequences, whole step: 1 slice
     // 29.3 us, 2 slices 31.3, 4 slices 27.8; 8 slices, two rounds, 49).
@@ -591,12 +615,18 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
     int ns = need_stats && a.temperature > 0.f && ((uintptr_t)a.stats & 7) == 0 ? (a.gamma >= 4 ? 8 : (a.gamma >= 2 ? 4 : 2)) : 1;
     while (ns > 1 && (long)a.n_seqs * ns > 256) ns /= 2;
     const dim3 block(kSampThreads);
-    if (!fits) hipLaunchKernelGGL(accept_decide_kernel, dim3(a.n_seqs), block, 0, stream, a);
-    else if (ns == 8 && a.gamma <= kEarlyGamma) hipLaunchKernelGGL((accept_decide_slices_kernel<8, true>), dim3(a.n_seqs * 8), block, 0, stream, a);
-    else if (ns == 8) hipLaunchKernelGGL((accept_decide_slices_kernel<8, false>), dim3(a.n_seqs * 8), block, 0, stream, a);
-    else if (ns == 4) hipLaunchKernelGGL((accept_decide_slices_kernel<4, false>), dim3(a.n_seqs * 4), block, 0, stream, a);
-    else if (ns == 2) hipLaunchKernelGGL((accept_decide_slices_kernel<2, false>), dim3(a.n_seqs * 2), block, 0, stream, a);
-    else hipLaunchKernelGGL((accept_decide_slices_kernel<1, false>), dim3(a.n_seqs), block, 0, stream, a);
+#define SPD_SLICES(NS_, EARLY_)                                                                                                             \
+    do {                                                                                                                                   \
+        if (kind == ROW_ALIGNED) hipLaunchKernelGGL((accept_decide_slices_kernel<NS_, EARLY_, true>), dim3(a.n_seqs * NS_), block, 0, stream, a); \
+        else hipLaunchKernelGGL((accept_decide_slices_kernel<NS_, EARLY_, false>), dim3(a.n_seqs * NS_), block, 0, stream, a);              \
+    } while (0)
+    if (kind == ROW_MEMORY) hipLaunchKernelGGL(accept_decide_kernel, dim3(a.n_seqs), block, 0, stream, a);
+    else if (ns == 8 && a.gamma <= kEarlyGamma) SPD_SLICES(8, true);
+    else if (ns == 8) SPD_SLICES(8, false);
+    else if (ns == 4) SPD_SLICES(4, false);
+    else if (ns == 2) SPD_SLICES(2, false);
+    else SPD_SLICES(1, false);
+#undef SPD_SLICES
     return hipGetLastError();
 }
 
@@ -620,14 +650,10 @@ __global__ __launch_bounds__(kSampThreads) void softmax_sample_kernel(const floa
     RowProb p;
     p.row = row; p.inv_temp = inv_temp; p.mode = temperature > 0.f ? 1 : 2;
     int y;
-    if (row_fits_registers(row, V) && row_fits_registers(out, V)) {
-        const int n4 = V >> 2;
+    if (row_kind(row, out, V) == ROW_ALIGNED) {
         float4 v[kRowVec];
 #pragma unroll
-        for (int i = 0; i < kRowVec; ++i) {
-            const int q = quad_of<kRowVec, true>(i);
-            v[i] = q < n4 ? reinterpret_cast<const float4 *>(row)[q] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        }
+        for (int i = 0; i < kRowVec; ++i) v[i] = load_quad<true>(row, quad_of<kRowVec, true>(i), V, -INFINITY);
         row_stats_regs<true, true>(v, p.mode == 2, inv_temp, &st);
         p.st = st; p.inv_sum = 1.0f / st.sum;
 #pragma unroll
@@ -636,7 +662,7 @@ __global__ __launch_bounds__(kSampThreads) void softmax_sample_kernel(const floa
             const int x0 = 4 * q;
             if (p.mode == 1) v[i] = float4{v[i].x * p.inv_sum, v[i].y * p.inv_sum, v[i].z * p.inv_sum, v[i].w * p.inv_sum};
             else v[i] = float4{p.of(v[i].x, x0), p.of(v[i].y, x0 + 1), p.of(v[i].z, x0 + 2), p.of(v[i].w, x0 + 3)};
-            if (q < n4) reinterpret_cast<float4 *>(out)[q] = v[i];
+            if (4 * q < V) reinterpret_cast<float4 *>(out)[q] = v[i];
         }
         SliceSampler<kRowVec> s;
         s.weigh(v);

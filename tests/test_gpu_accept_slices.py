@@ -1,7 +1,7 @@
 """The accept step's sliced draw against the oracle where its dispatch changes: 1, 2, 4 or 8 slices by draft length and
 batch size, rows loaded early up to draft length 7, slices emptier than others (small and ragged vocabularies), each
-mix of logit and probability inputs, the generic kernel next to them (vocabularies that are not a multiple of 4, rows
-that are not 16-byte aligned)."""
+mix of logit and probability inputs, rows that end in a part of a quad or are not 16-byte aligned, and the generic kernel
+next to them (vocabularies beyond 32768)."""
 import numpy as np
 import pytest
 import torch
@@ -53,7 +53,7 @@ def test_slices_by_draft_length_and_batch(gamma, n_seqs):
     check(1024, gamma, n_seqs, False, False, 1.0, repeat=2)
 
 
-@pytest.mark.parametrize("V", [4, 16, 36, 1000, 4096, 4100, 32000, 32764, 32768, 4099, 32772])
+@pytest.mark.parametrize("V", [1, 2, 3, 4, 5, 16, 36, 1000, 4096, 4097, 4098, 4099, 4100, 32000, 32003, 32764, 32767, 32768, 32769, 32772])
 def test_slices_by_vocabulary(V):
     check(V, 4, 2, False, False, 1.0)
 
@@ -64,5 +64,7 @@ def test_slices_by_kind_of_input(target_probs, draft_probs, temp):
     check(2048, 4, 3, target_probs, draft_probs, temp, repeat=2)
 
 
-def test_rows_that_are_not_16_byte_aligned():
-    check(2048, 4, 3, False, False, 1.0, misalign=True)
+@pytest.mark.parametrize("V", [2048, 2047, 32765])
+def test_rows_that_are_not_16_byte_aligned(V):
+    check(V, 4, 3, False, False, 1.0, misalign=True)
+    check(V, 1, 2, False, True, 1.0, misalign=True)
