@@ -1,6 +1,8 @@
 // Measurement aid, not part of the method: plain streaming-read kernels of given sizes, back to back on one
 // stream, to establish what the chip gives a kernel chain that does nothing but read -- the ceiling the
 // projection kernels of a verify step are compared with.
+#include <chrono>
+
 #include <hip/hip_runtime.h>
 
 #include <vector>
@@ -68,8 +70,12 @@ extern "C" int32_t spd_probe_read_chain(const void *buffer, size_t buffer_bytes,
             base += h_stage_bytes[i];
         }
     };
-    run_chain(false);
-    run_chain(false);
+    // after an idle gap the device takes about 0.2 s of work to reach its steady clocks
+    const auto began = std::chrono::steady_clock::now();
+    do {
+        for (int i = 0; i < 16; ++i) run_chain(false);
+        if (hipStreamSynchronize(st) != hipSuccess) { rc = SPD_ERR_HIP; break; }
+    } while (std::chrono::steady_clock::now() - began < std::chrono::milliseconds(300));
     // (a) the chain as a whole, untimed launches
     if (hipEventRecord(c0, st) != hipSuccess) rc = SPD_ERR_HIP;
     for (int r = 0; r < reps; ++r) run_chain(false);
