@@ -239,7 +239,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 const float m_new = fmaxf(m_run[qg], mx);              // finite: a unit has >= 1 valid key
-                const float rescale = (m_run[qg] == -INFINITY) ? 0.f : exp_neg(m_run[qg] - m_new);
+                const float rescale = (m_run[qg] == -INFINITY) ? 0.f : expf(m_run[qg] - m_new);   // NaN at inf - inf
                 float lsum = 0.f;
                 uint32_t hv[8];
 #pragma unroll
@@ -317,6 +317,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     __syncthreads();
 
     // ---- merge the AW + 1 partials in index order, write the B operand of the O projection ----
+    // (expf here and in the rescaling above, not exp_neg, whose lower bound would turn NaN into a small weight: a score that
+    // overflowed to +inf has to leave NaN, as inf - inf does, and not plausible values)
     const int KS = H * DH / 32;
     constexpr int kPart = 8 * DW + 16;            // floats of a partial result: [8][DW] sums, 8 maxima, 8 denominators
     const size_t group = pair * DS + ds;
@@ -330,7 +332,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
 #pragma unroll
         for (int p = 0; p < AW; ++p) {
             const float pm = part_m[p][m];
-            const float wg = (pm == -INFINITY) ? 0.f : exp_neg(pm - mstar);
+            const float wg = (pm == -INFINITY) ? 0.f : expf(pm - mstar);
             den += wg * part_l[p][m];
             num += wg * part_o[p][m][dd];
         }
@@ -338,7 +340,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
             float o = 0.f;
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) o += pn[m][jj] * vf[jj][dim0 + dd];
-            const float wg = exp_neg(part_m[AW][m] - mstar);           // every query sees itself
+            const float pm = part_m[AW][m];
+            const float wg = (pm == -INFINITY) ? 0.f : expf(pm - mstar);
             den += wg * part_l[AW][m];
             num += wg * o;
         }
@@ -378,13 +381,13 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 pl[p] = ldf<true>(all + (size_t)p * kPart + 8 * DW + 8 + m);
                 po[p] = ldf<true>(all + (size_t)p * kPart + idx);
             }
-            float mstar = pm[0];                                       // run 0 holds the query itself: finite
+            float mstar = pm[0];                                       // run 0 holds the query itself
 #pragma unroll
             for (int p = 1; p < KSP; ++p) mstar = fmaxf(mstar, pm[p]);
             float num = 0.f, den = 0.f;
 #pragma unroll
             for (int p = 0; p < KSP; ++p) {
-                const float wg = pm[p] == -INFINITY ? 0.f : exp_neg(pm[p] - mstar);
+                const float wg = pm[p] == -INFINITY ? 0.f : expf(pm[p] - mstar);
                 den += wg * pl[p];
                 num += wg * po[p];
             }

@@ -1,0 +1,64 @@
+"""Attention scores beyond float32: an overflowed score leaves NaN behind, as inf - inf does in any softmax, and never
+plausible values; one that overflowed to -inf weighs nothing.
+
+The weights are steered so that token 0 is a key that every query of token 1 scores with 8 * a * b and nothing else is
+scored at all; RoPE is the identity on the dimension used (its angle is below 1e-29)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decoder as dec
+from paper_2404_08856_amd import synth
+from tests.helpers import check_logits, oracle_cfg, to_device
+
+pytestmark = pytest.mark.gpu
+
+KEY, QUERY, PLAIN = 0, 1, 2                     # tokens
+
+
+def steered(heads, a, key_b, query_b=0.0, layers=1):
+    """Queries of QUERY: 8 a on one dimension; keys of KEY and QUERY: 8 key_b and 8 query_b on it, all others 0."""
+    shape = synth.ModelShape(layers, 64, heads, 64, 64, 64, rope_theta=1e30)
+    w = synth.make_weights(shape, 3)
+    w["embed"] = torch.zeros(64, 64, dtype=torch.bfloat16)
+    for t in range(64):
+        w["embed"][t, min(t, 2)] = 1.0          # an RMS norm of 1 / 8: the normalised row is 8 on this dimension
+    for lw in w["layers"]:
+        lw["wq"].zero_()
+        lw["wk"].zero_()
+        for h in range(heads):
+            lw["wq"][64 * h + 31, QUERY] = a
+            lw["wk"][64 * h + 31, KEY] = key_b
+            lw["wk"][64 * h + 31, QUERY] = query_b
+    return shape, w
+
+
+def prompt(n, at):
+    ids = np.full(n, PLAIN, dtype=np.int32)
+    ids[at] = KEY
+    return ids
+
+
+# one wave of keys; several units per wave; more pairs than slices; runs of keys (33 to 64 pairs, a long cache); two query groups
+@pytest.mark.parametrize("n_seqs,heads,context,M", [(1, 1, 40, 1), (1, 2, 1500, 1), (2, 65, 200, 1), (5, 8, 900, 1), (1, 2, 1500, 6)])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_cached_key_with_an_overflowed_score(n_seqs, heads, context, M, sign):
+    from paper_2404_08856_amd import spd
+    print(f"overflowed score: {n_seqs} x {heads} heads, context {context}, M {M}, sign {sign}", flush=True)
+    shape, w = steered(heads, 1e19, sign * 1e19)            # 8e38: beyond float32's 3.4e38
+    model = spd.Model(spd.make_config(shape, n_seqs, context + M), to_device(w))
+    ids = prompt(context, context // 3)
+    for s in range(n_seqs):
+        model.spd_prefill_tokens(s, torch.from_numpy(ids).cuda())
+    vt = torch.full((n_seqs, M), QUERY, dtype=torch.int32, device="cuda")
+    out = torch.empty((n_seqs, M, shape.vocab), device="cuda")
+    model.spd_verify_forward(vt, out)
+    if sign > 0:
+        assert torch.isnan(out).all()
+        return
+    cfg, wn = oracle_cfg(shape), synth.weights_to_numpy(w)
+    cache = dec.KVCache(cfg, context + M)
+    dec.forward_tokens(cfg, wn, cache, ids)
+    want = dec.forward_tokens(cfg, wn, cache, np.full(M, QUERY, dtype=np.int32))
+    for s in range(n_seqs):
+        check_logits(out[s].cpu().numpy(), want, f"seq {s}")
