@@ -509,6 +509,17 @@ __device__ __forceinline__ uint32_t finite_pair(uint32_t p) {
     return p;
 }
 
+__device__ __forceinline__ uint32_t exponent_carry(uint32_t p) { return (p & 0x7f807f80u) + 0x00800080u; }
+// A operand of ones where a bf16 value is +inf (or -inf) or NaN, zeros elsewhere (both signs count a NaN: inf - inf again)
+__device__ __forceinline__ uint4 ones_where(const uint4 &q, bool negative) {
+    auto half = [&](uint32_t h) {
+        const bool nan = (h & 0x7fffu) > 0x7f80u;
+        return nan || h == (negative ? 0xff80u : 0x7f80u) ? 0x3f80u : 0u;
+    };
+    auto pair = [&](uint32_t p) { return half(p & 0xffffu) | (half(p >> 16) << 16); };
+    return uint4{pair(q.x), pair(q.y), pair(q.z), pair(q.w)};
+}
+
 constexpr float kHidden = -1.0e30f;    // score of a hidden key: finite, so that differences stay finite, and exp gives exactly 0
 
 // exp(x) for x <= 0 like exp_neg, but NaN stays NaN and very negative arguments give exactly 0
@@ -640,11 +651,19 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
             uint4 vf[NDT];
 #pragma unroll
             for (int i = 0; i < NDT; ++i) vf[i] = S[buf][2 * NC + i][lane];
-            if (diagonal) {                                      // a hidden key's V must not leak through 0 * inf
+            bool odd = false;                                    // wave-uniform: some V of a unit with hidden keys is not finite
+            if (diagonal) {
+                uint32_t top = 0;                                // an exponent of all ones carries into its half's sign bit
 #pragma unroll
-                for (int i = 0; i < NDT; ++i) {
-                    vf[i].x = finite_pair(vf[i].x); vf[i].y = finite_pair(vf[i].y);
-                    vf[i].z = finite_pair(vf[i].z); vf[i].w = finite_pair(vf[i].w);
+                for (int i = 0; i < NDT; ++i)
+                    top |= exponent_carry(vf[i].x) | exponent_carry(vf[i].y) | exponent_carry(vf[i].z) | exponent_carry(vf[i].w);
+                odd = __any((top & 0x80008000u) != 0);
+                if (odd) {                                       // a hidden key's V must not leak through 0 * inf
+#pragma unroll
+                    for (int i = 0; i < NDT; ++i) {
+                        vf[i].x = finite_pair(vf[i].x); vf[i].y = finite_pair(vf[i].y);
+                        vf[i].z = finite_pair(vf[i].z); vf[i].w = finite_pair(vf[i].w);
+                    }
                 }
             }
 #pragma unroll
@@ -654,6 +673,24 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
                 for (int t = kTerms - 1; t >= 0; --t) o = mfma_bf16(vf[i], pb[t].v, o);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[i][v] = __builtin_fmaf(acc[i][v], rescale, o[v]);
+            }
+            if (odd) {                                           // rare: a V that is not finite reaches the queries that see its key
+                uint4 seen = {0, 0, 0, 0};                       // B operand: 1 where this lane's query sees the key
+                const int n_seen = q_pos + 1 - (32 * u + 8 * g); // of the lane's 8 keys
+                uint32_t *sw = reinterpret_cast<uint32_t *>(&seen);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sw[e] = (2 * e < n_seen ? 0x3f80u : 0u) | (2 * e + 1 < n_seen ? 0x3f800000u : 0u);
+#pragma unroll
+                for (int i = 0; i < NDT; ++i) {
+                    const uint4 raw = S[buf][2 * NC + i][lane];
+                    const f32x4_t pos = mfma_bf16(ones_where(raw, false), seen, f32x4_t{0.f, 0.f, 0.f, 0.f});
+                    const f32x4_t neg = mfma_bf16(ones_where(raw, true), seen, f32x4_t{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if (pos[v] > 0.f) acc[i][v] += INFINITY;
+                        if (neg[v] > 0.f) acc[i][v] -= INFINITY;
+                    }
+                }
             }
         }
         buf = buf + 1 == kPaBuf ? 0 : buf + 1;

@@ -1,5 +1,6 @@
 """Attention scores beyond float32: an overflowed score leaves NaN behind, as inf - inf does in any softmax, and never
-plausible values; one that overflowed to -inf weighs nothing.
+plausible values; one that overflowed to -inf weighs nothing.  Values beyond bf16: an infinite V reaches every query that
+sees its key and no other.
 
 The weights are steered so that token 0 is a key that every query of token 1 scores with 8 * a * b and nothing else is
 scored at all; RoPE is the identity on the dimension used (its angle is below 1e-29)."""
@@ -62,3 +63,23 @@ def test_cached_key_with_an_overflowed_score(n_seqs, heads, context, M, sign):
     want = dec.forward_tokens(cfg, wn, cache, np.full(M, QUERY, dtype=np.int32))
     for s in range(n_seqs):
         check_logits(out[s].cpu().numpy(), want, f"seq {s}")
+
+
+@pytest.mark.parametrize("at,n", [(39, 40), (31, 48), (32, 33), (0, 40), (50, 150), (127, 200)])
+def test_an_infinite_value_reaches_the_queries_that_see_it(at, n):
+    """Two layers: keys and values of the second are finite before the row whose first-layer V overflows bf16, and not from there on."""
+    from paper_2404_08856_amd import spd
+    print(f"infinite value at {at} of {n}", flush=True)
+    shape, w = steered(2, 0.0, 0.0, layers=2)
+    w["layers"][0]["wv"][5, KEY] = 2.0 ** 127                   # times 8: one component of V is infinite
+    model = spd.Model(spd.make_config(shape, 1, n), to_device(w))
+    last = torch.empty(shape.vocab, device="cuda")
+    model.spd_prefill_tokens(0, torch.from_numpy(prompt(n, at)).cuda(), last)
+    k, v = (torch.empty((n, shape.n_heads, shape.head_dim), device="cuda") for _ in range(2))
+    model.spd_kv_export(0, 0, 0, k, v)
+    assert torch.isinf(v[at, 0, 5]) and torch.isinf(v).sum() == 1 and torch.isfinite(k).all()
+    model.spd_kv_export(1, 0, 0, k, v)
+    v = v.cpu().numpy()
+    assert np.isfinite(v[:at]).all()
+    assert (~np.isfinite(v[at:])).all()
+    assert not torch.isfinite(last).any()
