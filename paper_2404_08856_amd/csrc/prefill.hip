@@ -520,10 +520,11 @@ __device__ __forceinline__ uint4 ones_where(const uint4 &q, bool negative) {
     return uint4{pair(q.x), pair(q.y), pair(q.z), pair(q.w)};
 }
 
-constexpr float kHidden = -1.0e30f;    // score of a hidden key: finite, so that differences stay finite, and exp gives exactly 0
+constexpr float kLowest = -3.402823466e38f;      // start of the running maximum: below every score but -inf
 
-// exp(x) for x <= 0 like exp_neg, but NaN stays NaN and very negative arguments give exactly 0
+// exp(x) for x <= 0 like exp_neg, but NaN stays NaN and very negative arguments (-inf too) give exactly 0
 __device__ __forceinline__ float exp_score(float x) {
+    x = __builtin_elementwise_maximum(x, -150.0f);
     const float c1 = 1.44269502162933349609375f, c2 = 1.925963033500011e-8f;   // log2(e) = c1 + c2
     const float t = x * c1;
     const float lo = __builtin_fmaf(x, c1, -t) + x * c2;
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
 
     const int q_pos = P0 + row, w_first = P0 + qt * 64 + w * 16, w_last = min(w_first + 15, k_end);
     const bool wave_has_rows = w_first <= k_end;
-    float m_run = kHidden, l_run = 0.f;
+    float m_run = kLowest, l_run = 0.f;
     f32x4_t acc[NDT];
 #pragma unroll
     for (int i = 0; i < NDT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -626,12 +627,12 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
 #pragma unroll
                 for (int ab = 0; ab < 2; ++ab)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) sc[ab][v] = 32 * u + 8 * g + 4 * ab + v > q_pos ? kHidden : sc[ab][v];
+                    for (int v = 0; v < 4; ++v) sc[ab][v] = 32 * u + 8 * g + 4 * ab + v > q_pos ? -INFINITY : sc[ab][v];
             }
             float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])), fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
             mx = max_over_rows(mx);
             const float m_new = fmaxf(m_run, mx);
-            const float rescale = exp_score(m_run - m_new);      // first unit (key 0 is visible to every query): exp(-1e30) = 0
+            const float rescale = exp_score(m_run - m_new);      // (a first unit: 0)
             m_run = m_new;
             float p[8], lsum = 0.f;
 #pragma unroll

@@ -83,3 +83,28 @@ def test_an_infinite_value_reaches_the_queries_that_see_it(at, n):
     assert np.isfinite(v[:at]).all()
     assert (~np.isfinite(v[at:])).all()
     assert not torch.isfinite(last).any()
+
+
+@pytest.mark.parametrize("n", [33, 40, 130])
+@pytest.mark.parametrize("what", ["inf", "minus_inf", "all_very_low"])
+def test_prompt_with_scores_of_any_size(n, what):
+    """The last row's score of one key overflows, or every score of every row is near -1e31 (all values are equal then, so
+    that the softmax of any such scores gives the value)."""
+    from paper_2404_08856_amd import spd
+    print(f"prompt of {n}, scores {what}", flush=True)
+    if what == "all_very_low":
+        shape, w = steered(2, 1.0, 0.0, query_b=-1.25e30)
+        ids = np.full(n, QUERY, dtype=np.int32)
+    else:
+        shape, w = steered(2, 1e19, 1e19 if what == "inf" else -1e19)
+        ids = prompt(n, n // 2)
+        ids[-1] = QUERY
+    model = spd.Model(spd.make_config(shape, 1, n), to_device(w))
+    last = torch.empty(shape.vocab, device="cuda")
+    model.spd_prefill_tokens(0, torch.from_numpy(ids).cuda(), last)
+    if what == "inf":
+        assert torch.isnan(last).all()
+        return
+    cfg, wn = oracle_cfg(shape), synth.weights_to_numpy(w)
+    cache = dec.KVCache(cfg, n)
+    check_logits(last.cpu().numpy(), dec.forward_tokens(cfg, wn, cache, ids)[-1], "last row")
