@@ -993,16 +993,17 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
     // LM head 51 / 91, QKV 28 / 40, O 22 / 23; beyond 40 rows the K-splitting kernel needs a second pass.  Rows 6..10 only
     // where K is too long for resident activations (7B down: 22.3 / 24.1).
     const bool batch_pays = groups > 2 || k.KS > 128;
-    if (a.batch_partials && a.batch_arrive && a.batch_zero && groups > 1 && !tune.no_batch && (batch_pays || tune.force_batch)) {
-        // Row groups the kernel is built for: a group without rows costs the same traffic and products as one with (15 rows
-        // on 3 groups instead of 4, four 7B layers + head: 469 us a step against 478; 48 rows on 10 instead of 13: 702 against 784)
-        int NG = groups <= 4 ? groups : groups <= 6 ? 6 : groups <= 8 ? 8 : groups <= 10 ? 10 : kMaxGroups;
-        BatchPlan p = batch_plan(k.n_tiles, k.KS, NG);
-        if (p.TT == 2) {                                     // very wide matrices: fewer instances
-            NG = groups <= 2 ? 2 : groups <= 4 ? 4 : groups <= 8 ? 8 : kMaxGroups;
-            p = batch_plan(k.n_tiles, k.KS, NG);
-        }
-        if (p.n_tgroups > kBatchMaxTileGroups) return hipErrorInvalidValue;     // more than 256 K output columns
+    // Row groups the kernel is built for: a group without rows costs the same traffic and products as one with (15 rows
+    // on 3 groups instead of 4, four 7B layers + head: 469 us a step against 478; 48 rows on 10 instead of 13: 702 against 784)
+    int NG = groups <= 4 ? groups : groups <= 6 ? 6 : groups <= 8 ? 8 : groups <= 10 ? 10 : kMaxGroups;
+    BatchPlan p = batch_plan(k.n_tiles, k.KS, NG);
+    if (p.TT == 2) {                                         // very wide matrices: fewer instances
+        NG = groups <= 2 ? 2 : groups <= 4 ? 4 : groups <= 8 ? 8 : kMaxGroups;
+        p = batch_plan(k.n_tiles, k.KS, NG);
+    }
+    // (more than 262144 output columns: more tile groups than arrival counters, the K-splitting kernel takes them)
+    if (a.batch_partials && a.batch_arrive && a.batch_zero && groups > 1 && !tune.no_batch && (batch_pays || tune.force_batch) &&
+        p.n_tgroups <= kBatchMaxTileGroups) {
         if (tune.grid_cap > 0 && tune.grid_cap / p.n_tgroups < p.J)          // a cap on the grid means fewer K slices here
             p.J = tune.grid_cap / p.n_tgroups > 0 ? tune.grid_cap / p.n_tgroups : 1;
         BatchArgs b{a.batch_partials, a.batch_arrive, p.J, (const uint4 *)a.batch_zero};

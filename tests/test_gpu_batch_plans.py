@@ -1,5 +1,5 @@
 """GPU parity of the batched projection kernel's plans: 6 and 8 multiplying waves, one and several K slices with ragged last
-units, two row groups with a long K; and the wave counts of
+units, two row groups with a long K, two tiles per wave, matrices too wide for the kernel; and the wave counts of
 the kernels for one row group over a short K -- over models whose matrices make the plan come out that way."""
 import numpy as np
 import pytest
@@ -22,6 +22,9 @@ SHAPES = {
     "wide_head": synth.ModelShape(1, 256, 4, 64, 688, 4128),
     # down: K = 4352 (136 steps) with 256 tiles -- two row groups through the batched kernel at 6..10 rows
     "long_down": synth.ModelShape(1, 4096, 2, 128, 4352, 512),
+    # LM heads of 8194 tiles (more than 1024 groups of 8: two tiles per wave) and of 16386 (more than 1024 groups of 16)
+    "two_tiles": synth.ModelShape(1, 64, 1, 64, 64, 131104),
+    "too_wide": synth.ModelShape(1, 64, 1, 64, 64, 262176),
 }
 
 
@@ -30,6 +33,17 @@ SHAPES = {
                                            ("k768", 1, 1), ("k768", 3, 1), ("k768", 4, 1), ("k768", 1, 5), ("k768", 6, 1),
                                            ("long_down", 1, 6), ("long_down", 2, 5), ("long_down", 7, 1), ("long_down", 3, 4)])
 def test_batched_step_against_oracle(name, n_seqs, M):
+    check(name, n_seqs, M)
+
+
+# rows 6..10 take the batched kernel at a short K only when told to
+@pytest.mark.parametrize("name,n_seqs,M,batch_kernel", [("two_tiles", 2, 4, 1), ("two_tiles", 3, 4, 0), ("two_tiles", 5, 8, 0), ("two_tiles", 6, 8, 0),
+                                                        ("too_wide", 2, 4, 1), ("too_wide", 3, 4, 0), ("too_wide", 6, 8, 0)])
+def test_very_wide_head_against_oracle(name, n_seqs, M, batch_kernel):
+    check(name, n_seqs, M, batch_kernel)
+
+
+def check(name, n_seqs, M, batch_kernel=0):
     from paper_2404_08856_amd import spd
     shape = SHAPES[name]
     print(f"batch plan {name} {n_seqs}x{M}", flush=True)
@@ -37,6 +51,8 @@ def test_batched_step_against_oracle(name, n_seqs, M):
     wn = synth.weights_to_numpy(w)
     cfg = oracle_cfg(shape)
     model = spd.Model(spd.make_config(shape, n_seqs, 64), to_device(w))
+    if batch_kernel:
+        model.spd_model_set_tuning(batch_kernel=batch_kernel)
     caches = []
     for s in range(n_seqs):
         ids = synth.text_tokens(9 + 2 * s, shape.vocab, 30 + s)
