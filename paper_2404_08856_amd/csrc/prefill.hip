@@ -37,13 +37,13 @@ __device__ __forceinline__ void ppack_store4(uint16_t *X, int row, int k, int KS
 // 1 KiB from memory (16 bytes per lane) to LDS (lane-linear from `dst`, wave-uniform), without registers; counts on
 // vmcnt.  As inline assembly because the compiler makes every LDS read wait for ALL outstanding LDS-direct loads it
 // knows of (vmcnt(0)), which would undo the pipelining: the waits are written out in the loops below.  M0 carries the
-// LDS address; nothing else in these kernels uses it.
+// LDS address.
 __device__ __forceinline__ unsigned lds_addr(const void *p) { return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void *)p; }
 __device__ __forceinline__ void lds_dma16(const void *base_uniform, unsigned lane_offset, unsigned dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_offset), "s"(base_uniform) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_offset), "s"(base_uniform) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_dma16(const void *src, unsigned dst) {     // any address per lane
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory", "m0");
 }
 
 // ---------------------------------------------------------------------------------
@@ -222,10 +222,11 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                 for (int j = 0; j < NX; ++j) { sum[i][j] += part[i][j]; part[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
         }
     };
-    // stage s has landed for everyone, nobody reads stage s - 1 any more: refill its buffer with stage s + 2
+    // stage s has landed for everyone, nobody reads stage s - 1 any more (lgkmcnt: not a read of it is still under way when
+    // a wave passes the barrier, wherever the compiler put the products): refill its buffer with stage s + 2
     int buf = 0, nbuf = kPgBuf - 1;
     auto arrive = [&](int s) __attribute__((always_inline)) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kPgBuf - 2) * PB) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kPgBuf - 2) * PB) : "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         issue(s + kPgBuf - 1, nbuf);
@@ -605,7 +606,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
 
     int buf = 0, nbuf = 2;
     for (int u = 0; u < n_units; ++u) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PB) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PB) : "memory");   // as in the GEMM: unit u is there, reads of u - 1 are done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         issue(u + 2, nbuf);
