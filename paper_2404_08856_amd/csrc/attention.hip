@@ -1,6 +1,4 @@
 // Stand-alone attention kernel: RoPE + KV-cache append + causal attention (see attention_core.h).
-#include <algorithm>
-
 #include "attention_core.h"
 
 namespace spd {
@@ -48,7 +46,7 @@ constexpr int kAttnRuns = 4;
 // at most 64 (sequence, head) pairs; a run's result is [8][dh] sums and 16 statistics
 size_t attention_partial_bytes(int dh) { return (size_t)64 * kAttnRuns * (8 * dh + 16) * sizeof(float); }
 
-hipError_t launch_attention(const AttnArgs &a, const WeightPrefetch &pf, hipStream_t stream) {
+hipError_t launch_attention(const AttnArgs &a, int longest, const WeightPrefetch &pf, hipStream_t stream) {
     if (a.M < 1 || a.M > kMaxRows || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
     if (a.Mq < 1 || a.Mq > 8 || a.m0 < 0 || a.m0 + a.Mq > a.M || a.M > a.max_positions) return hipErrorInvalidValue;
     // Workgroups per head (slices of the head dimension).  One sequence: 16 output dimensions per
@@ -82,9 +80,9 @@ hipError_t launch_attention(const AttnArgs &a, const WeightPrefetch &pf, hipStre
     // Where 4 slices of a head would all score all keys of a long cache, its keys are cut into 4 runs instead, if they pay for the
     // exchange of the runs' results (about 4 us, more with more queries).  Per layer, runs / slices, 64 pairs: 4-layer
     // draft, one query, 512 positions 35.7 / 35.6 us, 1000 38.5 / 40.5, 2000 44.1 / 49.4; five queries, 1000 70.8 / 71.1,
-    // 2000 77.1 / 80.2.  Two runs instead of two slices (65 to 128 pairs) gain 1 us at 1500 positions and lose 3 below 1000.
-    int longest = 0;
-    for (int q = 0; q < a.n_seqs; ++q) longest = std::max(longest, a.lens.len[q]);       // (an upper bound with device lengths)
+    // 2000 77.1 / 80.2.  With lengths on the device only their lower bound is known: an upper bound, which grows by gamma + 1 a
+    // block whatever is accepted, would put short caches through the runs (a whole draft step of that batch at 40 positions
+    // 152.6 us against 142.8, at 256 156.8 / 149.4).  Two runs instead of two slices (65 to 128 pairs) gain 1 us at 1500 positions and lose 3 below 1000.
     if (a.slices == 0 && a.partials && a.arrive && pairs > 32 && pairs <= 64 && a.Mq <= kGroupRows && a.m0 == 0 && longest >= 512 + 96 * a.Mq) {
         const dim3 grid(a.H, kAttnRuns, a.n_seqs);
         if (a.dh == 128) hipLaunchKernelGGL((attention_kernel<128, 1, 8, 1, kAttnRuns>), grid, dim3(8 * 64), 0, stream, a, WeightPrefetch{});

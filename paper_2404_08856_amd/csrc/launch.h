@@ -124,7 +124,8 @@ struct WeightPrefetch {
     struct { const void *w; int tiles, tile_bytes; } m[4];
     int n;                   // matrices; 0: none
 };
-hipError_t launch_attention(const AttnArgs &a, const WeightPrefetch &pf, hipStream_t stream);
+// longest: cached positions of the longest sequence as far as the host knows (any value is correct, it chooses the kernel)
+hipError_t launch_attention(const AttnArgs &a, int longest, const WeightPrefetch &pf, hipStream_t stream);
 
 // ---- QKV projection and attention in one kernel (one row group, one sequence, K = 4096, head_dim 128) ----
 // One workgroup per (head, 16 output dimensions) computes the three 16-row tiles of the fused

@@ -169,6 +169,7 @@ struct spd_model {
     Layout L;
     char *packed, *kv, *ws;
     std::vector<int32_t> lens;         // KV lengths (host).  With dev_lens: only an upper bound
+    std::vector<int32_t> lens_least;   // with dev_lens: what the lengths have at least (chooses kernels, bounds nothing)
     bool dev_lens = false;             // the kernels read the lengths from device memory (ws + L.d_lens)
     bool fuse_qa = false;              // QKV projection + attention as one kernel where the shape allows it
     bool fuse_qa2 = false;             // ... also for 6..8 rows of one sequence
@@ -400,6 +401,7 @@ int32_t spd_kv_lens_to_device(spd_model *m, void *stream) {
     HIP_TRY(launch_fill_zero(m->ws + m->L.d_error, 16, (hipStream_t)stream));
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));          // the host array may change right after this call
     m->dev_lens = true;
+    m->lens_least = m->lens;
     return SPD_OK;
 }
 
@@ -466,8 +468,10 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
     if (M > c.max_positions) return fail(SPD_ERR_CAPACITY, "M = %d exceeds max_positions %d", M, c.max_positions);
     if (tokens && token_stride < M) return fail(SPD_ERR_INVALID_ARG, "token stride %d below M = %d", token_stride, M);
     AttnArgs at{};
+    int longest = 0;                                     // positions cached, as far as the host can tell
     for (int s = 0; s < n_seqs; ++s) {
         int len = m->lens[seq0 + s];
+        longest = std::max(longest, m->dev_lens ? m->lens_least[seq0 + s] : len);
         // lengths on the device: the host value is an upper bound and the kernels guard themselves
         if (!m->dev_lens && len + M > c.max_positions)
             return fail(SPD_ERR_CAPACITY, "KV cache overflow: sequence %d has %d positions, +%d > %d", seq0 + s, len, M, c.max_positions);
@@ -535,7 +539,7 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
             }
             for (int m0 = 0; m0 < M; m0 += 8) {         // at most 8 queries per sequence and launch
                 at.m0 = m0; at.Mq = std::min(8, M - m0);
-                PROF_TRY(PK_ATTENTION, launch_attention(at, m0 == 0 ? pf : WeightPrefetch{}, st));
+                PROF_TRY(PK_ATTENTION, launch_attention(at, longest, m0 == 0 ? pf : WeightPrefetch{}, st));
             }
         }
         g = GemmArgs{};
@@ -633,6 +637,7 @@ int32_t prefill_common(spd_model *m, int32_t seq, const float *embeds, const int
     if (m->lens[seq] + n_rows > m->cfg.max_positions)
         return fail(SPD_ERR_CAPACITY, "KV cache overflow in prefill: %d + %d > %d", m->lens[seq], n_rows, m->cfg.max_positions);
     float *scratch = (float *)(m->ws + m->L.logits);
+    if (m->dev_lens) m->lens_least[seq] = std::min(m->lens_least[seq] + n_rows, m->cfg.max_positions);
     // passes through the prefill kernels, unless a kernel family was asked for (batch_kernel = 1 or 2)
     if (!m->t_qkv.no_batch && !m->t_qkv.force_batch) {
         const int min_rows = prefill_min_rows(m->cfg.d_model);
@@ -835,7 +840,9 @@ int32_t spd_block_finish(spd_model *target, spd_model *draft, const float *targe
     cm.target_lens = (int32_t *)(target->ws + target->L.d_lens); cm.draft_lens = (int32_t *)(draft->ws + draft->L.d_lens);
     cm.out_tokens = out_tokens; cm.n_out = n_out; cm.n_seqs = n_seqs; cm.gamma = gamma; cm.out_capacity = out_capacity;
     HIP_TRY(launch_block_commit(cm, (hipStream_t)stream));
-    // host bounds: at most gamma + 1 positions per sequence were added by the verify call and stay
+    // host bounds: at most gamma + 1 positions per sequence were added by the verify call and stay, at least one did
+    for (spd_model *m : {target, draft})
+        for (int s = 0; s < n_seqs; ++s) m->lens_least[s] = std::min(m->lens_least[s] + 1, m->cfg.max_positions);
     return SPD_OK;
 }
 

@@ -47,3 +47,39 @@ def test_runs_of_keys_against_oracle(name, lens, M, device_lens):
     if device_lens:
         model.spd_kv_lens_from_device()
     assert model.spd_kv_get_len(n) == [c + 2 * M for c in lens]
+
+
+def test_lengths_on_the_device_that_stay_short_do_not_take_the_runs():
+    """Blocks that accept nothing: the host's upper bound passes the rule's line while the caches hold 124 positions.  The
+    step then has the bits of the same step with the lengths on the host."""
+    from paper_2404_08856_amd import spd
+    shape, gamma, n = SHAPES["dh64"], 7, 3
+    target = spd.Model(spd.make_config(shape, n, 700), to_device(synth.make_weights(shape, 31)))
+    draft_shape = synth.ModelShape(1, 64, 1, 64, 64, shape.vocab)
+    draft = spd.Model(spd.make_config(draft_shape, n, 700), to_device(synth.make_weights(draft_shape, 32)))
+    for m in (target, draft):
+        for s in range(n):
+            m.spd_prefill_tokens(s, torch.from_numpy(synth.text_tokens(40, shape.vocab, 50 + s)).cuda())
+        m.spd_kv_lens_to_device()
+    vt = torch.ones((n, gamma + 1), dtype=torch.int32, device="cuda")
+    logits = torch.empty((n, gamma + 1, shape.vocab), device="cuda")
+    other = torch.empty_like(logits)
+    D = torch.zeros((n, gamma, shape.vocab), device="cuda")
+    u = torch.full((n, gamma + 1), 0.75, device="cuda")
+    k, y, n_out = (torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(3))
+    draft_in = torch.zeros((n, 2), dtype=torch.int32, device="cuda")
+    for _ in range(84):
+        vt[:, 1:] = 1
+        D.zero_()
+        D[:, :, 1] = 1.0                     # 0.75 * 1 is not below T(1): rejected
+        target.spd_verify_forward(vt, logits)
+        draft.spd_verify_forward(vt, other)
+        spd.spd_block_finish(target, draft, logits, D, vt, u, 1.0, k, y, draft_in)
+    step = torch.full((n, 1), 5, dtype=torch.int32, device="cuda")
+    outs = [torch.empty((n, 1, shape.vocab), device="cuda") for _ in range(2)]
+    target.spd_verify_forward(step, outs[0])
+    target.spd_kv_lens_from_device()
+    assert target.spd_kv_get_len(n) == [125] * n
+    target.spd_kv_set_len([124] * n)
+    target.spd_verify_forward(step, outs[1])
+    assert torch.equal(outs[0], outs[1])
