@@ -471,12 +471,10 @@ __global__ __launch_bounds__(kSampThreads) void accept_decide_kernel(AcceptArgs 
 // Totals and ticket live in the words of the row statistics nobody else uses at a temperature above 0 (argmax and
 // padding): the ticket in the padding of the first target row, which the statistics kernel clears, slice total i
 // behind row i + 1 of the 2 gamma rows that follow -- so NS <= 2 gamma.
-// EARLY: with few sequences the slices of ALL their rows are requested before the accept tests, which takes the
-// round trip of the rows out of the chain.
-// Bound by a chain of dependent round trips (statistics and tokens, drafted entries, total, ticket, totals, the hit slice),
-// no longer by one CU's vector instructions: 10.8 us for one sequence (one workgroup: 14.4), 12.9 for 64 (18.9).
-constexpr int kEarlyGamma = 7;
-template <int NS, bool EARLY, bool ALIGNED>
+// Bound by a chain of dependent round trips (statistics and tokens, drafted entries, rows, total, ticket, totals, the hit
+// slice), no longer by one CU's vector instructions.
+constexpr int kSlices = 4;
+template <int NS, bool ALIGNED>
 __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(AcceptArgs a) {
     constexpr int NV = kRowVec / NS;
     const int seq = blockIdx.x / NS, slice = blockIdx.x % NS, G = a.gamma, V = a.vocab;
@@ -497,29 +495,9 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
             v[i] = load_quad<ALIGNED>(row, qi < q1 ? qi : n4, V, ALIGNED || mode == 0 ? 0.f : -INFINITY);
         }
     };
-    int k;
-    if (EARLY) {
-        float4 te[kEarlyGamma + 1][NV], de[kEarlyGamma][NV];
-#pragma unroll
-        for (int j = 0; j <= kEarlyGamma; ++j) {
-            if (j <= G) load(q.t_ptr(j), q.t_mode, slice, te[j]);
-            if (j < kEarlyGamma && j < G) load(q.d_ptr(j), q.d_mode, slice, de[j]);
-        }
-        k = q.accepted(slice == 0);
-#pragma unroll
-        for (int j = 0; j <= kEarlyGamma; ++j)
-            if (j == k) {
-#pragma unroll
-                for (int i = 0; i < NV; ++i) {
-                    t[i] = te[j][i];
-                    if (j < kEarlyGamma) d[i] = de[j][i];
-                }
-            }
-    } else {
-        k = q.accepted(slice == 0);
-        load(q.t_ptr(k), q.t_mode, slice, t);
-        if (k < G) load(q.d_ptr(k), q.d_mode, slice, d);
-    }
+    const int k = q.accepted(slice == 0);
+    load(q.t_ptr(k), q.t_mode, slice, t);
+    if (k < G) load(q.d_ptr(k), q.d_mode, slice, d);
     const RowProb T = q.t_row(k), D = k < G ? q.d_row(k) : T;
     // the values of the distribution to draw from: residual max(0, T - D), or the bonus row
     float4 r[NV];
@@ -608,25 +586,21 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
         else if (kind == ROW_QUADS) hipLaunchKernelGGL(accept_stats_kernel<ROW_QUADS>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
         else hipLaunchKernelGGL(accept_stats_kernel<ROW_MEMORY>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
     }
-    // Slices per sequence: as many as there are words for their totals (2 gamma, none without statistics or where the
-    // statistics' argmax is in use) and as run in one round of one workgroup per CU (64 sequences, whole step: 1 slice
-    // 29.3 us, 2 slices 31.3, 4 slices 27.8; 8 slices, two rounds, 49).
-    // (the totals are 8-byte words: a workspace aligned to single floats only keeps one slice)
-    int ns = need_stats && a.temperature > 0.f && ((uintptr_t)a.stats & 7) == 0 ? (a.gamma >= 4 ? 8 : (a.gamma >= 2 ? 4 : 2)) : 1;
-    while (ns > 1 && (long)a.n_seqs * ns > 256) ns /= 2;
-    const dim3 block(kSampThreads);
-#define SPD_SLICES(NS_, EARLY_)                                                                                                             \
-    do {                                                                                                                                   \
-        if (kind == ROW_ALIGNED) hipLaunchKernelGGL((accept_decide_slices_kernel<NS_, EARLY_, true>), dim3(a.n_seqs * NS_), block, 0, stream, a); \
-        else hipLaunchKernelGGL((accept_decide_slices_kernel<NS_, EARLY_, false>), dim3(a.n_seqs * NS_), block, 0, stream, a);              \
-    } while (0)
+    // Four slices per sequence where there are words for their totals (2 gamma of them, none without statistics or where
+    // the statistics' argmax is in use; 8-byte words: a workspace aligned to single floats only keeps one slice) and where
+    // they run in one round of one workgroup per CU.  Whole step, 32000 entries, 1 / 2 / 4 / 8 slices, the same inputs again
+    // and again: one sequence, draft length 4, 14.8 / 14 / 13.9 / 14.5 us, 8 sequences 17.4 / 18.8 / 15.5 / 15.8, 32 19.0 /
+    // 19.9 / 16.8 / 21.8; inputs that are not in any cache: 17.0 / 16 / 16.1 / 18.0, 22.0 / 22.0 / 18.9 / 19.5, 23.2 / 23.4 /
+    // 20.1 / 23.1.  At 1000 entries the same order (8 sequences 16.0 / 17.7 / 14.8 / 15.0).  Two slices never paid: 96
+    // sequences 26.9 / 28.4, draft length 1, 8 sequences 17.2 / 18.7.
+    const bool sliced = need_stats && a.temperature > 0.f && ((uintptr_t)a.stats & 7) == 0 && 2 * a.gamma >= kSlices && (long)a.n_seqs * kSlices <= 256;
+    const int ns = sliced ? kSlices : 1;
+    const dim3 grid(a.n_seqs * ns), block(kSampThreads);
     if (kind == ROW_MEMORY) hipLaunchKernelGGL(accept_decide_kernel, dim3(a.n_seqs), block, 0, stream, a);
-    else if (ns == 8 && a.gamma <= kEarlyGamma) SPD_SLICES(8, true);
-    else if (ns == 8) SPD_SLICES(8, false);
-    else if (ns == 4) SPD_SLICES(4, false);
-    else if (ns == 2) SPD_SLICES(2, false);
-    else SPD_SLICES(1, false);
-#undef SPD_SLICES
+    else if (sliced && kind == ROW_ALIGNED) hipLaunchKernelGGL((accept_decide_slices_kernel<kSlices, true>), grid, block, 0, stream, a);
+    else if (sliced) hipLaunchKernelGGL((accept_decide_slices_kernel<kSlices, false>), grid, block, 0, stream, a);
+    else if (kind == ROW_ALIGNED) hipLaunchKernelGGL((accept_decide_slices_kernel<1, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((accept_decide_slices_kernel<1, false>), grid, block, 0, stream, a);
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
-"""The accept step's sliced draw against the oracle where its dispatch changes: 1, 2, 4 or 8 slices by draft length and
-batch size, rows loaded early up to draft length 7, slices emptier than others (small and ragged vocabularies), each
+"""The accept step's sliced draw against the oracle where its dispatch changes: 1 or 4 slices by draft length, batch
+size and alignment of the workspace, slices emptier than others (small and ragged vocabularies), each
 mix of logit and probability inputs, rows that end in a part of a quad or are not 16-byte aligned, and the generic kernel
 next to them (vocabularies beyond 32768)."""
 import numpy as np
@@ -13,7 +13,7 @@ from tests.helpers import accept_margins, drawn_token_is_valid
 pytestmark = pytest.mark.gpu
 
 
-def check(V, gamma, n_seqs, target_probs, draft_probs, temp, misalign=False, repeat=1):
+def check(V, gamma, n_seqs, target_probs, draft_probs, temp, misalign=False, repeat=1, ws_offset=0):
     from paper_2404_08856_amd import spd
     print(f"accept slices V={V} gamma={gamma} n={n_seqs} T {target_probs} D {draft_probs} temp {temp} misaligned {misalign}", flush=True)
     lt, ld = synth.accept_workload(n_seqs, gamma, V, 1.0, seed=V + 64 * gamma + n_seqs)
@@ -31,7 +31,7 @@ def check(V, gamma, n_seqs, target_probs, draft_probs, temp, misalign=False, rep
 
     flags = (spd.SPD_TARGET_IS_PROBS if target_probs else 0) | (spd.SPD_DRAFT_IS_PROBS if draft_probs else 0)
     gt, gd = place(T if target_probs else lt), place(D if draft_probs else ld)
-    ws = torch.full((spd.spd_accept_workspace_bytes(n_seqs, gamma, V),), 0xAB, dtype=torch.uint8, device="cuda")
+    ws = torch.full((spd.spd_accept_workspace_bytes(n_seqs, gamma, V) + ws_offset,), 0xAB, dtype=torch.uint8, device="cuda")[ws_offset:]
     for _ in range(repeat):                                # the workspace starts dirty and is used again as it is
         k, y = (torch.full((n_seqs,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
         ap = torch.empty((n_seqs, gamma), device="cuda")
@@ -68,3 +68,9 @@ def test_slices_by_kind_of_input(target_probs, draft_probs, temp):
 def test_rows_that_are_not_16_byte_aligned(V):
     check(V, 4, 3, False, False, 1.0, misalign=True)
     check(V, 1, 2, False, True, 1.0, misalign=True)
+
+
+@pytest.mark.parametrize("offset", [4, 8, 12])
+def test_workspace_not_aligned_to_its_rows(offset):
+    """The slices' totals are 8-byte words: a workspace aligned to single floats only keeps one slice."""
+    check(2048, 4, 3, False, False, 1.0, repeat=2, ws_offset=offset)
