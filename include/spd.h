@@ -312,8 +312,9 @@ int32_t spd_trace_read(spd_model *model, int32_t n_kinds, double *h_ms_sum, int3
  * of buffer_bytes >= the sum; consecutive repetitions read different windows of it), `reps` times, and reports
  * in microseconds each kernel's own execution time (mean over the repetitions) and the wall time of one chain
  * (events around all repetitions).  This is what a chain of kernels of the projections' sizes costs on the
- * device when the kernels do nothing but read.  `sink`: 4 KiB of device memory the kernels may write.  Blocks
- * the host.  Errors: SPD_ERR_INVALID_ARG, SPD_ERR_CAPACITY (buffer too small / misaligned), SPD_ERR_HIP. */
+ * device when the kernels do nothing but read.  `sink`: 4 KiB of device memory the kernels may write.  The chain
+ * runs untimed for 0.3 s first (steady clocks), synchronising the stream as it goes, so that every call takes at
+ * least that long and blocks the host.  Errors: SPD_ERR_INVALID_ARG, SPD_ERR_CAPACITY (buffer too small / misaligned), SPD_ERR_HIP. */
 int32_t spd_probe_read_chain(const void *buffer, size_t buffer_bytes, const size_t *h_stage_bytes, int32_t n_stages,
                              int32_t reps, void *sink, double *h_kernel_us, double *h_chain_us_per_rep, void *stream);
 

@@ -77,9 +77,9 @@ extern "C" int32_t spd_probe_read_chain(const void *buffer, size_t buffer_bytes,
         if (hipStreamSynchronize(st) != hipSuccess) { rc = SPD_ERR_HIP; break; }
     } while (std::chrono::steady_clock::now() - began < std::chrono::milliseconds(300));
     // (a) the chain as a whole, untimed launches
-    if (hipEventRecord(c0, st) != hipSuccess) rc = SPD_ERR_HIP;
-    for (int r = 0; r < reps; ++r) run_chain(false);
-    if (hipEventRecord(c1, st) != hipSuccess || hipEventSynchronize(c1) != hipSuccess) rc = SPD_ERR_HIP;
+    if (rc == SPD_OK && hipEventRecord(c0, st) != hipSuccess) rc = SPD_ERR_HIP;
+    for (int r = 0; r < reps && rc == SPD_OK; ++r) run_chain(false);
+    if (rc == SPD_OK && (hipEventRecord(c1, st) != hipSuccess || hipEventSynchronize(c1) != hipSuccess)) rc = SPD_ERR_HIP;
     float ms = 0.f;
     if (rc == SPD_OK && hipEventElapsedTime(&ms, c0, c1) != hipSuccess) rc = SPD_ERR_HIP;
     *h_chain_us_per_rep = (double)ms * 1e3 / reps;
