@@ -1,6 +1,7 @@
 """GPU parity of the prefill passes (many rows of one sequence per pass) against the float64 oracle: row counts around
-the edges of the row tiles, workgroup tiles, slices of K and key units, a second pass on top of a cached prefix, ragged d_ffn,
-both head sizes, the KV cache it leaves and the decode step that follows."""
+the edges of the row tiles, workgroup tiles, slices of K and key units, a second pass on top of a cached prefix, prompts of
+more than one pass with a long or a short rest, ragged d_ffn, both head sizes, the KV cache it leaves and the decode step that
+follows; and the read-out of that cache."""
 import numpy as np
 import pytest
 import torch
@@ -16,6 +17,8 @@ SHAPES = {
     "dh128": synth.ModelShape(2, 512, 4, 128, 1408, 512),
     "deep_k": synth.ModelShape(2, 128, 32, 64, 2728, 256),                # O and down: one feature tile, K cut into 8 slices
     "heads_wider_than_d": synth.ModelShape(1, 160, 3, 64, 424, 256),      # 10 feature tiles: a workgroup tile is partly empty
+    "wide": synth.ModelShape(2, 4096, 2, 128, 264, 256),                  # above 1024 rows O and down take the large workgroup shape
+    "small": synth.ModelShape(2, 128, 2, 64, 168, 256),
 }
 
 
@@ -29,6 +32,8 @@ def cached(model, layer, n, shape):
     ("dh64_ragged_ffn", 45, 0), ("dh64_ragged_ffn", 64, 65), ("dh64_ragged_ffn", 127, 128), ("dh64_ragged_ffn", 255, 47),
     ("dh128", 48, 0), ("dh128", 129, 63), ("dh128", 300, 45), ("heads_wider_than_d", 81, 79),
     ("deep_k", 25, 64), ("deep_k", 129, 47), ("deep_k", 700, 0),
+    ("wide", 1025, 0), ("wide", 1100, 1037),
+    ("small", 2048 + 10, 0), ("small", 2048 + 70, 40),                    # a rest below and above the shortest run these kernels take
 ])
 def test_prefill_passes_against_oracle(name, first, second):
     from paper_2404_08856_amd import spd
@@ -37,8 +42,11 @@ def test_prefill_passes_against_oracle(name, first, second):
     w = randomize_gains(synth.make_weights(shape, 5))
     wn = synth.weights_to_numpy(w)
     n = first + second
-    img = synth.image_rows(n // 2, shape.d_model, 3)
-    toks = synth.text_tokens(n - n // 2, shape.vocab, 4)
+    # (wide: unit rows only -- against text rows, 0.02 per entry, a flipped step of V weighs up to 50 times as much, which the
+    # bound on K and V below leaves out and 4096 columns show: 2e-3 of a row on this path and on the batched verify path)
+    n_img = n if name == "wide" else n // 2
+    img = synth.image_rows(n_img, shape.d_model, 3)
+    toks = synth.text_tokens(n - n_img, shape.vocab, 4)
     x = np.concatenate([img.astype(np.float64), dec.embed_tokens(wn, toks)])
     cfg = oracle_cfg(shape)
     cache = dec.KVCache(cfg, n + 4)
@@ -110,3 +118,44 @@ def test_a_row_that_is_not_finite_does_not_reach_earlier_rows():
     for a, b in zip(clean, dirty):
         assert np.array_equal(a[:60], b[:60]) and np.isnan(b[60:]).all()
     assert torch.isnan(last).all()
+
+
+@pytest.mark.parametrize("n", [2048 + 10, 2048 + 70, 4096 + 25])
+def test_a_prompt_of_several_passes_by_ids_has_the_bits_of_its_rows(n):
+    from paper_2404_08856_amd import spd
+    shape = SHAPES["small"]
+    w = to_device(synth.make_weights(shape, 13))
+    ids = torch.from_numpy(synth.text_tokens(n, shape.vocab, 14)).cuda()
+    outs = []
+    for by_ids in (True, False):
+        m = spd.Model(spd.make_config(shape, 1, n), w)
+        last = torch.empty(shape.vocab, device="cuda")
+        if by_ids:
+            m.spd_prefill_tokens(0, ids, last)
+        else:
+            m.spd_prefill(0, w["embed"][ids.long()].float().contiguous(), last)
+        assert m.spd_kv_get_len(1) == [n]
+        outs.append((last.cpu().numpy(), *cached(m, 0, n, shape), *cached(m, 1, n, shape)))
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("name,capacity", [("dh128", 150), ("dh64_ragged_ffn", 160)])
+def test_cache_read_out_of_any_range(name, capacity):
+    """Ranges that start and end inside a unit of 32 positions, into outputs aligned to 16 bytes and to single floats only."""
+    from paper_2404_08856_amd import spd
+    shape = SHAPES[name]
+    m = spd.Model(spd.make_config(shape, 2, capacity), to_device(synth.make_weights(shape, 15)))
+    m.spd_prefill_tokens(1, torch.from_numpy(synth.text_tokens(capacity, shape.vocab, 16)).cuda())
+    H, dh = shape.n_heads, shape.head_dim
+    full = [torch.empty((capacity, H, dh), device="cuda") for _ in range(2)]
+    m.spd_kv_export(1, 1, 0, *full)
+    assert all(len(torch.unique(x)) > 1000 for x in full)
+    for pos0, n in ((0, 1), (31, 2), (5, 20), (32, 32), (33, 64), (capacity - 1, 1), (7, capacity - 7)):
+        for offset in (0, 1, 2):
+            flat = [torch.full((n * H * dh + 8,), -9.0, device="cuda") for _ in range(2)]
+            out = [f[offset:offset + n * H * dh].view(n, H, dh) for f in flat]
+            m.spd_kv_export(1, 1, pos0, *out)
+            for f, o, want in zip(flat, out, full):
+                assert torch.equal(o, want[pos0:pos0 + n]), (pos0, n, offset)
+                assert (f[:offset] == -9.0).all() and (f[offset + n * H * dh:] == -9.0).all()
