@@ -120,7 +120,7 @@ typedef struct {
     int32_t  separate_qkv_attention; /* 1: QKV projection and attention always as two kernels;
                                         0 = default: one kernel where the shape allows */
     int32_t  attention_slices;       /* workgroups per head of the stand-alone attention kernel at head_dim 128:
-                                        1, 2, 4 or 8; 0 = chosen by batch size */
+                                        1, 2, 4 or 8; 0 = chosen by batch size and length of the caches */
     int32_t  gemm_waves[SPD_N_PROJECTIONS];          /* waves per workgroup: 4, 8 or 16; 0 = default */
     int32_t  gemm_grid_cap[SPD_N_PROJECTIONS];       /* upper bound of the grid; 0 = default         */
     int32_t  gemm_general_kernel[SPD_N_PROJECTIONS]; /* 1: never the register-resident variant       */
@@ -128,8 +128,10 @@ typedef struct {
     int32_t  batch_kernel;           /* calls of more than 5 rows, where no register-resident kernel fits: 0 = the library
                                         chooses per projection between the tile-splitting batched kernel (one pass over
                                         the weights for up to 64 rows) and the K-splitting kernels (passes of 40 rows);
-                                        1 = always the former, 2 = always the latter.  Either one also keeps prompts on
-                                        the batched verify path */
+                                        1 = the former, 2 = the latter, also where the library would not.  (At 6 to 10 rows a
+                                        matrix of fewer than 256 tiles of 16 columns takes the general kernel at any setting,
+                                        and one of more than 262144 columns the K-splitting kernels.)  1 and 2 also keep
+                                        prompts on the batched verify path */
     uint32_t wait_spin_limit;        /* polls before a wait between workgroups gives up and raises the flag that
                                         spd_device_status reports (0 = default, 2^22); a tiny value lets a test
                                         drive that error path from the host while every kernel still exits */

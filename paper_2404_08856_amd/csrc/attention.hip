@@ -63,7 +63,8 @@ hipError_t launch_attention(const AttnArgs &a, int longest, const WeightPrefetch
     // up to 5 queries per sequence: one query group; 6..8: two groups share the cached keys' registers
     // Prefetching workgroups: whole (head, slice) planes of the grid, at least kPrefetchWgs together, where attention leaves at
     // least half of the CUs idle.  12-layer draft, one sequence (48 workgroups): attention 5.9 -> 6.2 us, the projections
-    // behind it 18.3 -> 16.0 per layer, draft step 301 -> 285.  4-layer draft, 8 sequences (256 workgroups): attention
+    // behind it 18.3 -> 16.0 per layer.  Whole draft step without / with, one sequence, 12 layers: 66 cached positions 287 / 253 us,
+    // 1000 350 / 316, 2000 412 / 377; two sequences 2000 415 / 387; 4 layers, one sequence 66 125 / 113, 2000 191 / 178.  4-layer draft, 8 sequences (256 workgroups): attention
     // 18.7 -> 23.0, projections 25.1 -> 20.6: nothing gained, so not there.  From the O projection's idle CUs instead: O itself
     // 1 to 3 us slower, no gain.
     constexpr int kPrefetchWgs = 192;

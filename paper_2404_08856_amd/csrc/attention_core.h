@@ -9,10 +9,12 @@
 // into units of 32; every wave owns a contiguous run of units and walks it 2 units (64 keys)
 // at a time.  All loads of an iteration -- the K rows and the V columns of the wave's keys --
 // are issued before anything is computed, so for contexts up to 768 keys the whole kernel pays
-// a single round trip.  There is no cross-workgroup merge: every workgroup of a head scores
-// all keys and produces its own slice of the output dimensions.  K is therefore read by all
-// slices of a head; they are launched so that they share an XCD, whose L2 then serves the
-// repeats (HBM sees K once), and V, the other half of the bytes, is read exactly once.
+// a single round trip.  Every workgroup of a head scores all keys and produces its own slice of the
+// output dimensions; nothing is merged across workgroups.  K is therefore read by all slices of a
+// head; they are launched so that they share an XCD, whose L2 then serves the repeats (HBM sees
+// K once), and V, the other half of the bytes, is read exactly once.  Over a long cache the keys of
+// a head may be cut into KSP runs instead: a workgroup then scores one run for all output
+// dimensions, and the last of the KSP to arrive merges their results through memory.
 //
 //   scores  S[key, m] = sum_d K[key, d] q[m, d]     v_mfma_f32_16x16x32_bf16, A = 16 keys x 32 dims
 //           of the bf16 cache as stored, B = q as three bf16 terms (columns m, m + 5, m + 10 of

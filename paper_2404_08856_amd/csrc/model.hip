@@ -118,7 +118,8 @@ void make_layout(const spd_model_config &c, Layout &L) {
     L.part = take(pb);
     L.arrive = take((size_t)kBatchMaxTileGroups * 4);
     L.zero = take(1024);
-    // prefill: activations of one pass, row tiles of 16 rows, whole workgroup tiles of 128 rows
+    // prefill: activations of one pass, whole row tiles of 16 rows (a workgroup tile may reach beyond the last one: the kernel
+    // clamps the row tiles that it reads and writes no row that is not there)
     L.prefill_rows = std::min((int)kPrefillRows, c.max_positions);
     L.pssq_ld = (d / 16 + 3) / 4;
     const size_t pr = align_up((size_t)L.prefill_rows, 16);

@@ -74,3 +74,9 @@ def test_rows_that_are_not_16_byte_aligned(V):
 def test_workspace_not_aligned_to_its_rows(offset):
     """The slices' totals are 8-byte words: a workspace aligned to single floats only keeps one slice."""
     check(2048, 4, 3, False, False, 1.0, repeat=2, ws_offset=offset)
+
+
+@pytest.mark.parametrize("V", [1000, 32003, 32768, 40000])
+def test_greedy_draw(V):
+    """Temperature 0: one-hot rows, so accept counts and tokens are exact."""
+    check(V, 4, 5, False, False, 0.0, repeat=2)

@@ -268,7 +268,7 @@ def test_llama7b_benchmark_point_against_oracle():
     """The benchmarked configuration itself -- Table 1 target shape, all 32 layers, KV prefix of 576 image rows
     + 64 text tokens, gamma + 1 = 5 tokens, the benchmark's seeds -- against the oracle.  One oracle pass over
     all 645 rows gives the prefill's last row and the 5 verify rows (cached forward = full recompute, an
-    invariant the oracle is pinned by); the device runs the prefill in 40-row passes and then the 5-row step."""
+    invariant the oracle is pinned by); the device runs image rows and text as one prefill pass each and then the 5-row step."""
     shape = synth.SHAPES["llama7b"]
     spd = spd_mod()
     seed, m_img, n_text, M = 0, 576, 64, 5
