@@ -105,6 +105,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     __shared__ float pn[8][8];
     __shared__ float part_m[AW + 1][8];
     __shared__ float part_l[AW + 1][8];
+    __shared__ float part_w[AW + 1][8];           // weights of the partials in the merge
+    __shared__ float top_m[8];                    // maxima over the partials
     __shared__ float part_o[AW][8][DW];
 
     // ---- key units of this wave; first iteration's loads go out before anything else --------
@@ -319,22 +321,29 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     __syncthreads();
 
     // ---- merge the AW + 1 partials in index order, write the B operand of the O projection ----
-    // (expf here and in the rescaling above, not exp_neg, whose lower bound would turn NaN into a small weight: a score that
-    // overflowed to +inf has to leave NaN, as inf - inf does, and not plausible values)
+    // The weights once per (partial, query), not once per output: exponentials in every thread were 1 us of a launch with 8
+    // queries per sequence and 256 pairs.  (expf here and in the rescaling above, not exp_neg, whose lower bound would turn NaN
+    // into a small weight: a score that overflowed to +inf has to leave NaN, as inf - inf does, and not plausible values)
+    if (tid < (AW + 1) * 8) {
+        const int p = tid >> 3, m = tid & 7;
+        float mstar = -INFINITY;
+#pragma unroll
+        for (int i = 0; i <= AW; ++i) mstar = fmaxf(mstar, part_m[i][m]);
+        const float pm = part_m[p][m];
+        part_w[p][m] = (pm == -INFINITY) ? 0.f : expf(pm - mstar);
+        if (p == 0) top_m[m] = mstar;
+    }
+    __syncthreads();
     const int KS = H * DH / 32;
     constexpr int kPart = 8 * DW + 16;            // floats of a partial result: [8][DW] sums, 8 maxima, 8 denominators
     const size_t group = pair * DS + ds;
     float *mine = KSP > 1 ? a.partials + (group * KSP + ks) * kPart : nullptr;
     for (int idx = tid; idx < M * DW; idx += AW * 64) {
         const int m = idx / DW, dd = idx % DW;
-        float mstar = -INFINITY;
-#pragma unroll
-        for (int p = 0; p <= AW; ++p) mstar = fmaxf(mstar, part_m[p][m]);
         float num = 0.f, den = 0.f;
 #pragma unroll
         for (int p = 0; p < AW; ++p) {
-            const float pm = part_m[p][m];
-            const float wg = (pm == -INFINITY) ? 0.f : expf(pm - mstar);
+            const float wg = part_w[p][m];
             den += wg * part_l[p][m];
             num += wg * part_o[p][m][dd];
         }
@@ -342,8 +351,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
             float o = 0.f;
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) o += pn[m][jj] * vf[jj][dim0 + dd];
-            const float pm = part_m[AW][m];
-            const float wg = (pm == -INFINITY) ? 0.f : expf(pm - mstar);
+            const float wg = part_w[AW][m];
             den += wg * part_l[AW][m];
             num += wg * o;
         }
@@ -351,7 +359,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
             float *out = mine + m * DW + dd;
             __hip_atomic_store(out, num, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (dd == 0) {
-                __hip_atomic_store(mine + 8 * DW + m, mstar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(mine + 8 * DW + m, top_m[m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(mine + 8 * DW + 8 + m, den, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             continue;
