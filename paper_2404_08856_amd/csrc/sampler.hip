@@ -340,7 +340,10 @@ struct SliceSampler {
     unsigned long long mine;            // this wave's total
 };
 
-template <RowKind KIND>
+// MIXED: rows are read from memory unless they are aligned themselves (only one side's are).  From 8000 entries on: 64
+// sequences, whole step, all from memory / MIXED, target or draft rows not aligned: 12000 entries 31.1 / 23.2 and 29.4 / 26.7
+// us, 8000 24.9 / 22.2 and 24.7 / 23.8; 4000 at temperature 0 15.4 / 16.7 and 15.5 / 17.2.
+template <RowKind KIND, bool MIXED>
 __global__ __launch_bounds__(kSampThreads) void accept_stats_kernel(AcceptArgs a) {
     // one workgroup per logits row: target rows first, then draft rows
     const int n_t = a.n_seqs * (a.gamma + 1);
@@ -353,9 +356,9 @@ __global__ __launch_bounds__(kSampThreads) void accept_stats_kernel(AcceptArgs a
     const float *row = is_t ? a.target + (size_t)r * a.vocab : a.draft + (size_t)(r - n_t) * a.vocab;
     const float inv_temp = a.temperature > 0.f ? 1.0f / a.temperature : 1.0f;
     __shared__ RowStats st;
-    if constexpr (KIND != ROW_MEMORY) {
+    if (KIND != ROW_MEMORY || (MIXED && ((uintptr_t)row & 15) == 0)) {
         float4 v[kRowVec];
-        load_row<KIND == ROW_ALIGNED>(row, a.vocab, -INFINITY, v);
+        load_row<KIND != ROW_QUADS>(row, a.vocab, -INFINITY, v);
         row_stats_regs<false, false>(v, !(a.temperature > 0.f), inv_temp, &st);
     } else {
         row_stats(row, a.vocab, inv_temp, &st);
@@ -582,9 +585,12 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
     const bool need_stats = ((a.flags & 3u) != 3u);
     if (need_stats) {
         int n_rows = a.n_seqs * (2 * a.gamma + 1);
-        if (kind == ROW_ALIGNED) hipLaunchKernelGGL(accept_stats_kernel<ROW_ALIGNED>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
-        else if (kind == ROW_QUADS) hipLaunchKernelGGL(accept_stats_kernel<ROW_QUADS>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
-        else hipLaunchKernelGGL(accept_stats_kernel<ROW_MEMORY>, dim3(n_rows), dim3(kSampThreads), 0, stream, a);
+        const dim3 grid(n_rows), block(kSampThreads);
+        const bool one_aligned = a.vocab >= 8000 && (row_kind(a.target, a.target, a.vocab) == ROW_ALIGNED || row_kind(a.draft, a.draft, a.vocab) == ROW_ALIGNED);
+        if (kind == ROW_ALIGNED) hipLaunchKernelGGL((accept_stats_kernel<ROW_ALIGNED, false>), grid, block, 0, stream, a);
+        else if (kind == ROW_QUADS) hipLaunchKernelGGL((accept_stats_kernel<ROW_QUADS, false>), grid, block, 0, stream, a);
+        else if (one_aligned) hipLaunchKernelGGL((accept_stats_kernel<ROW_MEMORY, true>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((accept_stats_kernel<ROW_MEMORY, false>), grid, block, 0, stream, a);
     }
     // Four slices per sequence where there are words for their totals (2 gamma of them, none without statistics or where
     // the statistics' argmax is in use; 8-byte words: a workspace aligned to single floats only keeps one slice) and where

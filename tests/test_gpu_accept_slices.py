@@ -23,14 +23,14 @@ def check(V, gamma, n_seqs, target_probs, draft_probs, temp, misalign=False, rep
     u[0, -1] = 0.0
     u[-1, -1] = np.float32(1 - 2.0 ** -24)
 
-    def place(x):
+    def place(x, side):
         flat = torch.zeros(x.size + 4, device="cuda")
-        out = flat[1 if misalign else 0:][:x.size].view(x.shape)
+        out = flat[1 if misalign in (True, side) else 0:][:x.size].view(x.shape)
         out.copy_(torch.from_numpy(np.ascontiguousarray(x)))
         return out
 
     flags = (spd.SPD_TARGET_IS_PROBS if target_probs else 0) | (spd.SPD_DRAFT_IS_PROBS if draft_probs else 0)
-    gt, gd = place(T if target_probs else lt), place(D if draft_probs else ld)
+    gt, gd = place(T if target_probs else lt, "target"), place(D if draft_probs else ld, "draft")
     ws = torch.full((spd.spd_accept_workspace_bytes(n_seqs, gamma, V) + ws_offset,), 0xAB, dtype=torch.uint8, device="cuda")[ws_offset:]
     for _ in range(repeat):                                # the workspace starts dirty and is used again as it is
         k, y = (torch.full((n_seqs,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
@@ -80,3 +80,10 @@ def test_workspace_not_aligned_to_its_rows(offset):
 def test_greedy_draw(V):
     """Temperature 0: one-hot rows, so accept counts and tokens are exact."""
     check(V, 4, 5, False, False, 0.0, repeat=2)
+
+
+@pytest.mark.parametrize("side", ["target", "draft"])
+@pytest.mark.parametrize("V,temp", [(2048, 1.0), (8000, 1.0), (12284, 1.0), (12284, 0.0), (16384, 0.7)])
+def test_one_side_s_rows_not_aligned(side, V, temp):
+    """Statistics in registers for the aligned side and from memory for the other, from 8000 to 12287 entries."""
+    check(V, 4, 3, False, False, temp, misalign=side, repeat=2)
