@@ -30,7 +30,7 @@ __device__ __forceinline__ void prefetch_tiles(const WeightPrefetch &pf, int id,
 }
 
 // grid: heads, slices x runs of keys, sequences (and planes of prefetching workgroups behind them)
-template <int DH, int DS, int AW, int QG, int KSP>
+template <int DH, int DS, int AW, int QG, int KSP, bool K_ONCE>
 __global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPrefetch pf) {
     if ((int)blockIdx.z >= a.n_seqs) {
         const int id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPr
     }
     // head index fastest: consecutive workgroups go to consecutive XCDs, so with a head count that is
     // a multiple of 8 all slices of one head share an XCD and its L2 holds that head's K once
-    attention_core<DH, DS, AW, kUnitsPerIter, false, QG, KSP>(a, blockIdx.x, KSP == 1 ? blockIdx.y : blockIdx.y % DS, KSP == 1 ? 0 : blockIdx.y / DS, blockIdx.z, [] {});
+    attention_core<DH, DS, AW, kUnitsPerIter, false, QG, KSP, K_ONCE>(a, blockIdx.x, KSP == 1 ? blockIdx.y : blockIdx.y % DS, KSP == 1 ? 0 : blockIdx.y / DS, blockIdx.z, [] {});
 }
 
 constexpr int kAttnRuns = 4;
@@ -74,9 +74,9 @@ hipError_t launch_attention(const AttnArgs &a, int longest, const WeightPrefetch
         const int planes = pf.n > 0 && plane * a.n_seqs <= 128 ? (kPrefetchWgs + plane - 1) / plane : 0;                     \
         const dim3 grid(a.H, DS_, a.n_seqs + planes);                                                                        \
         if (a.Mq <= kGroupRows)                                                                                              \
-            hipLaunchKernelGGL((attention_kernel<DH_, DS_, AW_, 1, 1>), grid, dim3(AW_ * 64), 0, stream, a, pf);                \
+            hipLaunchKernelGGL((attention_kernel<DH_, DS_, AW_, 1, 1, false>), grid, dim3(AW_ * 64), 0, stream, a, pf);                \
         else                                                                                                                 \
-            hipLaunchKernelGGL((attention_kernel<DH_, DS_, 8, 2, 1>), grid, dim3(8 * 64), 0, stream, a, pf);                    \
+            hipLaunchKernelGGL((attention_kernel<DH_, DS_, 8, 2, 1, false>), grid, dim3(8 * 64), 0, stream, a, pf);                    \
     } while (0)
     // Where 4 slices of a head would all score all keys of a long cache, its keys are cut into 4 runs instead, if they pay for the
     // exchange of the runs' results (about 4 us, more with more queries).  Per layer, runs / slices, 64 pairs: 4-layer
@@ -86,12 +86,19 @@ hipError_t launch_attention(const AttnArgs &a, int longest, const WeightPrefetch
     // 152.6 us against 142.8, at 256 156.8 / 149.4).  Two runs instead of two slices (65 to 128 pairs) gain 1 us at 1500 positions and lose 3 below 1000.
     if (a.slices == 0 && a.partials && a.arrive && pairs > 32 && pairs <= 64 && a.Mq <= kGroupRows && a.m0 == 0 && longest >= 512 + 96 * a.Mq) {
         const dim3 grid(a.H, kAttnRuns, a.n_seqs);
-        if (a.dh == 128) hipLaunchKernelGGL((attention_kernel<128, 1, 8, 1, kAttnRuns>), grid, dim3(8 * 64), 0, stream, a, WeightPrefetch{});
-        else if (a.dh == 64) hipLaunchKernelGGL((attention_kernel<64, 1, kAttnWaves, 1, kAttnRuns>), grid, dim3(kAttnWaves * 64), 0, stream, a, WeightPrefetch{});
+        if (a.dh == 128) hipLaunchKernelGGL((attention_kernel<128, 1, 8, 1, kAttnRuns, true>), grid, dim3(8 * 64), 0, stream, a, WeightPrefetch{});
+        else if (a.dh == 64) hipLaunchKernelGGL((attention_kernel<64, 1, kAttnWaves, 1, kAttnRuns, true>), grid, dim3(kAttnWaves * 64), 0, stream, a, WeightPrefetch{});
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
-    if (a.dh == 128 && slices == 1) {
+    // Keys by non-temporal loads where nearly every CU holds one workgroup of a long cache.  Whole step of eight 7B layers,
+    // non-temporal / plain, one query: 256 pairs, 300 positions 834 / 826 us, 700 891 / 894, 1900 1094 / 1105; 224 pairs, 300
+    // 827 / 819, 1900 1069 / 1068; 160 pairs, 700 822 / 801, 1900 997 / 970; 384 pairs, 1900 1451 / 1434; five queries, 256
+    // pairs, 700 1226 / 1238, 1900 1427 / 1444.  (Values so everywhere: 256 pairs, 1900 1105 against 1132.  The runs of keys above
+    // too: the 4-layer draft, 8 sequences at 1472, 977 / 986 a case of five steps; two 7B sequences at 1900 go the other way, 804 / 796.)
+    if (a.dh == 128 && slices == 1 && a.Mq <= kGroupRows && pairs > 224 && pairs <= 256 && longest >= 600) {
+        hipLaunchKernelGGL((attention_kernel<128, 1, 8, 1, 1, true>), dim3(a.H, 1, a.n_seqs), dim3(8 * 64), 0, stream, a, WeightPrefetch{});
+    } else if (a.dh == 128 && slices == 1) {
         SPD_ATTN(128, 1, 8);
     } else if (a.dh == 128 && slices == 2) {
         SPD_ATTN(128, 2, kAttnWaves);

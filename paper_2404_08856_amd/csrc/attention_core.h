@@ -51,8 +51,7 @@ __device__ __forceinline__ f32x4_t mfma16(const uint4 &a, const uint4 &b, f32x4_
                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// Cached keys and values that this launch reads exactly once: non-temporal loads (8 sequences at context 2048, 32 heads:
-// 51.7 -> 48.9 us with one query each, 55.6 -> 52.4 with five).
+// Cached values, which this launch reads exactly once (and keys where K_ONCE says so): non-temporal loads.
 __device__ __forceinline__ uint4 load_once(const uint4 *p) {
     typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
     const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
@@ -74,7 +73,8 @@ __device__ __forceinline__ uint32_t pack2(uint16_t lo, uint16_t hi) { return (ui
 // KSP > 1: the cached keys are cut into KSP contiguous runs of units, one workgroup (index ks) each.  Every one leaves its
 // unnormalised result in a.partials and takes a ticket; the last of the KSP to arrive (nobody waits) combines them in
 // order.  The new rows belong to run 0.
-template <int DH, int DS, int AW, int UPI, bool DEV, int QG, int KSP, class ReadyFn>
+// K_ONCE: non-temporal loads of the keys as well (only with DS == 1: several slices of a head share its K in L2).
+template <int DH, int DS, int AW, int UPI, bool DEV, int QG, int KSP, bool K_ONCE, class ReadyFn>
 __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, const int ds, const int ks, const int seq, ReadyFn rows_ready) {
     constexpr int HALF = DH / 2;
     constexpr int NC = DH / 32;                   // 32-dim chunks of a key row
@@ -128,7 +128,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
 #pragma unroll
                     for (int c = 0; c < NC; ++c) {
                         const uint4 *src = reinterpret_cast<const uint4 *>(row + c * 32);
-                        kreg[s][ab][c] = DS == 1 ? load_once(src) : *src;    // several slices of a head share its K in L2
+                        kreg[s][ab][c] = K_ONCE ? load_once(src) : *src;
                     }
                 }
 #pragma unroll

@@ -1,6 +1,6 @@
 """GPU parity of attention over runs of keys (a long cache, 33 to 64 (sequence, head) pairs): lengths on both sides of the rule's
 line, a sequence so short that later runs have no unit, both head sizes, one and five queries, launches repeated on the
-same counters, lengths on the device."""
+same counters, lengths on the device; and of whole heads with 225 to 256 pairs, where the keys' loads depend on the length."""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +17,7 @@ SHAPES = {"dh128": synth.ModelShape(1, 256, 16, 128, 688, 512), "dh64": synth.Mo
 @pytest.mark.parametrize("name,lens,M,device_lens", [
     ("dh128", [1100, 3, 40, 700], 5, False), ("dh128", [607, 1, 600], 1, False), ("dh128", [608, 0, 33], 1, True),
     ("dh64", [1024, 31, 32, 65], 4, False), ("dh64", [995, 500, 2], 5, True),
+    ("dh128", [600] + 15 * [33], 1, False), ("dh128", [650] + 14 * [70], 4, True), ("dh128", [599] + 15 * [2], 3, False),
 ])
 def test_runs_of_keys_against_oracle(name, lens, M, device_lens):
     from paper_2404_08856_amd import spd
