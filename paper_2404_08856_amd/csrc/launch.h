@@ -187,8 +187,8 @@ struct PrefillAttnArgs {
     int32_t *d_error;
     int len;
 };
-// RoPE + append of the rows' keys and values, then attention of the rows over everything cached (two kernels)
-hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t stream);
+// RoPE + append of the rows' keys and values, then (attend) attention of the rows over everything cached (two kernels)
+hipError_t launch_prefill_attention(const PrefillAttnArgs &a, bool attend, hipStream_t stream);
 
 // ---- sampling ---------------------------------------------------------------------
 struct AcceptArgs {

@@ -715,16 +715,16 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
     }
 }
 
-hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t stream) {
+hipError_t launch_prefill_attention(const PrefillAttnArgs &a, bool attend, hipStream_t stream) {
     if (a.rows < 1 || a.rows > a.max_positions || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
     const dim3 g1(a.H, (a.rows + 31) / 32 + 1), g2(a.H, (a.rows + 63) / 64);
     if (a.dh != 128 && a.dh != 64) return hipErrorInvalidValue;
     if (a.dh == 128) {
         hipLaunchKernelGGL(prefill_append_kernel<128>, g1, dim3(256), 0, stream, a);
-        hipLaunchKernelGGL(prefill_attention_kernel<128>, g2, dim3(256), 0, stream, a);
+        if (attend) hipLaunchKernelGGL(prefill_attention_kernel<128>, g2, dim3(256), 0, stream, a);
     } else {
         hipLaunchKernelGGL(prefill_append_kernel<64>, g1, dim3(256), 0, stream, a);
-        hipLaunchKernelGGL(prefill_attention_kernel<64>, g2, dim3(256), 0, stream, a);
+        if (attend) hipLaunchKernelGGL(prefill_attention_kernel<64>, g2, dim3(256), 0, stream, a);
     }
     return hipGetLastError();
 }

@@ -159,3 +159,31 @@ def test_cache_read_out_of_any_range(name, capacity):
             for f, o, want in zip(flat, out, full):
                 assert torch.equal(o, want[pos0:pos0 + n]), (pos0, n, offset)
                 assert (f[:offset] == -9.0).all() and (f[offset + n * H * dh:] == -9.0).all()
+
+
+@pytest.mark.parametrize("name,n", [("dh64_ragged_ffn", 25), ("dh128", 33), ("dh128", 130), ("wide", 70), ("small", 2048 + 40)])
+@pytest.mark.parametrize("on_device", [False, True])
+def test_a_prompt_without_logits_leaves_the_cache_of_one_with_them(name, n, on_device):
+    """Only the last row passes through the whole last layer, and only where its logits are asked for: every other key and value has the
+    same bits, and those of that row are one bf16 step away at most (its projection runs through another kernel)."""
+    from paper_2404_08856_amd import spd
+    shape = SHAPES[name]
+    w = to_device(randomize_gains(synth.make_weights(shape, 17)))
+    rows = torch.from_numpy(synth.image_rows(n, shape.d_model, 18)).cuda()
+    kv, steps = [], []
+    for with_logits in (True, False):
+        m = spd.Model(spd.make_config(shape, 1, n + 4), w)
+        if on_device:
+            m.spd_kv_lens_to_device()
+        m.spd_prefill(0, rows, torch.empty(shape.vocab, device="cuda") if with_logits else None)
+        if on_device:
+            m.spd_kv_lens_from_device()
+        assert m.spd_kv_get_len(1) == [n]
+        kv.append([x for l in range(shape.n_layers) for x in cached(m, l, n, shape)])
+        out = torch.empty((1, 2, shape.vocab), device="cuda")
+        m.spd_verify_forward(torch.tensor([[1, 2]], dtype=torch.int32, device="cuda"), out)
+        steps.append(out.cpu().numpy())
+    for a, b in zip(*kv):
+        assert np.array_equal(a[:n - 1], b[:n - 1])
+        assert np.all(np.abs(a - b) <= np.maximum(2.0 ** -7 * np.abs(a), 1e-5 * np.sqrt(np.mean(a * a))))
+    check_logits(steps[1][0], steps[0][0], "step after the prompt without logits")
