@@ -1,0 +1,106 @@
+"""GPU parity of the prompt kernels with two f16 terms (models whose projections all contract over 2048 values or more, passes of
+385 rows or more) against the float64 oracle: both workgroup shapes, K slices, K ranges that end inside a group of four steps and
+inside a block, both head sizes, a second pass over a cached prefix, passes on either side of the rule, factors far from one."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decoder as dec
+from paper_2404_08856_amd import synth
+from tests.helpers import check_logits, oracle_cfg, randomize_gains, to_device
+from tests.test_gpu_prefill import cached
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "even": synth.ModelShape(2, 2048, 16, 128, 2048, 256),
+    "ragged": synth.ModelShape(2, 2080, 33, 64, 2056, 256),               # 65, 66 and 64.25 K-steps; 257 gate|up tiles
+    "ragged128": synth.ModelShape(2, 2144, 17, 128, 2120, 256),           # 67, 68 and 66.25
+    "deep": synth.ModelShape(2, 2048, 16, 128, 4104, 128),                # down: 128.25 K-steps
+}
+
+
+def check_cache(model, cache, shape, n):
+    """K and V are bf16 on both sides.  Layer 0: equal or one step apart, near zero float32 rounding.  Layer 1: a flipped step of one V
+    component (2^-8 of up to 4 units) reaches early rows with a weight near 1, through Wo (0.02) and Wk (0.02, 2048 columns): 2^-8 * 4 *
+    0.02 * 0.02 * sqrt(2048) = 2.8e-4 against values of 0.9; at 4 sigma and with room for a second flip 2e-3 of them."""
+    for l in range(shape.n_layers):
+        for got, want in zip(cached(model, l, n, shape), (cache.k[l][:n], cache.v[l][:n])):
+            want = np.asarray(want, dtype=np.float64).reshape(got.shape)
+            err = np.abs(got - want)
+            floor = (1e-5 if l == 0 else 2e-3) * np.sqrt(np.mean(want * want))
+            assert np.all(err <= np.maximum(2.0 ** -7 * np.abs(want), floor)), (l, err.max())
+            assert np.mean(err > 0) < 0.02, (l, np.mean(err > 0))
+            assert np.linalg.norm(err) <= 1e-3 * np.linalg.norm(want), (l, np.linalg.norm(err) / np.linalg.norm(want))
+
+
+def run_prompt(shape, w, x, parts, capacity):
+    """One sequence, the prompt in the given parts; checks the logits behind every part and the cache against the oracle."""
+    from paper_2404_08856_amd import spd
+    n = len(x)
+    cfg, wn = oracle_cfg(shape), synth.weights_to_numpy(w)
+    cache = dec.KVCache(cfg, n + 4)
+    ref = dec.forward_rows(cfg, wn, cache, x)
+    model = spd.Model(spd.make_config(shape, 1, capacity), to_device(w))
+    rows = torch.from_numpy(x.astype(np.float32)).cuda()
+    last = torch.empty(shape.vocab, device="cuda")
+    at = 0
+    for part in parts:
+        model.spd_prefill(0, rows[at:at + part].contiguous(), last)
+        at += part
+        check_logits(last.cpu().numpy(), ref[at - 1], f"row {at}")
+    assert at == n
+    check_cache(model, cache, shape, n)
+
+
+@pytest.mark.parametrize("name,parts", [
+    ("even", (385,)), ("even", (384,)), ("even", (641, 400)), ("even", (1100,)),
+    ("ragged", (385,)), ("ragged", (500, 40, 390)), ("ragged128", (449,)), ("ragged128", (1030,)), ("deep", (512,)),
+])
+def test_wide_prompts_against_oracle(name, parts):
+    shape = SHAPES[name]
+    print(f"wide {name} {parts}", flush=True)
+    n = sum(parts)
+    w = randomize_gains(synth.make_weights(shape, 5))
+    run_prompt(shape, w, synth.image_rows(n, shape.d_model, 3).astype(np.float64), parts, n + 4)
+
+
+def test_wide_prompt_with_factors_far_from_one():
+    """Powers of two moved between gains and columns, query and key rows, up rows and down columns: the same function, but rows and blocks
+    that differ by up to 2^80 in size, and columns inside one row by up to 2^16."""
+    shape = SHAPES["even"]
+    w = randomize_gains(synth.make_weights(shape, 6))
+    g = torch.Generator().manual_seed(9)
+    for lw in w["layers"]:
+        for gain, mats in (("attn_norm", ("wq", "wk", "wv")), ("mlp_norm", ("w_gate", "w_up"))):
+            p = 2.0 ** torch.randint(-8, 9, (shape.d_model,), generator=g)
+            lw[gain] = (lw[gain].float() * p).to(lw[gain].dtype)
+            for m in mats:
+                lw[m] = (lw[m].float() / p).to(lw[m].dtype)
+        lw["wq"] = (lw["wq"].float() * 2.0 ** 40).to(lw["wq"].dtype)
+        lw["wk"] = (lw["wk"].float() * 2.0 ** -40).to(lw["wk"].dtype)
+        p = 2.0 ** torch.randint(-8, 9, (shape.d_ffn,), generator=g)
+        lw["w_up"] = (lw["w_up"].float() * p[:, None]).to(lw["w_up"].dtype)
+        lw["w_down"] = (lw["w_down"].float() / p).to(lw["w_down"].dtype)
+    run_prompt(shape, w, synth.image_rows(400, shape.d_model, 7).astype(np.float64), (400,), 404)
+
+
+def test_wide_prompt_with_a_row_that_is_not_finite_and_a_zero_row():
+    from paper_2404_08856_amd import spd
+    shape = SHAPES["ragged"]
+    w = to_device(synth.make_weights(shape, 11))
+    rows = torch.from_numpy(synth.image_rows(400, shape.d_model, 12)).cuda()
+    rows[20] = 0.0
+    bad = rows.clone()
+    bad[300, 5] = float("nan")
+    bad[310, 7] = float("inf")
+    kv = []
+    for x in (rows, bad):
+        m = spd.Model(spd.make_config(shape, 1, 400), w)
+        last = torch.empty(shape.vocab, device="cuda")
+        m.spd_prefill(0, x.contiguous(), last)
+        kv.append((cached(m, 1, 400, shape), last.cpu()))
+    (clean, last), (dirty, bad_last) = kv
+    for a, b in zip(clean, dirty):
+        assert np.isfinite(a).all() and np.array_equal(a[:300], b[:300]) and np.isnan(b[300:]).all()
+    assert torch.isfinite(last).all() and torch.isnan(bad_last).all()
