@@ -376,15 +376,16 @@ static bool prefill_large(int n_tiles, int rows) {
     const int rounds_large = (large + 255) / 256, rounds_small = (small + 511) / 512;
     return rounds_large * 2 <= rounds_small;
 }
-// K slices of the small shape, so that a matrix with few tiles still fills the chip: the smallest estimate, in K-steps of
-// a CU shared by two workgroups (0.67 us; 0.45 where a workgroup has a CU of its own), of rounds x steps, plus the
-// exchange of the partial sums (a few round trips, and 64 KiB per workgroup across the chip through memory).  Four 7B layers, unsliced / sliced:
-// 128 rows 1457 / 1025 us, 320 rows 1922 / 1667, 640 rows 3077 / 2852; the 12-layer draft, 64 rows 1015 / 770, 640 rows
-// 1249 / 1106.
+// K slices of the small shape, so that a matrix with few tiles still fills the chip: the smallest estimate in us of rounds, each
+// a start and an end (6) and the K-steps (0.65 on a CU shared by two workgroups, 0.45 on one of its own), and the exchange of the partial sums (a round
+// trip, reading J of them, and 32 KiB per workgroup across the chip).  A fit to 1 to 8 slices of 12 matrices (K = 768 to 11008)
+// at 14 row counts: on average 0.8 % slower than the fastest of them, at most 8 % (with an exchange of 6.7 us, whatever J, 5 % and 32 %).
+// The 4-layer draft's QKV at 64 rows: 17.2 -> 14.1 us (8 -> 4 slices), its O at 256 rows 19.1 -> 15.0 (8 -> 5); gate|up of the 12-layer draft at 64 rows
+// 15.6 -> 13.2 (1 -> 3); O of the 7B shape at 128 rows 31.3 -> 25.2 (8 -> 6).
 static int prefill_slices(int tiles, int KS) {
     auto cost = [&](int J) {
         const int n = tiles * J, steps = (KS + J - 1) / J;
-        return (n <= 256 ? 0.67f : (float)((n + 511) / 512)) * steps + (J > 1 ? 10.f + 0.02f * n : 0.f);
+        return (float)((n + 511) / 512) * (6.f + (n <= 256 ? 0.45f : 0.65f) * steps) + (J > 1 ? 1.1f + 1.15f * J + 0.0088f * n : 0.f);
     };
     int best = 1;
     for (int J = 2; J <= kPrefillMaxSlices && tiles * J <= kPrefillMaxSplit && KS / J >= 4; ++J)
