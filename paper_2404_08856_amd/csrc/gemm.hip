@@ -502,19 +502,38 @@ __global__ __launch_bounds__((WAVES + kBatchLoaders) * 64) void gemm_batch_kerne
     if (w >= WAVES) {
         // ---- loader waves: chunk c + NBUF - 1 is requested while chunk c is multiplied; their loads wait in
         // their own queues, so the multiplying waves' weight rings are never held up by them ----
+        // Whole chunks in a handful of scalar instructions per load: a loader wave that worked out every address, and branched around
+        // K-steps beyond the matrix, took longer to issue the 26 loads of 13 groups than the others to multiply a chunk (four 7B layers, 64 rows:
+        // 1650 us a pair of calls, 1563 like this; up to 40 rows no difference).
+        unsigned offset[PB];                                  // bytes from K-step 0 of group g0 to this wave's blocks of a chunk
+#pragma unroll
+        for (int r = 0; r < PB; ++r) {
+            const int blk = (w - WAVES) + r * LW;             // wave-uniform
+            const int bb = blk < NG * CH ? blk : 0;           // (an odd block count: the last one twice)
+            const int k = bb % CH, g = bb / CH;
+            offset[r] = (unsigned)((g < ngv ? g : 0) * KS + k) * 1024u;
+        }
         auto issue_chunk = [&](int c) __attribute__((always_inline)) {
             const int cc = chunk_at(c);
             const int bufi = (c - c_begin) % NBUF;
+            const bool whole = (cc + 1) * CH <= KS;
+            const char *base = reinterpret_cast<const char *>(a.X + ((size_t)g0 * KS + cc * CH) * 64);
+            if (whole) {
 #pragma unroll
-            for (int r = 0; r < PB; ++r) {
-                const int blk = (w - WAVES) + r * LW;         // wave-uniform
-                const int bb = blk < NG * CH ? blk : 0;       // (an odd block count: the last one twice)
-                const int k = bb % CH, g = bb / CH;
-                const int s = cc * CH + k;
-                // K-steps beyond the matrix read a block of zeros: they contribute nothing
-                const uint4 *src = (s < KS ? a.X + ((size_t)(g0 + (g < ngv ? g : 0)) * KS + s) * 64 : b.zero_block) + lane;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                                 (__attribute__((address_space(3))) void *)&Xs[bufi][g][k][0], 16, 0, 0);
+                for (int r = 0; r < PB; ++r) {
+                    const int blk = (w - WAVES) + r * LW, bb = blk < NG * CH ? blk : 0;
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + offset[r] + 16u * lane),
+                                                     (__attribute__((address_space(3))) void *)&Xs[bufi][bb / CH][bb % CH][0], 16, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < PB; ++r) {
+                    const int blk = (w - WAVES) + r * LW, bb = blk < NG * CH ? blk : 0;
+                    // K-steps beyond the matrix read a block of zeros: they contribute nothing
+                    const char *src = (cc * CH + bb % CH < KS ? base + offset[r] : reinterpret_cast<const char *>(b.zero_block)) + 16u * lane;
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                                     (__attribute__((address_space(3))) void *)&Xs[bufi][bb / CH][bb % CH][0], 16, 0, 0);
+                }
             }
         };
 #pragma unroll
