@@ -6,6 +6,8 @@
 // (common.h), each wave reads 1 KiB blocks with one coalesced load per block and
 // feeds them straight to v_mfma_f32_16x16x32_bf16; nothing goes through LDS except
 // the final cross-wave reduction of a 16 x 8 output tile.
+#include <algorithm>
+
 #include "gemm_core.h"
 #include "launch.h"
 
@@ -395,9 +397,9 @@ static hipError_t launch_multi(const GemmKernelArgs &k, int epilogue, int grid, 
 // ---------------------------------------------------------------------------------
 // With many row groups the activation operand is as large as a weight tile group (40 rows x K = 4096 x 3
 // terms = 1 MiB), so a kernel whose waves split K re-reads it from L2 for every few tiles and is bound by
-// that traffic, not by HBM.  Here the waves of a workgroup split TILES instead: all 8 (or 6) waves walk the same
+// that traffic, not by HBM.  Here the waves of a workgroup split TILES instead: all 8 (6, 4) waves walk the same
 // K range, each with its own TT tiles, so an activation block is fetched once per workgroup (into LDS, CH
-// K-steps at a time, several chunks ahead) and used by 8 (or 6) * TT tiles.  No cross-wave reduction is needed.  To keep
+// K-steps at a time, several chunks ahead) and used by 8 (6, 4) * TT tiles.  No cross-wave reduction is needed.  To keep
 // enough workgroups for the chip the K range is split ACROSS workgroups (J slices): every workgroup writes
 // its partial tiles to a scratch buffer and counts itself in on its tile group's arrival counter; the one
 // that arrives last (its ticket says so -- nobody ever waits) adds the J partials in slice order and runs
@@ -410,9 +412,18 @@ constexpr int kBatchCH = 4;      // K-steps per activation chunk: every LDS buff
 constexpr int batch_ring_chunks(int NG, int TT) { return (TT * NG * 4 + TT * 2 * kBatchCH * 4 <= 144) ? 2 : 1; }
 
 struct BatchPlan { int waves, TT, J, n_tgroups; };
-// waves multiplying waves per workgroup (8 or 6), TT tiles per wave (accumulators = TT * NG * 4 VGPRs, weight ring = TT * CH
-// blocks in flight per wave and ring chunk), J K-slices (at most 8: the last arriver reads J partials per output) so that
-// there is about one workgroup per CU: the J in range with the shortest longest slice.
+// Estimate in us of what a plan costs beyond a launch: rounds x K-steps of the longest slice x (weight tiles, which come from memory, and
+// row groups, which L2 serves), and, for slices, the exchange: a round trip, and one workgroup reading the slices' partials (320
+// bytes per tile and group each).  Fitted to launches at the 7B shapes (cold weights) with loads and products and without:
+// O at 40 rows, 8 slices x 8 waves / 4 x 4: 18.8 / 15.6 us, of which 13.6 / 9.2 without any load; at 15 rows 12.8 / 11.7, at 64
+// 23.5 / 19.4; down at 15 rows 22.7 / 21.1, at 40 29.2 / 29.2; QKV at 40 rows, 2 x 6 waves / 2 x 8 / 1 x 4: 27.2 / 28.7 / 32.2.
+static float batch_cost(const BatchPlan &p, int KS, int NG) {
+    const int unit = batch_ring_chunks(NG, p.TT) * kBatchCH, steps = unit * (((KS + unit - 1) / unit + p.J - 1) / p.J), tiles = p.waves * p.TT;
+    const float stream = (float)((p.n_tgroups * p.J + 255) / 256 * steps) * (0.031f * tiles + 0.0094f * NG);
+    return stream + (p.J > 1 ? 2.f + 0.011f * (p.J * tiles * NG) : 0.f);
+}
+// waves multiplying waves per workgroup (8, 6 or 4), TT tiles per wave (accumulators = TT * NG * 4 VGPRs, weight ring = TT * CH
+// blocks in flight per wave and ring chunk), J K-slices (at most 8: the last arriver reads J partials per output), at most one workgroup per CU
 static BatchPlan batch_plan_for(int n_tiles, int KS, int NG, int waves, int TT) {
     BatchPlan p;
     p.waves = waves;
@@ -420,31 +431,28 @@ static BatchPlan batch_plan_for(int n_tiles, int KS, int NG, int waves, int TT) 
     p.n_tgroups = (n_tiles + waves * TT - 1) / (waves * TT);
     const int unit = batch_ring_chunks(NG, TT) * kBatchCH;
     const int n_units = (KS + unit - 1) / unit;
-    int Jmax = 256 / p.n_tgroups;                             // at most one workgroup per CU: a single round
-    if (Jmax > kBatchMaxJ) Jmax = kBatchMaxJ;
-    if (Jmax > n_units) Jmax = n_units;
-    if (Jmax < 1) Jmax = 1;
-    int J = 1;
-    for (int c = 2; c <= Jmax; ++c)                           // slices are whole units: the longest one has ceil(n_units / c)
-        if ((n_units + c - 1) / c < (n_units + J - 1) / J) J = c;
-    p.J = J;
+    const int Jmax = std::min({256 / p.n_tgroups, kBatchMaxJ, n_units});
+    p.J = 1;
+    for (int c = 2; c <= Jmax; ++c) {
+        BatchPlan q = p;
+        q.J = c;
+        if (batch_cost(q, KS, NG) < batch_cost(p, KS, NG)) p = q;
+    }
     return p;
 }
-// KiB that the busiest CU pulls in: rounds x K-steps of the longest slice x (weight tiles + row groups)
-static long batch_cost(const BatchPlan &p, int KS, int NG) {
-    const int unit = batch_ring_chunks(NG, p.TT) * kBatchCH;
-    const long steps = (long)unit * (((KS + unit - 1) / unit + p.J - 1) / p.J);
-    return (long)((p.n_tgroups * p.J + 255) / 256) * steps * (p.waves * p.TT + NG);
-}
-// A workgroup's time is what its CU pulls through its memory path, so the plan with less to pull for the busiest CU wins:
-// 6 waves where 8 would leave CUs without a tile group (7B gate|up: 172 groups of 8 or 230 of 6; QKV 96 x 2 or 128 x 2).
-// Measured at the 7B shapes: one tile per wave beats two everywhere (40 rows: 5.31 against 5.45 ms per step, 20 rows:
-// 4.02 against 4.27) -- twice the workgroups, and the larger matrices then need no K slices at all.  Two tiles per
-// wave remain for matrices with more tile groups than arrival counters.
+// The cheapest of 8, 6 and 4 waves: 6 where 8 would leave CUs without a tile group (7B gate|up: 172 groups of 8 or 230 of 6; QKV 96 x 2 or
+// 128 x 2), 4 where that halves the number of K slices (O, down) or the matrix is small.  Four 7B layers against 8 or 6 waves only: 8 x 5 rows
+// 1287 / 1246 us, 3 x 5 967 / 933, 8 x 1 935 / 917; drafts of 8 rows (110M shape) 1678 / 1650.  One tile per wave beats two everywhere (7B, 40 rows: 5.31
+// against 5.45 ms per step, 20 rows: 4.02 against 4.27) -- twice the workgroups, and the larger matrices then need no K slices at all.
+// Two tiles per wave remain for matrices with more tile groups than arrival counters.
 static BatchPlan batch_plan(int n_tiles, int KS, int NG) {
-    const BatchPlan p8 = batch_plan_for(n_tiles, KS, NG, 8, 1), p6 = batch_plan_for(n_tiles, KS, NG, 6, 1);
-    if (p8.n_tgroups > kBatchMaxTileGroups) return batch_plan_for(n_tiles, KS, NG, 8, 2);
-    return p6.n_tgroups <= kBatchMaxTileGroups && batch_cost(p6, KS, NG) < batch_cost(p8, KS, NG) ? p6 : p8;
+    BatchPlan best = batch_plan_for(n_tiles, KS, NG, 8, 1);
+    if (best.n_tgroups > kBatchMaxTileGroups) return batch_plan_for(n_tiles, KS, NG, 8, 2);
+    for (int waves : {6, 4}) {
+        const BatchPlan p = batch_plan_for(n_tiles, KS, NG, waves, 1);
+        if (p.n_tgroups <= kBatchMaxTileGroups && batch_cost(p, KS, NG) < batch_cost(best, KS, NG)) best = p;
+    }
+    return best;
 }
 size_t gemm_batch_scratch_bytes(int N, int K) {
     const int n_tiles = N / 16, KS = (K + 31) / 32;
@@ -1028,6 +1036,8 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
         BatchArgs b{a.batch_partials, a.batch_arrive, p.J, (const uint4 *)a.batch_zero};
         const int bgrid = p.n_tgroups * p.J;
 #define SPD_BATCH_CASE(W_, NG_, TT_) if (p.waves == W_ && NG == NG_ && p.TT == TT_) return launch_batch<W_, NG_, TT_>(k, b, epilogue, bgrid, stream)
+        SPD_BATCH_CASE(4, 2, 1); SPD_BATCH_CASE(4, 3, 1); SPD_BATCH_CASE(4, 4, 1); SPD_BATCH_CASE(4, 6, 1);
+        SPD_BATCH_CASE(4, 8, 1); SPD_BATCH_CASE(4, 10, 1); SPD_BATCH_CASE(4, kMaxGroups, 1);
         SPD_BATCH_CASE(8, 2, 1); SPD_BATCH_CASE(6, 2, 1); SPD_BATCH_CASE(8, 2, 2);
         SPD_BATCH_CASE(8, 3, 1); SPD_BATCH_CASE(6, 3, 1);
         SPD_BATCH_CASE(8, 4, 1); SPD_BATCH_CASE(6, 4, 1); SPD_BATCH_CASE(8, 4, 2);

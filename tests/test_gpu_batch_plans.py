@@ -1,4 +1,4 @@
-"""GPU parity of the batched projection kernel's plans: 6 and 8 multiplying waves, one and several K slices with ragged last
+"""GPU parity of the batched projection kernel's plans: 4, 6 and 8 multiplying waves, one and several K slices with ragged last
 units, two row groups with a long K, two tiles per wave, matrices too wide for the kernel; and the wave counts of
 the kernels for one row group over a short K -- over models whose matrices make the plan come out that way."""
 import numpy as np
@@ -16,12 +16,15 @@ SHAPES = {
     "k2048": synth.ModelShape(1, 2048, 16, 128, 2048, 1024),
     # K = 768: waves of 6, 3 or 1.5 K-steps by the number of rows
     "k768": synth.ModelShape(1, 768, 12, 64, 768, 512),
-    # QKV 96 tiles (6 waves: 16 groups), gate|up 172, down K = 1376: 43 steps, the last unit ragged
+    # QKV 96 tiles, gate|up 172 (4 waves: 24 and 43 groups), down K = 1376: 43 steps, the last unit ragged
     "d512": synth.ModelShape(1, 512, 4, 128, 1376, 1040),
-    # LM head 258 tiles of 16: 43 groups of 6 or 33 of 8, the last one partly empty
+    # LM head 258 tiles of 16: 65 groups of 4, the last one partly empty
     "wide_head": synth.ModelShape(1, 256, 4, 64, 688, 4128),
-    # down: K = 4352 (136 steps) with 256 tiles -- two row groups through the batched kernel at 6..10 rows
+    # gate|up 68 groups of 8 in 3 slices; down: K = 4352 (136 steps) with 256 tiles -- two row groups through the batched kernel at 6..10 rows
     "long_down": synth.ModelShape(1, 4096, 2, 128, 4352, 512),
+    # LM heads of 1030 and 1541 tiles: 172 groups of 6 and 193 of 8, the last ones partly empty
+    "head_of_sixes": synth.ModelShape(1, 256, 4, 64, 688, 16480),
+    "head_of_eights": synth.ModelShape(1, 256, 4, 64, 688, 24656),
     # LM heads of 8194 tiles (more than 1024 groups of 8: two tiles per wave) and of 16386 (more than 1024 groups of 16)
     "two_tiles": synth.ModelShape(1, 64, 1, 64, 64, 131104),
     "too_wide": synth.ModelShape(1, 64, 1, 64, 64, 262176),
@@ -33,6 +36,14 @@ SHAPES = {
                                            ("k768", 1, 1), ("k768", 3, 1), ("k768", 4, 1), ("k768", 1, 5), ("k768", 6, 1),
                                            ("long_down", 1, 6), ("long_down", 2, 5), ("long_down", 7, 1), ("long_down", 3, 4)])
 def test_batched_step_against_oracle(name, n_seqs, M):
+    check(name, n_seqs, M)
+
+
+# k2048: QKV 64 groups of 6 waves in 4 slices, the others 4 waves in 4 (more than 8 row groups) or 8 slices, the most there are
+@pytest.mark.parametrize("name,n_seqs,M", [("k2048", 3, 4), ("k2048", 4, 4), ("k2048", 5, 4), ("k2048", 6, 5), ("k2048", 8, 5), ("k2048", 7, 7), ("k2048", 8, 8),
+                                           ("k768", 3, 4), ("k768", 8, 8), ("long_down", 8, 8),
+                                           ("head_of_sixes", 3, 4), ("head_of_sixes", 8, 8), ("head_of_eights", 3, 4), ("head_of_eights", 8, 5)])
+def test_waves_and_slices_against_oracle(name, n_seqs, M):
     check(name, n_seqs, M)
 
 
@@ -68,3 +79,8 @@ def check(name, n_seqs, M, batch_kernel=0):
     got = out.cpu().numpy()
     for s in range(n_seqs):
         check_logits(got[s], dec.forward_tokens(cfg, wn, caches[s], vt[s]), f"{name} seq {s}")
+
+
+@pytest.mark.parametrize("n_seqs,M", [(1, 6), (2, 5)])
+def test_two_groups_in_eight_slices_against_oracle(n_seqs, M):
+    check("k2048", n_seqs, M, batch_kernel=1)
