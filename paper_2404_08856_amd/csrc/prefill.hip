@@ -491,7 +491,11 @@ __global__ __launch_bounds__(256) void prefill_append_kernel(PrefillAttnArgs a) 
 // branches per key, packed conversions and register swaps instead of LDS for the maximum took the 7B shape at 2047
 // rows from 133 to 114 us per layer, the 12-layer draft at 1472 rows from 58 to 34.  A second set of 4 waves on every other
 // unit of the same queries (merged at the end) was no faster where workgroups are few (31 us) and slower at 2047 rows (157).
-constexpr int kPaBuf = 3;
+// Heads of 64 take two units per step: a wave is alone on its SIMD for most of a launch (12 heads x 23 blocks of queries), and one unit's
+// products run next to the other's softmax (1472 rows, 36.2 to 32.4 us).  Heads of 128 come with more workgroups: at 2047 rows three of them per CU
+// (one unit per step, at most 168 registers) take 113 us, two 125 with two units and 131 with one.
+constexpr int kPaBuf = 3;                        // steps in LDS: one in use, one there, one on its way
+constexpr int prefill_step_units(int DH) { return DH == 64 ? 2 : 1; }
 
 // bf16 pairs with an infinite or NaN value replaced by 0
 __device__ __forceinline__ uint32_t finite_pair(uint32_t p) {
@@ -526,7 +530,8 @@ __device__ __forceinline__ float exp_score(float x) {
 template <int DH, int T>
 __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnArgs a) {
     constexpr int HALF = DH / 2, NC = DH / 32, NDT = DH / 16, BLK = 2 * NC + NDT, PB = BLK / 4;
-    __shared__ uint4 S[kPaBuf][BLK][64];
+    constexpr int U = prefill_step_units(DH);
+    __shared__ uint4 S[kPaBuf][U][BLK][64];
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hh = blockIdx.x, qt = gridDim.y - 1 - blockIdx.y;
@@ -538,20 +543,23 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
     const int n_units = min(P0 + qt * 64 + 63, k_end) / 32 + 1;  // units any query of this workgroup sees
 
     // this wave's share of a unit: blocks w, w + 4, ...; 0 .. 2 NC - 1: K (tile ab, chunk c), then V (dim tile)
-    const unsigned lds0 = lds_addr(&S[0][0][0]);
+    const unsigned lds0 = lds_addr(&S[0][0][0][0]);
     auto issue = [&](int u, int buf) __attribute__((always_inline)) {
-        const int uu = min(u, n_units - 1);                      // past the end: a harmless re-read
 #pragma unroll
-        for (int i = 0; i < PB; ++i) {
-            const int b = w + 4 * i;
-            const uint16_t *src;
-            if (i < NC / 2) {                                    // b < 2 NC
-                const int key = min(32 * uu + 8 * (r >> 2) + 4 * (b / NC) + (r & 3), k_end);
-                src = Kc + (size_t)key * DH + 32 * (b % NC) + 8 * g;
-            } else {
-                src = Vt + ((size_t)uu * DH + 16 * (b - 2 * NC) + r) * 32 + 8 * g;
+        for (int h = 0; h < U; ++h) {
+            const int uu = min(u + h, n_units - 1);              // past the end: a harmless re-read
+#pragma unroll
+            for (int i = 0; i < PB; ++i) {
+                const int b = w + 4 * i;
+                const uint16_t *src;
+                if (i < NC / 2) {                                // b < 2 NC
+                    const int key = min(32 * uu + 8 * (r >> 2) + 4 * (b / NC) + (r & 3), k_end);
+                    src = Kc + (size_t)key * DH + 32 * (b % NC) + 8 * g;
+                } else {
+                    src = Vt + ((size_t)uu * DH + 16 * (b - 2 * NC) + r) * 32 + 8 * g;
+                }
+                lds_dma16(src, lds0 + (unsigned)(((buf * U + h) * BLK + b) * 1024));
             }
-            lds_dma16(src, lds0 + (unsigned)((buf * BLK + b) * 1024));
         }
     };
     const int row = qt * 64 + w * 16 + r;                       // this lane's query
@@ -585,7 +593,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
         }
     }
     issue(0, 0);
-    issue(1, 1);
+    issue(U, 1);
 
     const int q_pos = P0 + row, w_first = P0 + qt * 64 + w * 16, w_last = min(w_first + 15, k_end);
     const bool wave_has_rows = w_first <= k_end;
@@ -594,93 +602,133 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
 #pragma unroll
     for (int i = 0; i < NDT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+    // scores of a unit: keys 32 u + 8 g + 4 ab + v of this lane's query
+    auto scores = [&](const uint4 (*X)[64], f32x4_t (&sc)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ab = 0; ab < 2; ++ab) {
+            sc[ab] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            uint4 kf[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) kf[c] = X[ab * NC + c][lane];
+#pragma unroll
+            for (int t = kTerms - 1; t >= 0; --t)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) sc[ab] = mfma_bf16(kf[c], q[c][t], sc[ab]);
+        }
+    };
+    auto max_of = [&](const f32x4_t (&sc)[2]) __attribute__((always_inline)) {
+        return max_over_rows(fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])), fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3]))));
+    };
+    union Terms { uint4 v; uint32_t h[4]; };
+    // probabilities of a unit in three terms; their sum over this lane's keys
+    auto probabilities = [&](const f32x4_t (&sc)[2], float m_new, Terms (&pb)[kTerms]) __attribute__((always_inline)) {
+        float p[8], lsum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            p[e] = exp_score(sc[e >> 2][e & 3] - m_new);
+            lsum += p[e];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            uint32_t t3[kTerms];
+            split3_pair(p[e], p[e + 1], t3);
+#pragma unroll
+            for (int t = 0; t < kTerms; ++t) pb[t].h[e / 2] = t3[t];
+        }
+        return lsum;
+    };
+    // two units all of whose keys every query of the wave sees: the same steps in the same order, side by side
+    auto two_units = [&](const uint4 (*X0)[64], const uint4 (*X1)[64]) __attribute__((always_inline)) {
+        f32x4_t s0[2], s1[2];
+        scores(X0, s0);
+        scores(X1, s1);
+        const float m0 = fmaxf(m_run, max_of(s0)), m1 = fmaxf(m0, max_of(s1));
+        const float rescale0 = exp_score(m_run - m0), rescale1 = exp_score(m0 - m1);
+        m_run = m1;
+        Terms p0[kTerms], p1[kTerms];
+        l_run = l_run * rescale0 + probabilities(s0, m0, p0);
+        l_run = l_run * rescale1 + probabilities(s1, m1, p1);
+#pragma unroll
+        for (int i = 0; i < NDT; ++i) {
+            const uint4 v0 = X0[2 * NC + i][lane], v1 = X1[2 * NC + i][lane];
+            f32x4_t o0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, o1 = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = kTerms - 1; t >= 0; --t) {
+                o0 = mfma_bf16(v0, p0[t].v, o0);
+                o1 = mfma_bf16(v1, p1[t].v, o1);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[i][v] = __builtin_fmaf(__builtin_fmaf(acc[i][v], rescale0, o0[v]), rescale1, o1[v]);
+        }
+    };
+
     int buf = 0, nbuf = 2;
-    for (int u = 0; u < n_units; ++u) {
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PB) : "memory");   // as in the GEMM: unit u is there, reads of u - 1 are done
+    for (int u = 0; u < n_units; u += U) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(U * PB) : "memory");   // as in the GEMM: this step's units are there, reads of the last step's are done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        issue(u + 2, nbuf);
-        if (wave_has_rows && 32 * u <= w_last) {                 // wave-uniform
-            const bool diagonal = 32 * u + 31 > w_first;         // some key is hidden from some query of the wave
-            f32x4_t sc[2];
+        issue(u + 2 * U, nbuf);
+        const bool both = U == 2 && 32 * u + 63 <= w_first && wave_has_rows;    // wave-uniform, like the conditions below
+        if (both) two_units(S[buf][0], S[buf][U - 1]);
 #pragma unroll
-            for (int ab = 0; ab < 2; ++ab) {
-                sc[ab] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                uint4 kf[NC];
+        for (int h = 0; h < U; ++h) {
+            if (!both && wave_has_rows && 32 * (u + h) <= w_last) {
+                const bool diagonal = 32 * (u + h) + 31 > w_first;         // some key is hidden from some query of the wave
+                f32x4_t sc[2];
+                scores(S[buf][h], sc);
+                if (diagonal) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) kf[c] = S[buf][ab * NC + c][lane];
+                    for (int ab = 0; ab < 2; ++ab)
 #pragma unroll
-                for (int t = kTerms - 1; t >= 0; --t)
+                        for (int v = 0; v < 4; ++v) sc[ab][v] = 32 * (u + h) + 8 * g + 4 * ab + v > q_pos ? -INFINITY : sc[ab][v];
+                }
+                const float m_new = fmaxf(m_run, max_of(sc));
+                const float rescale = exp_score(m_run - m_new);      // (a first unit: 0)
+                m_run = m_new;
+                Terms pb[kTerms];
+                l_run = l_run * rescale + probabilities(sc, m_new, pb);   // this lane's keys only: added up over the lane groups at the end
+                uint4 vf[NDT];
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) sc[ab] = mfma_bf16(kf[c], q[c][t], sc[ab]);
-            }
-            if (diagonal) {
+                for (int i = 0; i < NDT; ++i) vf[i] = S[buf][h][2 * NC + i][lane];
+                bool odd = false;                                    // wave-uniform: some V of a unit with hidden keys is not finite
+                if (diagonal) {
+                    uint32_t top = 0;                                // an exponent of all ones carries into its half's sign bit
 #pragma unroll
-                for (int ab = 0; ab < 2; ++ab)
+                    for (int i = 0; i < NDT; ++i)
+                        top |= exponent_carry(vf[i].x) | exponent_carry(vf[i].y) | exponent_carry(vf[i].z) | exponent_carry(vf[i].w);
+                    odd = __any((top & 0x80008000u) != 0);
+                    if (odd) {                                       // a hidden key's V must not leak through 0 * inf
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) sc[ab][v] = 32 * u + 8 * g + 4 * ab + v > q_pos ? -INFINITY : sc[ab][v];
-            }
-            float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])), fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-            mx = max_over_rows(mx);
-            const float m_new = fmaxf(m_run, mx);
-            const float rescale = exp_score(m_run - m_new);      // (a first unit: 0)
-            m_run = m_new;
-            float p[8], lsum = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                p[e] = exp_score(sc[e >> 2][e & 3] - m_new);
-                lsum += p[e];
-            }
-            l_run = l_run * rescale + lsum;                      // this lane's keys only: added up over the lane groups at the end
-            union { uint4 v; uint32_t h[4]; } pb[kTerms];
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                uint32_t t3[kTerms];
-                split3_pair(p[e], p[e + 1], t3);
-#pragma unroll
-                for (int t = 0; t < kTerms; ++t) pb[t].h[e / 2] = t3[t];
-            }
-            uint4 vf[NDT];
-#pragma unroll
-            for (int i = 0; i < NDT; ++i) vf[i] = S[buf][2 * NC + i][lane];
-            bool odd = false;                                    // wave-uniform: some V of a unit with hidden keys is not finite
-            if (diagonal) {
-                uint32_t top = 0;                                // an exponent of all ones carries into its half's sign bit
-#pragma unroll
-                for (int i = 0; i < NDT; ++i)
-                    top |= exponent_carry(vf[i].x) | exponent_carry(vf[i].y) | exponent_carry(vf[i].z) | exponent_carry(vf[i].w);
-                odd = __any((top & 0x80008000u) != 0);
-                if (odd) {                                       // a hidden key's V must not leak through 0 * inf
-#pragma unroll
-                    for (int i = 0; i < NDT; ++i) {
-                        vf[i].x = finite_pair(vf[i].x); vf[i].y = finite_pair(vf[i].y);
-                        vf[i].z = finite_pair(vf[i].z); vf[i].w = finite_pair(vf[i].w);
+                        for (int i = 0; i < NDT; ++i) {
+                            vf[i].x = finite_pair(vf[i].x); vf[i].y = finite_pair(vf[i].y);
+                            vf[i].z = finite_pair(vf[i].z); vf[i].w = finite_pair(vf[i].w);
+                        }
                     }
                 }
-            }
-#pragma unroll
-            for (int i = 0; i < NDT; ++i) {
-                f32x4_t o = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int t = kTerms - 1; t >= 0; --t) o = mfma_bf16(vf[i], pb[t].v, o);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][v] = __builtin_fmaf(acc[i][v], rescale, o[v]);
-            }
-            if (odd) {                                           // rare: a V that is not finite reaches the queries that see its key
-                uint4 seen = {0, 0, 0, 0};                       // B operand: 1 where this lane's query sees the key
-                const int n_seen = q_pos + 1 - (32 * u + 8 * g); // of the lane's 8 keys
-                uint32_t *sw = reinterpret_cast<uint32_t *>(&seen);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sw[e] = (2 * e < n_seen ? 0x3f80u : 0u) | (2 * e + 1 < n_seen ? 0x3f800000u : 0u);
 #pragma unroll
                 for (int i = 0; i < NDT; ++i) {
-                    const uint4 raw = S[buf][2 * NC + i][lane];
-                    const f32x4_t pos = mfma_bf16(ones_where(raw, false), seen, f32x4_t{0.f, 0.f, 0.f, 0.f});
-                    const f32x4_t neg = mfma_bf16(ones_where(raw, true), seen, f32x4_t{0.f, 0.f, 0.f, 0.f});
+                    f32x4_t o = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        if (pos[v] > 0.f) acc[i][v] += INFINITY;
-                        if (neg[v] > 0.f) acc[i][v] -= INFINITY;
+                    for (int t = kTerms - 1; t >= 0; --t) o = mfma_bf16(vf[i], pb[t].v, o);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[i][v] = __builtin_fmaf(acc[i][v], rescale, o[v]);
+                }
+                if (odd) {                                           // rare: a V that is not finite reaches the queries that see its key
+                    uint4 seen = {0, 0, 0, 0};                       // B operand: 1 where this lane's query sees the key
+                    const int n_seen = q_pos + 1 - (32 * (u + h) + 8 * g); // of the lane's 8 keys
+                    uint32_t *sw = reinterpret_cast<uint32_t *>(&seen);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sw[e] = (2 * e < n_seen ? 0x3f80u : 0u) | (2 * e + 1 < n_seen ? 0x3f800000u : 0u);
+#pragma unroll
+                    for (int i = 0; i < NDT; ++i) {
+                        const uint4 raw = S[buf][h][2 * NC + i][lane];
+                        const f32x4_t pos = mfma_bf16(ones_where(raw, false), seen, f32x4_t{0.f, 0.f, 0.f, 0.f});
+                        const f32x4_t neg = mfma_bf16(ones_where(raw, true), seen, f32x4_t{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            if (pos[v] > 0.f) acc[i][v] += INFINITY;
+                            if (neg[v] > 0.f) acc[i][v] -= INFINITY;
+                        }
                     }
                 }
             }

@@ -120,6 +120,12 @@ def test_a_row_that_is_not_finite_does_not_reach_earlier_rows():
     assert torch.isnan(last).all()
 
 
+# heads of 64 take two units of 32 keys per step: prompts that end, and second passes that start, at every place of a step
+@pytest.mark.parametrize("first,second", [(32, 0), (33, 0), (63, 0), (65, 0), (95, 0), (96, 0), (97, 0), (128, 33), (31, 98), (47, 65), (64, 128), (79, 130)])
+def test_steps_of_two_units_against_oracle(first, second):
+    test_prefill_passes_against_oracle("small", first, second)
+
+
 @pytest.mark.parametrize("n", [2048 + 10, 2048 + 70, 4096 + 25])
 def test_a_prompt_of_several_passes_by_ids_has_the_bits_of_its_rows(n):
     from paper_2404_08856_amd import spd
