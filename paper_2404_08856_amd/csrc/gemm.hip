@@ -1016,9 +1016,9 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
 #undef SPD_GEMM_CASE
     // Several row groups with a scratch buffer: the tile-splitting kernel makes one pass over the weights for up to 13
     // row groups (65 rows).  It takes all calls of more than 10 rows.  Measured at the 7B shapes against the K-splitting kernel (microseconds per launch), 20 rows:
-    // gate|up 35 / 48, down 28 / 36, LM head 46 / 66, QKV 23 / 29, O 17 / 17; 40 rows: gate|up 44 / 67, down 34 / 52,
-    // LM head 51 / 91, QKV 28 / 40, O 22 / 23; beyond 40 rows the K-splitting kernel needs a second pass.  Rows 6..10 only
-    // where K is too long for resident activations (7B down: 22.3 / 24.1).
+    // gate|up 35 / 48, down 22 / 36, LM head 46 / 66, QKV 23 / 29, O 12 / 17; 40 rows: gate|up 44 / 67, down 29 / 52,
+    // LM head 51 / 91, QKV 28 / 40, O 16 / 23; beyond 40 rows the K-splitting kernel needs a second pass.  Rows 6..10 only
+    // where K is too long for resident activations (7B down: 20.0 / 24.1).
     const bool batch_pays = groups > 2 || k.KS > 128;
     // Row groups the kernel is built for: a group without rows costs the same traffic and products as one with (15 rows
     // on 3 groups instead of 4, four 7B layers + head: 469 us a step against 478; 48 rows on 10 instead of 13: 702 against 784)

@@ -8,7 +8,7 @@
 //  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
 //    the pass's own rows).
 // Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
-// four 7B layers, 2047 rows 8.8 ms (was 41.1), 640 rows 2.95 (10.2); 12-layer draft, 1472 rows 1.78 ms (47.1).
+// four 7B layers, 2047 rows 5.3 ms (was 41.1), 640 rows 2.0 (10.2), with prefill_wide.hip; 12-layer draft, 1472 rows 1.65 ms (47.1).
 #include <algorithm>
 
 #include "gemm_core.h"

@@ -81,6 +81,7 @@ def check(name, n_seqs, M, batch_kernel=0):
         check_logits(got[s], dec.forward_tokens(cfg, wn, caches[s], vt[s]), f"{name} seq {s}")
 
 
+# rows 6..10, matrices of 256 tiles or more: QKV in groups of 6 waves, gate|up of 4, both in 4 slices
 @pytest.mark.parametrize("n_seqs,M", [(1, 6), (2, 5)])
-def test_two_groups_in_eight_slices_against_oracle(n_seqs, M):
+def test_two_groups_in_four_slices_against_oracle(n_seqs, M):
     check("k2048", n_seqs, M, batch_kernel=1)
