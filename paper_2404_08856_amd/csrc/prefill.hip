@@ -261,11 +261,24 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
         }
         __syncthreads();
         if (!is_last) return;
+        // This slice's sums are still here: added in their place without the way back through memory (12-layer draft, 200 rows: 857 -> 831 us).
+        float own[NW][NX][4];
 #pragma unroll
         for (int i = 0; i < NW; ++i)
 #pragma unroll
-            for (int j = 0; j < NX; ++j) sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < NX; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) { own[i][j][v] = sum[i][j][v]; sum[i][j][v] = 0.f; }
         for (int s = 0; s < a.J; ++s) {
+            if (s == slice) {                             // workgroup-uniform
+#pragma unroll
+                for (int i = 0; i < NW; ++i)
+#pragma unroll
+                    for (int j = 0; j < NX; ++j)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sum[i][j][v] += own[i][j][v];
+                continue;
+            }
             const unsigned long long *src = reinterpret_cast<const unsigned long long *>(a.partials) + ((size_t)tile * a.J + s) * kTile * 2;
             unsigned long long lo[NW][NX], hi[NW][NX];
 #pragma unroll

@@ -391,13 +391,24 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void wide_gemm_kernel(WideGemmKerne
         }
         __syncthreads();
         if (!is_last) return;
+        // This slice's sums are still here: added in their place without the way back through memory (four 7B layers, 640 rows: 1960 -> 1944 us).
+        float own[NW][NX][4];
 #pragma unroll
         for (int i = 0; i < NW; ++i)
 #pragma unroll
             for (int j = 0; j < NX; ++j)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) sum[i][j][v] = 0.f;
+                for (int v = 0; v < 4; ++v) { own[i][j][v] = sum[i][j][v]; sum[i][j][v] = 0.f; }
         for (int s = 0; s < a.J; ++s) {
+            if (s == slice) {                             // workgroup-uniform
+#pragma unroll
+                for (int i = 0; i < NW; ++i)
+#pragma unroll
+                    for (int j = 0; j < NX; ++j)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sum[i][j][v] += own[i][j][v];
+                continue;
+            }
             const unsigned long long *src = reinterpret_cast<const unsigned long long *>(a.partials) + ((size_t)tile * a.J + s) * kTile * 2;
             unsigned long long lo[NW][NX], hi[NW][NX];
 #pragma unroll
