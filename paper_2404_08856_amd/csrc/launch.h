@@ -177,49 +177,11 @@ constexpr int kPrefillMaxSlices = 8, kPrefillMaxSplit = 1024;    // K slices per
 size_t prefill_partial_bytes(int N, int max_rows);
 int prefill_ssq_parts(int n_tiles, int rows);
 hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream_t stream);
-// ---- the same GEMM with two f16 terms (prefill_wide.hip) ----
-// Two thirds of the matrix work.  Used where its error against 64 bits is no larger than that of three bf16 terms: by models whose
-// projections all contract over at least kWideK values, for passes of at least kWideRows rows -- from there on the other kernels have
-// no accumulator of their own for the small terms either.  Four 7B layers, error of the cached keys and values, three terms / two:
-// 200 rows 5.3e-4 / 5.8e-4, 385 rows 5.7e-4 / 5.5e-4, 640 rows 5.4e-4 / 5.2e-4, 2047 rows 5.0e-4 / 4.8e-4; models of K = 128 to 512 have up to
-// 1.7 times as many flipped roundings.  Times: 385 rows 1.91 / 1.71 ms, 640 rows 2.42 / 1.99, 2047 rows 6.99 / 5.29.
-constexpr int kWideK = 2048, kWideRows = 385, kWideTerms = 2;
-hipError_t launch_wide_rows(const void *embed_bf16, const int32_t *tokens, const float *embeds, int rows, int d, int vocab,
-                            const float *gain, float *h, void *X, float *x_scale, float *ssq, int ssq_ld, hipStream_t stream);
-// factor (a power of two) of each of the N rows of a packed weight matrix (model creation)
-hipError_t launch_weight_factors(const void *packed, int N, int K, float *out, hipStream_t stream);
-struct WideGemmArgs {
-    const void *W;            // packed weights [N, K]
-    const float *w_factor;    // [N] from launch_weight_factors
-    const void *X;            // activations in the prefill layout (ceil(rows / 16) row tiles)
-    const float *x_scale;     // their blocks' inverse factors
-    int chunk;                // K-steps per block: 4 or 2
-    int N, K, rows;
-    float *Y;                 // STORE: Y = s * acc; RESIDUAL: Y += acc
-    int ldy;
-    const float *ssq_in;      // [rows][ssq_ld]: ssq_parts partial sums of squares per row (NULL: s = 1)
-    int ssq_ld, ssq_parts;
-    float eps;
-    const float *gain_next;   // RESIDUAL: gain of the following norm; then Xout, xout_scale and ssq_out are written too
-    float *ssq_out;           // wide_ssq_parts parts per row
-    void *Xout;               // RESIDUAL: the new rows times the gain; SWIGLU: activations of N / 2 columns
-    float *xout_scale;        // in blocks of wide_out_chunk K-steps
-    float *partials;          // scratch for the sums of K slices (wide_partial_bytes), or NULL: K is never sliced
-    unsigned *arrive;         // kPrefillMaxSplit counters, zero between launches
-};
-struct WidePlan { bool large; int slices; };
-WidePlan wide_plan(int N, int K, int rows);
-size_t wide_partial_bytes(int N, int K, int max_rows);
-int wide_ssq_parts(int N, int K, int rows);
-int wide_out_chunk(int N, int K, int rows, int epilogue);
-hipError_t launch_wide_gemm(const WideGemmArgs &a, int epilogue, hipStream_t stream);
 struct PrefillAttnArgs {
     const float *qkv;         // [rows, 3 * H * dh] before RoPE
     const float *rope;
     void *k_cache, *v_cache;  // this layer and sequence, layouts as in AttnArgs
     void *xout;               // attention output in the prefill layout, K = H * dh
-    int terms;                // its terms per value, 3 or 2; 2: one block per head
-    float *xout_scale;        // 2 terms: the inverse factors
     int rows, H, dh, max_positions, v_stride;
     const int32_t *d_len;     // KV length in device memory, or NULL: `len`
     int32_t *d_error;

@@ -46,16 +46,14 @@ struct Layout {                    // byte offsets inside the three buffers
     // packed
     size_t embed, lm_head, final_norm;
     std::vector<size_t> attn_norm, wqkv, wo, mlp_norm, wgu, wdown;
-    std::vector<size_t> fqkv, fo, fgu, fdown;      // factors of the matrices' rows (prefill with two terms)
     size_t packed_total;
     // kv
     size_t kv_layer_stride, kv_k_bytes, kv_v_bytes, kv_total;
     int v_stride;
     // workspace
     size_t h, qkv, xn, xo, xf, rope, logits, ssq_a, ssq_b, d_lens, d_error, qa_count, qa_abort, part, arrive, zero;
-    size_t ph, pqkv, pxn, pxo, pxf, pxn_scale, pxo_scale, pxf_scale, pssq_a, pssq_b, ppart;      // prefill passes of up to prefill_rows rows
+    size_t ph, pqkv, pxn, pxo, pxf, pssq_a, pssq_b, ppart;      // prefill passes of up to prefill_rows rows
     int prefill_rows, pssq_ld;
-    bool wide;                     // prefill passes of at least kWideRows rows take the kernels with two terms
     size_t ws_total;
 };
 
@@ -77,7 +75,6 @@ int32_t check_shape(const spd_model_config &c) {
 
 void make_layout(const spd_model_config &c, Layout &L) {
     const int d = c.d_model, HD = c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
-    L.wide = std::min({d, HD, F}) >= kWideK && c.max_positions >= kWideRows;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     L.embed = take((size_t)V * d * 2);
@@ -90,12 +87,6 @@ void make_layout(const spd_model_config &c, Layout &L) {
         L.mlp_norm.push_back(take((size_t)d * 4));
         L.wgu.push_back(take(packed_matrix_bytes(2 * F, d)));
         L.wdown.push_back(take(packed_matrix_bytes(d, F)));
-        if (L.wide) {
-            L.fqkv.push_back(take((size_t)3 * HD * 4));
-            L.fo.push_back(take((size_t)d * 4));
-            L.fgu.push_back(take((size_t)2 * F * 4));
-            L.fdown.push_back(take((size_t)d * 4));
-        }
     }
     L.packed_total = off;
 
@@ -134,22 +125,12 @@ void make_layout(const spd_model_config &c, Layout &L) {
     const size_t pr = align_up((size_t)L.prefill_rows, 16);
     L.ph = take(pr * d * 4);
     L.pqkv = take(pr * 3 * HD * 4);
-    // 16-bit terms per column: two of all rows, or three of the rows of a pass too short for two
-    const size_t px = L.wide ? std::max(pr * kWideTerms, align_up((size_t)kWideRows - 1, 16) * kTerms) : pr * kTerms;
-    L.pxn = take(px * KSd * 64);
-    L.pxo = take(px * KShd * 64);
-    L.pxf = take(px * KSf * 64);
-    L.pxn_scale = L.wide ? take(pr * ((KSd + 3) / 4) * 4) : 0;    // one factor per row and block of 4 or 2 K-steps
-    L.pxo_scale = L.wide ? take(pr * c.n_heads * 4) : 0;
-    L.pxf_scale = L.wide ? take(pr * ((KSf + 1) / 2) * 4) : 0;
+    L.pxn = take(pr * KSd * 64 * kTerms);
+    L.pxo = take(pr * KShd * 64 * kTerms);
+    L.pxf = take(pr * KSf * 64 * kTerms);
     L.pssq_a = take(pr * L.pssq_ld * 4);
     L.pssq_b = take(pr * L.pssq_ld * 4);
-    const int pm = L.prefill_rows;
-    size_t pp = std::max({prefill_partial_bytes(3 * HD, pm), prefill_partial_bytes(d, pm), prefill_partial_bytes(2 * F, pm)});
-    if (L.wide)                                              // (2 HD: the last layer's keys and values alone)
-        pp = std::max({pp, wide_partial_bytes(3 * HD, d, pm), wide_partial_bytes(2 * HD, d, pm), wide_partial_bytes(d, HD, pm),
-                       wide_partial_bytes(2 * F, d, pm), wide_partial_bytes(d, F, pm)});
-    L.ppart = take(pp);
+    L.ppart = take(std::max({prefill_partial_bytes(3 * HD, L.prefill_rows), prefill_partial_bytes(d, L.prefill_rows), prefill_partial_bytes(2 * F, L.prefill_rows)}));
     L.ws_total = off;
 }
 
@@ -333,12 +314,6 @@ int32_t spd_model_create(const spd_model_config *cfg, const spd_weights *w, void
         CREATE_TRY(hipMemcpyAsync(m->packed + L.mlp_norm[l], w->mlp_norm[l], (size_t)d * 4, hipMemcpyDeviceToDevice, st));
         CREATE_TRY(launch_pack_weight(w->w_gate[l], w->w_up[l], nullptr, PACK_GATE_UP, 2 * F, d, m->packed + L.wgu[l], st));
         CREATE_TRY(launch_pack_weight(w->w_down[l], nullptr, nullptr, PACK_PLAIN, d, F, m->packed + L.wdown[l], st));
-        if (L.wide) {
-            CREATE_TRY(launch_weight_factors(m->packed + L.wqkv[l], 3 * HD, d, (float *)(m->packed + L.fqkv[l]), st));
-            CREATE_TRY(launch_weight_factors(m->packed + L.wo[l], d, HD, (float *)(m->packed + L.fo[l]), st));
-            CREATE_TRY(launch_weight_factors(m->packed + L.wgu[l], 2 * F, d, (float *)(m->packed + L.fgu[l]), st));
-            CREATE_TRY(launch_weight_factors(m->packed + L.wdown[l], d, F, (float *)(m->packed + L.fdown[l]), st));
-        }
     }
     // workspace starts cleared: the padding columns of the packed activation buffers must be zero;
     // the KV cache too: the attention kernel reads (and masks) whole 32-position units, so every
@@ -619,23 +594,20 @@ int32_t prefill_pass(spd_model *m, int32_t seq, const float *embeds, const int32
     const spd_model_config &c = m->cfg;
     const Layout &L = m->L;
     const int d = c.d_model, HD = c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
-    const bool wide = L.wide && M >= kWideRows;
     float *h = (float *)(m->ws + L.ph), *qkv = (float *)(m->ws + L.pqkv);
     float *ssq_a = (float *)(m->ws + L.pssq_a), *ssq_b = (float *)(m->ws + L.pssq_b);
-    float *xn_scale = (float *)(m->ws + L.pxn_scale), *xo_scale = (float *)(m->ws + L.pxo_scale), *xf_scale = (float *)(m->ws + L.pxf_scale);
     void *xn = m->ws + L.pxn, *xo = m->ws + L.pxo, *xf = m->ws + L.pxf;
     auto gain_of = [&](size_t off) { return (const float *)(m->packed + off); };
-    PROF_TRY(PK_EMBED, wide ? launch_wide_rows(m->packed + L.embed, tokens, embeds, M, d, V, gain_of(L.attn_norm[0]), h, xn, xn_scale, ssq_b, L.pssq_ld, st)
-                            : launch_prefill_rows(m->packed + L.embed, tokens, embeds, M, d, V, gain_of(L.attn_norm[0]), h, xn, ssq_b, L.pssq_ld, st));
+    PROF_TRY(PK_EMBED, launch_prefill_rows(m->packed + L.embed, tokens, embeds, M, d, V, gain_of(L.attn_norm[0]), h, xn, ssq_b, L.pssq_ld, st));
     PrefillAttnArgs at{};
-    at.qkv = qkv; at.rope = (const float *)(m->ws + L.rope); at.xout = xo; at.terms = wide ? kWideTerms : kTerms; at.xout_scale = xo_scale;
+    at.qkv = qkv; at.rope = (const float *)(m->ws + L.rope); at.xout = xo;
     at.rows = M; at.H = c.n_heads; at.dh = c.head_dim; at.max_positions = c.max_positions; at.v_stride = L.v_stride;
     at.len = m->lens[seq];
     if (m->dev_lens) {
         at.d_len = (const int32_t *)(m->ws + L.d_lens) + seq;
         at.d_error = (int32_t *)(m->ws + L.d_error);
     }
-    const int parts_a = wide ? wide_ssq_parts(d, HD, M) : prefill_ssq_parts(d / 16, M), parts_b = wide ? wide_ssq_parts(d, F, M) : parts_a;
+    const int parts = prefill_ssq_parts(d / 16, M);
     for (int l = 0; l < c.n_layers; ++l) {
         const bool last = l + 1 == c.n_layers;
         char *kv_l = m->kv + (size_t)l * L.kv_layer_stride;
@@ -643,52 +615,27 @@ int32_t prefill_pass(spd_model *m, int32_t seq, const float *embeds, const int32
         at.v_cache = kv_l + align_up(L.kv_k_bytes, 256) + (size_t)seq * c.n_heads * c.head_dim * L.v_stride * 2;
         const int q0 = last ? HD : 0;                     // the last layer's queries are not needed: features HD .. 3 HD - 1
         const char *wqkv = m->packed + L.wqkv[l] + packed_matrix_bytes(q0, d);
-        if (wide) {
-            WideGemmArgs common{};
-            common.rows = M; common.ssq_ld = L.pssq_ld; common.eps = c.rms_eps; common.chunk = 4;
-            common.partials = (float *)(m->ws + L.ppart); common.arrive = (unsigned *)(m->ws + L.arrive);
-            WideGemmArgs g = common;
-            g.W = wqkv; g.w_factor = gain_of(L.fqkv[l]) + q0; g.X = xn; g.x_scale = xn_scale; g.N = 3 * HD - q0; g.K = d; g.Y = qkv + q0; g.ldy = 3 * HD;
-            g.ssq_in = ssq_b; g.ssq_parts = l == 0 ? 1 : parts_b;
-            PROF_TRY(PK_QKV, launch_wide_gemm(g, EPI_STORE, st));
-            PROF_TRY(PK_ATTENTION, launch_prefill_attention(at, !last, st));
-            if (last) break;
-            g = common;
-            g.W = m->packed + L.wo[l]; g.w_factor = gain_of(L.fo[l]); g.X = xo; g.x_scale = xo_scale; g.chunk = c.head_dim / 32; g.N = d; g.K = HD; g.Y = h; g.ldy = d;
-            g.gain_next = gain_of(L.mlp_norm[l]); g.Xout = xn; g.xout_scale = xn_scale; g.ssq_out = ssq_a;
-            PROF_TRY(PK_O, launch_wide_gemm(g, EPI_RESIDUAL, st));
-            g = common;
-            g.W = m->packed + L.wgu[l]; g.w_factor = gain_of(L.fgu[l]); g.X = xn; g.x_scale = xn_scale; g.N = 2 * F; g.K = d; g.Xout = xf; g.xout_scale = xf_scale;
-            g.ssq_in = ssq_a; g.ssq_parts = parts_a;
-            PROF_TRY(PK_GATE_UP, launch_wide_gemm(g, EPI_SWIGLU, st));
-            g = common;
-            g.W = m->packed + L.wdown[l]; g.w_factor = gain_of(L.fdown[l]); g.X = xf; g.x_scale = xf_scale; g.chunk = wide_out_chunk(2 * F, d, M, EPI_SWIGLU);
-            g.N = d; g.K = F; g.Y = h; g.ldy = d;
-            g.gain_next = gain_of(L.attn_norm[l + 1]); g.Xout = xn; g.xout_scale = xn_scale; g.ssq_out = ssq_b;
-            PROF_TRY(PK_DOWN, launch_wide_gemm(g, EPI_RESIDUAL, st));
-        } else {
-            PrefillGemmArgs common{};
-            common.rows = M; common.ssq_ld = L.pssq_ld; common.eps = c.rms_eps;
-            common.partials = (float *)(m->ws + L.ppart); common.arrive = (unsigned *)(m->ws + L.arrive);
-            PrefillGemmArgs g = common;
-            g.W = wqkv; g.X = xn; g.N = 3 * HD - q0; g.K = d; g.Y = qkv + q0; g.ldy = 3 * HD;
-            g.ssq_in = ssq_b; g.ssq_parts = l == 0 ? 1 : parts_b;
-            PROF_TRY(PK_QKV, launch_prefill_gemm(g, EPI_STORE, st));
-            PROF_TRY(PK_ATTENTION, launch_prefill_attention(at, !last, st));
-            if (last) break;
-            g = common;
-            g.W = m->packed + L.wo[l]; g.X = xo; g.N = d; g.K = HD; g.Y = h; g.ldy = d;
-            g.gain_next = gain_of(L.mlp_norm[l]); g.Xnext = xn; g.ssq_out = ssq_a;
-            PROF_TRY(PK_O, launch_prefill_gemm(g, EPI_RESIDUAL, st));
-            g = common;
-            g.W = m->packed + L.wgu[l]; g.X = xn; g.N = 2 * F; g.K = d; g.Xout = xf;
-            g.ssq_in = ssq_a; g.ssq_parts = parts_a;
-            PROF_TRY(PK_GATE_UP, launch_prefill_gemm(g, EPI_SWIGLU, st));
-            g = common;
-            g.W = m->packed + L.wdown[l]; g.X = xf; g.N = d; g.K = F; g.Y = h; g.ldy = d;
-            g.gain_next = gain_of(L.attn_norm[l + 1]); g.Xnext = xn; g.ssq_out = ssq_b;
-            PROF_TRY(PK_DOWN, launch_prefill_gemm(g, EPI_RESIDUAL, st));
-        }
+        PrefillGemmArgs common{};
+        common.rows = M; common.ssq_ld = L.pssq_ld; common.eps = c.rms_eps;
+        common.partials = (float *)(m->ws + L.ppart); common.arrive = (unsigned *)(m->ws + L.arrive);
+        PrefillGemmArgs g = common;
+        g.W = wqkv; g.X = xn; g.N = 3 * HD - q0; g.K = d; g.Y = qkv + q0; g.ldy = 3 * HD;
+        g.ssq_in = ssq_b; g.ssq_parts = l == 0 ? 1 : parts;
+        PROF_TRY(PK_QKV, launch_prefill_gemm(g, EPI_STORE, st));
+        PROF_TRY(PK_ATTENTION, launch_prefill_attention(at, !last, st));
+        if (last) break;
+        g = common;
+        g.W = m->packed + L.wo[l]; g.X = xo; g.N = d; g.K = HD; g.Y = h; g.ldy = d;
+        g.gain_next = gain_of(L.mlp_norm[l]); g.Xnext = xn; g.ssq_out = ssq_a;
+        PROF_TRY(PK_O, launch_prefill_gemm(g, EPI_RESIDUAL, st));
+        g = common;
+        g.W = m->packed + L.wgu[l]; g.X = xn; g.N = 2 * F; g.K = d; g.Xout = xf;
+        g.ssq_in = ssq_a; g.ssq_parts = parts;
+        PROF_TRY(PK_GATE_UP, launch_prefill_gemm(g, EPI_SWIGLU, st));
+        g = common;
+        g.W = m->packed + L.wdown[l]; g.X = xf; g.N = d; g.K = F; g.Y = h; g.ldy = d;
+        g.gain_next = gain_of(L.attn_norm[l + 1]); g.Xnext = xn; g.ssq_out = ssq_b;
+        PROF_TRY(PK_DOWN, launch_prefill_gemm(g, EPI_RESIDUAL, st));
     }
     int32_t *d_len = (int32_t *)(m->ws + L.d_lens) + seq;
     if (last_logits) {

@@ -2,20 +2,37 @@
 // pass over the weights.  With hundreds of rows the projections are bound by the matrix cores, not by the
 // weight stream, so everything here is organised around them:
 //
-//  * Operand layouts (prefill_core.h): every value as three bf16 terms, or, in prefill_wide.hip, as two f16 terms.
+//  * Operand layouts.  Weights: the packed 1 KiB blocks of common.h, unchanged (A operand).  Activations X[R, K]:
+//    three bf16 terms per value as everywhere, but each term is a matrix-core operand of its own -- 16 rows fill
+//    the 16 columns of the B operand -- and the three products go into the same accumulator: no column of a tile
+//    is unused and no sum over term columns is needed.  Block (row tile rt of 16 rows, K-step s, term t) is the
+//    1 KiB at index (rt * KS + s) * 3 + t, lane l = r + 16 g holding X[16 rt + r][32 s + 8 g .. + 7].
 //  * prefill_gemm_kernel: tiled GEMM, both operands through LDS.  Bound by the matrix cores: the 7B QKV projection of
 //    2047 rows runs at 1.31 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.28).
 //  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
 //    the pass's own rows).
 // Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
-// four 7B layers, 2047 rows 5.3 ms (was 41.1), 640 rows 2.0 (10.2), with prefill_wide.hip; 12-layer draft, 1472 rows 1.65 ms (47.1).
+// four 7B layers, 2047 rows 7.0 ms (was 41.1), 640 rows 2.4 (10.2); 12-layer draft, 1472 rows 1.65 ms (47.1).
 #include <algorithm>
 
 #include "gemm_core.h"
 #include "launch.h"
-#include "prefill_core.h"
 
 namespace spd {
+
+// element offset (bf16 units) of X[row][k] term t in the layout above
+__device__ __forceinline__ size_t ppack_index(int row, int k, int KS, int t) {
+    return (((size_t)(row >> 4) * KS + (k >> 5)) * kTerms + t) * 512 + packed_elem_index(row & 15, k & 31);
+}
+
+// four consecutive values (k % 4 == 0) of one row into the packed layout, 8 bytes per term
+__device__ __forceinline__ void ppack_store4(uint16_t *X, int row, int k, int KS, const float (&y)[4]) {
+    uint32_t lo[kTerms], hi[kTerms];
+    split3_pair(y[0], y[1], lo);
+    split3_pair(y[2], y[3], hi);
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t) *reinterpret_cast<uint2 *>(X + ppack_index(row, k, KS, t)) = uint2{lo[t], hi[t]};
+}
 
 // 1 KiB from memory (16 bytes per lane) to LDS (lane-linear from `dst`, wave-uniform), without registers; counts on
 // vmcnt.  As inline assembly because the compiler makes every LDS read wait for ALL outstanding LDS-direct loads it
@@ -58,8 +75,8 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(const uint16_t *__res
         *reinterpret_cast<float4 *>(h + (size_t)row * d + k) = v;
         ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
         const float4 g = *reinterpret_cast<const float4 *>(gain + k);
-        const float x[4] = {v.x, v.y, v.z, v.w}, y[4] = {g.x, g.y, g.z, g.w};
-        ppack_store4<kTerms>(X, row, k, KS, x, y, 1.f);
+        const float y[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
+        ppack_store4(X, row, k, KS, y);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
@@ -325,7 +342,6 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
             for (int i = 0; i < NW; i += 2) {
                 const int t = t0 + wn * NW + i + (g >> 1);
                 float y[4];
-                const float one[4] = {1.f, 1.f, 1.f, 1.f};
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const float p = sum[i][j][v] * inv, q = sum[i + 1][j][v] * inv;
@@ -333,7 +349,7 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                     const float gate = g < 2 ? p : got, up = g < 2 ? got : q;
                     y[v] = gate / (1.0f + expf(-gate)) * up;
                 }
-                if (row_ok && t < a.n_tiles) ppack_store4<kTerms>(a.Xout, row, t * 8 + 4 * (g & 1), a.KS_out, y, one, 1.f);
+                if (row_ok && t < a.n_tiles) ppack_store4(a.Xout, row, t * 8 + 4 * (g & 1), a.KS_out, y);
             }
         } else {
             float sq = 0.f;
@@ -349,8 +365,8 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                     h.x += sum[i][j][0]; h.y += sum[i][j][1]; h.z += sum[i][j][2]; h.w += sum[i][j][3];
                     *dst = h;
                     if (a.gain_next) {
-                        const float y[4] = {h.x, h.y, h.z, h.w}, gv[4] = {gn[i].x, gn[i].y, gn[i].z, gn[i].w};
-                        ppack_store4<kTerms>(a.Xnext, row, col, a.n_tiles / 2, y, gv, 1.f);
+                        const float y[4] = {h.x * gn[i].x, h.y * gn[i].y, h.z * gn[i].z, h.w * gn[i].w};
+                        ppack_store4(a.Xnext, row, col, a.n_tiles / 2, y);
                         sq += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
                     }
                 }
@@ -540,7 +556,7 @@ __device__ __forceinline__ float exp_score(float x) {
     return __builtin_fmaf(p, lo * 0.693147180559945f, p);
 }
 
-template <int DH, int T>
+template <int DH>
 __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnArgs a) {
     constexpr int HALF = DH / 2, NC = DH / 32, NDT = DH / 16, BLK = 2 * NC + NDT, PB = BLK / 4;
     constexpr int U = prefill_step_units(DH);
@@ -752,29 +768,11 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
-    const int KS = (int)(HD / 32);
-    if constexpr (T == 2) {
-        // a head is a block of the O projection's operand: one factor per (row, head)
-        float top = 0.f;
-#pragma unroll
-        for (int i = 0; i < NDT; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) top = fmaxf(top, fabsf(acc[i][v]));
-        const float inv = 1.0f / l_run, factor = block_factor(max_over_rows(top) * inv), f[4] = {inv, inv, inv, inv};
-        if (row < a.rows) {
-#pragma unroll
-            for (int i = 0; i < NDT; ++i) {
-                const float y[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-                ppack_store4<T>((uint16_t *)a.xout, row, hh * DH + 16 * i + 4 * g, KS, y, f, factor);
-            }
-            if (g == 0) a.xout_scale[pscale_index(row, hh, a.H)] = power_inverse(factor);
-        }
-    } else if (row < a.rows) {
-        const float one[4] = {1.f, 1.f, 1.f, 1.f};
+    if (row < a.rows) {
 #pragma unroll
         for (int i = 0; i < NDT; ++i) {
             const float y[4] = {acc[i][0] / l_run, acc[i][1] / l_run, acc[i][2] / l_run, acc[i][3] / l_run};
-            ppack_store4<T>((uint16_t *)a.xout, row, hh * DH + 16 * i + 4 * g, KS, y, one, 1.f);
+            ppack_store4((uint16_t *)a.xout, row, hh * DH + 16 * i + 4 * g, (int)(HD / 32), y);
         }
     }
 }
@@ -783,11 +781,13 @@ hipError_t launch_prefill_attention(const PrefillAttnArgs &a, bool attend, hipSt
     if (a.rows < 1 || a.rows > a.max_positions || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
     const dim3 g1(a.H, (a.rows + 31) / 32 + 1), g2(a.H, (a.rows + 63) / 64);
     if (a.dh != 128 && a.dh != 64) return hipErrorInvalidValue;
-    auto *append = a.dh == 128 ? prefill_append_kernel<128> : prefill_append_kernel<64>;
-    auto *attention = a.terms == 2 ? (a.dh == 128 ? prefill_attention_kernel<128, 2> : prefill_attention_kernel<64, 2>)
-                                   : (a.dh == 128 ? prefill_attention_kernel<128, 3> : prefill_attention_kernel<64, 3>);
-    hipLaunchKernelGGL(append, g1, dim3(256), 0, stream, a);
-    if (attend) hipLaunchKernelGGL(attention, g2, dim3(256), 0, stream, a);
+    if (a.dh == 128) {
+        hipLaunchKernelGGL(prefill_append_kernel<128>, g1, dim3(256), 0, stream, a);
+        if (attend) hipLaunchKernelGGL(prefill_attention_kernel<128>, g2, dim3(256), 0, stream, a);
+    } else {
+        hipLaunchKernelGGL(prefill_append_kernel<64>, g1, dim3(256), 0, stream, a);
+        if (attend) hipLaunchKernelGGL(prefill_attention_kernel<64>, g2, dim3(256), 0, stream, a);
+    }
     return hipGetLastError();
 }
 

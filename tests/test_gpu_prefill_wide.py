@@ -1,6 +1,6 @@
-"""GPU parity of the prompt kernels with two f16 terms (models whose projections all contract over 2048 values or more, passes of
-385 rows or more) against the float64 oracle: both workgroup shapes, K slices, K ranges that end inside a group of four steps and
-inside a block, both head sizes, a second pass over a cached prefix, passes on either side of the rule, factors far from one."""
+"""GPU parity of long prompts of wide models (projections that contract over 2048 values or more, 385 rows and more, and fewer) against the
+float64 oracle: both head sizes, K ranges that end inside a K-step, a second pass over a cached prefix, factors far from one; that no prompt
+leaves anything behind for the next, and that every activation keeps its own 24 bits."""
 import numpy as np
 import pytest
 import torch
@@ -104,3 +104,52 @@ def test_wide_prompt_with_a_row_that_is_not_finite_and_a_zero_row():
     for a, b in zip(clean, dirty):
         assert np.isfinite(a).all() and np.array_equal(a[:300], b[:300]) and np.isnan(b[300:]).all()
     assert torch.isfinite(last).all() and torch.isnan(bad_last).all()
+
+
+@pytest.mark.parametrize("first,second", [(40, 400), (384, 385), (640, 129)])
+def test_a_prompt_behind_one_that_was_not_finite_has_the_bits_of_a_fresh_model(first, second):
+    """d_ffn = 2056: the last K-step of the down projection is a quarter full.  Whatever a prompt of another length left in the buffers, the
+    columns that pad that step count as zero: 0 * NaN would reach every later row."""
+    from paper_2404_08856_amd import spd
+    shape = SHAPES["ragged"]
+    w = to_device(synth.make_weights(shape, 19))
+    bad = torch.from_numpy(synth.image_rows(first, shape.d_model, 20)).cuda()
+    bad[:, 3] = float("nan")
+    rows = torch.from_numpy(synth.image_rows(second, shape.d_model, 21)).cuda()
+    outs = []
+    for dirty in (False, True):
+        m = spd.Model(spd.make_config(shape, 1, 700), w)
+        last = torch.empty(shape.vocab, device="cuda")
+        if dirty:
+            m.spd_prefill(0, bad.contiguous(), last)
+            assert torch.isnan(last).all()
+            m.spd_kv_set_len([0])
+        m.spd_prefill(0, rows, last)
+        outs.append([last.cpu().numpy()] + [x for l in range(shape.n_layers) for x in cached(m, l, second, shape)])
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n", [100, 384, 385, 640])
+def test_a_column_without_weights_takes_no_bits_from_its_neighbours(n):
+    """Every activation keeps its own 24 bits, whatever stands next to it: a column whose weights are zero changes no bit of the result, also where
+    its gain makes it 2^40 times as large as the others."""
+    from paper_2404_08856_amd import spd
+    shape = SHAPES["even"]
+    w = randomize_gains(synth.make_weights(shape, 22))
+    columns = torch.arange(5, shape.d_model, 64)                # two in every block of 128
+    for lw in w["layers"]:
+        for m in ("wq", "wk", "wv", "w_gate", "w_up"):
+            lw[m][:, columns] = 0
+    rows = torch.from_numpy(synth.image_rows(n, shape.d_model, 23)).cuda()
+    outs = []
+    for size in (1.0, 2.0 ** 40):
+        for lw in w["layers"]:
+            lw["attn_norm"][columns] = size
+            lw["mlp_norm"][columns] = size
+        m = spd.Model(spd.make_config(shape, 1, n), to_device(w))
+        last = torch.empty(shape.vocab, device="cuda")
+        m.spd_prefill(0, rows, last)
+        outs.append([last.cpu().numpy()] + [x for l in range(shape.n_layers) for x in cached(m, l, n, shape)])
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, b)

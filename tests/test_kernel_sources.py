@@ -24,10 +24,3 @@ def test_a_raw_barrier_waits_for_the_loads_and_for_the_wave_s_own_lds_reads():
     assert len(at) == 2
     for i in at:
         assert re.search(r'asm volatile\("s_waitcnt vmcnt\(%0\) lgkmcnt\(0\)"', code[i - 1]), code[i - 1]
-
-
-def test_the_wide_kernel_s_barrier_waits_for_the_wave_s_own_lds_writes():
-    text = open(os.path.join(os.path.dirname(SOURCE), "prefill_wide.hip")).read()
-    code = [s.strip() for s in re.sub(r"//[^\n]*", "", text).split(";")]
-    at = [i for i, s in enumerate(code) if "__builtin_amdgcn_s_barrier" in s]
-    assert len(at) == 1 and "lgkmcnt(0)" in code[at[0] - 1] and "global_load_lds" not in text
