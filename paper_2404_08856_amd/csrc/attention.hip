@@ -30,7 +30,7 @@ __device__ __forceinline__ void prefetch_tiles(const WeightPrefetch &pf, int id,
 }
 
 // grid: heads, slices x runs of keys, sequences (and planes of prefetching workgroups behind them)
-template <int DH, int DS, int AW, int QG, int KSP, bool K_ONCE>
+template <int DH, int DS, int AW, int QG, int KSP, bool K_ONCE, bool CACHED = false>
 __global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPrefetch pf) {
     if ((int)blockIdx.z >= a.n_seqs) {
         const int id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPr
     }
     // head index fastest: consecutive workgroups go to consecutive XCDs, so with a head count that is
     // a multiple of 8 all slices of one head share an XCD and its L2 holds that head's K once
-    attention_core<DH, DS, AW, kUnitsPerIter, false, QG, KSP, K_ONCE>(a, blockIdx.x, KSP == 1 ? blockIdx.y : blockIdx.y % DS, KSP == 1 ? 0 : blockIdx.y / DS, blockIdx.z, [] {});
+    attention_core<DH, DS, AW, kUnitsPerIter, false, QG, KSP, K_ONCE, CACHED>(a, blockIdx.x, KSP == 1 ? blockIdx.y : blockIdx.y % DS, KSP == 1 ? 0 : blockIdx.y / DS, blockIdx.z, [] {});
 }
 
 constexpr int kAttnRuns = 4;
@@ -49,6 +49,14 @@ size_t attention_partial_bytes(int dh) { return (size_t)64 * kAttnRuns * (8 * dh
 hipError_t launch_attention(const AttnArgs &a, int longest, const WeightPrefetch &pf, hipStream_t stream) {
     if (a.M < 1 || a.M > kMaxRows || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
     if (a.Mq < 1 || a.Mq > 8 || a.m0 < 0 || a.m0 + a.Mq > a.M || a.M > a.max_positions) return hipErrorInvalidValue;
+    // A prompt's last row: 16 output dimensions per workgroup, whatever the number of heads (one layer of a whole prompt)
+    if (a.row_cached) {
+        if (a.M != 1) return hipErrorInvalidValue;
+        if (a.dh == 128) hipLaunchKernelGGL((attention_kernel<128, 8, kAttnWaves, 1, 1, false, true>), dim3(a.H, 8, a.n_seqs), dim3(kAttnWaves * 64), 0, stream, a, WeightPrefetch{});
+        else if (a.dh == 64) hipLaunchKernelGGL((attention_kernel<64, 4, kAttnWaves, 1, 1, false, true>), dim3(a.H, 4, a.n_seqs), dim3(kAttnWaves * 64), 0, stream, a, WeightPrefetch{});
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
     // Workgroups per head (slices of the head dimension).  One sequence: 16 output dimensions per
     // workgroup is fastest at the 7B shape (15.4 us per layer against 16.2 with 32 and 18.8 with 64).
     // More (sequence, head) pairs: every slice re-reads K, so slices beyond one workgroup per CU only

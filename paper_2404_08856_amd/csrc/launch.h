@@ -112,6 +112,7 @@ struct AttnArgs {
     int32_t *d_error;        // set to 1 if a device length does not leave room for M rows (the launch then
                              // works on a clamped length: wrong results, but every access stays in bounds)
     SeqLens lens;            // KV length of every sequence before this call
+    bool row_cached;         // stand-alone kernel, M = 1: the row's key and value are in the cache and the length counts them
     float *partials;         // stand-alone kernel: scratch for results of runs of keys (attention_partial_bytes), or NULL
     unsigned *arrive;        // counters for them, zero between launches
 };

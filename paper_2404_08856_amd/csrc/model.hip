@@ -457,8 +457,9 @@ namespace {
 
 // Layers first .. of the decoder for M new rows of each of sequences seq0 .. seq0 + n_seqs - 1, and the LM head (logits_out may be NULL).
 // The input rows are in place: h, packed (h * attn_norm[first]) and their sums of squares (one part per row); `at` has the
-// KV lengths; longest: the longest of them as far as the host can tell.
-int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, int M, int longest, float *logits_out, hipStream_t st) {
+// KV lengths; longest: the longest of them as far as the host can tell.  kv_cached (one row only): layer
+// `first`'s key and value of the row are in the cache, and the length counts them.
+int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, int M, int longest, bool kv_cached, float *logits_out, hipStream_t st) {
     const spd_model_config &c = m->cfg;
     const Layout &L = m->L;
     const int rows = n_seqs * M;
@@ -493,7 +494,8 @@ int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, 
         at.v_cache = kv_l + align_up(L.kv_k_bytes, 256) + (size_t)seq0 * c.n_heads * c.head_dim * L.v_stride * 2;
         GemmArgs g{};
         g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero;
-        if (fused) {
+        at.row_cached = kv_cached && l == first;
+        if (fused && !at.row_cached) {
             QkvAttnArgs qa{};
             qa.W = m->packed + L.wqkv[l]; qa.X = xn; qa.K = d; qa.rows = rows;
             qa.ssq_in = ssq_b; qa.ssq_in_parts = l == first ? 1 : d_tiles; qa.eps = c.rms_eps;
@@ -503,7 +505,7 @@ int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, 
             qa.abort_flag = (int *)(m->ws + L.qa_abort);
             PROF_KERNEL(PK_QKV, launch_qkv_attention(qa, st));
         } else {
-            g.W = m->packed + L.wqkv[l]; g.X = xn; g.N = 3 * HD; g.K = d; g.rows = rows; g.Y = qkv; g.ldy = 3 * HD;
+            g.W = m->packed + L.wqkv[l]; g.X = xn; g.N = at.row_cached ? HD : 3 * HD; g.K = d; g.rows = rows; g.Y = qkv; g.ldy = 3 * HD;
             g.ssq_in = ssq_b; g.ssq_in_parts = l == first ? 1 : d_tiles; g.eps = c.rms_eps;
             PROF_GEMM(PK_QKV, launch_gemm(g, EPI_STORE, m->t_qkv, st));
             WeightPrefetch pf{};
@@ -576,7 +578,7 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
     // input rows -> h, packed (h * attn_norm[0]) and sum of squares (one part per row)
     PROF_TRY(PK_EMBED, launch_input_rows(m->packed + L.embed, tokens, M, tokens ? token_stride : M, embeds, rows, d, c.vocab,
                                          (const float *)(m->packed + L.attn_norm[0]), (float *)(m->ws + L.h), m->ws + L.xn, (float *)(m->ws + L.ssq_b), st));
-    const int32_t rc = run_layers(m, 0, at, seq0, n_seqs, M, longest, logits_out, st);
+    const int32_t rc = run_layers(m, 0, at, seq0, n_seqs, M, longest, false, logits_out, st);
     if (rc) return rc;
     if (m->dev_lens) HIP_TRY(launch_lens_add((int32_t *)(m->ws + L.d_lens) + seq0, n_seqs, M, st));
     for (int s = 0; s < n_seqs; ++s) m->lens[seq0 + s] = std::min(m->lens[seq0 + s] + M, c.max_positions);
@@ -588,7 +590,7 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
 //
 // What leaves the last layer is the keys and values of all rows and the logits of one, so nothing else of it is computed
 // for all rows: the projection makes K and V, and the last row goes through the layer and the LM head by the kernels of single rows
-// (its K and V are made once more on the way).  Four 7B layers, 2047 rows
+// with the K and V that the cache then has (they do not depend on whether logits were asked for).  Four 7B layers, 2047 rows
 // 8.62 -> 6.99 ms, 640 rows 2.89 -> 2.42, 33 rows 0.708 -> 0.668; the 12-layer draft, 1472 rows 1.76 -> 1.67, the 4-layer draft 0.88 -> 0.73.
 int32_t prefill_pass(spd_model *m, int32_t seq, const float *embeds, const int32_t *tokens, int M, float *last_logits, hipStream_t st) {
     const spd_model_config &c = m->cfg;
@@ -638,24 +640,19 @@ int32_t prefill_pass(spd_model *m, int32_t seq, const float *embeds, const int32
         PROF_TRY(PK_DOWN, launch_prefill_gemm(g, EPI_RESIDUAL, st));
     }
     int32_t *d_len = (int32_t *)(m->ws + L.d_lens) + seq;
+    if (m->dev_lens) HIP_TRY(launch_lens_add(d_len, 1, M, st));
     if (last_logits) {
         const int l = c.n_layers - 1;
         HIP_TRY(launch_input_rows(nullptr, nullptr, 1, 1, h + (size_t)(M - 1) * d, 1, d, V, gain_of(L.attn_norm[l]), (float *)(m->ws + L.h), m->ws + L.xn,
                                   (float *)(m->ws + L.ssq_b), st));
         AttnArgs one{};
-        one.lens.len[0] = m->lens[seq] + M - 1;
+        one.lens.len[0] = m->lens[seq] + M;
         if (m->dev_lens) {
-            if (M > 1) HIP_TRY(launch_lens_add(d_len, 1, M - 1, st));
             one.d_lens = d_len;
             one.d_error = at.d_error;
         }
-        // (lens_least counts the whole prompt already)
-        const int longest = m->dev_lens ? std::max(0, m->lens_least[seq] - 1) : one.lens.len[0];
-        const int32_t rc = run_layers(m, l, one, seq, 1, 1, longest, last_logits, st);
+        const int32_t rc = run_layers(m, l, one, seq, 1, 1, one.lens.len[0], true, last_logits, st);
         if (rc) return rc;
-        if (m->dev_lens) HIP_TRY(launch_lens_add(d_len, 1, 1, st));
-    } else if (m->dev_lens) {
-        HIP_TRY(launch_lens_add(d_len, 1, M, st));
     }
     m->lens[seq] = std::min(m->lens[seq] + M, c.max_positions);
     return SPD_OK;

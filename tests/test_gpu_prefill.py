@@ -167,11 +167,10 @@ def test_cache_read_out_of_any_range(name, capacity):
                 assert (f[:offset] == -9.0).all() and (f[offset + n * H * dh:] == -9.0).all()
 
 
-@pytest.mark.parametrize("name,n", [("dh64_ragged_ffn", 25), ("dh128", 33), ("dh128", 130), ("wide", 70), ("small", 2048 + 40)])
+@pytest.mark.parametrize("name,n", [("dh64_ragged_ffn", 25), ("dh128", 33), ("dh128", 130), ("wide", 70), ("wide", 1030), ("small", 2048 + 40)])
 @pytest.mark.parametrize("on_device", [False, True])
 def test_a_prompt_without_logits_leaves_the_cache_of_one_with_them(name, n, on_device):
-    """Only the last row passes through the whole last layer, and only where its logits are asked for: every other key and value has the
-    same bits, and those of that row are one bf16 step away at most (its projection runs through another kernel)."""
+    """Only the last row passes through the whole last layer, and only where its logits are asked for: no key and no value depends on that."""
     from paper_2404_08856_amd import spd
     shape = SHAPES[name]
     w = to_device(randomize_gains(synth.make_weights(shape, 17)))
@@ -190,6 +189,5 @@ def test_a_prompt_without_logits_leaves_the_cache_of_one_with_them(name, n, on_d
         m.spd_verify_forward(torch.tensor([[1, 2]], dtype=torch.int32, device="cuda"), out)
         steps.append(out.cpu().numpy())
     for a, b in zip(*kv):
-        assert np.array_equal(a[:n - 1], b[:n - 1])
-        assert np.all(np.abs(a - b) <= np.maximum(2.0 ** -7 * np.abs(a), 1e-5 * np.sqrt(np.mean(a * a))))
-    check_logits(steps[1][0], steps[0][0], "step after the prompt without logits")
+        assert np.array_equal(a, b)
+    assert np.array_equal(steps[1], steps[0])
