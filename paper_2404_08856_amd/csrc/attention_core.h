@@ -74,8 +74,8 @@ __device__ __forceinline__ uint32_t pack2(uint16_t lo, uint16_t hi) { return (ui
 // unnormalised result in a.partials and takes a ticket; the last of the KSP to arrive (nobody waits) combines them in
 // order.  The new rows belong to run 0.
 // K_ONCE: non-temporal loads of the keys as well (only with DS == 1: several slices of a head share its K in L2).
-// CACHED: one row whose key and value are the last ones in the cache already (the length counts them): nothing is appended, and
-// what lies behind the end of the cache counts as zero (a weight of zero alone would not do: rolled back values may not be finite.
+// CACHED: one row whose key and value are the last ones in the cache already (the length counts them): nothing is appended,
+// a score that is NaN (an infinite key on a dimension where the query is zero) leaves NaN as in the prompt's other rows, and what lies behind the end of the cache counts as zero (a weight of zero alone would not do: rolled back values may not be finite.
 // For every form of the kernel: 4 registers more, 12-layer draft of 2 sequences, a case of four steps, 1057 -> 1087 us).
 template <int DH, int DS, int AW, int UPI, bool DEV, int QG, int KSP, bool K_ONCE, bool CACHED, class ReadyFn>
 __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, const int ds, const int ks, const int seq, ReadyFn rows_ready) {
@@ -254,7 +254,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 for (int ab = 0; ab < 2; ++ab)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const float p = sv[ab][v] == -INFINITY ? 0.f : exp_neg(sv[ab][v] - m_new);   // masked keys: 0
+                        const float p = sv[ab][v] == -INFINITY ? 0.f : exp_neg<CACHED>(sv[ab][v] - m_new);   // masked keys: 0
                         lsum += p;
                         // this lane's column carries term r / 5 of query r % 5: p, p - t0 or p - t0 - t1
                         const float r1 = p - rne_bf16(p);

@@ -23,9 +23,10 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
     return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 // exp(x) for x <= 0 through the hardware base-2 exponential, with the rounding error of
-// x * log2(e) carried along (about 2 ulp overall); arguments below -87 give (nearly) 0.
+// x * log2(e) carried along (about 2 ulp overall); arguments below -87 give (nearly) 0, and so does NaN unless it is kept.
+template <bool KEEP_NAN>
 __device__ __forceinline__ float exp_neg(float x) {
-    x = fmaxf(x, -87.0f);
+    x = KEEP_NAN ? __builtin_elementwise_maximum(x, -87.0f) : fmaxf(x, -87.0f);
     const float c1 = 1.44269502162933349609375f, c2 = 1.925963033500011e-8f;   // log2(e) = c1 + c2
     const float t = x * c1;
     const float lo = __builtin_fmaf(x, c1, -t) + x * c2;

@@ -108,3 +108,19 @@ def test_prompt_with_scores_of_any_size(n, what):
     cfg, wn = oracle_cfg(shape), synth.weights_to_numpy(w)
     cache = dec.KVCache(cfg, n)
     check_logits(last.cpu().numpy(), dec.forward_tokens(cfg, wn, cache, ids)[-1], "last row")
+
+
+@pytest.mark.parametrize("heads,n", [(1, 40), (2, 64), (2, 1500), (33, 130)])
+def test_last_row_of_a_prompt_that_sees_an_infinite_key(heads, n):
+    """A key that is infinite on a dimension where the queries are zero: the score is 0 * inf, and every row that sees the key is NaN, as in
+    any softmax.  Values are finite everywhere, so nothing else makes it NaN."""
+    from paper_2404_08856_amd import spd
+    print(f"infinite key: {heads} heads, prompt of {n}", flush=True)
+    shape, w = steered(heads, 1.0, 2.0 ** 126)              # times 8: beyond float32
+    model = spd.Model(spd.make_config(shape, 1, n), to_device(w))
+    last = torch.empty(shape.vocab, device="cuda")
+    model.spd_prefill_tokens(0, torch.from_numpy(prompt(n, n // 3)).cuda(), last)
+    k, v = (torch.empty((n, shape.n_heads, shape.head_dim), device="cuda") for _ in range(2))
+    model.spd_kv_export(0, 0, 0, k, v)
+    assert torch.isinf(k[n // 3]).any() and torch.isfinite(v).all()
+    assert torch.isnan(last).all()
