@@ -85,3 +85,37 @@ def check(name, n_seqs, M, batch_kernel=0):
 @pytest.mark.parametrize("n_seqs,M", [(1, 6), (2, 5)])
 def test_two_groups_in_four_slices_against_oracle(n_seqs, M):
     check("k2048", n_seqs, M, batch_kernel=1)
+
+
+@pytest.mark.parametrize("d,heads,n_seqs", [(4096, 32, 12), (4096, 32, 40), (4096, 32, 64), (2048, 16, 64)])
+def test_slices_in_halves_are_as_exact_as_the_kernel_that_splits_k_over_waves(d, heads, n_seqs):
+    """The O projection alone: one row per sequence at position 0 (attention returns the cached value, which is read back), no MLP, an LM head that
+    hands the normalised row through.  A chain of n additions has an error that grows with sqrt(n) (roundings are independent): with the
+    chains of this kernel at most as long as the other kernel's (K / 8 waves) the ratio is at most 1, a chain twice as long makes it
+    1.41; 1.15 lies between.  An estimate from 50000 errors or more is good to 1 %."""
+    from paper_2404_08856_amd import spd
+    shape = synth.ModelShape(1, d, heads, 128, 64, d)
+    w = to_device(synth.make_weights(shape, 41))
+    w["embed"] = (0.01 * w["embed"].float()).to(torch.bfloat16)
+    w["lm_head"] = torch.eye(d, device="cuda").to(torch.bfloat16)
+    w["layers"][0]["w_down"].zero_()
+    ids = torch.from_numpy(synth.text_tokens(n_seqs, shape.vocab, 42)).cuda()
+    errors = []
+    for batch_kernel in (1, 2):
+        m = spd.Model(spd.make_config(shape, n_seqs, 8), w)
+        m.spd_model_set_tuning(batch_kernel=batch_kernel)
+        out = torch.empty((n_seqs, 1, shape.vocab), device="cuda")
+        m.spd_verify_forward(ids[:, None].contiguous(), out)
+        values = []
+        for s in range(n_seqs):
+            k, v = (torch.empty((1, heads, 128), device="cuda") for _ in range(2))
+            m.spd_kv_export(0, s, 0, k, v)
+            values.append(v.reshape(-1).double())
+        x = w["embed"][ids.long()].double() + torch.stack(values) @ w["layers"][0]["wo"].double().T
+        want = x / torch.sqrt(x.square().mean(-1, keepdim=True) + shape.rms_eps)
+        # the row's common factor (its own rounding of 1 / rms) is not the sums' error
+        got = out[:, 0].double()
+        got = got * ((got * want).sum(-1, keepdim=True) / got.square().sum(-1, keepdim=True))
+        errors.append(((got - want).norm() / want.norm()).item())
+    print(f"O at {n_seqs} rows: {errors[0]:.3e}, K over waves {errors[1]:.3e}", flush=True)
+    assert errors[0] <= 1.15 * errors[1], errors
