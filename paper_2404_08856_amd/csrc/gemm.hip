@@ -102,7 +102,9 @@ struct GemmKernelArgs {
 // register slot is refilled with the block U steps ahead -- of the same tile or of the
 // workgroup's next tile -- so the HBM stream never drains at a tile boundary, during the
 // cross-wave reduction or during the epilogue.
-template <int NG, int WAVES, int EPI, int U>
+// FOLD: as in regb_tile, for the last row of a prompt, whose sums are to be as exact as the prompt kernels' (7B shape, one layer and the
+// head, error against 64 bits: prompt kernels at 64 rows 2.5e-7, this row without 3.2e-7, with 2.5e-7).
+template <int NG, int WAVES, int EPI, int U, bool FOLD = false>
 __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs a) {
     static_assert(NG * 128 <= WAVES * 64, "one epilogue thread per (group, row slot, column)");
     const int lane = threadIdx.x & 63;
@@ -158,9 +160,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
             if (a.gain_next) gnext = a.gain_next[t * 16 + en];
         }
 
-        f32x4_t acc[NG];
+        f32x4_t acc[NG], fold[FOLD ? NG : 1];
 #pragma unroll
-        for (int g = 0; g < NG; ++g) acc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < NG; ++g) acc[g] = fold[FOLD ? g : 0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         // Steady state: straight-line code, no branch between a matrix-core step and the
         // refill of its slot, so that the compiler can wait for exactly the oldest block.
         // A slot whose next block lies beyond the workgroup's last tile re-reads an
@@ -171,6 +173,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
             for (int u = 0; u < U; ++u) {
 #pragma unroll
                 for (int g = 0; g < NG; ++g) acc[g] = mfma_bf16(av[u], bv[g][u], acc[g]);
+                if (FOLD && u % 4 == 3) fold_sums<NG>(acc, fold);
                 const int i2 = c * U + u + U;
                 const bool same = i2 < ns;
                 const uint4 *wsrc = (same || has_next) ? a.W : a.X;
@@ -188,6 +191,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
                 if (u < rem) {
 #pragma unroll
                     for (int g = 0; g < NG; ++g) acc[g] = mfma_bf16(av[u], bv[g][u], acc[g]);
+                    if (FOLD && u % 4 == 3) fold_sums<NG>(acc, fold);
                     if (has_next) {
                         av[u] = load_stream(a.W + ((size_t)tn * KS + s0 + u) * 64 + lane);
 #pragma unroll
@@ -195,6 +199,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
                     }
                 }
             }
+        }
+        if (FOLD) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] += fold[FOLD ? g : 0];
         }
         // D[n = 4 (lane / 16) + v][c = lane % 16]; columns c, c + 5, c + 10 are the three terms of row c
 #pragma unroll
@@ -210,11 +218,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
             // rows 0..7 of a tile are gate features f0..f0+7, rows 8..15 the matching up features
             if (e_active) {
                 float gate = 0.f, up = 0.f;
-#pragma unroll
-                for (int ww = 0; ww < WAVES; ++ww) {            // fixed order: deterministic
-                    gate += red[parity][ww][eg][en][em];
-                    up += red[parity][ww][eg][en + 8][em];
-                }
+                sum_waves<WAVES, FOLD>([&](int ww) { return float2{red[parity][ww][eg][en][em], red[parity][ww][eg][en + 8][em]}; }, gate, up);   // fixed order: deterministic
                 gate *= inv_s[erow];
                 up *= inv_s[erow];
                 float val = gate / (1.0f + expf(-gate)) * up;
@@ -225,9 +229,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
                 for (int q = 0; q < kTerms; ++q) a.Xout[xpack_index(erow, f, a.KS_out, q)] = t3[q];
             }
         } else if (e < NG * 128) {
-            float sum = 0.f;
-#pragma unroll
-            for (int ww = 0; ww < WAVES; ++ww) sum += red[parity][ww][eg][en][em];
+            float sum = 0.f, none = 0.f;
+            sum_waves<WAVES, FOLD>([&](int ww) { return float2{red[parity][ww][eg][en][em], 0.f}; }, sum, none);
             sum *= inv_s[erow < kMaxRows ? erow : 0];
             if (EPI == EPI_STORE) {
                 if (e_active) a.Y[(size_t)erow * a.ldy + (size_t)t * 16 + en] = sum;
@@ -817,7 +820,7 @@ static hipError_t launch_batch(const GemmKernelArgs &k, const BatchArgs &b, int 
 // reduced across waves and written out.
 // NG = 2: rows 6..10 (two row groups) with both groups' activation slices resident: every weight block
 // feeds two matrix-core steps; the epilogue duty of a tile goes to four waves (a pair per group).
-template <int WAVES, int EPI, int NB, int U, int NG = 1>
+template <int WAVES, int EPI, int NB, int U, int NG = 1, bool FOLD = false>
 __global__ __launch_bounds__(WAVES * 64, (NG > 1 ? 1 : (NB <= 8 ? 4 : 2))) void gemm_regb_kernel(GemmKernelArgs a) {
     static_assert(NB % U == 0, "ring must divide the per-wave K range");
     static_assert(2 * NG <= WAVES && WAVES % (2 * NG) == 0, "a pair of epilogue waves per row group");
@@ -878,7 +881,7 @@ __global__ __launch_bounds__(WAVES * 64, (NG > 1 ? 1 : (NB <= 8 ? 4 : 2))) void 
         f32x4_t acc[NG];
         const uint4 *wcur = a.W + ((size_t)t * KS + s0) * 64 + lane;
         const uint4 *wnext = (has_next ? a.W + ((size_t)tn * KS + s0) * 64 : a.X) + lane;   // past the end: harmless re-read
-        regb_tile<NB, U, NG>(acc, av, bv, wcur, wnext, has_next);
+        regb_tile<NB, U, NG, FOLD>(acc, av, bv, wcur, wnext, has_next);
         store_partial<NG>(acc, red[parity][w], lane);
         __syncthreads();
         if (!my_turn) continue;
@@ -886,11 +889,7 @@ __global__ __launch_bounds__(WAVES * 64, (NG > 1 ? 1 : (NB <= 8 ? 4 : 2))) void 
         if (EPI == EPI_SWIGLU) {
             if (e_active) {
                 float gate = 0.f, up = 0.f;
-#pragma unroll
-                for (int ww = 0; ww < WAVES; ++ww) {
-                    gate += red[parity][ww][eg][en][em];
-                    up += red[parity][ww][eg][en + 8][em];
-                }
+                sum_waves<WAVES, FOLD>([&](int ww) { return float2{red[parity][ww][eg][en][em], red[parity][ww][eg][en + 8][em]}; }, gate, up);
                 gate *= inv;
                 up *= inv;
                 float val = gate / (1.0f + expf(-gate)) * up;
@@ -901,9 +900,8 @@ __global__ __launch_bounds__(WAVES * 64, (NG > 1 ? 1 : (NB <= 8 ? 4 : 2))) void 
                 for (int q = 0; q < kTerms; ++q) a.Xout[xpack_index(erow, f, a.KS_out, q)] = t3[q];
             }
         } else {
-            float sum = 0.f;
-#pragma unroll
-            for (int ww = 0; ww < WAVES; ++ww) sum += red[parity][ww][eg][en][em];
+            float sum = 0.f, none = 0.f;
+            sum_waves<WAVES, FOLD>([&](int ww) { return float2{red[parity][ww][eg][en][em], 0.f}; }, sum, none);
             sum *= inv;
             const int col = t * 16 + en;
             if (EPI == EPI_STORE) {
@@ -929,18 +927,18 @@ __global__ __launch_bounds__(WAVES * 64, (NG > 1 ? 1 : (NB <= 8 ? 4 : 2))) void 
     }
 }
 
-template <int WAVES, int NB, int U, int NG = 1>
+template <int WAVES, int NB, int U, int NG = 1, bool FOLD = false>
 static hipError_t launch_regb(const GemmKernelArgs &k, int epilogue, int grid, hipStream_t stream) {
     dim3 g(grid), block(WAVES * 64);
     switch (epilogue) {
         case EPI_STORE:
-            launch_kernel(gemm_regb_kernel<WAVES, EPI_STORE, NB, U, NG>, g, block, stream, k);
+            launch_kernel(gemm_regb_kernel<WAVES, EPI_STORE, NB, U, NG, FOLD>, g, block, stream, k);
             break;
         case EPI_RESIDUAL:
-            launch_kernel(gemm_regb_kernel<WAVES, EPI_RESIDUAL, NB, U, NG>, g, block, stream, k);
+            launch_kernel(gemm_regb_kernel<WAVES, EPI_RESIDUAL, NB, U, NG, FOLD>, g, block, stream, k);
             break;
         case EPI_SWIGLU:
-            launch_kernel(gemm_regb_kernel<WAVES, EPI_SWIGLU, NB, U, NG>, g, block, stream, k);
+            launch_kernel(gemm_regb_kernel<WAVES, EPI_SWIGLU, NB, U, NG, FOLD>, g, block, stream, k);
             break;
         default:
             return hipErrorInvalidValue;
@@ -948,18 +946,18 @@ static hipError_t launch_regb(const GemmKernelArgs &k, int epilogue, int grid, h
     return hipGetLastError();
 }
 
-template <int NG, int WAVES, int U>
+template <int NG, int WAVES, int U, bool FOLD = false>
 static hipError_t launch_epi(const GemmKernelArgs &k, int epilogue, int grid, hipStream_t stream) {
     dim3 g(grid), block(WAVES * 64);
     switch (epilogue) {
         case EPI_STORE:
-            launch_kernel(gemm_stream_kernel<NG, WAVES, EPI_STORE, U>, g, block, stream, k);
+            launch_kernel(gemm_stream_kernel<NG, WAVES, EPI_STORE, U, FOLD>, g, block, stream, k);
             break;
         case EPI_RESIDUAL:
-            launch_kernel(gemm_stream_kernel<NG, WAVES, EPI_RESIDUAL, U>, g, block, stream, k);
+            launch_kernel(gemm_stream_kernel<NG, WAVES, EPI_RESIDUAL, U, FOLD>, g, block, stream, k);
             break;
         case EPI_SWIGLU:
-            launch_kernel(gemm_stream_kernel<NG, WAVES, EPI_SWIGLU, U>, g, block, stream, k);
+            launch_kernel(gemm_stream_kernel<NG, WAVES, EPI_SWIGLU, U, FOLD>, g, block, stream, k);
             break;
         default:
             return hipErrorInvalidValue;
@@ -1006,13 +1004,15 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
     if (groups == 1 && !tune.no_regb) {
         // register-resident activation slice: every wave owns exactly 8 or 16 K-steps.
         // Resident workgroups per CU follow from the register budget of each variant.
+#define SPD_REGB(W_, NB_, U_, grid_) return a.fold ? launch_regb<W_, NB_, U_, 1, true>(k, epilogue, grid_, stream) : launch_regb<W_, NB_, U_>(k, epilogue, grid_, stream)
         auto grid_for = [&](int per_cu) { return pick_grid(k.n_tiles, tune.grid_cap > 0 ? tune.grid_cap : 256 * per_cu); };
-        if (waves == 16 && k.KS == 16 * 8) return launch_regb<16, 8, 8>(k, epilogue, grid_for(1), stream);
-        if (waves == 8 && k.KS == 8 * 16) return launch_regb<8, 16, 8>(k, epilogue, grid_for(1), stream);
-        if (waves == 8 && k.KS == 8 * 8) return launch_regb<8, 8, 8>(k, epilogue, grid_for(2), stream);
-        if (waves == 4 && k.KS == 4 * 8) return launch_regb<4, 8, 8>(k, epilogue, grid_for(4), stream);
-        if (waves == 4 && k.KS == 4 * 16) return launch_regb<4, 16, 8>(k, epilogue, grid_for(2), stream);
+        if (waves == 16 && k.KS == 16 * 8) SPD_REGB(16, 8, 8, grid_for(1));
+        if (waves == 8 && k.KS == 8 * 16) SPD_REGB(8, 16, 8, grid_for(1));
+        if (waves == 8 && k.KS == 8 * 8) SPD_REGB(8, 8, 8, grid_for(2));
+        if (waves == 4 && k.KS == 4 * 8) SPD_REGB(4, 8, 8, grid_for(4));
+        if (waves == 4 && k.KS == 4 * 16) SPD_REGB(4, 16, 8, grid_for(2));
     }
+#undef SPD_REGB
     if (groups == 2 && !tune.no_regb) {                 // rows 6..10: both activation slices register-resident
         const int g1 = pick_grid(k.n_tiles, tune.grid_cap > 0 ? tune.grid_cap : 256);
         if (waves == 16 && k.KS == 16 * 8) return launch_regb<16, 8, 8, 2>(k, epilogue, g1, stream);
@@ -1022,10 +1022,13 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
     }
 #define SPD_GEMM_CASE(NG_, W_, U_) return launch_epi<NG_, W_, U_>(k, epilogue, grid, stream)
     if (groups == 1) {
-        if (tune.ring == 16 && waves != 16) {
+        if (tune.ring == 16 && waves != 16 && !a.fold) {
             if (waves == 4) SPD_GEMM_CASE(1, 4, 16);
             SPD_GEMM_CASE(1, 8, 16);
         }
+        if (waves == 4 && a.fold) return launch_epi<1, 4, 8, true>(k, epilogue, grid, stream);
+        if (waves == 8 && a.fold) return launch_epi<1, 8, 8, true>(k, epilogue, grid, stream);
+        if (a.fold) return launch_epi<1, 16, 8, true>(k, epilogue, grid, stream);
         if (waves == 4) SPD_GEMM_CASE(1, 4, 8);
         if (waves == 8) SPD_GEMM_CASE(1, 8, 8);
         SPD_GEMM_CASE(1, 16, 8);

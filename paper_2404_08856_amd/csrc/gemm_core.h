@@ -40,25 +40,55 @@ __device__ __forceinline__ float rms_inv_from_parts(const float *part, int parts
     return 1.0f / sqrtf(sum * inv_d + eps);
 }
 
+// partial sums into the sums, and from zero again
+template <int NG, int N>
+__device__ __forceinline__ void fold_sums(f32x4_t (&acc)[NG], f32x4_t (&sum)[N]) {
+#pragma unroll
+    for (int g = 0; g < N; ++g) { sum[g] += acc[g]; acc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+}
+// adds the WAVES pairs at(w) to (x, y) in a fixed order: one after the other, or (FOLD) four at a time
+template <int WAVES, bool FOLD, class At>
+__device__ __forceinline__ void sum_waves(At at, float &x, float &y) {
+#pragma unroll
+    for (int w = 0; w < WAVES; w += FOLD ? 4 : 1) {
+        const float2 p = at(w);
+        if (FOLD) {
+            const float2 q = at(w + 1), r = at(w + 2), s = at(w + 3);
+            x += (p.x + q.x) + (r.x + s.x);
+            y += (p.y + q.y) + (r.y + s.y);
+        } else {
+            x += p.x;
+            y += p.y;
+        }
+    }
+}
+
 // One tile of the register-resident projection for one wave: NB matrix-core steps over the wave's
 // K slice (activation blocks bv resident), each followed by the refill of its ring slot with the
 // block U steps ahead -- of the same tile (`wcur` = block (tile, s0) + lane) or, past its end, of the
 // next tile (`wnext` = block (next tile, s0) + lane; with has_next = false any readable address:
 // the refill is then a harmless re-read of its first block).  Straight-line code: no branch between
 // a step and its refill, so the compiler waits for exactly the oldest block.
-template <int NB, int U, int NG>
+// FOLD: the products of 4 K-steps have a sum of their own, as in the prompt kernels (shorter chains of additions).
+template <int NB, int U, int NG, bool FOLD = false>
 __device__ __forceinline__ void regb_tile(f32x4_t (&acc)[NG], uint4 (&av)[U], const uint4 (&bv)[NG][NB],
                                           const uint4 *wcur, const uint4 *wnext, bool has_next) {
     static_assert(NB % U == 0, "ring must divide the per-wave K range");
+    f32x4_t sum[FOLD ? NG : 1];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) acc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < NG; ++g) acc[g] = sum[FOLD ? g : 0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) acc[g] = mfma_bf16(av[i % U], bv[g][i], acc[g]);
+        if (FOLD && i % 4 == 3) fold_sums<NG>(acc, sum);
         if (i + U < NB) av[i % U] = load_stream(wcur + (size_t)(i + U) * 64);
         else av[i % U] = load_stream(wnext + (size_t)(has_next ? (i + U - NB) : 0) * 64);
         __builtin_amdgcn_sched_barrier(0);                // keep "consume slot, refill slot" in program order
+    }
+    if (FOLD) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[g] += sum[FOLD ? g : 0];
     }
 }
 

@@ -66,6 +66,7 @@ struct GemmArgs {
     float *batch_partials;
     unsigned *batch_arrive;
     const void *batch_zero;   // 1 KiB of zeros that nobody writes
+    bool fold;            // one row group: short chains of additions, as in the prompt kernels
 };
 size_t gemm_batch_scratch_bytes(int N, int K);
 hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStream_t stream);

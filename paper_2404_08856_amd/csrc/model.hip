@@ -457,8 +457,8 @@ namespace {
 
 // Layers first .. of the decoder for M new rows of each of sequences seq0 .. seq0 + n_seqs - 1, and the LM head (logits_out may be NULL).
 // The input rows are in place: h, packed (h * attn_norm[first]) and their sums of squares (one part per row); `at` has the
-// KV lengths; longest: the longest of them as far as the host can tell.  kv_cached (one row only): layer
-// `first`'s key and value of the row are in the cache, and the length counts them.
+// KV lengths; longest: the longest of them as far as the host can tell.  kv_cached (a prompt's last row): layer
+// `first`'s key and value of the row are in the cache, and the length counts them; the sums are as exact as the prompt kernels'.
 int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, int M, int longest, bool kv_cached, float *logits_out, hipStream_t st) {
     const spd_model_config &c = m->cfg;
     const Layout &L = m->L;
@@ -493,7 +493,7 @@ int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, 
         at.k_cache = kv_l + (size_t)seq0 * c.n_heads * c.max_positions * c.head_dim * 2;
         at.v_cache = kv_l + align_up(L.kv_k_bytes, 256) + (size_t)seq0 * c.n_heads * c.head_dim * L.v_stride * 2;
         GemmArgs g{};
-        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero;
+        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero; g.fold = kv_cached;
         at.row_cached = kv_cached && l == first;
         if (fused && !at.row_cached) {
             QkvAttnArgs qa{};
@@ -522,17 +522,17 @@ int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, 
             }
         }
         g = GemmArgs{};
-        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero;
+        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero; g.fold = kv_cached;
         g.W = m->packed + L.wo[l]; g.X = xo; g.N = d; g.K = HD; g.rows = rows; g.Y = h; g.ldy = d;
         g.gain_next = gain_of(L.mlp_norm[l]); g.Xnext = xn; g.ssq_out = ssq_a;
         PROF_GEMM(PK_O, launch_gemm(g, EPI_RESIDUAL, m->t_o, st));
         g = GemmArgs{};
-        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero;
+        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero; g.fold = kv_cached;
         g.W = m->packed + L.wgu[l]; g.X = xn; g.N = 2 * F; g.K = d; g.rows = rows; g.Xout = xf; g.K_out = F;
         g.ssq_in = ssq_a; g.ssq_in_parts = d_tiles; g.eps = c.rms_eps;
         PROF_GEMM(PK_GATE_UP, launch_gemm(g, EPI_SWIGLU, m->t_gu, st));
         g = GemmArgs{};
-        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero;
+        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero; g.fold = kv_cached;
         g.W = m->packed + L.wdown[l]; g.X = xf; g.N = d; g.K = F; g.rows = rows; g.Y = h; g.ldy = d;
         g.gain_next = gain_of(l + 1 < c.n_layers ? L.attn_norm[l + 1] : L.final_norm); g.Xnext = xn; g.ssq_out = ssq_b;
         PROF_GEMM(PK_DOWN, launch_gemm(g, EPI_RESIDUAL, m->t_down, st));

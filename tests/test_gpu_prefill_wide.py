@@ -173,37 +173,54 @@ def test_the_last_position_s_keys_and_values_do_not_depend_on_the_logits():
             assert np.array_equal(a, b), n
 
 
-def test_a_prompt_s_sums_are_as_exact_in_few_slices_as_in_many():
-    """The O projection of a prompt's first layer: one token repeated and no queries, so that attention returns the cached value; no MLP; a second
-    layer that adds nothing and an LM head that hands the normalised row through.  64 rows take 6 slices of K, 384 rows 2.  Chains of
-    additions of independent roundings: the errors go with the square root of their lengths, 22 / 4 + 6 additions next to the
-    products' own (about 4 additions' worth for each of 4) and 64 / 4 + 2 (11 % more) or, with sums of 16 steps in between, 4 + 4 + 2.  65536
-    errors tell the ratio to 0.4 %."""
+def o_model(layers):
+    """The O projection alone: no queries (one token repeated: attention returns the cached value), no MLP, an LM head that hands the
+    normalised row through.  Of two layers the second adds nothing: the prompt kernels' O.  One layer: the last row's."""
     from paper_2404_08856_amd import spd
-    shape = synth.ModelShape(2, 4096, 32, 128, 64, 4096)
+    shape = synth.ModelShape(layers, 4096, 32, 128, 64, 4096)
     w = to_device(synth.make_weights(shape, 26))
     w["embed"] = (0.01 * w["embed"].float()).to(torch.bfloat16)
     w["lm_head"] = torch.eye(4096, device="cuda").to(torch.bfloat16)
     w["layers"][0]["wq"].zero_()
-    w["layers"][1]["wo"].zero_()
+    w["layers"][-1]["wo"].mul_(0 if layers > 1 else 1)
     for lw in w["layers"]:
         lw["w_down"].zero_()
-    m = spd.Model(spd.make_config(shape, 1, 384), w)
+    return shape, w, spd.Model(spd.make_config(shape, 1, 384), w)
+
+
+def o_error(shape, w, m, n):
+    """Relative error of the O projection over prompts of n equal tokens, 16 tokens."""
     last = torch.empty(shape.vocab, device="cuda")
-    errors = []
-    for n in (64, 384):
-        square = 0.0
-        k, v = (torch.empty((n, shape.n_heads, shape.head_dim), device="cuda") for _ in range(2))
-        for token in range(16):
-            m.spd_kv_set_len([0])
-            m.spd_prefill_tokens(0, torch.full((n,), token, dtype=torch.int32, device="cuda"), last)
-            m.spd_kv_export(0, 0, 0, k, v)
-            assert (v == v[0]).all()
-            x = w["embed"][token].double() + w["layers"][0]["wo"].double() @ v[0].reshape(-1).double()
-            want = x / torch.sqrt(x.square().mean() + shape.rms_eps)
-            got = last.double()
-            got = got * ((got * want).sum() / got.square().sum())       # the row's common factor is not the sums' error
-            square += ((got - want).square().sum() / want.square().sum()).item()
-        errors.append((square / 16) ** 0.5)
-    print(f"O of a prompt: 64 rows {errors[0]:.3e}, 384 rows {errors[1]:.3e}", flush=True)
-    assert errors[1] <= 1.05 * errors[0], errors
+    k, v = (torch.empty((n, shape.n_heads, shape.head_dim), device="cuda") for _ in range(2))
+    square = 0.0
+    for token in range(16):
+        m.spd_kv_set_len([0])
+        m.spd_prefill_tokens(0, torch.full((n,), token, dtype=torch.int32, device="cuda"), last)
+        m.spd_kv_export(0, 0, 0, k, v)
+        assert (v == v[0]).all()
+        x = w["embed"][token].double() + w["layers"][0]["wo"].double() @ v[0].reshape(-1).double()
+        want = x / torch.sqrt(x.square().mean() + shape.rms_eps)
+        got = last.double()
+        got = got * ((got * want).sum() / got.square().sum())       # the row's common factor is not the sums' error
+        square += ((got - want).square().sum() / want.square().sum()).item()
+    return (square / 16) ** 0.5
+
+
+def test_a_prompt_s_sums_are_as_exact_in_few_slices_as_in_many():
+    """64 rows take 6 slices of K, 384 rows 2.  Chains of additions of independent roundings: the errors go with the square root of
+    their lengths, 22 / 4 + 6 additions next to the products' own (about 4 additions' worth for each of 4) and 64 / 4 + 2 (11 %
+    more) or, with sums of 16 steps in between, 4 + 4 + 2.  65536 errors tell the ratio to 0.4 %."""
+    shape, w, m = o_model(2)
+    many, few = o_error(shape, w, m, 64), o_error(shape, w, m, 384)
+    print(f"O of a prompt: 64 rows {many:.3e}, 384 rows {few:.3e}", flush=True)
+    assert few <= 1.05 * many
+
+
+@pytest.mark.parametrize("n", [40, 384])
+def test_the_last_row_s_sums_are_as_exact_as_the_other_rows(n):
+    """The last row goes through its layer by the kernels of single rows: 8 waves of 16 K-steps, each with sums of 4, in the end 4 + 8
+    additions next to the products' own, as many as a prompt of few rows has.  In chains of 16 the products' own errors alone
+    would be half as large again."""
+    others, last = (o_error(*o_model(layers), n) for layers in (2, 1))
+    print(f"O at {n} rows: others {others:.3e}, last {last:.3e}", flush=True)
+    assert last <= 1.1 * others
