@@ -168,11 +168,11 @@ struct PrefillGemmArgs {
     const float *ssq_in;      // [rows][ssq_ld]: ssq_parts partial sums of squares per row (NULL: s = 1)
     int ssq_ld, ssq_parts;
     float eps;
-    const float *gain_next;   // RESIDUAL: gain of the following norm; then Xnext and ssq_out are written too
+    const float *gain_next;   // RESIDUAL: gain of the following norm, whose operand and partial sums of squares are written too
     void *Xnext;
     float *ssq_out;           // prefill_ssq_parts(N / 16, rows) parts per row
     void *Xout;               // SWIGLU: activations of N / 2 columns
-    float *partials;          // scratch for the sums of K slices (prefill_partial_bytes), or NULL: K is never sliced
+    float *partials;          // scratch for the sums of K slices (prefill_partial_bytes)
     unsigned *arrive;         // kPrefillMaxSplit counters, zero between launches
 };
 constexpr int kPrefillMaxSlices = 8, kPrefillMaxSplit = 1024;    // K slices per tile; workgroups of a sliced launch

@@ -107,7 +107,7 @@ struct PrefillGemmKernelArgs {
     const float *ssq_in;      // [rows][ssq_ld], ssq_parts valid: partial sums of squares, or NULL
     int ssq_ld, ssq_parts;
     float inv_d, eps;
-    const float *gain_next;   // RESIDUAL: gain of the following norm, or NULL: no Xnext, no ssq_out
+    const float *gain_next;   // RESIDUAL: gain of the following norm
     uint16_t *Xnext;
     float *ssq_out;           // RESIDUAL: [rows][ssq_ld], one part per NW tiles
     uint16_t *Xout;           // SWIGLU
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
             const int t = min(t0 + wn * NW + i, a.n_tiles - 1), col = t * 16 + 4 * g;
-            gn[i] = a.gain_next ? *reinterpret_cast<const float4 *>(a.gain_next + col) : float4{0.f, 0.f, 0.f, 0.f};
+            gn[i] = *reinterpret_cast<const float4 *>(a.gain_next + col);
 #pragma unroll
             for (int j = 0; j < NX; ++j) {
                 const int row = min((rt0 + wr * NX + j) * 16 + r, a.rows - 1);
@@ -385,14 +385,12 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                     float4 h = hold[i][j];
                     h.x += sum[i][j][0]; h.y += sum[i][j][1]; h.z += sum[i][j][2]; h.w += sum[i][j][3];
                     *dst = h;
-                    if (a.gain_next) {
-                        const float y[4] = {h.x * gn[i].x, h.y * gn[i].y, h.z * gn[i].z, h.w * gn[i].w};
-                        ppack_store4(a.Xnext, row, col, a.n_tiles / 2, y);
-                        sq += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
-                    }
+                    const float y[4] = {h.x * gn[i].x, h.y * gn[i].y, h.z * gn[i].z, h.w * gn[i].w};
+                    ppack_store4(a.Xnext, row, col, a.n_tiles / 2, y);
+                    sq += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
                 }
             }
-            if (EPI == EPI_RESIDUAL && a.gain_next) {
+            if (EPI == EPI_RESIDUAL) {
                 sq += __shfl_xor(sq, 16);
                 sq += __shfl_xor(sq, 32);
                 const int p = nb * WN + wn;
@@ -450,7 +448,8 @@ int prefill_ssq_parts(int n_tiles, int rows) { return prefill_large(n_tiles, row
 
 hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream_t stream) {
     if (a.N % 16 != 0 || a.rows < 1 || a.rows > kPrefillRows) return hipErrorInvalidValue;
-    if (epilogue == EPI_RESIDUAL && a.gain_next && a.N % 32 != 0) return hipErrorInvalidValue;
+    if (epilogue == EPI_RESIDUAL && (a.N % 32 != 0 || !a.gain_next || !a.Xnext || !a.ssq_out)) return hipErrorInvalidValue;
+    if (!a.partials || !a.arrive) return hipErrorInvalidValue;
     PrefillGemmKernelArgs k;
     k.W = (const uint4 *)a.W; k.X = (const uint4 *)a.X;
     k.KS = (a.K + 31) / 32; k.n_tiles = a.N / 16; k.n_rt = (a.rows + 15) / 16; k.rows = a.rows;
@@ -462,7 +461,7 @@ hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream
     k.J = 1;
     k.partials = a.partials; k.arrive = a.arrive;
     if (prefill_large(k.n_tiles, a.rows)) return launch_pg<2, 4, 8, 2>(k, epilogue, stream);
-    if (a.partials && a.arrive) k.J = prefill_slices(((k.n_tiles + 7) / 8) * ((a.rows + 63) / 64), k.KS);
+    k.J = prefill_slices(((k.n_tiles + 7) / 8) * ((a.rows + 63) / 64), k.KS);
     return launch_pg<2, 2, 4, 2>(k, epilogue, stream);
 }
 
