@@ -113,6 +113,7 @@ struct PrefillGemmKernelArgs {
     uint16_t *Xout;           // SWIGLU
     int KS_out;
     int J;                    // K slices
+    bool fold;                // sums of 16 K-steps between the partial and the running sum (small shape)
     float *partials;          // J > 1: [tile][slice][TN * TR * 256] sums
     unsigned *arrive;         // J > 1: one counter per tile, zero between launches
 };
@@ -198,11 +199,9 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
             part[i][j] = sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             if (OWN_REST) rest[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         }
-    // K-steps per partial sum.  Where K is sliced (the small shape) partial sums go into sums of four first: slices are chosen for their time, few long
-    // ones or many short ones, and the running sum of a long one would be a longer chain of additions (two slices of 64 steps instead of
-    // five of 26, 7B QKV at 100 rows: 10 % more flipped roundings of K and V without, as many with; 0.3 % of a short prompt's time).
-    const int chunk = a.J > 1 || KS <= 64 ? 4 : 8;
-    int left = chunk, quarter = a.J > 1 ? 4 : 1 << 30;
+    // K-steps per partial sum; fold: partial sums go into sums of four before they reach the running sum
+    const int chunk = a.fold || KS <= 64 ? 4 : 8;
+    int left = chunk, quarter = a.fold ? 4 : 1 << 30;
     f32x4_t mid[OWN_REST ? NW : 1][NX];
     if (OWN_REST) {
 #pragma unroll
@@ -459,9 +458,15 @@ hipError_t launch_prefill_gemm(const PrefillGemmArgs &a, int epilogue, hipStream
     k.gain_next = a.gain_next; k.Xnext = (uint16_t *)a.Xnext; k.ssq_out = a.ssq_out;
     k.Xout = (uint16_t *)a.Xout; k.KS_out = (a.N / 2 + 31) / 32;
     k.J = 1;
+    k.fold = false;
     k.partials = a.partials; k.arrive = a.arrive;
     if (prefill_large(k.n_tiles, a.rows)) return launch_pg<2, 4, 8, 2>(k, epilogue, stream);
-    k.J = prefill_slices(((k.n_tiles + 7) / 8) * ((a.rows + 63) / 64), k.KS);
+    const int tiles = ((k.n_tiles + 7) / 8) * ((a.rows + 63) / 64);
+    k.J = prefill_slices(tiles, k.KS);
+    // Slices that fill the chip's 512 places are as short as they can be.  Where the estimate leaves places empty, fewer and longer ones were
+    // faster, and their running sums would be longer chains of additions: 7B QKV at 100 rows, two slices of 64 steps instead of five of 26,
+    // 10 % more flipped roundings of K and V, and as many with sums in between (0.3 % of a short prompt's time).
+    k.fold = k.J > 1 && tiles * k.J <= 384;
     return launch_pg<2, 2, 4, 2>(k, epilogue, stream);
 }
 
