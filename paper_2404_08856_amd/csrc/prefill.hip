@@ -8,7 +8,7 @@
 //    is unused and no sum over term columns is needed.  Block (row tile rt of 16 rows, K-step s, term t) is the
 //    1 KiB at index (rt * KS + s) * 3 + t, lane l = r + 16 g holding X[16 rt + r][32 s + 8 g .. + 7].
 //  * prefill_gemm_kernel: tiled GEMM, both operands through LDS.  Bound by the matrix cores: the 7B QKV projection of
-//    2047 rows runs at 1.31 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.28).
+//    2047 rows runs at 1.27 to 1.32 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.28).
 //  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
 //    the pass's own rows).
 // Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
