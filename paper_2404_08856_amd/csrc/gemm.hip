@@ -1055,9 +1055,10 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, GemmTuning tune, hipStre
         NG = groups <= 2 ? 2 : groups <= 4 ? 4 : groups <= 8 ? 8 : kMaxGroups;
         p = batch_plan(k.n_tiles, k.KS, NG);
     }
-    // (more than 262144 output columns: more tile groups than arrival counters, the K-splitting kernel takes them)
+    // (more than 262144 output columns: more tile groups than arrival counters, or more than 4 GiB of activations, which its loader waves address
+    // with 32 bits: the K-splitting kernel takes them)
     if (a.batch_partials && a.batch_arrive && a.batch_zero && groups > 1 && !tune.no_batch && (batch_pays || tune.force_batch) &&
-        p.n_tgroups <= kBatchMaxTileGroups) {
+        p.n_tgroups <= kBatchMaxTileGroups && (size_t)groups * k.KS <= (size_t)1 << 22) {
         if (tune.grid_cap > 0 && tune.grid_cap / p.n_tgroups < p.J)          // a cap on the grid means fewer K slices here
             p.J = tune.grid_cap / p.n_tgroups > 0 ? tune.grid_cap / p.n_tgroups : 1;
         BatchArgs b{a.batch_partials, a.batch_arrive, p.J, (const uint4 *)a.batch_zero};

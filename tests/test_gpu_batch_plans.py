@@ -119,3 +119,28 @@ def test_slices_in_halves_are_as_exact_as_the_kernel_that_splits_k_over_waves(d,
         errors.append(((got - want).norm() / want.norm()).item())
     print(f"O at {n_seqs} rows: {errors[0]:.3e}, K over waves {errors[1]:.3e}", flush=True)
     assert errors[0] <= 1.15 * errors[1], errors
+
+
+def test_activations_of_more_than_four_gib():
+    """64 rows of 11.2 million columns: 13 row groups of 350000 K-steps of 1 KiB.  The last rows' activations lie beyond 2^32 bytes."""
+    from paper_2404_08856_amd import spd
+    shape = synth.ModelShape(1, 64, 1, 64, 11_200_000, 64)
+    g = torch.Generator(device="cuda").manual_seed(51)
+    mat = lambda *s: (0.02 * torch.randn(s, generator=g, device="cuda")).to(torch.bfloat16)
+    w = to_device(synth.make_weights(synth.ModelShape(1, 64, 1, 64, 64, 64), 50))
+    lw = w["layers"][0]
+    lw["wo"].zero_()
+    lw["w_gate"], lw["w_up"], lw["w_down"] = mat(shape.d_ffn, 64), mat(shape.d_ffn, 64), mat(64, shape.d_ffn)
+    ids = torch.arange(64, dtype=torch.int32, device="cuda")
+    m = spd.Model(spd.make_config(shape, 64, 1), w)
+    out = torch.empty((64, 1, 64), device="cuda")
+    m.spd_verify_forward(ids[:, None].contiguous(), out)
+    x = w["embed"].double()
+    b = x / torch.sqrt(x.square().mean(-1, keepdim=True) + shape.rms_eps)
+    y = x.clone()
+    for at in range(0, shape.d_ffn, 800_000):
+        part = slice(at, at + 800_000)
+        act = torch.nn.functional.silu(b @ lw["w_gate"][part].double().T) * (b @ lw["w_up"][part].double().T)
+        y += act @ lw["w_down"][:, part].double().T
+    want = y / torch.sqrt(y.square().mean(-1, keepdim=True) + shape.rms_eps) @ w["lm_head"].double().T
+    check_logits(out[:, 0].cpu().numpy(), want.cpu().numpy(), "rows behind 4 GiB")
