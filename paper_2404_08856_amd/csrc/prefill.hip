@@ -119,11 +119,17 @@ struct PrefillGemmKernelArgs {
 };
 
 // J > 1: the K range is cut into J slices, one workgroup each.
-constexpr int kPgBuf = 3;     // LDS stages: one being multiplied, two on their way
+constexpr int kPgBuf = 3;     // LDS stages: one whose fragments are read, two on their way
 
 // WN x WR waves; a wave owns NW weight tiles (16 features each) and NX row tiles (16 rows each).  One K-step of
-// both operands (WN * NW + 3 * WR * NX blocks of 1 KiB) is one LDS stage, brought in by LDS-direct loads two stages
-// ahead; all blocks are in operand order already, so the fragment reads are lane-linear and conflict-free.
+// both operands (WN * NW + 3 * WR * NX blocks of 1 KiB) is one LDS stage, brought in by LDS-direct loads; all blocks are in
+// operand order already, so the fragment reads are lane-linear and conflict-free.  A step multiplies fragments that are in
+// registers; behind the products of each weight fragment go the read of the next step's one and one load of the stage three
+// steps ahead (its buffer's fragments are in registers by then).  All loads of a stage at once held the wave up until the
+// memory pipe had taken them (16 cycles each, 40 of them per step and CU), and the fragments' reads were a wait of their own: four 7B layers, 2047
+// rows 6.94 -> 6.83 ms with the reads a step ahead, 7.14 -> 6.75 with the loads spread too; 640 rows 2.52 -> 2.41; the 12-layer draft, 1472
+// rows 1.69 -> 1.67.  What is left is not the pipeline's depth (a fourth stage changes nothing) nor the barrier (without: -1.5 %) but the
+// card's power: the matrix cores are busy 70 % of the cycles at 1.85 GHz, 60 % at 1.99 before; the loads into LDS alone cost 16 % and the reads 7 %.
 // Accumulation: partial sums over 4 or 8 K-steps are added to a running sum, so no long chain rounds at the size of
 // the result.  The second and third terms (2^-8 and 2^-16 of the first) have an accumulator of their own where the
 // registers allow it (NW * NX <= 8); otherwise they go into the short partial sum ahead of the first term.
@@ -134,7 +140,6 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
     constexpr bool OWN_REST = NW * NX <= 8;
     static_assert(NW % 2 == 0, "the SwiGLU epilogue takes tiles in pairs");
     __shared__ uint4 S[kPgBuf][BLK][64];
-    __shared__ float inv_s[TR * 16];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // Workgroup -> tile.  Workgroups go round robin over the 8 XCDs; each XCD takes a contiguous run of an order that
@@ -170,27 +175,33 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
         }
     }
     const unsigned lds0 = lds_addr(&S[0][0][0]);
-    auto issue = [&](int s, int buf) __attribute__((always_inline)) {
+    auto issue_one = [&](int s, int buf, int i) __attribute__((always_inline)) {
         const int ss = s < KS ? s : KS - 1;               // past the end: a harmless re-read
+        lds_dma16(src[i] + (size_t)ss * step[i], 16u * lane, lds0 + (unsigned)((buf * BLK + w + i * WAVES) * 1024));
+    };
+    auto issue = [&](int s, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < PB; ++i) lds_dma16(src[i] + (size_t)ss * step[i], 16u * lane, lds0 + (unsigned)((buf * BLK + w + i * WAVES) * 1024));
+        for (int i = 0; i < PB; ++i) issue_one(s, buf, i);
     };
     issue(0, 0);
     issue(1, 1);
 
-    // 1 / rms of the workgroup's rows, 4 threads per row, fixed order; read behind the loop's barriers
-    if (a.ssq_in) {
-        for (int i = threadIdx.x; i < TR * 64; i += WAVES * 64) {
-            const int row = min(rt0 * 16 + i / 4, a.rows - 1), q = i & 3;
+    const int wn = w % WN, wr = w / WN;
+    // 1 / rms of this lane's rows from the producer's partial sums: a lane group takes every fourth, fixed order
+    float inv[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+        inv[j] = 1.0f;
+        if (a.ssq_in) {
+            const int row = min((rt0 + wr * NX + j) * 16 + (lane & 15), a.rows - 1);
             float ss = 0.f;
-            for (int p = q; p < a.ssq_parts; p += 4) ss += a.ssq_in[(size_t)row * a.ssq_ld + p];
-            ss += __shfl_xor(ss, 1);
-            ss += __shfl_xor(ss, 2);
-            if (q == 0) inv_s[i / 4] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
+            for (int p = lane >> 4; p < a.ssq_parts; p += 4) ss += a.ssq_in[(size_t)row * a.ssq_ld + p];
+            ss += __shfl_xor(ss, 16);
+            ss += __shfl_xor(ss, 32);
+            inv[j] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
         }
     }
 
-    const int wn = w % WN, wr = w / WN;
     f32x4_t part[NW][NX], sum[NW][NX], rest[OWN_REST ? NW : 1][NX];
 #pragma unroll
     for (int i = 0; i < NW; ++i)
@@ -209,25 +220,7 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
 #pragma unroll
             for (int j = 0; j < NX; ++j) mid[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-    uint4 wf[NW], xf[kTerms][NX];
-    auto fetch = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < NW; ++i) wf[i] = S[buf][wn * NW + i][lane];
-#pragma unroll
-        for (int t = kTerms - 1; t >= 0; --t)
-#pragma unroll
-            for (int j = 0; j < NX; ++j) xf[t][j] = S[buf][TN + (wr * NX + j) * kTerms + t][lane];
-    };
-    auto multiply = [&] __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = kTerms - 1; t >= 0; --t)
-#pragma unroll
-            for (int j = 0; j < NX; ++j)
-#pragma unroll
-                for (int i = 0; i < NW; ++i) {
-                    if (OWN_REST && t > 0) rest[i][j] = mfma_bf16(wf[i], xf[t][j], rest[i][j]);
-                    else part[i][j] = mfma_bf16(wf[i], xf[t][j], part[i][j]);
-                }
+    auto fold_partial = [&] __attribute__((always_inline)) {
         if (--left == 0) {
             left = chunk;
 #pragma unroll
@@ -247,21 +240,62 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
             }
         }
     };
-    // stage s has landed for everyone, nobody reads stage s - 1 any more (lgkmcnt: not a read of it is still under way when
-    // a wave passes the barrier, wherever the compiler put the products): refill its buffer with stage s + 2
-    int buf = 0, nbuf = kPgBuf - 1;
-    auto arrive = [&](int s) __attribute__((always_inline)) {
+    uint4 wf[NW], xa[kTerms][NX], xb[kTerms][NX];
+    auto read_x = [&](uint4 (&x)[kTerms][NX], int q, int buf) __attribute__((always_inline)) {   // fragment q of the row tiles
+        const int t = kTerms - 1 - q / NX, j = q % NX;
+        x[t][j] = S[buf][TN + (wr * NX + j) * kTerms + t][lane];
+    };
+    // One K-step: its fragments are in wf and x, the next one's are read from buffer `next` (into wf and xn), stage `later` goes into `buf`
+    auto multiply = [&](uint4 (&x)[kTerms][NX], uint4 (&xn)[kTerms][NX], int next, int later, int buf) __attribute__((always_inline)) {
+        constexpr int XR = (kTerms * NX + NW - 1) / NW, LR = (PB + NW - 1) / NW;     // reads and loads per weight fragment
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+#pragma unroll
+            for (int q = i * XR; q < (i + 1) * XR && q < kTerms * NX; ++q) read_x(xn, q, next);
+#pragma unroll
+            for (int t = kTerms - 1; t >= 0; --t)
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    if (OWN_REST && t > 0) rest[i][j] = mfma_bf16(wf[i], x[t][j], rest[i][j]);
+                    else part[i][j] = mfma_bf16(wf[i], x[t][j], part[i][j]);
+                }
+            wf[i] = S[next][wn * NW + i][lane];
+#pragma unroll
+            for (int q = i * LR; q < (i + 1) * LR && q < PB; ++q) issue_one(later, buf, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        fold_partial();
+    };
+    // the older of the two stages on their way has landed for everyone, and nobody reads the one before it any more (lgkmcnt: not
+    // a read of it is still under way when a wave passes the barrier, wherever the compiler put the products)
+    auto arrive = [&] __attribute__((always_inline)) {
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kPgBuf - 2) * PB) : "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        issue(s + kPgBuf - 1, nbuf);
     };
-    for (int s = 0; s < KS; ++s) {
-        arrive(s);
-        fetch(buf);
-        multiply();
-        buf = buf + 1 == kPgBuf ? 0 : buf + 1;
-        nbuf = nbuf + 1 == kPgBuf ? 0 : nbuf + 1;
+    int cur = 0, nxt = 1;
+    auto advance = [&] __attribute__((always_inline)) {
+        cur = nxt;
+        nxt = nxt + 1 == kPgBuf ? 0 : nxt + 1;
+    };
+    arrive();
+    issue(2, 2);
+#pragma unroll
+    for (int q = 0; q < kTerms * NX; ++q) read_x(xa, q, 0);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) wf[i] = S[0][wn * NW + i][lane];
+    int s = 0;
+    for (; s + 1 < KS; s += 2) {
+        arrive();
+        multiply(xa, xb, nxt, s + kPgBuf, cur);
+        advance();
+        arrive();
+        multiply(xb, xa, nxt, s + 1 + kPgBuf, cur);
+        advance();
+    }
+    if (s < KS) {
+        arrive();
+        multiply(xa, xb, nxt, s + kPgBuf, cur);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // no load to LDS may outlive the workgroup
 #pragma unroll
@@ -272,7 +306,6 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
             sum[i][j] += part[i][j];
         }
 
-    __syncthreads();                                      // inv_s
     if (a.J > 1) {
         // This slice's sums in whole lines (512 contiguous bytes per store), written through to memory; once they are acknowledged take a
         // ticket.  The last slice of the tile to arrive (nobody waits) adds all of them in slice order and goes on.
@@ -289,8 +322,8 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                 __hip_atomic_store(mine + at(i, j, 1), v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __shared__ int is_last;
-        __syncthreads();
+        __syncthreads();                                  // (nobody reads the stages any more either)
+        int &is_last = *reinterpret_cast<int *>(&S[0][0][0]);
         if (threadIdx.x == 0) {
             const unsigned ticket = __hip_atomic_fetch_add(a.arrive + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             is_last = ticket == (unsigned)(a.J - 1);
@@ -352,9 +385,8 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
     }
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
-        const int lrow = (wr * NX + j) * 16 + r, row = rt0 * 16 + lrow;
+        const int row = (rt0 + wr * NX + j) * 16 + r;
         const bool row_ok = row < a.rows;
-        const float inv = a.ssq_in ? inv_s[lrow] : 1.0f;
         if (EPI == EPI_SWIGLU) {
             // rows 0..7 of a tile are gate features (g = 0, 1), rows 8..15 the matching up features (g = 2, 3): of a pair
             // of tiles the lower half-wave finishes the first, the upper half the second
@@ -364,7 +396,7 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                 float y[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const float p = sum[i][j][v] * inv, q = sum[i + 1][j][v] * inv;
+                    const float p = sum[i][j][v] * inv[j], q = sum[i + 1][j][v] * inv[j];
                     const float got = __shfl_xor(g < 2 ? q : p, 32);
                     const float gate = g < 2 ? p : got, up = g < 2 ? got : q;
                     y[v] = gate / (1.0f + expf(-gate)) * up;
@@ -379,7 +411,7 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                 if (!(row_ok && t < a.n_tiles)) continue;
                 float4 *dst = reinterpret_cast<float4 *>(a.Y + (size_t)row * a.ldy + col);
                 if (EPI == EPI_STORE) {
-                    *dst = float4{sum[i][j][0] * inv, sum[i][j][1] * inv, sum[i][j][2] * inv, sum[i][j][3] * inv};
+                    *dst = float4{sum[i][j][0] * inv[j], sum[i][j][1] * inv[j], sum[i][j][2] * inv[j], sum[i][j][3] * inv[j]};
                 } else {
                     float4 h = hold[i][j];
                     h.x += sum[i][j][0]; h.y += sum[i][j][1]; h.z += sum[i][j][2]; h.w += sum[i][j][3];
