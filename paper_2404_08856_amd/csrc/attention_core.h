@@ -244,8 +244,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                         mx = fmaxf(mx, x);
                     }
                 }
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                mx = max_over_rows(mx);
                 const float m_new = fmaxf(m_run[qg], mx);              // finite: a unit has >= 1 valid key
                 const float rescale = (m_run[qg] == -INFINITY) ? 0.f : expf(m_run[qg] - m_new);   // NaN at inf - inf
                 float lsum = 0.f;
@@ -262,8 +261,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                         hv[4 * ab + v] = f32_to_bf16_bits(sel0 * p + sel1 * r1 + sel2 * r2);
                     }
                 const uint4 pb = uint4{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16), hv[4] | (hv[5] << 16), hv[6] | (hv[7] << 16)};
-                lsum += __shfl_xor(lsum, 16);
-                lsum += __shfl_xor(lsum, 32);
+                lsum = xor_step<16>(lsum, AddOp());
+                lsum = xor_step<32>(lsum, AddOp());
                 l_run[qg] = l_run[qg] * rescale + lsum;
                 m_run[qg] = m_new;
                 if constexpr (CACHED) {
@@ -317,18 +316,16 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 s += (x.x * y.x + x.y * y.y) + (x.z * y.z + x.w * y.w);
             }
         }
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
+        s += lane_xor<1>(s);
+        s += lane_xor<2>(s);
         if (m >= M || j > m) s = -INFINITY;
         float mx = s;
-        mx = fmaxf(mx, __shfl_xor(mx, 4));
-        mx = fmaxf(mx, __shfl_xor(mx, 8));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = xor_reduce<16, 4>(mx, MaxOp());
         const float p = (mx == -INFINITY) ? 0.f : expf(s - mx);        // rows m >= M: nothing visible
         float l = p;
-        l += __shfl_xor(l, 4);
-        l += __shfl_xor(l, 8);
-        l += __shfl_xor(l, 16);
+        l = xor_step<4>(l, AddOp());
+        l = xor_step<8>(l, AddOp());
+        l = xor_step<16>(l, AddOp());
         if (part == 0) {
             pn[m][j] = p;
             if (j == 0) { part_m[AW][m] = mx; part_l[AW][m] = l; }

@@ -71,6 +71,49 @@ __device__ __forceinline__ float max_over_rows(float x) {
     r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+// The value of lane l ^ N (all 64 lanes active): moves inside a row of 16 lanes and register swaps between rows, a few cycles
+// of latency each, where a shuffle is a round trip through LDS.  Kernels that are chains of reductions are mostly such round
+// trips: draft step of the 12-layer shape, accept step, last rows of the projections (lane semantics checked on the device).
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true); }
+template <int N, class T>
+__device__ __forceinline__ T lane_xor(T v) {
+    static_assert(sizeof(T) == 4 && (N == 1 || N == 2 || N == 4 || N == 8 || N == 16 || N == 32), "one register, one bit");
+    const int x = __builtin_bit_cast(int, v);
+    int y;
+    if constexpr (N == 1) y = dpp_move<0xB1>(x);                         // quad permutations 1 0 3 2
+    else if constexpr (N == 2) y = dpp_move<0x4E>(x);                    // 2 3 0 1
+    else if constexpr (N == 4) y = dpp_move<0x1B>(dpp_move<0x141>(x));   // l ^ 7, then l ^ 3
+    else if constexpr (N == 8) y = dpp_move<0x128>(x);                   // row of 16 turned by 8
+    else {
+        const auto r = N == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false) : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        y = (threadIdx.x & N) ? r[0] : r[1];
+    }
+    return __builtin_bit_cast(T, y);
+}
+// x of this lane and of lane l ^ N through a commutative operation (no choice between the swap's halves is needed)
+template <int N, class T, class Op>
+__device__ __forceinline__ T xor_step(T v, Op op) {
+    if constexpr (N < 16) return op(v, lane_xor<N>(v));
+    else {
+        const int x = __builtin_bit_cast(int, v);
+        const auto r = N == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false) : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return op(__builtin_bit_cast(T, (int)r[0]), __builtin_bit_cast(T, (int)r[1]));
+    }
+}
+struct AddOp { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct MaxOp { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+// Over the lanes FROM, FROM / 2, ... TO away, in that order; every lane ends with the result.
+template <int FROM, int TO, class Op>
+__device__ __forceinline__ float xor_reduce(float x, Op op) {
+    x = xor_step<FROM>(x, op);
+    if constexpr (FROM > TO) x = xor_reduce<FROM / 2, TO>(x, op);
+    return x;
+}
+__device__ __forceinline__ float wave_sum(float x) { return xor_reduce<32, 1>(x, AddOp()); }
+__device__ __forceinline__ float wave_max(float x) { return xor_reduce<32, 1>(x, MaxOp()); }
+__device__ __forceinline__ float row_sum(float x) { return xor_reduce<8, 1>(x, AddOp()); }   // over a row of 16 lanes
+__device__ __forceinline__ float row_max(float x) { return xor_reduce<8, 1>(x, MaxOp()); }
 // Data-parallel-primitive moves inside a row of 16 lanes (no LDS traffic, no wait): lane i of a row
 // receives the value of lane i + n (row_shl) or i - n (row_shr) of the same row, 0 beyond the row
 // (lane semantics checked on the device).

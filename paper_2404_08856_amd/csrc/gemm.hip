@@ -136,8 +136,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
         for (int r = a.row0 + w; r < a.row0 + a.rows; r += WAVES) {
             float sum = 0.f;
             for (int p = lane; p < a.ssq_in_parts; p += 64) sum += a.ssq_in[(size_t)r * (KS * 2) + p];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            sum = wave_sum(sum);
             if (lane == 0) inv_s[r] = 1.0f / sqrtf(sum * a.inv_d + a.eps);
         }
     } else {
@@ -249,8 +248,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_stream_kernel(GemmKernelArgs 
                 }
                 // sum of squares of the 16 new values of this row in this tile (lanes en = 0..15)
                 float sq = hnew * hnew;
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+                sq = row_sum(sq);
                 if (a.ssq_out && en == 0 && e_active) a.ssq_out[(size_t)erow * a.n_tiles + t] = sq;
             }
         }
@@ -284,8 +282,7 @@ __global__ __launch_bounds__(512) void gemm_multi_kernel(GemmKernelArgs a) {
         for (int r = a.row0 + w; r < a.row0 + a.rows; r += WAVES) {
             float sum = 0.f;
             for (int p = lane; p < a.ssq_in_parts; p += 64) sum += a.ssq_in[(size_t)r * (KS * 2) + p];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            sum = wave_sum(sum);
             if (lane == 0) inv_s[r] = 1.0f / sqrtf(sum * a.inv_d + a.eps);
         }
     } else if (threadIdx.x < kMaxRows) {
@@ -373,8 +370,7 @@ __global__ __launch_bounds__(512) void gemm_multi_kernel(GemmKernelArgs a) {
                         }
                     }
                     float sq = hnew * hnew;                // the 16 columns of a row slot sit in 16 neighbouring lanes
-#pragma unroll
-                    for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+                    sq = row_sum(sq);
                     if (a.ssq_out && en == 0 && ok) a.ssq_out[(size_t)erow * a.n_tiles + t] = sq;
                 }
             }
@@ -741,7 +737,7 @@ __global__ __launch_bounds__((WAVES + kBatchLoaders) * 64) void gemm_batch_kerne
                 float out4[4];
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    const float up = __shfl_down(v[x], 2, 4);
+                    const float up = lane_xor<2>(v[x]);
                     out4[x] = v[x] / (1.0f + expf(-v[x])) * up;
                 }
                 if (ok[i] && q < 2) {
@@ -784,8 +780,7 @@ __global__ __launch_bounds__((WAVES + kBatchLoaders) * 64) void gemm_batch_kerne
                                 *reinterpret_cast<uint2 *>(a.Xnext + xpack_index(erow, col, a.n_tiles / 2, y)) = term[y].u;
                         }
                     }
-                    sq += __shfl_xor(sq, 2);
-                    sq += __shfl_xor(sq, 1);
+                    sq = xor_reduce<2, 1>(sq, AddOp());
                     if (a.ssq_out && q == 0 && ok[i]) a.ssq_out[(size_t)erow * a.n_tiles + t] = sq;
                 }
             }
@@ -919,8 +914,7 @@ __global__ __launch_bounds__(WAVES * 64, (NG > 1 ? 1 : (NB <= 8 ? 4 : 2))) void 
                     }
                 }
                 float sq = hnew * hnew;
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+                sq = row_sum(sq);
                 if (a.ssq_out && en == 0 && e_active) a.ssq_out[(size_t)erow * a.n_tiles + t] = sq;
             }
         }

@@ -35,8 +35,7 @@ __device__ __forceinline__ float rms_inv_from_parts(const float *part, int parts
             for (int p = en16; p < parts; p += 16) sum += part[p];
         }
     }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    sum = row_sum(sum);
     return 1.0f / sqrtf(sum * inv_d + eps);
 }
 

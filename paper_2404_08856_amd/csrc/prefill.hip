@@ -78,8 +78,7 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(const uint16_t *__res
         const float y[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
         ppack_store4(X, row, k, KS, y);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    ss = wave_sum(ss);
     __shared__ float part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
     __syncthreads();
@@ -196,8 +195,8 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
             const int row = min((rt0 + wr * NX + j) * 16 + (lane & 15), a.rows - 1);
             float ss = 0.f;
             for (int p = lane >> 4; p < a.ssq_parts; p += 4) ss += a.ssq_in[(size_t)row * a.ssq_ld + p];
-            ss += __shfl_xor(ss, 16);
-            ss += __shfl_xor(ss, 32);
+            ss = xor_step<16>(ss, AddOp());
+            ss = xor_step<32>(ss, AddOp());
             inv[j] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
         }
     }
@@ -397,7 +396,7 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const float p = sum[i][j][v] * inv[j], q = sum[i + 1][j][v] * inv[j];
-                    const float got = __shfl_xor(g < 2 ? q : p, 32);
+                    const float got = lane_xor<32>(g < 2 ? q : p);
                     const float gate = g < 2 ? p : got, up = g < 2 ? got : q;
                     y[v] = gate / (1.0f + expf(-gate)) * up;
                 }
@@ -422,8 +421,8 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                 }
             }
             if (EPI == EPI_RESIDUAL) {
-                sq += __shfl_xor(sq, 16);
-                sq += __shfl_xor(sq, 32);
+                sq = xor_step<16>(sq, AddOp());
+                sq = xor_step<32>(sq, AddOp());
                 const int p = nb * WN + wn;
                 if (g == 0 && row_ok && p * NW < a.n_tiles) a.ssq_out[(size_t)row * a.ssq_ld + p] = sq;
             }
@@ -823,8 +822,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
         nbuf = nbuf + 1 == kPaBuf ? 0 : nbuf + 1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    l_run = xor_step<16>(l_run, AddOp());
+    l_run = xor_step<32>(l_run, AddOp());
     if (row < a.rows) {
 #pragma unroll
         for (int i = 0; i < NDT; ++i) {

@@ -49,8 +49,7 @@ __global__ __launch_bounds__(256) void input_rows_kernel(const uint16_t *__restr
 #pragma unroll
         for (int t = 0; t < kTerms; ++t) *reinterpret_cast<uint2 *>(xpack + xpack_index(row, k, KS, t)) = term[t].v;
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    ss = wave_sum(ss);
     __shared__ float part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
     __syncthreads();

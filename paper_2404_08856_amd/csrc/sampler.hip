@@ -20,11 +20,27 @@ struct RowStats { float mx; float sum; int argmax; int pad; };
 // use this one function, so the probabilities of a row are consistent with its sum.
 __device__ __forceinline__ float softmax_num(float l, float mx, float inv_temp) { return __expf((l - mx) * inv_temp); }
 
-__device__ __forceinline__ unsigned long long shfl_up_u64(unsigned long long v, int off) {
-    unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
-    lo = __shfl_up(lo, off);
-    hi = __shfl_up(hi, off);
-    return ((unsigned long long)hi << 32) | lo;
+__device__ __forceinline__ unsigned long long join_u64(unsigned lo, unsigned hi) { return ((unsigned long long)hi << 32) | lo; }
+// Sum over the wave, on every lane, and inclusive prefix sum over the lanes, without a trip through LDS (integers: any order)
+template <int N = 32>
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
+    v += join_u64(lane_xor<N>((unsigned)v), lane_xor<N>((unsigned)(v >> 32)));
+    if constexpr (N > 1) v = wave_sum_u64<N / 2>(v);
+    return v;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_from_below(unsigned long long v) {    // 0 where no lane is below, and outside ROWS
+    return join_u64((unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, ROWS, 0xf, false),
+                    (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v) {
+    v += dpp_from_below<0x111, 0xf>(v);                       // 1, 2, 4, 8 lanes below in the row of 16
+    v += dpp_from_below<0x112, 0xf>(v);
+    v += dpp_from_below<0x114, 0xf>(v);
+    v += dpp_from_below<0x118, 0xf>(v);
+    v += dpp_from_below<0x142, 0xa>(v);                       // last lane of rows 0 and 2 to rows 1 and 3
+    v += dpp_from_below<0x143, 0xc>(v);                       // last lane of row 1 to rows 2 and 3
+    return v;
 }
 
 // Exclusive prefix sum of one value per thread over the whole workgroup (1024 threads);
@@ -32,12 +48,7 @@ __device__ __forceinline__ unsigned long long shfl_up_u64(unsigned long long v, 
 __device__ unsigned long long block_exclusive_scan(unsigned long long v, unsigned long long *tmp,
                                                    unsigned long long *total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    unsigned long long incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        unsigned long long t = shfl_up_u64(incl, off);
-        if (lane >= off) incl += t;
-    }
+    const unsigned long long incl = wave_scan_u64(v);
     __syncthreads();                      // tmp may still be in use by a previous call
     if (lane == 63) tmp[w] = incl;
     __syncthreads();
@@ -95,6 +106,14 @@ __device__ int sample_inverse_cdf(F r, int V, float u, unsigned long long *tmp, 
 // ---------------------------------------------------------------------------------
 // softmax statistics of logit rows: max, argmax (lowest index), sum exp((l - max) / temp)
 // ---------------------------------------------------------------------------------
+// maximum and its lowest index over the lanes N, N / 2, ... 1 away
+template <int N>
+__device__ __forceinline__ void argmax_over(float &mx, int &arg) {
+    const float om = lane_xor<N>(mx);
+    const int oa = lane_xor<N>(arg);
+    if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+    if constexpr (N > 1) argmax_over<N / 2>(mx, arg);
+}
 __device__ void row_stats(const float *__restrict__ row, int V, float inv_temp, RowStats *out_shared) {
     // out_shared: one RowStats in shared memory, valid after the call for all threads
     __shared__ float s_mx[kSampThreads / 64];
@@ -106,12 +125,7 @@ __device__ void row_stats(const float *__restrict__ row, int V, float inv_temp, 
         float v = row[x];
         if (v > mx) { mx = v; arg = x; }                       // strided: first hit is the lowest index
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        float om = __shfl_xor(mx, off);
-        int oa = __shfl_xor(arg, off);
-        if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-    }
+    argmax_over<32>(mx, arg);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     if (lane == 0) { s_mx[w] = mx; s_arg[w] = arg; }
     __syncthreads();
@@ -120,8 +134,7 @@ __device__ void row_stats(const float *__restrict__ row, int V, float inv_temp, 
         if (s_mx[i] > mx || (s_mx[i] == mx && s_arg[i] < arg)) { mx = s_mx[i]; arg = s_arg[i]; }
     float sum = 0.f;
     for (int x = threadIdx.x; x < V; x += blockDim.x) sum += softmax_num(row[x], mx, inv_temp);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    sum = wave_sum(sum);
     if (lane == 0) s_sum[w] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -202,31 +215,18 @@ __device__ void row_stats_regs(Row &v, bool greedy, float inv_temp, RowStats *ou
             for (int j = 0; j < 4; ++j)
                 if (e[j] > mx) { mx = e[j]; arg = x0 + j; }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            float om = __shfl_xor(mx, off);
-            int oa = __shfl_xor(arg, off);
-            if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-        }
+        argmax_over<32>(mx, arg);
         if (lane == 0) { s_mx[w] = mx; s_arg[w] = arg; }
         __syncthreads();
         mx = s_mx[lane & 15]; arg = s_arg[lane & 15];         // 16 wave results, combined by every 16-lane group
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) {
-            float om = __shfl_xor(mx, off);
-            int oa = __shfl_xor(arg, off);
-            if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-        }
+        argmax_over<8>(mx, arg);
     } else {
 #pragma unroll
         for (int i = 0; i < kRowVec; ++i) mx = fmaxf(mx, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        mx = wave_max(mx);
         if (lane == 0) s_mx[w] = mx;
         __syncthreads();
-        mx = s_mx[lane & 15];
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        mx = row_max(s_mx[lane & 15]);
     }
     float sum = 0.f;
 #pragma unroll
@@ -240,24 +240,12 @@ __device__ void row_stats_regs(Row &v, bool greedy, float inv_temp, RowStats *ou
         if constexpr (KEEP)
             if (!greedy) v[i] = e;
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    sum = wave_sum(sum);
     if (lane == 0) s_sum[w] = sum;
     __syncthreads();
-    float t = s_sum[lane & 15];                               // fixed tree over the 16 wave sums
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off);
+    const float t = row_sum(s_sum[lane & 15]);                // fixed tree over the 16 wave sums
     if (threadIdx.x == 0) { out_shared->mx = mx; out_shared->sum = t; out_shared->argmax = arg; out_shared->pad = 0; }
     __syncthreads();
-}
-
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned lo = __shfl_xor((unsigned)v, off), hi = __shfl_xor((unsigned)(v >> 32), off);
-        v += ((unsigned long long)hi << 32) | lo;
-    }
-    return v;
 }
 
 // Inverse-CDF draw (same definition as sample_inverse_cdf) over a row, or one slice of it, whose values r >= 0 sit in
@@ -307,18 +295,12 @@ struct SliceSampler {
     // one thread to *result: the caller synchronises
     __device__ __forceinline__ void find(const float4 (&r)[NV], unsigned long long thr, int first_quad, int *result) const {
         if (!(before <= thr && thr < before + mine)) return;  // wave-uniform
-        const int lane = threadIdx.x & 63;
         unsigned long long run = before;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const unsigned long long t = wave_sum_u64(part[i]);
             if (run <= thr && thr < run + t) {                // exactly one slot
-                unsigned long long incl = part[i];
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const unsigned long long o = shfl_up_u64(incl, off);
-                    if (lane >= off) incl += o;
-                }
+                const unsigned long long incl = wave_scan_u64(part[i]);
                 unsigned long long c = run + incl - part[i];
                 if (c <= thr && thr < run + incl) {           // exactly one lane
                     const int x0 = 4 * (first_quad + quad_of<NV, true>(i));
