@@ -197,8 +197,10 @@ __device__ __forceinline__ int quad_of(int i) {
 
 // softmax statistics from a row held in registers (same definition as row_stats; the argmax only where it is used)
 // KEEP: above temperature 0 the numerators exp((l - max) / temp) take the place of the row's entries.
+// Every thread gets the result.  Two calls may follow each other without a barrier between them: a wave writes a call's partials behind a
+// barrier that the others reach after reading the same partials of the call before.
 template <bool WAVE_MAJOR, bool KEEP, class Row>
-__device__ void row_stats_regs(Row &v, bool greedy, float inv_temp, RowStats *out_shared) {
+__device__ RowStats row_stats_regs(Row &v, bool greedy, float inv_temp) {
     __shared__ float s_mx[kSampThreads / 64];
     __shared__ int s_arg[kSampThreads / 64];
     __shared__ float s_sum[kSampThreads / 64];
@@ -244,8 +246,7 @@ __device__ void row_stats_regs(Row &v, bool greedy, float inv_temp, RowStats *ou
     if (lane == 0) s_sum[w] = sum;
     __syncthreads();
     const float t = row_sum(s_sum[lane & 15]);                // fixed tree over the 16 wave sums
-    if (threadIdx.x == 0) { out_shared->mx = mx; out_shared->sum = t; out_shared->argmax = arg; out_shared->pad = 0; }
-    __syncthreads();
+    return RowStats{mx, t, arg, 0};
 }
 
 // Inverse-CDF draw (same definition as sample_inverse_cdf) over a row, or one slice of it, whose values r >= 0 sit in
@@ -295,10 +296,12 @@ struct SliceSampler {
     // one thread to *result: the caller synchronises
     __device__ __forceinline__ void find(const float4 (&r)[NV], unsigned long long thr, int first_quad, int *result) const {
         if (!(before <= thr && thr < before + mine)) return;  // wave-uniform
-        unsigned long long run = before;
+        unsigned long long run = before, slot[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) slot[i] = wave_sum_u64(part[i]);        // side by side
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const unsigned long long t = wave_sum_u64(part[i]);
+            const unsigned long long t = slot[i];
             if (run <= thr && thr < run + t) {                // exactly one slot
                 const unsigned long long incl = wave_scan_u64(part[i]);
                 unsigned long long c = run + incl - part[i];
@@ -341,11 +344,12 @@ __global__ __launch_bounds__(kSampThreads) void accept_stats_kernel(AcceptArgs a
     if (KIND != ROW_MEMORY || (MIXED && ((uintptr_t)row & 15) == 0)) {
         float4 v[kRowVec];
         load_row<KIND != ROW_QUADS>(row, a.vocab, -INFINITY, v);
-        row_stats_regs<false, false>(v, !(a.temperature > 0.f), inv_temp, &st);
+        const RowStats got = row_stats_regs<false, false>(v, !(a.temperature > 0.f), inv_temp);
+        if (threadIdx.x == 0) reinterpret_cast<RowStats *>(a.stats)[r] = got;
     } else {
         row_stats(row, a.vocab, inv_temp, &st);
+        if (threadIdx.x == 0) reinterpret_cast<RowStats *>(a.stats)[r] = st;
     }
-    if (threadIdx.x == 0) reinterpret_cast<RowStats *>(a.stats)[r] = st;
 }
 
 // probability of token x in a row given its statistics (or the row itself if it holds probabilities)
@@ -557,6 +561,101 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
     }
 }
 
+// The whole accept step in one launch: a workgroup per (sequence, position j) holds both rows of its position in registers,
+// takes their statistics, runs its accept test and, if that rejects (or j is the bonus position), draws the token that the
+// sequence goes on with should j be its first reject.  Every position leaves its answer in the words of target row j's
+// statistics; then it looks at all answers of its sequence, and whoever finds them complete writes the result (the last one
+// to arrive does for certain, since its own answer is acknowledged before it looks; two may, with the same values) and takes the
+// answers away again.  Nobody waits, nothing needs clearing before the launch, and no row is read twice.
+// An answer is the token (or kAccepted) under a mark, and its complement under another: 96 bits that memory which
+// was never written would have to hold by chance; the statistics' words never do (the first mark is a NaN, where they have the sum).
+// Bound by one CU's vector instructions (about 64 cycles per entry and wave: 3 us) and its loads (256 KiB, 4 us).  32000 entries, draft
+// length 4, graph replays, one launch / statistics and slices: draft as probabilities, 1 sequence 10.1 / 14.9 us, 8 10.3 / 15.7, 32 12.3 / 16.9, 51
+// 16.5 / 19.9, 64 (a second round of workgroups) 21.8 / 21.9; draft as logits, 1 9.6 / 14.1, 51 19.3 / 24.6, 64 26.1 / 26.1; 1000 entries, 51 10.0 / 15.3,
+// 64 15.2 / 16.3.
+constexpr unsigned kAnswerMark = 0xffc5a11cu, kAnswerMark2 = 0x9e3779b9u, kAccepted = 0x80000000u;
+template <bool ALIGNED>
+__global__ __launch_bounds__(kSampThreads) void accept_positions_kernel(AcceptArgs a) {
+    const int G = a.gamma, V = a.vocab, seq = blockIdx.x / (G + 1), j = blockIdx.x - seq * (G + 1);
+    __shared__ SeqRows rows;            // (only for the view below)
+    __shared__ unsigned long long tmp[17];
+    __shared__ int result;
+    if (threadIdx.x == 0) result = -1;                        // (barriers before it is written again)
+    const SeqView q(a, rows, seq);
+    const bool greedy = !(a.temperature > 0.f), bonus = j == G;
+    float4 t[kRowVec], d[kRowVec];
+    auto load = [&](const float *row, int mode, float4 (&v)[kRowVec]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kRowVec; ++i) v[i] = load_quad<ALIGNED>(row, quad_of<kRowVec, true>(i), V, mode == 0 ? 0.f : -INFINITY);
+    };
+    const float *t_row = q.t_ptr(j), *d_row = bonus ? t_row : q.d_ptr(j);
+    const int token = bonus ? 0 : min(max(a.draft_tokens[(size_t)seq * a.token_stride + j], 0), V - 1);     // never index outside the row
+    const float u_j = a.u[seq * (G + 1) + j], u_last = a.u[seq * (G + 1) + G];
+    load(t_row, q.t_mode, t);
+    if (!bonus) load(d_row, q.d_mode, d);
+    const float t_at = t_row[token], d_at = d_row[token];
+    // probabilities in place of the entries; what the drafted token's entry becomes
+    auto probabilities = [&](const float *row, int mode, float at, RowStats &stats, float4 (&v)[kRowVec]) __attribute__((always_inline)) {
+        if (mode == 0) return at;
+        stats = row_stats_regs<true, true>(v, greedy, q.inv_temp);
+        const RowProb p = q.prob(row, stats, mode);
+#pragma unroll
+        for (int i = 0; i < kRowVec; ++i) {
+            const int x0 = 4 * quad_of<kRowVec, true>(i);
+            if (mode == 1) v[i] = float4{v[i].x * p.inv_sum, v[i].y * p.inv_sum, v[i].z * p.inv_sum, v[i].w * p.inv_sum};
+            else v[i] = float4{p.of(v[i].x, x0), p.of(v[i].y, x0 + 1), p.of(v[i].z, x0 + 2), p.of(v[i].w, x0 + 3)};
+            if (x0 >= V) v[i] = float4{0.f, 0.f, 0.f, 0.f};
+        }
+        return p.of(at, token);
+    };
+    RowStats st = {0.f, 1.f, 0, 0}, sd = st;
+    const float Tx = probabilities(t_row, q.t_mode, t_at, st, t);
+    unsigned answer = kAccepted;
+    bool accepted = false;
+    if (!bonus) {
+        const float Dx = probabilities(d_row, q.d_mode, d_at, sd, d);
+        accepted = __fmul_rn(u_j, Dx) < Tx;                   // one float32 multiply and one compare
+        if (threadIdx.x == 0 && a.accept_prob) a.accept_prob[seq * G + j] = (Dx == 0.f) ? (Tx > 0.f ? 1.0f : 0.0f) : fminf(1.0f, Tx / Dx);
+#pragma unroll
+        for (int i = 0; i < kRowVec; ++i)                     // residual max(0, T - D), in the target's place
+            t[i] = float4{fmaxf(0.0f, __fsub_rn(t[i].x, d[i].x)), fmaxf(0.0f, __fsub_rn(t[i].y, d[i].y)),
+                          fmaxf(0.0f, __fsub_rn(t[i].z, d[i].z)), fmaxf(0.0f, __fsub_rn(t[i].w, d[i].w))};
+    }
+    if (!accepted) {                                          // workgroup-uniform
+        SliceSampler<kRowVec> s;
+        s.weigh(t);
+        const unsigned long long S = s.total(tmp);
+        int y = -1;
+        if (S != 0) {
+            s.find(t, threshold_of(u_last, S), 0, &result);
+            __syncthreads();
+            y = result;
+        } else if (!bonus) {
+            y = sample_row_slowly(q.prob(t_row, st, q.t_mode), V, u_last, tmp, &result);   // residual mass truncates to zero: rare
+        }
+        answer = (unsigned)max(y, 0);
+    }
+    if (threadIdx.x >= kWave) return;
+    unsigned long long *slot = reinterpret_cast<unsigned long long *>(q.stats_t(min((int)threadIdx.x, G)));
+    auto marked = [](unsigned mark, unsigned v) { return (unsigned long long)mark << 32 | v; };
+    if ((int)threadIdx.x == j) {
+        __hip_atomic_store(slot, marked(kAnswerMark, answer), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(slot + 1, marked(kAnswerMark2, ~answer), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // acknowledged before any answer is looked at
+    const unsigned long long w0 = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long w1 = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned got = (unsigned)w0;
+    if (!__all(w0 == marked(kAnswerMark, got) && w1 == marked(kAnswerMark2, ~got))) return;
+    const unsigned long long stops = __ballot(got != kAccepted);   // positions G and beyond stop always
+    const int k = min(__ffsll((long long)stops) - 1, G);
+    if ((int)threadIdx.x == k) {
+        a.n_accepted[seq] = k;
+        a.next_token[seq] = (int)got;
+    }
+    if ((int)threadIdx.x <= G) __hip_atomic_store(slot, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 size_t accept_workspace_bytes(int n_seqs, int gamma) {
     return (size_t)n_seqs * (2 * gamma + 1) * sizeof(RowStats);
 }
@@ -565,6 +664,13 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
     if (a.gamma < 1 || a.gamma > 63) return hipErrorInvalidValue;
     const RowKind kind = row_kind(a.target, a.draft, a.vocab);
     const bool need_stats = ((a.flags & 3u) != 3u);
+    // one round of workgroups, one per CU (a second one costs more than it saves: see above); answers are 8-byte words
+    if (kind != ROW_MEMORY && ((uintptr_t)a.stats & 7) == 0 && (long)a.n_seqs * (a.gamma + 1) <= 256) {
+        const dim3 grid(a.n_seqs * (a.gamma + 1)), block(kSampThreads);
+        if (kind == ROW_ALIGNED) hipLaunchKernelGGL(accept_positions_kernel<true>, grid, block, 0, stream, a);
+        else hipLaunchKernelGGL(accept_positions_kernel<false>, grid, block, 0, stream, a);
+        return hipGetLastError();
+    }
     if (need_stats) {
         int n_rows = a.n_seqs * (2 * a.gamma + 1);
         const dim3 grid(n_rows), block(kSampThreads);
@@ -614,10 +720,11 @@ __global__ __launch_bounds__(kSampThreads) void softmax_sample_kernel(const floa
     int y;
     if (row_kind(row, out, V) == ROW_ALIGNED) {
         float4 v[kRowVec];
+        if (threadIdx.x == 0) result = -1;                    // (several barriers before it is written again)
 #pragma unroll
         for (int i = 0; i < kRowVec; ++i) v[i] = load_quad<true>(row, quad_of<kRowVec, true>(i), V, -INFINITY);
-        row_stats_regs<true, true>(v, p.mode == 2, inv_temp, &st);
-        p.st = st; p.inv_sum = 1.0f / st.sum;
+        p.st = row_stats_regs<true, true>(v, p.mode == 2, inv_temp);
+        p.inv_sum = 1.0f / p.st.sum;
 #pragma unroll
         for (int i = 0; i < kRowVec; ++i) {
             const int q = quad_of<kRowVec, true>(i);
@@ -629,8 +736,6 @@ __global__ __launch_bounds__(kSampThreads) void softmax_sample_kernel(const floa
         SliceSampler<kRowVec> s;
         s.weigh(v);
         const unsigned long long S = s.total(tmp);
-        if (threadIdx.x == 0) result = -1;
-        __syncthreads();
         if (S != 0) s.find(v, threshold_of(u_seq, S), 0, &result);
         __syncthreads();
         y = result;
