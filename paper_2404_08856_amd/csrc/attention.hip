@@ -39,7 +39,8 @@ __global__ __launch_bounds__(AW * 64) void attention_kernel(AttnArgs a, WeightPr
     }
     // head index fastest: consecutive workgroups go to consecutive XCDs, so with a head count that is
     // a multiple of 8 all slices of one head share an XCD and its L2 holds that head's K once
-    attention_core<DH, DS, AW, kUnitsPerIter, false, QG, KSP, K_ONCE, CACHED>(a, blockIdx.x, KSP == 1 ? blockIdx.y : blockIdx.y % DS, KSP == 1 ? 0 : blockIdx.y / DS, blockIdx.z, [] {});
+    attention_core<DH, DS, AW, kUnitsPerIter, QG, KSP, K_ONCE, CACHED, false>(a, blockIdx.x, KSP == 1 ? blockIdx.y : blockIdx.y % DS, KSP == 1 ? 0 : blockIdx.y / DS, blockIdx.z,
+                                                                       PlainRows<false>{a.qkv}, PackedOut{(uint16_t *)a.xout, a.H * DH / 32}, [] {});
 }
 
 constexpr int kAttnRuns = 4;

@@ -46,6 +46,30 @@ __device__ __forceinline__ float ldf(const float *p) {
     return *p;
 }
 
+// Where the new rows come from: q, k and v of row `row` at head columns j and j + half (hd: columns of q, of k, of v).  DEV: written by other
+// workgroups of the same kernel, read with device-scope loads.
+template <bool DEV>
+struct PlainRows {
+    const float *qkv;
+    __device__ __forceinline__ void load(int row, size_t col, size_t half, size_t hd, bool kv, float (&x)[6]) const {
+        const float *p = qkv + (size_t)row * 3 * hd + col;
+        x[0] = ldf<DEV>(p); x[1] = ldf<DEV>(p + half);
+        x[2] = kv ? ldf<DEV>(p + hd) : 0.f; x[3] = kv ? ldf<DEV>(p + hd + half) : 0.f;
+        x[4] = kv ? ldf<DEV>(p + 2 * hd) : 0.f; x[5] = kv ? ldf<DEV>(p + 2 * hd + half) : 0.f;
+    }
+};
+// Where the results go: value k of row `row` as three bf16 terms in B-operand order (KS K-steps)
+struct PackedOut {
+    uint16_t *x;
+    int KS;
+    __device__ __forceinline__ void store(int row, int k, float y) const {
+        uint16_t t3[kTerms];
+        split3(y, t3);
+#pragma unroll
+        for (int t = 0; t < kTerms; ++t) x[xpack_index(row, k, KS, t)] = t3[t];
+    }
+};
+
 __device__ __forceinline__ f32x4_t mfma16(const uint4 &a, const uint4 &b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
@@ -64,21 +88,22 @@ __device__ __forceinline__ float rne_bf16(float x) { return bf16_bits_to_f32(f32
 __device__ __forceinline__ uint32_t pack2(uint16_t lo, uint16_t hi) { return (uint32_t)lo | ((uint32_t)hi << 16); }
 
 // One (sequence, head, slice of the head dimension).  Must be called by all AW waves of the
-// workgroup.  DEV: the float32 QKV rows were written by other workgroups of the same kernel and
-// are read with device-scope loads.
+// workgroup.
 // `rows_ready()` is called by every thread after the loads of the cached keys have been issued and
 // before the new rows are read: the place to wait for their producer.
 // QG: query groups of 5 handled by one launch (1: up to 5 new rows per sequence, 2: up to 8; the
 // cached keys are then multiplied with both groups from the same registers).
 // KSP > 1: the cached keys are cut into KSP contiguous runs of units, one workgroup (index ks) each.  Every one leaves its
 // unnormalised result in a.partials and takes a ticket; the last of the KSP to arrive (nobody waits) combines them in
-// order.  The new rows belong to run 0.
+// order.  The new rows belong to run 0.  COUNTS_ON: the counters are never cleared (KSP is a power of two, and all rounds are whole).
+// cache_offset: bytes from a.k_cache and a.v_cache to the layer at hand.
 // K_ONCE: non-temporal loads of the keys as well (only with DS == 1: several slices of a head share its K in L2).
 // CACHED: one row whose key and value are the last ones in the cache already (the length counts them): nothing is appended,
 // a score that is NaN (an infinite key on a dimension where the query is zero) leaves NaN as in the prompt's other rows, and what lies behind the end of the cache counts as zero (a weight of zero alone would not do: rolled back values may not be finite.
 // For every form of the kernel: 4 registers more, 12-layer draft of 2 sequences, a case of four steps, 1057 -> 1087 us).
-template <int DH, int DS, int AW, int UPI, bool DEV, int QG, int KSP, bool K_ONCE, bool CACHED, class ReadyFn>
-__device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, const int ds, const int ks, const int seq, ReadyFn rows_ready) {
+template <int DH, int DS, int AW, int UPI, int QG, int KSP, bool K_ONCE, bool CACHED, bool COUNTS_ON, class Rows, class Out, class ReadyFn>
+__device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, const int ds, const int ks, const int seq, const Rows &rows, const Out &out_rows, ReadyFn rows_ready,
+                                               const size_t cache_offset = 0) {
     constexpr int HALF = DH / 2;
     constexpr int NC = DH / 32;                   // 32-dim chunks of a key row
     constexpr int DW = DH / DS;                   // output dims of this workgroup
@@ -99,8 +124,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
     const size_t pair = (size_t)seq * H + hh;
     const size_t HD = (size_t)H * DH;
     const int VS = a.v_stride;                    // positions per row of the transposed V cache
-    uint16_t *Kc = (uint16_t *)a.k_cache + pair * a.max_positions * DH;        // [pos][DH]
-    uint16_t *Vt = (uint16_t *)a.v_cache + pair * (size_t)DH * VS;             // [VS / 32][DH][32]: see launch.h
+    uint16_t *Kc = (uint16_t *)((char *)a.k_cache + cache_offset) + pair * a.max_positions * DH;        // [pos][DH]
+    uint16_t *Vt = (uint16_t *)((char *)a.v_cache + cache_offset) + pair * (size_t)DH * VS;             // [VS / 32][DH][32]: see launch.h
 
     __shared__ float qf[8][DH + 4];               // rows 4 banks apart: 8 rows are read side by side below
     __shared__ float kf[8][DH + 4];
@@ -153,12 +178,11 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
             float qa = 0.f, qc = 0.f;
             if (i < M) {
                 const int pos = CACHED ? P - 1 : P + i;
-                const float *row = a.qkv + (size_t)(row_base + i) * 3 * HD + (size_t)hh * DH;
                 const float c = a.rope[((size_t)pos * HALF + j) * 2 + 0];
                 const float s = a.rope[((size_t)pos * HALF + j) * 2 + 1];
-                const float q1 = ldf<DEV>(row + j), q2 = ldf<DEV>(row + j + HALF);
-                const float k1 = own ? ldf<DEV>(row + HD + j) : 0.f, k2 = own ? ldf<DEV>(row + HD + j + HALF) : 0.f;
-                const float v1 = own ? ldf<DEV>(row + 2 * HD + j) : 0.f, v2 = own ? ldf<DEV>(row + 2 * HD + j + HALF) : 0.f;
+                float x[6];
+                rows.load(row_base + i, (size_t)hh * DH + j, HALF, HD, own, x);
+                const float q1 = x[0], q2 = x[1], k1 = x[2], k2 = x[3], v1 = x[4], v2 = x[5];
                 qa = (q1 * c - q2 * s) * scale;
                 qc = (q2 * c + q1 * s) * scale;
                 const uint16_t kb1 = f32_to_bf16_bits(k1 * c - k2 * s);
@@ -347,7 +371,6 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
         if (p == 0) top_m[m] = mstar;
     }
     __syncthreads();
-    const int KS = H * DH / 32;
     constexpr int kPart = 8 * DW + 16;            // floats of a partial result: [8][DW] sums, 8 maxima, 8 denominators
     const size_t group = pair * DS + ds;
     float *mine = KSP > 1 ? a.partials + (group * KSP + ks) * kPart : nullptr;
@@ -377,11 +400,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
             }
             continue;
         }
-        uint16_t t3[kTerms];
-        split3(num / den, t3);
-        const int row = row_base + m, k = hh * DH + dim0 + dd;
-#pragma unroll
-        for (int t = 0; t < kTerms; ++t) ((uint16_t *)a.xout)[xpack_index(row, k, KS, t)] = t3[t];
+        out_rows.store(row_base + m, hh * DH + dim0 + dd, num / den);
     }
     if (KSP > 1) {
         __shared__ int is_last;
@@ -389,8 +408,8 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
         __syncthreads();
         if (tid == 0) {
             const unsigned ticket = __hip_atomic_fetch_add(a.arrive + group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            is_last = ticket == (unsigned)(KSP - 1);
-            if (is_last) __hip_atomic_store(a.arrive + group, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+            is_last = (COUNTS_ON ? ticket % (unsigned)KSP : ticket) == (unsigned)(KSP - 1);
+            if (is_last && !COUNTS_ON) __hip_atomic_store(a.arrive + group, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
         }
         __syncthreads();
         if (!is_last) return;
@@ -414,11 +433,7 @@ __device__ __forceinline__ void attention_core(const AttnArgs &a, const int hh, 
                 den += wg * pl[p];
                 num += wg * po[p];
             }
-            uint16_t t3[kTerms];
-            split3(num / den, t3);
-            const int row = row_base + m, k = hh * DH + dim0 + dd;
-#pragma unroll
-            for (int t = 0; t < kTerms; ++t) ((uint16_t *)a.xout)[xpack_index(row, k, KS, t)] = t3[t];
+            out_rows.store(row_base + m, hh * DH + dim0 + dd, num / den);
         }
     }
 }

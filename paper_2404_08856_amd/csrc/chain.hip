@@ -1,0 +1,431 @@
+// All layers of a small decoder, up to 5 rows, in one launch.
+//
+// One projection or attention of a small model lasts as long as a launch: 63 launches of 3.3 to 6 us made a step of the 12-layer
+// draft.  Here every (layer, stage, one or two tiles) is a workgroup of one grid, in the order of the data: QKV, attention, O, gate|up, down of
+// layer 0, then of layer 1, and so on.  A workgroup brings its weights (or cached keys and values) into registers, waits for the
+// vector it works on, and leaves its columns to the next stage.  It only ever waits for workgroups with a lower index.  Workgroups start in the
+// order of their index on each XCD, so the unfinished one with the lowest index runs or is the next to run there, whatever later
+// ones hold: the launch ends.  Later stages' workgroups that are resident already have their weights by the time their turn comes.
+// (Waits are bounded all the same, as in the fused QKV + attention kernel.)
+//
+// Between two stages a value travels with its proof of arrival: 8-byte words, stored and loaded whole at device scope, that hold the
+// value and the number of the layer pass (a float32 and the number, or the three bf16 terms and 16 bits of it).
+// A consumer loads the words until the number fits.  That is one trip through memory per stage, where data behind a counter takes three (stores
+// acknowledged, counter, data).  Words of one line come from one workgroup: parts of a line from several are merged one after the other (a line of
+// sums of squares, a word from each tile, cost 1.2 us a stage, so the consumers work out 1 / rms themselves).
+//
+// A word's buffer is used again by the next layer.  Nobody can be late: whoever writes a stage's words of layer l + 1 has waited for words that
+// depend on every workgroup of the following stage of layer l, each of which had read all its words before it wrote.  The number of a pass
+// counts layers over all launches with the same count of rows, each count has buffers of its own, and every launch writes
+// all their words: a word holds this pass's number or the one before, so 16 bits are plenty.  The number comes
+// from device memory (chain_input_kernel counts it), so that a captured launch can be replayed.
+//
+// Bound by the stages' latency, about 2.4 us each (12-layer draft, 66 positions, from the last word written to the last word written: QKV 1.9, attention
+// 2.6, O 2.0, gate|up 2.3, down 3.0).  Whole draft step, one by one / in one launch, 12-layer draft: 1 sequence, 66 cached positions 249 / 160 us,
+// 500 274 / 181, 2000 375 / 204; 3 sequences, 640 310 / 253; 5 sequences, 66 289 / 250, 2000 372 / 300; 4-layer draft: 1 sequence 112 / 81 and 178 / 100,
+// 4 sequences, 1472 171 / 124.
+#include <algorithm>
+
+#include "attention_core.h"
+#include "gemm_core.h"
+
+namespace spd {
+
+typedef unsigned long long u64;
+
+constexpr int kChainWaves = 8, kChainThreads = kChainWaves * 64;
+constexpr int kChainTiles = 2;   // tiles per workgroup of QKV and gate|up
+
+struct ChainKernelArgs {
+    ChainArgs c;
+    int KSd, KShd, KSf, n_qkv, n_att, n_gu, per_layer;     // K-steps; workgroups per stage (O and down: d / 16) and layer
+    u64 *H1, *H2, *Q, *A, *Fw;                              // words of this count of rows: h before QKV and before gate|up (float32), q | k | v
+                                                            // (float32), attention's result and the activations (terms)
+    const unsigned *pass;                                   // number of this launch's first layer pass
+    unsigned *pass_next;                                    // number of its last one
+};
+
+__device__ __forceinline__ u64 load_word(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_word(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ u64 float_word(float x, unsigned pass) { return (u64)pass << 32 | __float_as_uint(x); }
+__device__ __forceinline__ float word_float(u64 w) { return __uint_as_float((unsigned)w); }
+__device__ __forceinline__ bool float_there(u64 w, unsigned pass) { return (unsigned)(w >> 32) == pass; }
+__device__ __forceinline__ u64 terms_word(float x, unsigned pass) {
+    uint16_t t[kTerms];
+    split3(x, t);
+    return (u64)(pass << 16 | t[2]) << 32 | (unsigned)t[1] << 16 | t[0];
+}
+__device__ __forceinline__ bool terms_there(u64 w, unsigned pass) { return (unsigned)(w >> 48) == (pass & 0xffffu); }
+
+// polls of one wait; after `limit` of them (or once another wait has given up) it is over, whatever has arrived
+struct Patience {
+    unsigned limit, n = 0;
+    int *abort_flag;
+    __device__ __forceinline__ Patience(const ChainArgs &c) : limit(c.spin_limit), abort_flag(c.abort_flag) {}
+    __device__ __forceinline__ bool over() {
+        if (++n > limit) {                                  // never in a healthy run: let everything drain
+            __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return true;
+        }
+        return (n & 1023) == 0 && __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    }
+};
+
+// q, k and v from words
+struct WordRows {
+    const u64 *q;
+    unsigned pass;
+    const ChainArgs &c;
+    __device__ __forceinline__ void load(int row, size_t col, size_t half, size_t hd, bool, float (&x)[6]) const {
+        const u64 *p = q + (size_t)row * 3 * hd + col;
+        u64 w[6];
+        Patience patience(c);
+        while (true) {
+            bool there = true;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) w[i] = load_word(p + (i >> 1) * hd + (i & 1) * half);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) there = there && float_there(w[i], pass);
+            if (there || patience.over()) break;
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) x[i] = word_float(w[i]);
+    }
+};
+struct WordsOut {
+    u64 *x;
+    int K;
+    unsigned pass;
+    __device__ __forceinline__ void store(int row, int k, float y) const { store_word(x + (size_t)row * K + k, terms_word(y, pass)); }
+};
+
+enum ChainStage { CH_QKV = 0, CH_ATT, CH_O, CH_GU, CH_DOWN };
+
+// The row of pair p of values, `per` pairs a row
+__device__ __forceinline__ int row_of(int p, int per) { return (p >= per) + (p >= 2 * per) + (p >= 3 * per) + (p >= 4 * per); }
+
+// Pairs of input values base, base + kChainThreads, ... (P of them, all loads of a look under way together): waits for their words and puts
+// three terms of each value into LDS in operand order.
+template <int P>
+struct Pairs {
+    const u64 *at[P];
+    int slot[P];                                            // of xs, in 16-bit units
+    bool mine[P], padding[P];
+    // pairs beyond the last one look at the last one's words; columns beyond K (which is even) are zero
+    __device__ __forceinline__ Pairs(const u64 *in, int K, int per, int n_pairs, int base, int R) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int p = base + i * kChainThreads, q = min(p, n_pairs - 1), row = row_of(q, per), k = 2 * (q - row * per);
+            mine[i] = p < n_pairs;
+            padding[i] = k >= K;
+            at[i] = in + (size_t)row * K + (padding[i] ? 0 : k);
+            slot[i] = ((k >> 3) * R + row) * (kTerms * 8) + (k & 7);
+        }
+    }
+    template <class There>
+    __device__ __forceinline__ void wait(const ChainArgs &c, There there, u64 (&v)[2 * P]) const {
+        Patience patience(c);
+        while (true) {
+            bool all = true;
+#pragma unroll
+            for (int i = 0; i < P; ++i) { v[2 * i] = load_word(at[i]); v[2 * i + 1] = load_word(at[i] + 1); }
+#pragma unroll
+            for (int i = 0; i < 2 * P; ++i) all &= there(v[i]);
+            if (all || patience.over()) break;
+        }
+    }
+    __device__ __forceinline__ void put(int i, unsigned t0, unsigned t1, unsigned t2, uint16_t *xs) const {
+        if (!mine[i]) return;
+        unsigned *dst = reinterpret_cast<unsigned *>(xs + slot[i]);
+        dst[0] = t0; dst[4] = t1; dst[8] = t2;
+    }
+    // words of three terms
+    __device__ __forceinline__ void take_terms(const ChainArgs &c, unsigned pass, uint16_t *xs) const {
+        u64 v[2 * P];
+        wait(c, [&](u64 w) { return terms_there(w, pass); }, v);
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const unsigned a0 = (unsigned)v[2 * i], a1 = (unsigned)(v[2 * i] >> 32), b0 = (unsigned)v[2 * i + 1], b1 = (unsigned)(v[2 * i + 1] >> 32);
+            const unsigned keep = padding[i] ? 0u : ~0u;
+            put(i, ((a0 & 0xffffu) | b0 << 16) & keep, (a0 >> 16 | (b0 & 0xffff0000u)) & keep, ((a1 & 0xffffu) | b1 << 16) & keep, xs);
+        }
+    }
+    // float words of h: the terms of h * gain, and the sum of squares of each run of 64 pairs, which is of one row (per is a multiple of 64)
+    __device__ __forceinline__ void take_norm(const ChainArgs &c, unsigned pass, const float2 (&gain)[P], int base, uint16_t *xs, float *squares) const {
+        u64 v[2 * P];
+        wait(c, [&](u64 w) { return float_there(w, pass); }, v);
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const float h0 = word_float(v[2 * i]), h1 = word_float(v[2 * i + 1]);
+            uint32_t t[kTerms];
+            split3_pair(h0 * gain[i].x, h1 * gain[i].y, t);
+            put(i, t[0], t[1], t[2], xs);
+            const float sq = wave_sum(h0 * h0 + h1 * h1);
+            if ((threadIdx.x & 63) == 0 && mine[i]) squares[(base + i * kChainThreads) >> 6] = sq;
+        }
+    }
+};
+
+// A launch argument as a value: a choice between two of them is otherwise made between their addresses, which puts all of them in scratch memory
+template <class T>
+__device__ __forceinline__ T *arg(T *p) {
+    asm("" : "+s"(p));
+    return p;
+}
+
+// NT tiles of a projection; K split over the waves, NB K-steps each at most
+template <int NB, int NT, class Gate>
+__device__ __forceinline__ void chain_project(const ChainKernelArgs &a, const int stage, const int l, const int id, const unsigned pass, Gate gate,
+                                              uint16_t *xs, float (*red)[kChainWaves][kGroupRows][16], float *squares) {
+    const ChainArgs &c = a.c;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr bool NORM = NT > 1;                           // QKV, gate|up
+    const int n_d = c.d / 16, R = c.rows;
+    const int KS = NORM ? a.KSd : stage == CH_O ? a.KShd : a.KSf;
+    const int K = NORM ? c.d : stage == CH_O ? c.HD : c.F;
+    const int n_tiles = stage == CH_QKV ? 3 * c.HD / 16 : stage == CH_GU ? c.F / 8 : n_d;
+    const char *w_qkv = arg(c.wqkv), *w_o = arg(c.wo), *w_gu = arg(c.wgu), *w_down = arg(c.wdown);
+    const char *Wb = stage == CH_QKV ? w_qkv : stage == CH_O ? w_o : stage == CH_GU ? w_gu : w_down;
+    const uint4 *W = reinterpret_cast<const uint4 *>(Wb + (size_t)l * c.layer_stride) + lane;
+    const int s0 = KS * w / kChainWaves, ns = KS * (w + 1) / kChainWaves - s0;
+    uint4 wv[NT][NB];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)                            // (beyond the wave's share or the matrix: some block, dropped below)
+#pragma unroll
+        for (int u = 0; u < NB; ++u) wv[t][u] = load_stream(W + ((size_t)min(id * NT + t, n_tiles - 1) * KS + min(s0 + u, KS - 1)) * 64);
+    // epilogue element of this thread: two waves a tile, column en, row em
+    const int en = lane & 15, em = (w & 1) * 4 + (lane >> 4), et = w >> 1, tile = id * NT + et;
+    const bool e_in = et < NT && em < R && tile < n_tiles;
+    const int col = tile * 16 + en;
+    const size_t norm_stride = c.layer_stride / sizeof(float);
+    const float *attn_norm = arg(c.attn_norm), *mlp_norm = arg(c.mlp_norm), *gain = (stage == CH_QKV ? attn_norm : mlp_norm) + l * norm_stride;
+    const bool to_head = stage == CH_DOWN && l + 1 == c.n_layers;
+    float gain_at = 0.f;
+    if (to_head && e_in) gain_at = c.final_norm[col];
+    u64 *h1 = arg(a.H1), *h2 = arg(a.H2), *att = arg(a.A), *act = arg(a.Fw);
+    const u64 *in = stage == CH_QKV ? h1 : stage == CH_O ? att : stage == CH_GU ? h2 : act;
+    const int per = KS * 16, n_pairs = R * per;
+    auto take = [&](auto pairs_, int base) __attribute__((always_inline)) {
+        constexpr int P = decltype(pairs_)::value;
+        const Pairs<P> pairs(in, K, per, n_pairs, base + (int)threadIdx.x, R);
+        if constexpr (NORM) {
+            float2 g[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const int q = min(base + (int)threadIdx.x + i * kChainThreads, n_pairs - 1);
+                g[i] = *reinterpret_cast<const float2 *>(gain + 2 * (q - row_of(q, per) * per));
+            }
+            if (base == 0) gate();
+            pairs.take_norm(c, pass, g, base + (int)threadIdx.x, xs, squares);
+        } else {
+            if (base == 0) gate();
+            pairs.take_terms(c, pass, xs);
+        }
+    };
+    if (n_pairs <= kChainThreads) take(std::integral_constant<int, 1>{}, 0);
+    else if (n_pairs <= 2 * kChainThreads) take(std::integral_constant<int, 2>{}, 0);
+    else
+        for (int base = 0; base < n_pairs; base += 4 * kChainThreads) take(std::integral_constant<int, 4>{}, base);
+    // the residual: one word per epilogue thread, left two stages ago
+    float residual = 0.f;
+    if (!NORM && e_in) {
+        const u64 *p = (stage == CH_O ? h1 : h2) + (size_t)em * c.d + col;
+        Patience patience(c);
+        u64 v;
+        do v = load_word(p); while (!float_there(v, pass) && !patience.over());
+        residual = word_float(v);
+    }
+    if (threadIdx.x < 8) reinterpret_cast<unsigned *>(xs)[KS * 4 * R * kTerms * 4 + (threadIdx.x & 3)] = 0u;      // a fragment of zeros
+    __syncthreads();
+
+    const int r = lane & 15, g = lane >> 4, rc = r % kGroupRows, rt = r / kGroupRows;
+    const bool used = r < 15 && rc < R;
+    const uint4 *xf = reinterpret_cast<const uint4 *>(xs);
+    const int zero = KS * 4 * R * kTerms, mine = (g * R + rc) * kTerms + rt;
+    uint4 b[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) b[u] = xf[used && u < ns ? (s0 + u) * 4 * R * kTerms + mine : zero];
+    f32x4_t acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = mfma_bf16(wv[t][u], b[u], acc[t]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const float4 x = {sum_terms(acc[t][0]), sum_terms(acc[t][1]), sum_terms(acc[t][2]), sum_terms(acc[t][3])};
+        if (r < kGroupRows) *reinterpret_cast<float4 *>(&red[t][w][r][4 * g]) = x;
+    }
+    const int er = min(em, R - 1);
+    float inv = 1.0f;
+    if (NORM && et < NT) {                                  // 1 / rms of row em, its runs in order
+        const int n_runs = per / 64;
+        float sq[8], ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sq[i] = squares[er * n_runs + min(i, n_runs - 1)];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ss += i < n_runs ? sq[i] : 0.f;
+        inv = 1.0f / sqrtf(ss * c.inv_d + c.eps);
+    }
+    __syncthreads();
+    if (et >= NT) return;                                   // two waves finish a tile
+
+    if (stage == CH_GU) {                                   // rows 0..7 of a tile are gate features, rows 8..15 the matching up features
+        float gate_v = 0.f, up_v = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < kChainWaves; ++ww) { gate_v += red[et][ww][er][en & 7]; up_v += red[et][ww][er][8 + (en & 7)]; }
+        gate_v *= inv;
+        up_v *= inv;
+        if (e_in && en < 8) store_word(act + (size_t)em * c.F + tile * 8 + en, terms_word(gate_v / (1.0f + expf(-gate_v)) * up_v, pass));
+        return;
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int ww = 0; ww < kChainWaves; ++ww) sum += red[et][ww][er][en];
+    if (stage == CH_QKV) {
+        if (e_in) store_word(a.Q + (size_t)em * 3 * c.HD + col, float_word(sum * inv, pass));
+        return;
+    }
+    const float h = residual + sum;
+    if (to_head) {                                          // what the LM head's projection reads
+        const float sq = row_sum(e_in ? h * h : 0.f);
+        if (!e_in) return;
+        uint16_t t3[kTerms];
+        split3(h * gain_at, t3);
+#pragma unroll
+        for (int q = 0; q < kTerms; ++q) c.x_final[xpack_index(em, col, a.KSd, q)] = t3[q];
+        if (en == 0) c.ssq_final[(size_t)em * n_d + tile] = sq;
+    } else if (e_in) {
+        store_word((stage == CH_O ? h2 : h1) + (size_t)em * c.d + col, float_word(h, stage == CH_O ? pass : pass + 1));
+    }
+}
+
+// LONG: the cached keys of a head are cut into kChainRuns runs (merged by the last workgroup to arrive) instead of its dimensions into slices of 16, all
+// of which score all keys.
+constexpr int kChainRuns = 4;
+constexpr int chain_slices(int DH, bool LONG) { return LONG ? (DH == 128 ? 2 : 1) : DH / 16; }
+template <int DH, bool LONG>
+__global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs a, AttnArgs at) {
+    constexpr int DS = chain_slices(DH, LONG), KSP = LONG ? kChainRuns : 1, UPI = LONG && DH == 128 ? 1 : kUnitsPerIter;
+    const ChainArgs &c = a.c;
+    extern __shared__ __align__(16) uint16_t xs[];                        // activations as operand fragments: [K-step][lane group][row][term][8]
+    __shared__ __align__(16) float red[kChainTiles][kChainWaves][kGroupRows][16];
+    __shared__ float squares[kGroupRows * 8];               // d <= 1024: at most 8 runs a row
+    const int l = blockIdx.x / a.per_layer;
+    int id = blockIdx.x - l * a.per_layer, stage = CH_QKV;
+    const int n_d = c.d / 16;
+    if (id >= a.n_qkv) { id -= a.n_qkv; stage = CH_ATT;
+        if (id >= a.n_att) { id -= a.n_att; stage = CH_O;
+            if (id >= n_d) { id -= n_d; stage = CH_GU;
+                if (id >= a.n_gu) { id -= a.n_gu; stage = CH_DOWN; } } } }
+    const unsigned pass = *a.pass + (unsigned)l;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.pass_next = *a.pass + (unsigned)c.n_layers - 1;    // (read by later launches only)
+
+    // Workgroups that are here early look at one word now and then, until the stage before the one they wait for has its input
+    auto gate_on = [&](const u64 *word, bool is_float, unsigned p) __attribute__((always_inline)) {
+        if (threadIdx.x == 0) {
+            Patience patience(c);
+            while (true) {
+                const u64 v = load_word(word);
+                if (is_float ? float_there(v, p) : terms_there(v, p)) break;
+                if (patience.over()) break;
+                __builtin_amdgcn_s_sleep(4);
+            }
+        }
+        __syncthreads();
+    };
+    if (stage == CH_ATT) {
+        const int H = at.H, hh = id % H, ds = (id / H) % DS, ks = (id / (H * DS)) % KSP, seq = id / (H * DS * KSP);
+        attention_core<DH, DS, kChainWaves, UPI, 1, KSP, false, false, true>(at, hh, ds, ks, seq, WordRows{a.Q, pass, c}, WordsOut{a.A, c.HD, pass},
+                                                                              [&] { gate_on(a.H1, true, pass); }, (size_t)l * c.kv_stride);
+        return;
+    }
+    auto gate = [&] __attribute__((always_inline)) {
+        const u64 *q = arg(a.Q), *att = arg(a.A), *h2 = arg(a.H2), *act = arg(a.Fw);
+        if (stage != CH_QKV || l > 0) gate_on(stage == CH_QKV ? act : stage == CH_O ? q : stage == CH_GU ? att : h2, stage == CH_O || stage == CH_DOWN, stage == CH_QKV ? pass - 1 : pass);
+    };
+    if (stage == CH_QKV || stage == CH_GU) {
+        if (a.KSd <= 3 * kChainWaves) chain_project<3, kChainTiles>(a, stage, l, id, pass, gate, xs, red, squares);
+        else chain_project<4, kChainTiles>(a, stage, l, id, pass, gate, xs, red, squares);
+    } else {
+        const int KS = stage == CH_O ? a.KShd : a.KSf;
+        if (KS <= 4 * kChainWaves) chain_project<4, 1>(a, stage, l, id, pass, gate, xs, red, squares);
+        else if (KS <= 8 * kChainWaves) chain_project<8, 1>(a, stage, l, id, pass, gate, xs, red, squares);
+        else chain_project<12, 1>(a, stage, l, id, pass, gate, xs, red, squares);
+    }
+}
+
+// Input rows (as input_rows_kernel) into words, and the number of the next layer pass for the chain that follows
+__global__ __launch_bounds__(256) void chain_input_kernel(ChainKernelArgs a, const uint16_t *E, const int32_t *tokens, int M, int token_stride, const float *embeds, int vocab, unsigned *pass_out) {
+    const int row = blockIdx.x, d = a.c.d;
+    const unsigned pass = *a.pass + 1;                      // (the words start at zero, which is no pass's number)
+    if (row == 0 && threadIdx.x == 0) *pass_out = pass;
+    const uint16_t *src_tok = nullptr;
+    if (tokens) src_tok = E + (size_t)min(max(tokens[(size_t)(row / M) * token_stride + row % M], 0), vocab - 1) * d;   // never read outside the table
+    const float *src_row = embeds ? embeds + (size_t)row * d : nullptr;
+    for (int k = threadIdx.x; k < d; k += 256) store_word(a.H1 + (size_t)row * d + k, float_word(src_tok ? bf16_bits_to_f32(src_tok[k]) : src_row[k], pass));
+}
+
+// From how many cached positions of the longest sequence on its keys are cut into runs.  Step of the 12-layer draft, slices / runs: 1 sequence, 300
+// positions 176 / 182 us, 500 179 / 183, 1000 220 / 186; 2 sequences, 300 199 / 205, 1472 275 / 222; 5 sequences, 66 250 / 254, 300 275 / 260; the 4-layer draft: 1
+// sequence, 500 87.2 / 88.3, 1000 106 / 89; 3 sequences, 200 108 / 106.
+static int chain_runs_from(int n_seqs) { return 256 + 256 / n_seqs; }
+// Fragments of the longest input in LDS: beyond this one workgroup per CU is left, whose place is missing (4-layer draft, 5 rows of 84 KiB: 300 cached
+// positions 139 us against 131 one by one; 4 rows of 68 KiB: 110 against 128).
+constexpr size_t kChainLds = 72 * 1024;
+static size_t words_per_row(int d, int HD, int F) { return (size_t)2 * d + 4 * (size_t)HD + F; }
+static size_t chain_lds(int KS, int rows) { return (size_t)KS * rows * 4 * kTerms * 16 + 16; }       // and a fragment of zeros
+
+bool chain_shape_ok(int d, int HD, int F) { return d % 128 == 0 && d <= 1024 && HD <= 3072 && F <= 3072; }
+// results and counters of the runs of up to 5 sequences (a slice's result: [8][dims] sums and 16 statistics)
+static size_t run_bytes(int HD) { return (size_t)kGroupRows * kChainRuns * (8 * HD + 16 * (HD / 32)) * sizeof(float); }
+size_t chain_bytes(int d, int HD, int F) {
+    return 256 + (size_t)kGroupRows * (HD / 32) * sizeof(unsigned) + 256 + run_bytes(HD) + words_per_row(d, HD, F) * sizeof(u64) * (kGroupRows * (kGroupRows + 1) / 2);     // counters; words for 1 .. 5 rows
+}
+
+int chain_rows(int d, int HD, int F) {
+    const int KS = std::max({d, HD, F + 31}) / 32;
+    int rows = chain_shape_ok(d, HD, F) ? kGroupRows : 0;
+    while (rows > 0 && chain_lds(KS, rows) > kChainLds) --rows;
+    return rows;
+}
+bool chain_supported(int d, int HD, int F, int dh) {
+    for (const void *f : {dh == 128 ? (const void *)chain_kernel<128, false> : (const void *)chain_kernel<64, false>,
+                          dh == 128 ? (const void *)chain_kernel<128, true> : (const void *)chain_kernel<64, true>})
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainLds) != hipSuccess) return false;
+    return chain_rows(d, HD, F) > 0;
+}
+
+hipError_t launch_chain(const ChainArgs &c, const AttnArgs &given, int longest, const void *embed_bf16, const int32_t *tokens, int token_stride, const float *embeds, int vocab, hipStream_t stream) {
+    AttnArgs t = given;
+    if (c.rows < 1 || c.rows > chain_rows(c.d, c.HD, c.F) || t.M < 1 || t.M * t.n_seqs != c.rows || t.m0 != 0 || t.Mq != t.M) return hipErrorInvalidValue;
+    if ((t.dh != 64 && t.dh != 128) || t.H * t.dh != c.HD || (t.v_stride % 32) != 0 || t.v_stride < t.max_positions || t.M > t.max_positions) return hipErrorInvalidValue;
+    if ((!tokens) == (!embeds) || token_stride < t.M || c.n_layers < 1 || c.d % 32 || c.HD % 32 || c.F % 8 || c.layer_stride % 256) return hipErrorInvalidValue;
+    const bool runs = longest >= chain_runs_from(t.n_seqs);
+    ChainKernelArgs k;
+    k.c = c;
+    k.KSd = c.d / 32; k.KShd = c.HD / 32; k.KSf = (c.F + 31) / 32;
+    k.n_qkv = (3 * c.HD / 16 + kChainTiles - 1) / kChainTiles; k.n_att = t.n_seqs * t.H * chain_slices(t.dh, runs) * (runs ? kChainRuns : 1); k.n_gu = (c.F / 8 + kChainTiles - 1) / kChainTiles;
+    k.per_layer = k.n_qkv + k.n_att + k.n_gu + 2 * (c.d / 16);
+    unsigned *count = (unsigned *)c.words + 2 * (c.rows - 1);            // number of the last pass, and of this launch's first one
+    t.arrive = (unsigned *)((char *)c.words + 256);
+    t.partials = (float *)((char *)c.words + 512 + (size_t)kGroupRows * (c.HD / 32) * sizeof(unsigned) / 256 * 256);
+    u64 *p = (u64 *)((char *)t.partials + run_bytes(c.HD)) + words_per_row(c.d, c.HD, c.F) * (c.rows * (c.rows - 1) / 2);
+    auto take = [&](size_t per_row) { u64 *q = p; p += per_row * c.rows; return q; };
+    k.H1 = take(c.d); k.H2 = take(c.d); k.Q = take(3 * c.HD); k.A = take(c.HD); k.Fw = take(c.F);
+    k.pass = count;
+    k.pass_next = nullptr;
+    hipLaunchKernelGGL(chain_input_kernel, dim3(c.rows), dim3(256), 0, stream, k, (const uint16_t *)embed_bf16, tokens, t.M, token_stride, embeds, vocab, count + 1);
+    k.pass = count + 1;
+    k.pass_next = count;
+    const size_t lds = chain_lds(std::max({k.KSd, k.KShd, k.KSf}), c.rows);
+    const dim3 grid((unsigned)k.per_layer * c.n_layers), block(kChainThreads);
+    if (t.dh == 128 && runs) hipLaunchKernelGGL((chain_kernel<128, true>), grid, block, lds, stream, k, t);
+    else if (t.dh == 128) hipLaunchKernelGGL((chain_kernel<128, false>), grid, block, lds, stream, k, t);
+    else if (runs) hipLaunchKernelGGL((chain_kernel<64, true>), grid, block, lds, stream, k, t);
+    else hipLaunchKernelGGL((chain_kernel<64, false>), grid, block, lds, stream, k, t);
+    return hipGetLastError();
+}
+
+}  // namespace spd

@@ -150,6 +150,26 @@ struct QkvAttnArgs {
 bool qkv_attention_supported(int K, int H, int dh, int rows, int n_seqs, int M);
 hipError_t launch_qkv_attention(const QkvAttnArgs &a, hipStream_t stream);
 
+// ---- all layers of a small model in one launch, few rows (chain.hip) ---------------
+struct ChainArgs {
+    const char *wqkv, *wo, *wgu, *wdown;                 // packed matrices of layer 0; layer l is layer_stride bytes behind (a multiple of 256)
+    const float *attn_norm, *mlp_norm, *final_norm;      // the first two with the same stride
+    size_t layer_stride, kv_stride;
+    int n_layers, rows, d, HD, F;
+    float eps, inv_d;
+    void *words;              // chain_bytes of scratch, zero before the first launch and nobody else's
+    uint16_t *x_final;        // packed (h * final_norm) and its sums of squares [rows][d / 16]: the LM head's input
+    float *ssq_final;
+    unsigned spin_limit;      // as in QkvAttnArgs
+    int *abort_flag;
+};
+bool chain_shape_ok(int d, int HD, int F);
+int chain_rows(int d, int HD, int F);                   // rows of a launch at most; 0: none
+size_t chain_bytes(int d, int HD, int F);
+bool chain_supported(int d, int HD, int F, int dh);     // on this device; prepares the kernel
+// at: k_cache, v_cache of layer 0; qkv, xout, slices, partials, arrive: unused; longest: as for launch_attention
+hipError_t launch_chain(const ChainArgs &c, const AttnArgs &at, int longest, const void *embed_bf16, const int32_t *tokens, int token_stride, const float *embeds, int vocab, hipStream_t stream);
+
 // ---- prefill: many rows of one sequence per pass (prefill.hip) ----------------------
 constexpr int kPrefillRows = 2048;   // rows per pass at most
 // Runs of at least this many rows take these kernels, shorter ones the batched verify path.  Measured (us per call,

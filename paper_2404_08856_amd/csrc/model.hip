@@ -51,7 +51,7 @@ struct Layout {                    // byte offsets inside the three buffers
     size_t kv_layer_stride, kv_k_bytes, kv_v_bytes, kv_total;
     int v_stride;
     // workspace
-    size_t h, qkv, xn, xo, xf, rope, logits, ssq_a, ssq_b, d_lens, d_error, qa_count, qa_abort, part, arrive, zero;
+    size_t h, qkv, xn, xo, xf, rope, logits, ssq_a, ssq_b, d_lens, d_error, qa_count, qa_abort, part, arrive, zero, chain;
     size_t ph, pqkv, pxn, pxo, pxf, pssq_a, pssq_b, ppart;      // prefill passes of up to prefill_rows rows
     int prefill_rows, pssq_ld;
     size_t ws_total;
@@ -118,6 +118,7 @@ void make_layout(const spd_model_config &c, Layout &L) {
     L.part = take(pb);
     L.arrive = take((size_t)kBatchMaxTileGroups * 4);
     L.zero = take(1024);
+    L.chain = chain_shape_ok(d, HD, F) ? take(chain_bytes(d, HD, F)) : 0;
     // prefill: activations of one pass, whole row tiles of 16 rows (a workgroup tile may reach beyond the last one: the kernel
     // clamps the row tiles that it reads and writes no row that is not there)
     L.prefill_rows = std::min((int)kPrefillRows, c.max_positions);
@@ -165,6 +166,13 @@ GemmTuning default_tuning(int N, int K) {
 
 }  // namespace
 
+// Bytes of a layer's packed matrices, and up to where a model counts as small: a layer fits the L2s (8 x 4 MiB) next to everything else.
+static size_t layer_weight_bytes(const spd_model_config &c) {
+    const int d = c.d_model, HD = c.n_heads * c.head_dim, F = c.d_ffn;
+    return packed_matrix_bytes(3 * HD, d) + packed_matrix_bytes(d, HD) + packed_matrix_bytes(2 * F, d) + packed_matrix_bytes(d, F);
+}
+constexpr size_t kSmallLayer = (size_t)26 << 20;
+
 struct spd_model {
     spd_model_config cfg;
     Layout L;
@@ -174,6 +182,7 @@ struct spd_model {
     bool dev_lens = false;             // the kernels read the lengths from device memory (ws + L.d_lens)
     bool fuse_qa = false;              // QKV projection + attention as one kernel where the shape allows it
     bool fuse_qa2 = false;             // ... also for 6..8 rows of one sequence
+    int chain = 0, chain_ok = 0;       // rows up to which all layers are one launch: as it is, and what shape and device allow
     bool fuse_qa_ok = false, fuse_qa2_ok = false;   // what the shape and the device allow (checked at creation)
     int attn_slices = 0;               // workgroups per head of the stand-alone attention kernel (0: chosen by batch size)
     unsigned spin_limit = 1u << 22;    // polls before a wait between workgroups gives up
@@ -342,6 +351,8 @@ int32_t spd_model_create(const spd_model_config *cfg, const spd_weights *w, void
     m->fuse_qa2_ok = m->fuse_qa_ok && qkv_attention_supported(cfg->d_model, cfg->n_heads, cfg->head_dim, 8, 1, 8);
     m->fuse_qa = m->fuse_qa_ok;
     m->fuse_qa2 = m->fuse_qa2_ok;
+    // (a layer has to fit the L2s: with more weights a launch per projection keeps the memory busier)
+    m->chain = m->chain_ok = layer_weight_bytes(*cfg) <= kSmallLayer && chain_supported(d, HD, F, cfg->head_dim) ? chain_rows(d, HD, F) : 0;
     *out = m;
     return SPD_OK;
 }
@@ -372,6 +383,10 @@ int32_t spd_model_set_tuning(spd_model *m, const spd_tuning *t) {
         gt[i]->no_batch = t->batch_kernel == 2 ? 1 : 0;
         gt[i]->force_batch = t->batch_kernel == 1 ? 1 : 0;
     }
+    const spd_tuning plain{};
+    spd_tuning chosen = *t;
+    chosen.wait_spin_limit = 0;
+    m->chain = memcmp(&chosen, &plain, sizeof(plain)) == 0 ? m->chain_ok : 0;     // any choice among the separate kernels means those
     m->fuse_qa = t->separate_qkv_attention ? false : m->fuse_qa_ok;
     m->fuse_qa2 = t->separate_qkv_attention ? false : m->fuse_qa2_ok;
     m->attn_slices = t->attention_slices;
@@ -455,6 +470,41 @@ int32_t spd_kv_get_len(const spd_model *m, int32_t *len, int32_t n_seqs) {
 
 namespace {
 
+// Final norm (folded in) and LM head on the packed rows that the last layer left
+int32_t run_lm_head(spd_model *m, int rows, float *logits_out, hipStream_t st) {
+    const spd_model_config &c = m->cfg;
+    const Layout &L = m->L;
+    GemmArgs g{};
+    g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero;
+    g.W = m->packed + L.lm_head; g.X = m->ws + L.xn; g.N = c.vocab; g.K = c.d_model; g.rows = rows; g.Y = logits_out; g.ldy = c.vocab;
+    g.ssq_in = (float *)(m->ws + L.ssq_b); g.ssq_in_parts = c.d_model / 16; g.eps = c.rms_eps;
+    PROF_GEMM(PK_LM_HEAD, launch_gemm(g, EPI_STORE, m->t_lm, st));
+    return SPD_OK;
+}
+
+// All layers in one launch (small models, up to 5 rows); at: lengths as for run_layers
+int32_t run_chain(spd_model *m, const AttnArgs &lens, int seq0, int n_seqs, int M, int longest, const int32_t *tokens, int token_stride, const float *embeds, hipStream_t st) {
+    const spd_model_config &c = m->cfg;
+    const Layout &L = m->L;
+    ChainArgs a{};
+    AttnArgs at = lens;
+    at.rope = (const float *)(m->ws + L.rope);
+    at.k_cache = m->kv + (size_t)seq0 * c.n_heads * c.max_positions * c.head_dim * 2;
+    at.v_cache = m->kv + align_up(L.kv_k_bytes, 256) + (size_t)seq0 * c.n_heads * c.head_dim * L.v_stride * 2;
+    at.n_seqs = n_seqs; at.M = at.Mq = M; at.m0 = 0; at.H = c.n_heads; at.dh = c.head_dim; at.max_positions = c.max_positions; at.v_stride = L.v_stride;
+    a.wqkv = m->packed + L.wqkv[0]; a.wo = m->packed + L.wo[0]; a.wgu = m->packed + L.wgu[0]; a.wdown = m->packed + L.wdown[0];
+    a.attn_norm = (const float *)(m->packed + L.attn_norm[0]); a.mlp_norm = (const float *)(m->packed + L.mlp_norm[0]); a.final_norm = (const float *)(m->packed + L.final_norm);
+    a.layer_stride = c.n_layers > 1 ? L.wqkv[1] - L.wqkv[0] : 0;             // every layer takes the same sizes, each a multiple of 256
+    a.kv_stride = L.kv_layer_stride;
+    a.n_layers = c.n_layers; a.rows = n_seqs * M; a.d = c.d_model; a.HD = c.n_heads * c.head_dim; a.F = c.d_ffn;
+    a.eps = c.rms_eps; a.inv_d = 1.0f / (float)c.d_model;
+    a.words = m->ws + L.chain;
+    a.x_final = (uint16_t *)(m->ws + L.xn); a.ssq_final = (float *)(m->ws + L.ssq_b);
+    a.spin_limit = m->spin_limit; a.abort_flag = (int *)(m->ws + L.qa_abort);
+    HIP_TRY(launch_chain(a, at, longest, m->packed + L.embed, tokens, token_stride, embeds, c.vocab, st));
+    return SPD_OK;
+}
+
 // Layers first .. of the decoder for M new rows of each of sequences seq0 .. seq0 + n_seqs - 1, and the LM head (logits_out may be NULL).
 // The input rows are in place: h, packed (h * attn_norm[first]) and their sums of squares (one part per row); `at` has the
 // KV lengths; longest: the longest of them as far as the host can tell.  kv_cached (a prompt's last row): layer
@@ -463,7 +513,7 @@ int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, 
     const spd_model_config &c = m->cfg;
     const Layout &L = m->L;
     const int rows = n_seqs * M;
-    const int d = c.d_model, HD = c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
+    const int d = c.d_model, HD = c.n_heads * c.head_dim, F = c.d_ffn;
     float *h = (float *)(m->ws + L.h);
     float *qkv = (float *)(m->ws + L.qkv);
     void *xn = m->ws + L.xn, *xo = m->ws + L.xo, *xf = m->ws + L.xf;
@@ -481,9 +531,8 @@ int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, 
     at.partials = (float *)(m->ws + L.part); at.arrive = (unsigned *)(m->ws + L.arrive);
 
     // Small models, few rows: a projection lasts about as long as its first loads take, so the weights of the next ones are
-    // brought into L2 meanwhile.  A layer has to fit the L2s (8 x 4 MiB) next to everything else.
-    const size_t layer_bytes = packed_matrix_bytes(3 * HD, d) + packed_matrix_bytes(d, HD) + packed_matrix_bytes(2 * F, d) + packed_matrix_bytes(d, F);
-    const bool prefetch = rows <= 2 * kGroupRows && layer_bytes <= ((size_t)26 << 20);
+    // brought into L2 meanwhile.
+    const bool prefetch = rows <= 2 * kGroupRows && layer_weight_bytes(c) <= kSmallLayer;
     const bool fused = m->fuse_qa && n_seqs == 1 && (rows <= kGroupRows || (rows <= 8 && m->fuse_qa2));   // shapes checked at creation
     for (int l = first; l < c.n_layers; ++l) {
         // RMSNorm is folded into the projections: the producer of h (input rows / O / down
@@ -537,14 +586,7 @@ int32_t run_layers(spd_model *m, int first, AttnArgs &at, int seq0, int n_seqs, 
         g.gain_next = gain_of(l + 1 < c.n_layers ? L.attn_norm[l + 1] : L.final_norm); g.Xnext = xn; g.ssq_out = ssq_b;
         PROF_GEMM(PK_DOWN, launch_gemm(g, EPI_RESIDUAL, m->t_down, st));
     }
-    if (logits_out) {
-        GemmArgs g{};
-        g.batch_partials = (float *)(m->ws + L.part); g.batch_arrive = (unsigned *)(m->ws + L.arrive); g.batch_zero = m->ws + L.zero;
-        g.W = m->packed + L.lm_head; g.X = xn; g.N = V; g.K = d; g.rows = rows; g.Y = logits_out; g.ldy = V;
-        g.ssq_in = ssq_b; g.ssq_in_parts = d_tiles; g.eps = c.rms_eps;
-        PROF_GEMM(PK_LM_HEAD, launch_gemm(g, EPI_STORE, m->t_lm, st));
-    }
-    return SPD_OK;
+    return logits_out ? run_lm_head(m, rows, logits_out, st) : SPD_OK;
 }
 
 // One decoder forward over M new rows for sequences seq0 .. seq0 + n_seqs - 1.
@@ -575,6 +617,14 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
         at.d_error = (int32_t *)(m->ws + L.d_error);
     }
     const int d = c.d_model;
+    if (rows <= m->chain && !m->prof_on) {      // (traced one by one: the launches of a layer)
+        int32_t rc = run_chain(m, at, seq0, n_seqs, M, longest, tokens, tokens ? token_stride : M, embeds, st);
+        if (rc == SPD_OK && logits_out) rc = run_lm_head(m, rows, logits_out, st);
+        if (rc) return rc;
+        if (m->dev_lens) HIP_TRY(launch_lens_add((int32_t *)(m->ws + L.d_lens) + seq0, n_seqs, M, st));
+        for (int s = 0; s < n_seqs; ++s) m->lens[seq0 + s] = std::min(m->lens[seq0 + s] + M, c.max_positions);
+        return SPD_OK;
+    }
     // input rows -> h, packed (h * attn_norm[0]) and sum of squares (one part per row)
     PROF_TRY(PK_EMBED, launch_input_rows(m->packed + L.embed, tokens, M, tokens ? token_stride : M, embeds, rows, d, c.vocab,
                                          (const float *)(m->packed + L.attn_norm[0]), (float *)(m->ws + L.h), m->ws + L.xn, (float *)(m->ws + L.ssq_b), st));

@@ -105,7 +105,7 @@ __global__ __launch_bounds__((NG == 1 ? kAttnWaves : kQaGemmWaves) * 64) void qk
         }
         __syncthreads();
     };
-    attention_core<DH, S, TW, kUnitsPerIter, true, NG, 1, false, false>(a.at, hh, ds, 0, 0, wait_head);
+    attention_core<DH, S, TW, kUnitsPerIter, NG, 1, false, false, false>(a.at, hh, ds, 0, 0, PlainRows<true>{a.at.qkv}, PackedOut{(uint16_t *)a.at.xout, H * DH / 32}, wait_head);
 }
 
 bool qkv_attention_supported(int K, int H, int dh, int rows, int n_seqs, int M) {
