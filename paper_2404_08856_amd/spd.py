@@ -102,8 +102,13 @@ def _check(rc):
         raise SpdError(rc, spd_last_error())
 
 
+# Pointers go to ctypes as plain integers, and the stream without a Python object around it: an accept call of one sequence was 12 us of this
+# and one launch, more than its kernel takes.
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_current_device())
 
 
 def _ptr(t, dtype=None):
@@ -112,13 +117,13 @@ def _ptr(t, dtype=None):
     assert t.is_cuda and t.is_contiguous(), "device, contiguous tensors only"
     if dtype is not None:
         assert t.dtype == dtype, f"expected {dtype}, got {t.dtype}"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _raw(t, dtype):
     """Data pointer of a device tensor that may be a strided view into a larger buffer."""
     assert t.is_cuda and t.dtype == dtype
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def make_config(shape, max_seqs, max_positions):
@@ -150,7 +155,7 @@ class Model:
         def arr(key, dtype):
             a = (ctypes.c_void_p * L)()
             for l, lw in enumerate(weights["layers"]):
-                a[l] = _ptr(lw[key], dtype).value
+                a[l] = _ptr(lw[key], dtype)
             return a
 
         bf, f32 = torch.bfloat16, torch.float32
