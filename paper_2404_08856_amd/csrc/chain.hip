@@ -16,14 +16,14 @@
 //
 // A word's buffer is used again by the next layer.  Nobody can be late: whoever writes a stage's words of layer l + 1 has waited for words that
 // depend on every workgroup of the following stage of layer l, each of which had read all its words before it wrote.  The number of a pass
-// counts layers over all launches with the same count of rows, each count has buffers of its own, and every launch writes
-// all their words: a word holds this pass's number or the one before, so 16 bits are plenty.  The number comes
-// from device memory (chain_input_kernel counts it), so that a captured launch can be replayed.
+// counts layers over all launches with the same count of rows, each count has buffers of its own, and every pass writes all
+// words of three terms: one holds this pass's number or the one before, so 16 bits are plenty.  The number comes
+// from device memory, where each launch leaves it for the next, so that a captured launch can be replayed.
 //
-// Bound by the stages' latency, about 2.4 us each (12-layer draft, 66 positions, from the last word written to the last word written: QKV 1.9, attention
-// 2.6, O 2.0, gate|up 2.3, down 3.0).  Whole draft step, one by one / in one launch, 12-layer draft: 1 sequence, 66 cached positions 249 / 160 us,
-// 500 274 / 181, 2000 375 / 204; 3 sequences, 640 310 / 253; 5 sequences, 66 289 / 250, 2000 372 / 300; 4-layer draft: 1 sequence 112 / 81 and 178 / 100,
-// 4 sequences, 1472 171 / 124.
+// Bound by the stages' latency, about 2.3 us each (12-layer draft, 66 positions, from the last word written to the last word written: QKV 1.9, attention
+// 2.6, O 2.0, gate|up 2.3, down 3.0).  Whole draft step, one by one / in one launch, 12-layer draft: 1 sequence, 66 cached positions 249 / 155 us,
+// 640 281 / 179, 2000 375 / 200; 3 sequences, 640 310 / 234; 5 sequences, 66 289 / 231, 640 320 / 257; 4-layer draft: 1 sequence 112 / 75 and 178 / 94,
+// 4 sequences, 1472 171 / 119.
 #include <algorithm>
 
 #include "attention_core.h"
@@ -41,12 +41,42 @@ struct ChainKernelArgs {
     int KSd, KShd, KSf, n_qkv, n_att, n_gu, per_layer;     // K-steps; workgroups per stage (O and down: d / 16) and layer
     u64 *H1, *H2, *Q, *A, *Fw;                              // words of this count of rows: h before QKV and before gate|up (float32), q | k | v
                                                             // (float32), attention's result and the activations (terms)
-    const unsigned *pass;                                   // number of this launch's first layer pass
-    unsigned *pass_next;                                    // number of its last one
+    unsigned *pass, *done;                                  // number of the last pass of the launch before; workgroups of this launch's last stage that are through
+    const uint16_t *E;                                      // input rows: of the embedding table, by token, or
+    const int32_t *tokens;
+    const float *embeds;                                    // as they are
+    int M, token_stride, vocab;
 };
+
+// Columns k and k + 1 of input row `row`
+__device__ __forceinline__ float2 input_pair(const ChainKernelArgs &a, int row, int k) {
+    if (a.embeds) return *reinterpret_cast<const float2 *>(a.embeds + (size_t)row * a.c.d + k);
+    const int token = min(max(a.tokens[(size_t)(row / a.M) * a.token_stride + row % a.M], 0), a.vocab - 1);     // never read outside the table
+    const uint32_t two = *reinterpret_cast<const uint32_t *>(a.E + (size_t)token * a.c.d + k);
+    return float2{bf16_lo(two), bf16_hi(two)};
+}
 
 __device__ __forceinline__ u64 load_word(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_word(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Two words next to each other per address (16-byte aligned), all of them on their way together; each word is whole, the pair need not be.  As
+// inline assembly for the scope.  With two 8-byte loads per pair a step of the 12-layer draft took 159 us instead of 156.5, with 5 rows 249 instead of 231.
+typedef __attribute__((ext_vector_type(2))) u64 u64x2_t;
+__device__ __forceinline__ void load_words(const u64 *const (&at)[1], u64 (&v)[2]) {
+    u64x2_t a;
+    asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(a) : "v"(at[0]) : "memory");
+    v[0] = a.x; v[1] = a.y;
+}
+__device__ __forceinline__ void load_words(const u64 *const (&at)[2], u64 (&v)[4]) {
+    u64x2_t a, b;
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(a), "=&v"(b) : "v"(at[0]), "v"(at[1]) : "memory");
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+__device__ __forceinline__ void load_words(const u64 *const (&at)[4], u64 (&v)[8]) {
+    u64x2_t a, b, c, d;
+    asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\tglobal_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)" : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d) : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]) : "memory");
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y; v[4] = c.x; v[5] = c.y; v[6] = d.x; v[7] = d.y;
+}
 __device__ __forceinline__ u64 float_word(float x, unsigned pass) { return (u64)pass << 32 | __float_as_uint(x); }
 __device__ __forceinline__ float word_float(u64 w) { return __uint_as_float((unsigned)w); }
 __device__ __forceinline__ bool float_there(u64 w, unsigned pass) { return (unsigned)(w >> 32) == pass; }
@@ -127,8 +157,7 @@ struct Pairs {
         Patience patience(c);
         while (true) {
             bool all = true;
-#pragma unroll
-            for (int i = 0; i < P; ++i) { v[2 * i] = load_word(at[i]); v[2 * i + 1] = load_word(at[i] + 1); }
+            load_words(at, v);
 #pragma unroll
             for (int i = 0; i < 2 * P; ++i) all &= there(v[i]);
             if (all || patience.over()) break;
@@ -150,13 +179,18 @@ struct Pairs {
             put(i, ((a0 & 0xffffu) | b0 << 16) & keep, (a0 >> 16 | (b0 & 0xffff0000u)) & keep, ((a1 & 0xffffu) | b1 << 16) & keep, xs);
         }
     }
-    // float words of h: the terms of h * gain, and the sum of squares of each run of 64 pairs, which is of one row (per is a multiple of 64)
-    __device__ __forceinline__ void take_norm(const ChainArgs &c, unsigned pass, const float2 (&gain)[P], int base, uint16_t *xs, float *squares) const {
+    // float words of h
+    __device__ __forceinline__ void take_floats(const ChainArgs &c, unsigned pass, float2 (&h)[P]) const {
         u64 v[2 * P];
         wait(c, [&](u64 w) { return float_there(w, pass); }, v);
 #pragma unroll
+        for (int i = 0; i < P; ++i) h[i] = float2{word_float(v[2 * i]), word_float(v[2 * i + 1])};
+    }
+    // the terms of h * gain, and the sum of squares of each run of 64 pairs, which is of one row (per is a multiple of 64)
+    __device__ __forceinline__ void put_norm(const float2 (&h)[P], const float2 (&gain)[P], int base, uint16_t *xs, float *squares) const {
+#pragma unroll
         for (int i = 0; i < P; ++i) {
-            const float h0 = word_float(v[2 * i]), h1 = word_float(v[2 * i + 1]);
+            const float h0 = h[i].x, h1 = h[i].y;
             uint32_t t[kTerms];
             split3_pair(h0 * gain[i].x, h1 * gain[i].y, t);
             put(i, t[0], t[1], t[2], xs);
@@ -215,8 +249,18 @@ __device__ __forceinline__ void chain_project(const ChainKernelArgs &a, const in
                 const int q = min(base + (int)threadIdx.x + i * kChainThreads, n_pairs - 1);
                 g[i] = *reinterpret_cast<const float2 *>(gain + 2 * (q - row_of(q, per) * per));
             }
-            if (base == 0) gate();
-            pairs.take_norm(c, pass, g, base + (int)threadIdx.x, xs, squares);
+            float2 h[P];
+            if (stage == CH_QKV && l == 0) {                // the input rows themselves
+#pragma unroll
+                for (int i = 0; i < P; ++i) {
+                    const int q = min(base + (int)threadIdx.x + i * kChainThreads, n_pairs - 1), row = row_of(q, per);
+                    h[i] = input_pair(a, row, 2 * (q - row * per));
+                }
+            } else {
+                if (base == 0) gate();
+                pairs.take_floats(c, pass, h);
+            }
+            pairs.put_norm(h, g, base + (int)threadIdx.x, xs, squares);
         } else {
             if (base == 0) gate();
             pairs.take_terms(c, pass, xs);
@@ -228,7 +272,10 @@ __device__ __forceinline__ void chain_project(const ChainKernelArgs &a, const in
         for (int base = 0; base < n_pairs; base += 4 * kChainThreads) take(std::integral_constant<int, 4>{}, base);
     // the residual: one word per epilogue thread, left two stages ago
     float residual = 0.f;
-    if (!NORM && e_in) {
+    if (!NORM && e_in && stage == CH_O && l == 0) {
+        const float2 two = input_pair(a, em, col & ~1);
+        residual = col & 1 ? two.y : two.x;
+    } else if (!NORM && e_in) {
         const u64 *p = (stage == CH_O ? h1 : h2) + (size_t)em * c.d + col;
         Patience patience(c);
         u64 v;
@@ -319,8 +366,14 @@ __global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs
         if (id >= a.n_att) { id -= a.n_att; stage = CH_O;
             if (id >= n_d) { id -= n_d; stage = CH_GU;
                 if (id >= a.n_gu) { id -= a.n_gu; stage = CH_DOWN; } } } }
-    const unsigned pass = *a.pass + (unsigned)l;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.pass_next = *a.pass + (unsigned)c.n_layers - 1;    // (read by later launches only)
+    const unsigned pass = *a.pass + 1 + (unsigned)l;        // (the words start at zero, which is no pass's number)
+    // Of the last stage's workgroups the last to come by here leaves the number for the next launch: all others have read theirs by then
+    asm volatile("" ::"s"(pass) : "memory");                // (and this one's is in its register)
+    if (stage == CH_DOWN && l + 1 == c.n_layers && threadIdx.x == 0 &&
+        __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)n_d - 1) {
+        __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.pass, pass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 
     // Workgroups that are here early look at one word now and then, until the stage before the one they wait for has its input
     auto gate_on = [&](const u64 *word, bool is_float, unsigned p) __attribute__((always_inline)) {
@@ -338,12 +391,12 @@ __global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs
     if (stage == CH_ATT) {
         const int H = at.H, hh = id % H, ds = (id / H) % DS, ks = (id / (H * DS)) % KSP, seq = id / (H * DS * KSP);
         attention_core<DH, DS, kChainWaves, UPI, 1, KSP, false, false, true>(at, hh, ds, ks, seq, WordRows{a.Q, pass, c}, WordsOut{a.A, c.HD, pass},
-                                                                              [&] { gate_on(a.H1, true, pass); }, (size_t)l * c.kv_stride);
+                                                                              [&] { if (l > 0) gate_on(a.H1, true, pass); }, (size_t)l * c.kv_stride);
         return;
     }
     auto gate = [&] __attribute__((always_inline)) {
         const u64 *q = arg(a.Q), *att = arg(a.A), *h2 = arg(a.H2), *act = arg(a.Fw);
-        if (stage != CH_QKV || l > 0) gate_on(stage == CH_QKV ? act : stage == CH_O ? q : stage == CH_GU ? att : h2, stage == CH_O || stage == CH_DOWN, stage == CH_QKV ? pass - 1 : pass);
+        gate_on(stage == CH_QKV ? act : stage == CH_O ? q : stage == CH_GU ? att : h2, stage == CH_O || stage == CH_DOWN, stage == CH_QKV ? pass - 1 : pass);
     };
     if (stage == CH_QKV || stage == CH_GU) {
         if (a.KSd <= 3 * kChainWaves) chain_project<3, kChainTiles>(a, stage, l, id, pass, gate, xs, red, squares);
@@ -354,17 +407,6 @@ __global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs
         else if (KS <= 8 * kChainWaves) chain_project<8, 1>(a, stage, l, id, pass, gate, xs, red, squares);
         else chain_project<12, 1>(a, stage, l, id, pass, gate, xs, red, squares);
     }
-}
-
-// Input rows (as input_rows_kernel) into words, and the number of the next layer pass for the chain that follows
-__global__ __launch_bounds__(256) void chain_input_kernel(ChainKernelArgs a, const uint16_t *E, const int32_t *tokens, int M, int token_stride, const float *embeds, int vocab, unsigned *pass_out) {
-    const int row = blockIdx.x, d = a.c.d;
-    const unsigned pass = *a.pass + 1;                      // (the words start at zero, which is no pass's number)
-    if (row == 0 && threadIdx.x == 0) *pass_out = pass;
-    const uint16_t *src_tok = nullptr;
-    if (tokens) src_tok = E + (size_t)min(max(tokens[(size_t)(row / M) * token_stride + row % M], 0), vocab - 1) * d;   // never read outside the table
-    const float *src_row = embeds ? embeds + (size_t)row * d : nullptr;
-    for (int k = threadIdx.x; k < d; k += 256) store_word(a.H1 + (size_t)row * d + k, float_word(src_tok ? bf16_bits_to_f32(src_tok[k]) : src_row[k], pass));
 }
 
 // From how many cached positions of the longest sequence on its keys are cut into runs.  Step of the 12-layer draft, slices / runs: 1 sequence, 300
@@ -408,17 +450,14 @@ hipError_t launch_chain(const ChainArgs &c, const AttnArgs &given, int longest, 
     k.KSd = c.d / 32; k.KShd = c.HD / 32; k.KSf = (c.F + 31) / 32;
     k.n_qkv = (3 * c.HD / 16 + kChainTiles - 1) / kChainTiles; k.n_att = t.n_seqs * t.H * chain_slices(t.dh, runs) * (runs ? kChainRuns : 1); k.n_gu = (c.F / 8 + kChainTiles - 1) / kChainTiles;
     k.per_layer = k.n_qkv + k.n_att + k.n_gu + 2 * (c.d / 16);
-    unsigned *count = (unsigned *)c.words + 2 * (c.rows - 1);            // number of the last pass, and of this launch's first one
+    unsigned *count = (unsigned *)c.words + 2 * (c.rows - 1);            // number of the last pass, and workgroups through with it
     t.arrive = (unsigned *)((char *)c.words + 256);
     t.partials = (float *)((char *)c.words + 512 + (size_t)kGroupRows * (c.HD / 32) * sizeof(unsigned) / 256 * 256);
     u64 *p = (u64 *)((char *)t.partials + run_bytes(c.HD)) + words_per_row(c.d, c.HD, c.F) * (c.rows * (c.rows - 1) / 2);
     auto take = [&](size_t per_row) { u64 *q = p; p += per_row * c.rows; return q; };
     k.H1 = take(c.d); k.H2 = take(c.d); k.Q = take(3 * c.HD); k.A = take(c.HD); k.Fw = take(c.F);
-    k.pass = count;
-    k.pass_next = nullptr;
-    hipLaunchKernelGGL(chain_input_kernel, dim3(c.rows), dim3(256), 0, stream, k, (const uint16_t *)embed_bf16, tokens, t.M, token_stride, embeds, vocab, count + 1);
-    k.pass = count + 1;
-    k.pass_next = count;
+    k.pass = count; k.done = count + 1;
+    k.E = (const uint16_t *)embed_bf16; k.tokens = tokens; k.embeds = embeds; k.M = t.M; k.token_stride = token_stride; k.vocab = vocab;
     const size_t lds = chain_lds(std::max({k.KSd, k.KShd, k.KSf}), c.rows);
     const dim3 grid((unsigned)k.per_layer * c.n_layers), block(kChainThreads);
     if (t.dh == 128 && runs) hipLaunchKernelGGL((chain_kernel<128, true>), grid, block, lds, stream, k, t);
