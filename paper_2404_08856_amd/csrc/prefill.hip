@@ -580,7 +580,7 @@ __global__ __launch_bounds__(256) void prefill_append_kernel(PrefillAttnArgs a) 
 // products run next to the other's softmax (1472 rows, 36.2 to 32.4 us).  Heads of 128 come with more workgroups: at 2047 rows three of them per CU
 // (one unit per step, at most 168 registers) take 113 us, two 125 with two units and 131 with one.
 constexpr int kPaBuf = 3;                        // steps in LDS: one in use, one there, one on its way
-constexpr int prefill_step_units(int DH) { return DH == 64 ? 2 : 1; }
+constexpr int prefill_step_units(int DH, bool SPLIT) { return SPLIT || DH == 64 ? 2 : 1; }
 
 // bf16 pairs with an infinite or NaN value replaced by 0
 __device__ __forceinline__ uint32_t finite_pair(uint32_t p) {
@@ -612,10 +612,11 @@ __device__ __forceinline__ float exp_score(float x) {
     return __builtin_fmaf(p, lo * 0.693147180559945f, p);
 }
 
-template <int DH>
-__global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnArgs a) {
+template <int DH, bool SPLIT>
+__global__ __launch_bounds__(256, SPLIT && DH == 128 ? 1 : 2) void prefill_attention_kernel(PrefillAttnArgs a) {
     constexpr int HALF = DH / 2, NC = DH / 32, NDT = DH / 16, BLK = 2 * NC + NDT, PB = BLK / 4;
-    constexpr int U = prefill_step_units(DH);
+    constexpr int U = prefill_step_units(DH, SPLIT);
+    constexpr int QW = SPLIT ? 2 : 4, QUERIES = 16 * QW;         // waves with queries of their own; queries of a workgroup
     __shared__ uint4 S[kPaBuf][U][BLK][64];
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -625,7 +626,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
     const uint16_t *Kc = (const uint16_t *)a.k_cache + (size_t)hh * a.max_positions * DH;
     const uint16_t *Vt = (const uint16_t *)a.v_cache + (size_t)hh * DH * a.v_stride;
     const int k_end = P0 + a.rows - 1;                           // last valid position
-    const int n_units = min(P0 + qt * 64 + 63, k_end) / 32 + 1;  // units any query of this workgroup sees
+    const int n_units = min(P0 + qt * QUERIES + QUERIES - 1, k_end) / 32 + 1;    // units any query of this workgroup sees
 
     // this wave's share of a unit: blocks w, w + 4, ...; 0 .. 2 NC - 1: K (tile ab, chunk c), then V (dim tile)
     const unsigned lds0 = lds_addr(&S[0][0][0][0]);
@@ -647,7 +648,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
             }
         }
     };
-    const int row = qt * 64 + w * 16 + r;                       // this lane's query
+    const int qw = w % QW, kw = w / QW;                         // SPLIT: wave kw of the two with these queries takes unit kw of a step
+    const int row = qt * QUERIES + qw * 16 + r;                 // this lane's query
     // q: RoPE, scale, three terms, as B operand blocks (chunk c: dims 32 c + 8 g .. + 7 of query r)
     uint4 q[NC][kTerms];
     {
@@ -680,7 +682,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
     issue(0, 0);
     issue(U, 1);
 
-    const int q_pos = P0 + row, w_first = P0 + qt * 64 + w * 16, w_last = min(w_first + 15, k_end);
+    const int q_pos = P0 + row, w_first = P0 + qt * QUERIES + qw * 16, w_last = min(w_first + 15, k_end);
     const bool wave_has_rows = w_first <= k_end;
     float m_run = kLowest, l_run = 0.f;
     f32x4_t acc[NDT];
@@ -753,11 +755,11 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         issue(u + 2 * U, nbuf);
-        const bool both = U == 2 && 32 * u + 63 <= w_first && wave_has_rows;    // wave-uniform, like the conditions below
+        const bool both = U == 2 && !SPLIT && 32 * u + 63 <= w_first && wave_has_rows;    // wave-uniform, like the conditions below
         if (both) two_units(S[buf][0], S[buf][U - 1]);
 #pragma unroll
         for (int h = 0; h < U; ++h) {
-            if (!both && wave_has_rows && 32 * (u + h) <= w_last) {
+            if (!both && wave_has_rows && (!SPLIT || h == kw) && 32 * (u + h) <= w_last) {
                 const bool diagonal = 32 * (u + h) + 31 > w_first;         // some key is hidden from some query of the wave
                 f32x4_t sc[2];
                 scores(S[buf][h], sc);
@@ -824,6 +826,26 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     l_run = xor_step<16>(l_run, AddOp());
     l_run = xor_step<32>(l_run, AddOp());
+    if constexpr (SPLIT) {                                       // the two waves' results meet in LDS
+        __syncthreads();                                         // (nobody reads the stages any more)
+        float (*other)[64] = reinterpret_cast<float (*)[64]>(&S[0][0][0][0]) + qw * (4 * NDT + 2);
+        if (kw == 1) {
+#pragma unroll
+            for (int i = 0; i < NDT; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) other[4 * i + v][lane] = acc[i][v];
+            other[4 * NDT][lane] = m_run;
+            other[4 * NDT + 1][lane] = l_run;
+        }
+        __syncthreads();
+        if (kw == 1) return;
+        const float m1 = other[4 * NDT][lane], m = fmaxf(m_run, m1), w0 = exp_score(m_run - m), w1 = exp_score(m1 - m);
+        l_run = l_run * w0 + other[4 * NDT + 1][lane] * w1;
+#pragma unroll
+        for (int i = 0; i < NDT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[i][v] = __builtin_fmaf(acc[i][v], w0, other[4 * i + v][lane] * w1);
+    }
     if (row < a.rows) {
 #pragma unroll
         for (int i = 0; i < NDT; ++i) {
@@ -833,17 +855,29 @@ __global__ __launch_bounds__(256, 2) void prefill_attention_kernel(PrefillAttnAr
     }
 }
 
+// Where few workgroups of 64 queries make a launch, its time is that of the last block of queries, which sees all keys.  With 32 queries per workgroup and two
+// waves for the same 16 (one takes every other unit, the two results are merged at the end) that block is spread over two CUs and its waves
+// go through half as many units each.  Prompt of the 12-layer draft, 64 / 32 queries: 200 rows 726 / 715 us, 700 962 / 917, 1472 1518 / 1435 (attention 32.7 / 25.3 a
+// layer), 2000 1866 / 1780; the 4-layer draft (heads of 128): 400 307 / 296, 1000 498 / 467, 2000 (256 workgroups) 809 / 762.  Heads of 128 take 96 KiB of
+// LDS then, one workgroup per CU: four 7B layers, 256 rows (128 workgroups) 1104 / 1100, 512 (256) 1890 / 1896, 640 (320) 2190 / 2217.
+static bool prefill_split(int heads, int rows, int dh) {
+    const int blocks = (rows + 63) / 64, wgs = heads * blocks;
+    return dh == 64 ? wgs <= 512 : wgs <= 128 || (wgs <= 256 && blocks >= 16);
+}
+
 hipError_t launch_prefill_attention(const PrefillAttnArgs &a, bool attend, hipStream_t stream) {
     if (a.rows < 1 || a.rows > a.max_positions || (a.v_stride % 32) != 0 || a.v_stride < a.max_positions) return hipErrorInvalidValue;
-    const dim3 g1(a.H, (a.rows + 31) / 32 + 1), g2(a.H, (a.rows + 63) / 64);
     if (a.dh != 128 && a.dh != 64) return hipErrorInvalidValue;
-    if (a.dh == 128) {
-        hipLaunchKernelGGL(prefill_append_kernel<128>, g1, dim3(256), 0, stream, a);
-        if (attend) hipLaunchKernelGGL(prefill_attention_kernel<128>, g2, dim3(256), 0, stream, a);
-    } else {
-        hipLaunchKernelGGL(prefill_append_kernel<64>, g1, dim3(256), 0, stream, a);
-        if (attend) hipLaunchKernelGGL(prefill_attention_kernel<64>, g2, dim3(256), 0, stream, a);
-    }
+    const bool split = prefill_split(a.H, a.rows, a.dh);
+    const int queries = split ? 32 : 64;
+    const dim3 g1(a.H, (a.rows + 31) / 32 + 1), g2(a.H, (a.rows + queries - 1) / queries);
+    if (a.dh == 128) hipLaunchKernelGGL(prefill_append_kernel<128>, g1, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL(prefill_append_kernel<64>, g1, dim3(256), 0, stream, a);
+    if (!attend) return hipGetLastError();
+    if (a.dh == 128 && split) hipLaunchKernelGGL((prefill_attention_kernel<128, true>), g2, dim3(256), 0, stream, a);
+    else if (a.dh == 128) hipLaunchKernelGGL((prefill_attention_kernel<128, false>), g2, dim3(256), 0, stream, a);
+    else if (split) hipLaunchKernelGGL((prefill_attention_kernel<64, true>), g2, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((prefill_attention_kernel<64, false>), g2, dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
