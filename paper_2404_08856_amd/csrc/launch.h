@@ -177,6 +177,7 @@ constexpr int kPrefillRows = 2048;   // rows per pass at most
 // 40 rows 712 / 699 and 864 / 763; the 12-layer draft, 24 rows 769 / 791 and 948 / 920, 32 rows 867 / 796 and 1110 / 924;
 // the 4-layer draft, 24 rows 294 / 307 and 382 / 368, 32 rows 330 / 309 and 450 / 370.
 inline int prefill_min_rows(int d_model) { return d_model >= 2048 ? 33 : 25; }
+int prefill_row_parts(int d);        // parts of the sums of squares that the input rows' kernel leaves per row
 hipError_t launch_prefill_rows(const void *embed_bf16, const int32_t *tokens, const float *embeds, int rows, int d, int vocab,
                                const float *gain, float *h, void *X, float *ssq, int ssq_ld, hipStream_t stream);
 struct PrefillGemmArgs {

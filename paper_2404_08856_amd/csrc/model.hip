@@ -672,7 +672,7 @@ int32_t prefill_pass(spd_model *m, int32_t seq, const float *embeds, const int32
         common.partials = (float *)(m->ws + L.ppart); common.arrive = (unsigned *)(m->ws + L.arrive);
         PrefillGemmArgs g = common;
         g.W = wqkv; g.X = xn; g.N = 3 * HD - q0; g.K = d; g.Y = qkv + q0; g.ldy = 3 * HD;
-        g.ssq_in = ssq_b; g.ssq_parts = l == 0 ? 1 : parts;
+        g.ssq_in = ssq_b; g.ssq_parts = l == 0 ? prefill_row_parts(d) : parts;
         PROF_TRY(PK_QKV, launch_prefill_gemm(g, EPI_STORE, st));
         PROF_TRY(PK_ATTENTION, launch_prefill_attention(at, !last, st));
         if (last) break;
