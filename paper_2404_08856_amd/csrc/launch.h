@@ -186,12 +186,12 @@ struct PrefillGemmArgs {
     int N, K, rows;
     float *Y;                 // STORE: Y = s * acc; RESIDUAL: Y += acc
     int ldy;
-    const float *ssq_in;      // [rows][ssq_ld]: ssq_parts partial sums of squares per row (NULL: s = 1)
+    const float *ssq_in;      // [ssq_parts][ssq_ld]: partial sums of squares of the rows (NULL: s = 1)
     int ssq_ld, ssq_parts;
     float eps;
     const float *gain_next;   // RESIDUAL: gain of the following norm, whose operand and partial sums of squares are written too
     void *Xnext;
-    float *ssq_out;           // prefill_ssq_parts(N / 16, rows) parts per row
+    float *ssq_out;           // [prefill_ssq_parts(N / 16, rows)][ssq_ld]
     void *Xout;               // SWIGLU: activations of N / 2 columns
     float *partials;          // scratch for the sums of K slices (prefill_partial_bytes)
     unsigned *arrive;         // kPrefillMaxSplit counters, zero between launches

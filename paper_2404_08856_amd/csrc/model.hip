@@ -53,7 +53,7 @@ struct Layout {                    // byte offsets inside the three buffers
     // workspace
     size_t h, qkv, xn, xo, xf, rope, logits, ssq_a, ssq_b, d_lens, d_error, qa_count, qa_abort, part, arrive, zero, chain;
     size_t ph, pqkv, pxn, pxo, pxf, pssq_a, pssq_b, ppart;      // prefill passes of up to prefill_rows rows
-    int prefill_rows, pssq_ld;
+    int prefill_rows, pssq_ld;      // pssq: [part][pssq_ld] of the rows
     size_t ws_total;
 };
 
@@ -122,15 +122,16 @@ void make_layout(const spd_model_config &c, Layout &L) {
     // prefill: activations of one pass, whole row tiles of 16 rows (a workgroup tile may reach beyond the last one: the kernel
     // clamps the row tiles that it reads and writes no row that is not there)
     L.prefill_rows = std::min((int)kPrefillRows, c.max_positions);
-    L.pssq_ld = (d / 16 + 3) / 4;
     const size_t pr = align_up((size_t)L.prefill_rows, 16);
+    L.pssq_ld = (int)pr;
+    const size_t pssq_parts = (d / 16 + 3) / 4;
     L.ph = take(pr * d * 4);
     L.pqkv = take(pr * 3 * HD * 4);
     L.pxn = take(pr * KSd * 64 * kTerms);
     L.pxo = take(pr * KShd * 64 * kTerms);
     L.pxf = take(pr * KSf * 64 * kTerms);
-    L.pssq_a = take(pr * L.pssq_ld * 4);
-    L.pssq_b = take(pr * L.pssq_ld * 4);
+    L.pssq_a = take(pr * pssq_parts * 4);
+    L.pssq_b = take(pr * pssq_parts * 4);
     L.ppart = take(std::max({prefill_partial_bytes(3 * HD, L.prefill_rows), prefill_partial_bytes(d, L.prefill_rows), prefill_partial_bytes(2 * F, L.prefill_rows)}));
     L.ws_total = off;
 }

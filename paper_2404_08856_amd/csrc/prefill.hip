@@ -7,12 +7,12 @@
 //    the 16 columns of the B operand -- and the three products go into the same accumulator: no column of a tile
 //    is unused and no sum over term columns is needed.  Block (row tile rt of 16 rows, K-step s, term t) is the
 //    1 KiB at index (rt * KS + s) * 3 + t, lane l = r + 16 g holding X[16 rt + r][32 s + 8 g .. + 7].
-//  * prefill_gemm_kernel: tiled GEMM, both operands through LDS.  Bound by the matrix cores: the 7B QKV projection of
-//    2047 rows runs at 1.27 to 1.32 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.28).
+//  * prefill_gemm_kernel: tiled GEMM, both operands through LDS.  Bound by the matrix cores and the card's power: the 7B QKV projection of
+//    2047 rows runs at 1.35 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.43 to 1.68).
 //  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
 //    the pass's own rows).
 // Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
-// four 7B layers, 2047 rows 7.0 ms (was 41.1), 640 rows 2.4 (10.2); 12-layer draft, 1472 rows 1.65 ms (47.1).
+// four 7B layers, 2047 rows 6.5 ms (was 41.1), 640 rows 2.3 (10.2); 12-layer draft, 1472 rows 1.50 ms (47.1).
 #include <algorithm>
 
 #include "gemm_core.h"
@@ -99,14 +99,14 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(const uint16_t *__res
     __shared__ float part[4][16];
     if (g == 0) part[w][r] = ss;
     __syncthreads();
-    if (threadIdx.x < 16 && ok) ssq[(size_t)row * ssq_ld + blockIdx.y] = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
+    if (threadIdx.x < 16 && ok) ssq[(size_t)blockIdx.y * ssq_ld + row] = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
 }
 
 int prefill_row_parts(int d) { return (d / 32 + kRowSteps - 1) / kRowSteps; }
 
 hipError_t launch_prefill_rows(const void *embed_bf16, const int32_t *tokens, const float *embeds, int rows, int d, int vocab,
                                const float *gain, float *h, void *X, float *ssq, int ssq_ld, hipStream_t stream) {
-    if ((!tokens) == (!embeds) || rows < 1 || prefill_row_parts(d) > ssq_ld) return hipErrorInvalidValue;
+    if ((!tokens) == (!embeds) || rows < 1 || rows > ssq_ld) return hipErrorInvalidValue;
     hipLaunchKernelGGL(prefill_rows_kernel, dim3((rows + 15) / 16, prefill_row_parts(d)), dim3(256), 0, stream, (const uint16_t *)embed_bf16, tokens, embeds, rows, d, vocab,
                        gain, h, (uint4 *)X, ssq, ssq_ld);
     return hipGetLastError();
@@ -122,12 +122,12 @@ struct PrefillGemmKernelArgs {
     int n_blk, r_blk;         // workgroups along the features / the rows
     float *Y;
     int ldy;
-    const float *ssq_in;      // [rows][ssq_ld], ssq_parts valid: partial sums of squares, or NULL
+    const float *ssq_in;      // [ssq_parts][ssq_ld]: partial sums of squares of the rows, or NULL
     int ssq_ld, ssq_parts;
     float inv_d, eps;
     const float *gain_next;   // RESIDUAL: gain of the following norm
     uint16_t *Xnext;
-    float *ssq_out;           // RESIDUAL: [rows][ssq_ld], one part per NW tiles
+    float *ssq_out;           // RESIDUAL: [part][ssq_ld], one part per NW tiles
     uint16_t *Xout;           // SWIGLU
     int KS_out;
     int J;                    // K slices
@@ -205,18 +205,36 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
     issue(1, 1);
 
     const int wn = w % WN, wr = w / WN;
-    // 1 / rms of this lane's rows from the producer's partial sums: a lane group takes every fourth, fixed order
+    // 1 / rms of this lane's rows from the producer's partial sums: a lane group takes every fourth, fixed order.  The loads of 32 parts of
+    // all rows go out together and read 16 neighbouring rows of a part.  Four 7B layers, a prompt of 64 rows: one part after the other, a
+    // row's parts side by side 671 us, together 678, together and rows side by side 651; 128 rows 890 / 897 / 859, 2000 rows 6668 / - / 6275.
     float inv[NX];
 #pragma unroll
-    for (int j = 0; j < NX; ++j) {
-        inv[j] = 1.0f;
-        if (a.ssq_in) {
-            const int row = min((rt0 + wr * NX + j) * 16 + (lane & 15), a.rows - 1);
-            float ss = 0.f;
-            for (int p = lane >> 4; p < a.ssq_parts; p += 4) ss += a.ssq_in[(size_t)row * a.ssq_ld + p];
-            ss = xor_step<16>(ss, AddOp());
-            ss = xor_step<32>(ss, AddOp());
-            inv[j] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
+    for (int j = 0; j < NX; ++j) inv[j] = 1.0f;
+    if (a.ssq_in) {
+        float ss[NX];
+        int row[NX];
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            ss[j] = 0.f;
+            row[j] = min((rt0 + wr * NX + j) * 16 + (lane & 15), a.rows - 1);
+        }
+        for (int p0 = lane >> 4; p0 < a.ssq_parts; p0 += 32) {
+            float t[8][NX];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int j = 0; j < NX; ++j) t[u][j] = a.ssq_in[(size_t)min(p0 + 4 * u, a.ssq_parts - 1) * a.ssq_ld + row[j]];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int j = 0; j < NX; ++j) ss[j] += p0 + 4 * u < a.ssq_parts ? t[u][j] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            ss[j] = xor_step<16>(ss[j], AddOp());
+            ss[j] = xor_step<32>(ss[j], AddOp());
+            inv[j] = 1.0f / sqrtf(ss[j] * a.inv_d + a.eps);
         }
     }
 
@@ -443,7 +461,7 @@ __global__ __launch_bounds__(WN *WR * 64, 2) void prefill_gemm_kernel(PrefillGem
                 sq = xor_step<16>(sq, AddOp());
                 sq = xor_step<32>(sq, AddOp());
                 const int p = nb * WN + wn;
-                if (g == 0 && row_ok && p * NW < a.n_tiles) a.ssq_out[(size_t)row * a.ssq_ld + p] = sq;
+                if (g == 0 && row_ok && p * NW < a.n_tiles) a.ssq_out[(size_t)p * a.ssq_ld + row] = sq;
             }
         }
     }
