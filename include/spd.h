@@ -113,7 +113,9 @@ int32_t spd_model_destroy(spd_model *model);
 
 /* Kernel-selection knobs of a model, for tests and sweeps (not part of the method; production
  * code never needs this call: spd_model_create picks the measured defaults).  Zero-initialise the
- * struct for "all defaults".  Takes effect from the next forward; host-side only.
+ * struct for "all defaults".  Takes effect from the next forward; host-side only.  All fields but wait_spin_limit choose
+ * among the kernels of single projections: while one of them is set, the layers of a small model, by default one
+ * launch for up to 5 rows, run kernel by kernel.
  * Projections are indexed qkv, o, gate_up, down, lm_head. */
 #define SPD_N_PROJECTIONS 5
 typedef struct {
@@ -211,7 +213,8 @@ int32_t spd_draft_step(spd_model *draft, const int32_t *tokens_in, int32_t n_seq
  *   n_accepted_out  int32 [n_seqs]      k
  *   next_token_out  int32 [n_seqs]      y
  *   accept_prob_out float32 [n_seqs, gamma] or NULL: min{1, T_j(d_j)/D_j(d_j)}
- *   workspace       float32 scratch, >= spd_accept_workspace_bytes(...) bytes
+ *   workspace       float32 scratch, >= spd_accept_workspace_bytes(...) bytes; it may hold anything before the call,
+ *                   and nothing in it has to survive between calls
  * Errors: SPD_ERR_INVALID_ARG (NULL, gamma < 1, temperature < 0),
  * SPD_ERR_CAPACITY (workspace too small). */
 int32_t spd_accept_workspace_bytes(int32_t n_seqs, int32_t gamma, int32_t vocab, size_t *h_bytes);
@@ -299,7 +302,8 @@ int32_t spd_device_status(spd_model *model, void *stream);
  * launch's own start / stop events (the kernel's execution time, as a profiler
  * reports it), a group of several launches is bracketed by events recorded on the
  * caller's stream.  Where QKV projection and attention run as one kernel, kind 0
- * covers both and kind 5 stays empty.  spd_trace_read WAITS for
+ * covers both and kind 5 stays empty.  The layers of a small model, otherwise one launch for up to 5 rows, run kernel by kernel
+ * while tracing is enabled.  spd_trace_read WAITS for
  * the recorded events (the one call here that blocks the host), adds the elapsed
  * milliseconds and launch counts per kind into h_ms_sum[n_kinds] / h_count[n_kinds] and
  * forgets them.  Kinds: 0 QKV projection, 1 O projection, 2 gate|up projection + SwiGLU,
