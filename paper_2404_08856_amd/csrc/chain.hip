@@ -3,9 +3,11 @@
 // One projection or attention of a small model lasts as long as a launch: 63 launches of 3.3 to 6 us made a step of the 12-layer
 // draft.  Here every (layer, stage, one or two tiles) is a workgroup of one grid, in the order of the data: QKV, attention, O, gate|up, down of
 // layer 0, then of layer 1, and so on.  A workgroup brings its weights (or cached keys and values) into registers, waits for the
-// vector it works on, and leaves its columns to the next stage.  It only ever waits for workgroups with a lower index.  Workgroups start in the
-// order of their index on each XCD, so the unfinished one with the lowest index runs or is the next to run there, whatever later
-// ones hold: the launch ends.  Later stages' workgroups that are resident already have their weights by the time their turn comes.
+// vector it works on, and leaves its columns to the next stage.  Its place in the
+// order is the count of workgroups that started before it, so it only ever waits for ones that have started: the first unfinished one in the
+// order runs and waits for nobody, whatever else the GPU runs, and the launch ends.  (By blockIdx two such launches side by side could each hold the
+// places on one XCD that the other's first unfinished workgroup needs: XCDs start workgroups in order, but each in its own.)  Later stages' workgroups that
+// are resident already have their weights by the time their turn comes.
 // (Waits are bounded all the same, as in the fused QKV + attention kernel.)
 //
 // Between two stages a value travels with its proof of arrival: 8-byte words, stored and loaded whole at device scope, that hold the
@@ -41,7 +43,7 @@ struct ChainKernelArgs {
     int KSd, KShd, KSf, n_qkv, n_att, n_gu, per_layer;     // K-steps; workgroups per stage (O and down: d / 16) and layer
     u64 *H1, *H2, *Q, *A, *Fw;                              // words of this count of rows: h before QKV and before gate|up (float32), q | k | v
                                                             // (float32), attention's result and the activations (terms)
-    unsigned *pass, *done;                                  // number of the last pass of the launch before; workgroups of this launch's last stage that are through
+    u64 *turn;                                              // number of the last pass of the launch before << 32 | workgroups of this launch that have started
     const uint16_t *E;                                      // input rows: of the embedding table, by token, or
     const int32_t *tokens;
     const float *embeds;                                    // as they are
@@ -359,21 +361,23 @@ __global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs
     extern __shared__ __align__(16) uint16_t xs[];                        // activations as operand fragments: [K-step][lane group][row][term][8]
     __shared__ __align__(16) float red[kChainTiles][kChainWaves][kGroupRows][16];
     __shared__ float squares[kGroupRows * 8];               // d <= 1024: at most 8 runs a row
-    const int l = blockIdx.x / a.per_layer;
-    int id = blockIdx.x - l * a.per_layer, stage = CH_QKV;
+    // This workgroup's place in the order, and the number of the pass with it.  Who starts last leaves the number for the next launch: all others have theirs.
+    __shared__ u64 turn_s;
+    if (threadIdx.x == 0) {
+        const u64 t = __hip_atomic_fetch_add(a.turn, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((unsigned)t == gridDim.x - 1) __hip_atomic_store(a.turn, (u64)((unsigned)(t >> 32) + (unsigned)c.n_layers) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        turn_s = t;
+    }
+    __syncthreads();
+    const int turn = __builtin_amdgcn_readfirstlane((int)(unsigned)turn_s);
+    const int l = turn / a.per_layer;
+    int id = turn - l * a.per_layer, stage = CH_QKV;
     const int n_d = c.d / 16;
     if (id >= a.n_qkv) { id -= a.n_qkv; stage = CH_ATT;
         if (id >= a.n_att) { id -= a.n_att; stage = CH_O;
             if (id >= n_d) { id -= n_d; stage = CH_GU;
                 if (id >= a.n_gu) { id -= a.n_gu; stage = CH_DOWN; } } } }
-    const unsigned pass = *a.pass + 1 + (unsigned)l;        // (the words start at zero, which is no pass's number)
-    // Of the last stage's workgroups the last to come by here leaves the number for the next launch: all others have read theirs by then
-    asm volatile("" ::"s"(pass) : "memory");                // (and this one's is in its register)
-    if (stage == CH_DOWN && l + 1 == c.n_layers && threadIdx.x == 0 &&
-        __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)n_d - 1) {
-        __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.pass, pass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    const unsigned pass = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(turn_s >> 32)) + 1 + (unsigned)l;     // (the words start at zero, which is no pass's number)
 
     // Workgroups that are here early look at one word now and then, until the stage before the one they wait for has its input
     auto gate_on = [&](const u64 *word, bool is_float, unsigned p) __attribute__((always_inline)) {
@@ -450,13 +454,12 @@ hipError_t launch_chain(const ChainArgs &c, const AttnArgs &given, int longest, 
     k.KSd = c.d / 32; k.KShd = c.HD / 32; k.KSf = (c.F + 31) / 32;
     k.n_qkv = (3 * c.HD / 16 + kChainTiles - 1) / kChainTiles; k.n_att = t.n_seqs * t.H * chain_slices(t.dh, runs) * (runs ? kChainRuns : 1); k.n_gu = (c.F / 8 + kChainTiles - 1) / kChainTiles;
     k.per_layer = k.n_qkv + k.n_att + k.n_gu + 2 * (c.d / 16);
-    unsigned *count = (unsigned *)c.words + 2 * (c.rows - 1);            // number of the last pass, and workgroups through with it
     t.arrive = (unsigned *)((char *)c.words + 256);
     t.partials = (float *)((char *)c.words + 512 + (size_t)kGroupRows * (c.HD / 32) * sizeof(unsigned) / 256 * 256);
     u64 *p = (u64 *)((char *)t.partials + run_bytes(c.HD)) + words_per_row(c.d, c.HD, c.F) * (c.rows * (c.rows - 1) / 2);
     auto take = [&](size_t per_row) { u64 *q = p; p += per_row * c.rows; return q; };
     k.H1 = take(c.d); k.H2 = take(c.d); k.Q = take(3 * c.HD); k.A = take(c.HD); k.Fw = take(c.F);
-    k.pass = count; k.done = count + 1;
+    k.turn = (u64 *)c.words + (c.rows - 1);
     k.E = (const uint16_t *)embed_bf16; k.tokens = tokens; k.embeds = embeds; k.M = t.M; k.token_stride = token_stride; k.vocab = vocab;
     const size_t lds = chain_lds(std::max({k.KSd, k.KShd, k.KSf}), c.rows);
     const dim3 grid((unsigned)k.per_layer * c.n_layers), block(kChainThreads);

@@ -110,3 +110,29 @@ def test_waits_that_give_up_are_reported():
     m.spd_verify_forward(tokens((1, 1), shape.vocab, 3), torch.zeros((1, 1, shape.vocab), device="cuda"))
     with pytest.raises(spd.SpdError):
         m.spd_device_status()
+
+
+def test_two_models_on_two_streams():
+    """Launches of two models side by side, each with more workgroups than the GPU has places for."""
+    pairs = [model(768, 12, 64, 2048, layers=8) for _ in range(2)]
+    t = [tokens((1, 1), 512, 5 + i) for i in range(2)]
+    want = []
+    for i, (m, _) in enumerate(pairs):
+        m.spd_prefill_tokens(0, tokens((60,), 512, 9 + i))
+        o = torch.zeros((1, 1, 512), device="cuda")
+        m.spd_kv_set_len([60])
+        m.spd_verify_forward(t[i], o)
+        want.append(o)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = [[torch.zeros((1, 1, 512), device="cuda") for _ in range(50)] for _ in range(2)]
+    torch.cuda.synchronize()
+    for n in range(50):
+        for i, (m, _) in enumerate(pairs):
+            with torch.cuda.stream(streams[i]):
+                m.spd_kv_set_len([60])
+                m.spd_verify_forward(t[i], got[i][n])
+    torch.cuda.synchronize()
+    for i, (m, _) in enumerate(pairs):
+        m.spd_device_status()
+        assert all(torch.equal(o, want[i]) for o in got[i])
