@@ -23,9 +23,10 @@
 // from device memory, where each launch leaves it for the next, so that a captured launch can be replayed.
 //
 // Bound by the stages' latency, about 2.3 us each (12-layer draft, 66 positions, from the last word written to the last word written: QKV 1.9, attention
-// 2.6, O 2.0, gate|up 2.3, down 3.0).  Whole draft step, one by one / in one launch, 12-layer draft: 1 sequence, 66 cached positions 249 / 155 us,
-// 640 281 / 179, 2000 375 / 200; 3 sequences, 640 310 / 234; 5 sequences, 66 289 / 231, 640 320 / 257; 4-layer draft: 1 sequence 112 / 75 and 178 / 94,
-// 4 sequences, 1472 171 / 119.
+// 2.6, O 2.0, gate|up 2.3, down 3.0), and by the count of starts at the beginning of a launch.  Whole draft step, one by one / in one launch, 12-layer draft:
+// 1 sequence, 66 cached positions 249 / 168 us, 640 281 / 194, 2000 375 / 221; 3 sequences, 200 289 / 233; 5 sequences, 66 289 / 260, 640 320 / 273, 2000
+// 373 / 308; 4-layer draft: 1 sequence, 66 112 / 84, 2000 178 / 112; 4 sequences, 66 122 / 110, 300 130 / 127, 1472 171 / 142.  (With the place by blockIdx, which is not
+// safe, 155 at 66 positions; with the count taken and not used 163: 8 us are the count, the rest is how a stage's workgroups spread over the CUs.)
 #include <algorithm>
 
 #include "attention_core.h"
@@ -61,7 +62,8 @@ __device__ __forceinline__ float2 input_pair(const ChainKernelArgs &a, int row, 
 __device__ __forceinline__ u64 load_word(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_word(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // Two words next to each other per address (16-byte aligned), all of them on their way together; each word is whole, the pair need not be.  As
-// inline assembly for the scope.  With two 8-byte loads per pair a step of the 12-layer draft took 159 us instead of 156.5, with 5 rows 249 instead of 231.
+// inline assembly for the scope.  With two 8-byte loads per pair a step of the 12-layer draft took 159 us instead of 156.5, with 5 rows 249 instead of 231
+// (places by blockIdx).
 typedef __attribute__((ext_vector_type(2))) u64 u64x2_t;
 __device__ __forceinline__ void load_words(const u64 *const (&at)[1], u64 (&v)[2]) {
     u64x2_t a;
@@ -413,12 +415,12 @@ __global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs
     }
 }
 
-// From how many cached positions of the longest sequence on its keys are cut into runs.  Step of the 12-layer draft, slices / runs: 1 sequence, 300
+// From how many cached positions of the longest sequence on its keys are cut into runs.  With places by blockIdx, step of the 12-layer draft, slices / runs: 1 sequence, 300
 // positions 176 / 182 us, 500 179 / 183, 1000 220 / 186; 2 sequences, 300 199 / 205, 1472 275 / 222; 5 sequences, 66 250 / 254, 300 275 / 260; the 4-layer draft: 1
 // sequence, 500 87.2 / 88.3, 1000 106 / 89; 3 sequences, 200 108 / 106.
 static int chain_runs_from(int n_seqs) { return 256 + 256 / n_seqs; }
-// Fragments of the longest input in LDS: beyond this one workgroup per CU is left, whose place is missing (4-layer draft, 5 rows of 84 KiB: 300 cached
-// positions 139 us against 131 one by one; 4 rows of 68 KiB: 110 against 128).
+// Fragments of the longest input in LDS: beyond this one workgroup per CU is left, whose place is missing (with places by blockIdx, 4-layer draft, 5 rows of 84 KiB:
+// 300 cached positions 139 us against 131 one by one; 4 rows of 68 KiB: 110 against 128, now 127 against 128).
 constexpr size_t kChainLds = 72 * 1024;
 static size_t words_per_row(int d, int HD, int F) { return (size_t)2 * d + 4 * (size_t)HD + F; }
 static size_t chain_lds(int KS, int rows) { return (size_t)KS * rows * 4 * kTerms * 16 + 16; }       // and a fragment of zeros
