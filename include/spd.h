@@ -214,7 +214,9 @@ int32_t spd_draft_step(spd_model *draft, const int32_t *tokens_in, int32_t n_seq
  *   next_token_out  int32 [n_seqs]      y
  *   accept_prob_out float32 [n_seqs, gamma] or NULL: min{1, T_j(d_j)/D_j(d_j)}
  *   workspace       float32 scratch, >= spd_accept_workspace_bytes(...) bytes; it may hold anything before the call,
- *                   and nothing in it has to survive between calls
+ *                   and nothing in it has to survive between calls.  Calls that share one must not overlap; the results of
+ *                   calls that do are undefined, those of later calls are not, with one exception: a call captured in a
+ *                   graph that overlapped with another needs the workspace cleared before its next replay
  * Errors: SPD_ERR_INVALID_ARG (NULL, gamma < 1, temperature < 0),
  * SPD_ERR_CAPACITY (workspace too small). */
 int32_t spd_accept_workspace_bytes(int32_t n_seqs, int32_t gamma, int32_t vocab, size_t *h_bytes);
@@ -231,7 +233,8 @@ int32_t spd_speculative_accept(const float *target, const float *draft, const in
  * allocates.  Limit: n_seqs * (2 gamma + 1) <= SPD_STATIC_ACCEPT_MAX_ROWS, else SPD_ERR_CAPACITY and
  * nothing is launched.  All calls on one GPU share that GPU's array: calls that may overlap (different
  * streams, different threads) race on it -- order them, or use spd_speculative_accept with one
- * workspace per stream.  Nothing in the array has to survive between calls. */
+ * workspace per stream (a captured call that did overlap has to be captured again).  Nothing in the array has to
+ * survive between calls. */
 #define SPD_STATIC_ACCEPT_MAX_ROWS 4096
 int32_t spd_speculative_accept_static(const float *target, const float *draft, const int32_t *draft_tokens,
                                       const float *u, int32_t n_seqs, int32_t gamma, int32_t vocab,

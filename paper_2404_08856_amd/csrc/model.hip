@@ -889,7 +889,7 @@ int32_t spd_speculative_accept_static(const float *target, const float *draft, c
     a.n_seqs = n_seqs; a.gamma = gamma; a.vocab = vocab; a.temperature = temperature; a.flags = flags;
     a.n_accepted = n_accepted_out; a.next_token = next_token_out; a.accept_prob = accept_prob_out;
     a.token_stride = gamma;
-    a.stats = (float *)ws;            // every entry the kernels read is written by this call first: nothing to clear
+    a.stats = (float *)ws;            // nothing to clear: entries that this call has not written are not taken for its own (its number marks the answers)
     HIP_TRY(launch_accept(a, (hipStream_t)stream));
     return SPD_OK;
 }

@@ -7,6 +7,8 @@
 // k_u = u * 2^24, result = first x whose inclusive running sum exceeds the threshold.
 // Every decision after the float32 probabilities is integer arithmetic, which is what
 // makes the result reproducible bit for bit by any other implementation.
+#include <atomic>
+
 #include "launch.h"
 
 namespace spd {
@@ -567,15 +569,15 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
 // statistics; then it looks at all answers of its sequence, and whoever finds them complete writes the result (the last one
 // to arrive does for certain, since its own answer is acknowledged before it looks; two may, with the same values) and takes the
 // answers away again.  Nobody waits, nothing needs clearing before the launch, and no row is read twice.
-// An answer is the token (or kAccepted) under a mark, and its complement under another: 96 bits that memory which
-// was never written would have to hold by chance; the statistics' words never do (the first mark is a NaN, where they have the sum).
+// An answer is the token (or kAccepted) under a mark, and its complement under another.  The marks hold the number of the call, so what calls that overlapped
+// on one workspace may have left (one can take half of the other's answers away) is nobody's answer later.  Only a captured call keeps its number from replay to replay.
 // Bound by one CU's vector instructions (about 64 cycles per entry and wave: 3 us) and its loads (256 KiB, 4 us).  32000 entries, draft
 // length 4, graph replays, one launch / statistics and slices: draft as probabilities, 1 sequence 10.1 / 14.9 us, 8 10.3 / 15.7, 32 12.3 / 16.9, 51
 // 16.5 / 19.9, 64 (a second round of workgroups) 21.8 / 21.9; draft as logits, 1 9.6 / 14.1, 51 19.3 / 24.6, 64 26.1 / 26.1; 1000 entries, 51 10.0 / 15.3,
 // 64 15.2 / 16.3.
-constexpr unsigned kAnswerMark = 0xffc5a11cu, kAnswerMark2 = 0x9e3779b9u, kAccepted = 0x80000000u;
+constexpr unsigned kAnswerMark = 0xffc5a11cu, kAnswerMark2 = 0x9e3779b9u, kAccepted = 0x80000000u;    // marks of call 0, which there is not
 template <bool ALIGNED>
-__global__ __launch_bounds__(kSampThreads) void accept_positions_kernel(AcceptArgs a) {
+__global__ __launch_bounds__(kSampThreads) void accept_positions_kernel(AcceptArgs a, unsigned long long call) {
     const int G = a.gamma, V = a.vocab, seq = blockIdx.x / (G + 1), j = blockIdx.x - seq * (G + 1);
     __shared__ SeqRows rows;            // (only for the view below)
     __shared__ unsigned long long tmp[17];
@@ -637,16 +639,17 @@ __global__ __launch_bounds__(kSampThreads) void accept_positions_kernel(AcceptAr
     }
     if (threadIdx.x >= kWave) return;
     unsigned long long *slot = reinterpret_cast<unsigned long long *>(q.stats_t(min((int)threadIdx.x, G)));
-    auto marked = [](unsigned mark, unsigned v) { return (unsigned long long)mark << 32 | v; };
+    const unsigned mark = kAnswerMark + (unsigned)call, mark2 = kAnswerMark2 + (unsigned)(call >> 32);
+    auto marked = [](unsigned m, unsigned v) { return (unsigned long long)m << 32 | v; };
     if ((int)threadIdx.x == j) {
-        __hip_atomic_store(slot, marked(kAnswerMark, answer), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(slot + 1, marked(kAnswerMark2, ~answer), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(slot, marked(mark, answer), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(slot + 1, marked(mark2, ~answer), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // acknowledged before any answer is looked at
     const unsigned long long w0 = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned long long w1 = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned got = (unsigned)w0;
-    if (!__all(w0 == marked(kAnswerMark, got) && w1 == marked(kAnswerMark2, ~got))) return;
+    if (!__all(w0 == marked(mark, got) && w1 == marked(mark2, ~got))) return;
     const unsigned long long stops = __ballot(got != kAccepted);   // positions G and beyond stop always
     const int k = min(__ffsll((long long)stops) - 1, G);
     if ((int)threadIdx.x == k) {
@@ -666,9 +669,11 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
     const bool need_stats = ((a.flags & 3u) != 3u);
     // one round of workgroups, one per CU (a second one costs more than it saves: see above); answers are 8-byte words
     if (kind != ROW_MEMORY && ((uintptr_t)a.stats & 7) == 0 && (long)a.n_seqs * (a.gamma + 1) <= 256) {
+        static std::atomic<unsigned long long> calls{0};          // numbers calls of all threads and devices
+        const unsigned long long call = calls.fetch_add(1, std::memory_order_relaxed) + 1;
         const dim3 grid(a.n_seqs * (a.gamma + 1)), block(kSampThreads);
-        if (kind == ROW_ALIGNED) hipLaunchKernelGGL(accept_positions_kernel<true>, grid, block, 0, stream, a);
-        else hipLaunchKernelGGL(accept_positions_kernel<false>, grid, block, 0, stream, a);
+        if (kind == ROW_ALIGNED) hipLaunchKernelGGL(accept_positions_kernel<true>, grid, block, 0, stream, a, call);
+        else hipLaunchKernelGGL(accept_positions_kernel<false>, grid, block, 0, stream, a, call);
         return hipGetLastError();
     }
     if (need_stats) {

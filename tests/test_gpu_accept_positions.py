@@ -53,6 +53,20 @@ def test_positions_by_kind_of_row(V, misalign):
     check(V, 2, 2, True, True, 1.0, misalign=misalign)
 
 
+@pytest.mark.parametrize("n,gamma", [(1, 1), (1, 4), (51, 4), (4, 63)])
+def test_answers_left_in_the_workspace(n, gamma):
+    """Words that look like another call's answers for every position (calls that overlapped leave some): each sequence would stop at its first
+    position with token 7."""
+    from paper_2404_08856_amd import spd
+    print(f"accept positions: leftovers n={n} gamma={gamma}", flush=True)
+    T, D, d, u = rows(n, gamma, 1024, 21)
+    T[:, :gamma] = D                                       # accepted wherever u < 1
+    left = torch.tensor([7, 0xffc5a11c, ~7 & 0xffffffff, 0x9e3779b9], dtype=torch.int64).to(torch.uint32).view(torch.uint8)
+    ws = torch.zeros(spd.spd_accept_workspace_bytes(n, gamma, 1024), dtype=torch.uint8, device="cuda")
+    ws.view(-1, 16)[:n * (gamma + 1)] = left.cuda()
+    exact(T, D, d, u, ws)
+
+
 def test_residual_that_truncates_to_zero():
     """A reject whose residual has no mass draws from the target row."""
     from paper_2404_08856_amd import spd
