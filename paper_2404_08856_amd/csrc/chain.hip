@@ -419,9 +419,9 @@ __global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs
 // positions 176 / 182 us, 500 179 / 183, 1000 220 / 186; 2 sequences, 300 199 / 205, 1472 275 / 222; 5 sequences, 66 250 / 254, 300 275 / 260; the 4-layer draft: 1
 // sequence, 500 87.2 / 88.3, 1000 106 / 89; 3 sequences, 200 108 / 106.
 static int chain_runs_from(int n_seqs) { return 256 + 256 / n_seqs; }
-// Fragments of the longest input in LDS: beyond this one workgroup per CU is left, whose place is missing (with places by blockIdx, 4-layer draft, 5 rows of 84 KiB:
-// 300 cached positions 139 us against 131 one by one; 4 rows of 68 KiB: 110 against 128, now 127 against 128).
-constexpr size_t kChainLds = 72 * 1024;
+// Fragments of the longest input in LDS.  Two workgroups fit a CU up to 52 KiB (kChainLdsTwo: next to 19 KiB of static LDS, heads of 64, or 27, heads of 128; 31 or 39
+// with runs of keys), one beyond.  One is enough for the 4-layer draft at 4 rows (66 KiB, 66 positions: 101 us a call against 111 one by one), not at 5 (82 KiB: 121 / 112).
+constexpr size_t kChainLds = 72 * 1024, kChainLdsTwo = 52 * 1024;
 static size_t words_per_row(int d, int HD, int F) { return (size_t)2 * d + 4 * (size_t)HD + F; }
 static size_t chain_lds(int KS, int rows) { return (size_t)KS * rows * 4 * kTerms * 16 + 16; }       // and a fragment of zeros
 
@@ -432,11 +432,21 @@ size_t chain_bytes(int d, int HD, int F) {
     return 256 + (size_t)kGroupRows * (HD / 32) * sizeof(unsigned) + 256 + run_bytes(HD) + words_per_row(d, HD, F) * sizeof(u64) * (kGroupRows * (kGroupRows + 1) / 2);     // counters; words for 1 .. 5 rows
 }
 
+static int chain_steps(int d, int HD, int F) { return std::max({d, HD, F + 31}) / 32; }
+// ... and QKV and gate|up look at all their inputs at once: up to 4096 values (4 pairs a thread).  A second look costs each of them a trip: calls of 5 rows and 66 positions,
+// one launch / one by one, 4 layers, d = 768 (12 heads of 64, ffn 2304) 0.88 of the time, 896 (14) 1.14 to 1.21, 1024 (16, ffn 2048) 1.15 to 1.22.
 int chain_rows(int d, int HD, int F) {
-    const int KS = std::max({d, HD, F + 31}) / 32;
     int rows = chain_shape_ok(d, HD, F) ? kGroupRows : 0;
-    while (rows > 0 && chain_lds(KS, rows) > kChainLds) --rows;
+    while (rows > 0 && (chain_lds(chain_steps(d, HD, F), rows) > kChainLds || rows * d > 8 * kChainThreads)) --rows;
     return rows;
+}
+// Attention cuts each head into workgroups of 16 dimensions that all score all keys (one by one it takes fewer where there are many pairs of sequence and head): worth it
+// while they leave places free.  One launch / one by one, 4 layers, 66 and 640 positions: d = 512, ffn 2048, heads of 128: 16, 3 sequences (384 workgroups) 0.93 and 0.91, 4 (512) 1.02
+// and 1.11, 5 (640) 1.21 and 1.17; 24, 3 sequences (576) 1.12 and 1.06; d = 256, 24 heads of 64, ffn 1024: 4 sequences (384) 0.89 and 0.84, 5 (480) 1.03 and 0.94;
+// one workgroup per CU: 4-layer draft, 4 sequences (256) 0.92 and 0.89, d = 512, 24 heads of 128, 2 sequences of 2 rows (384) 0.99 and 0.95, at 300 positions 1.05.
+bool chain_pays(int d, int HD, int F, int n_seqs, int M) {
+    const int rows = n_seqs * M, groups = n_seqs * (HD / 16);
+    return rows <= chain_rows(d, HD, F) && groups <= (chain_lds(chain_steps(d, HD, F), rows) <= kChainLdsTwo ? 384 : 256);
 }
 bool chain_supported(int d, int HD, int F, int dh) {
     for (const void *f : {dh == 128 ? (const void *)chain_kernel<128, false> : (const void *)chain_kernel<64, false>,

@@ -42,6 +42,13 @@ def forwards(m, shape, lens, M, one_by_one, calls=2):
     return torch.stack(out)
 
 
+def in_one_launch(shape, n_seqs, M):
+    """Whether calls of M rows for each of n_seqs sequences take the one launch: its input fragments, one look at a norm's inputs, places for attention."""
+    HD, rows = shape.n_heads * shape.head_dim, n_seqs * M
+    fragments = max(shape.d_model, HD, shape.d_ffn + 31) // 32 * rows * 192 + 16
+    return rows <= 5 and rows * shape.d_model <= 4096 and fragments <= 72 * 1024 and n_seqs * HD // 16 <= (384 if fragments <= 52 * 1024 else 256)
+
+
 def compare(m, shape, lens, M):
     print(f"chain {shape} lens {lens} M {M}", flush=True)
     for i, n in enumerate(lens):
@@ -51,6 +58,8 @@ def compare(m, shape, lens, M):
     want, got = (forwards(m, shape, lens, M, one) for one in (True, False))
     assert torch.isfinite(got).all()
     assert float((got - want).norm()) <= 1e-4 * float(want.norm()), float((got - want).norm() / want.norm())
+    # the two add in other orders, and a call that takes the same kernels repeats its bits: so this says which kernels ran
+    assert torch.equal(got, want) != in_one_launch(shape, len(lens), M)
 
 
 @pytest.mark.parametrize("d,heads,dh,ffn", [(128, 2, 64, 344), (256, 4, 64, 688), (384, 3, 128, 8), (768, 12, 64, 2048), (1024, 8, 128, 2816), (1024, 16, 64, 2048),
@@ -59,6 +68,15 @@ def compare(m, shape, lens, M):
 def test_shapes_and_rows(d, heads, dh, ffn, rows):
     m, shape = model(d, heads, dh, ffn)
     compare(m, shape, [37] * rows, 1)
+
+
+@pytest.mark.parametrize("d,heads,dh,ffn,n_seqs,M", [
+    (768, 12, 64, 2304, 1, 5), (896, 14, 64, 2048, 1, 4), (896, 14, 64, 2048, 1, 5), (1024, 16, 64, 2048, 4, 1), (1024, 16, 64, 2048, 5, 1),      # norm's inputs in one look
+    (256, 16, 128, 1024, 3, 1), (256, 16, 128, 1024, 4, 1), (256, 24, 64, 1024, 4, 1), (256, 24, 64, 1024, 5, 1),      # 384 workgroups of attention and more
+    (512, 24, 128, 2048, 2, 1), (512, 24, 128, 2048, 2, 2), (1024, 8, 128, 2816, 4, 1), (512, 8, 64, 3072, 2, 2), (512, 8, 64, 3072, 5, 1)])       # one workgroup per CU: 384, 256; too long
+def test_edges_of_the_rule(d, heads, dh, ffn, n_seqs, M):
+    m, shape = model(d, heads, dh, ffn)
+    compare(m, shape, [50] * n_seqs, M)
 
 
 @pytest.mark.parametrize("lens,M", [([0], 1), ([0], 5), ([1], 2), ([31], 2), ([32], 1), ([33], 4), ([511], 1), ([512], 1), ([1000], 5), ([383, 3], 2), ([384, 0], 2), ([700, 64, 1], 1),
