@@ -433,11 +433,12 @@ size_t chain_bytes(int d, int HD, int F) {
 }
 
 static int chain_steps(int d, int HD, int F) { return std::max({d, HD, F + 31}) / 32; }
-// ... and QKV and gate|up look at all their inputs at once: up to 4096 values (4 pairs a thread).  A second look costs each of them a trip: calls of 5 rows and 66 positions,
-// one launch / one by one, 4 layers, d = 768 (12 heads of 64, ffn 2304) 0.88 of the time, 896 (14) 1.14 to 1.21, 1024 (16, ffn 2048) 1.15 to 1.22.
+// The fifth row: where QKV, gate|up and O still see all their inputs in one look (4 pairs a thread, 4096 values); each further look is a trip more.  5 rows, 66 positions, 4 layers, one
+// launch / one by one: d = 768, 12 heads of 64, ffn 2304 77 / 89 us (1 sequence) and 84 / 96 (5); d = 896, 14 heads, ffn 2048 103 / 85 and 106 / 92; d = 1024, 16 heads 105 / 86 and
+// 108 / 93; d = 768, 18 heads 91 / 85; d = 512, 24 heads 90 / 87.
 int chain_rows(int d, int HD, int F) {
-    int rows = chain_shape_ok(d, HD, F) ? kGroupRows : 0;
-    while (rows > 0 && (chain_lds(chain_steps(d, HD, F), rows) > kChainLds || rows * d > 8 * kChainThreads)) --rows;
+    int rows = !chain_shape_ok(d, HD, F) ? 0 : kGroupRows * std::max(d, HD) <= 8 * kChainThreads ? kGroupRows : kGroupRows - 1;
+    while (rows > 0 && chain_lds(chain_steps(d, HD, F), rows) > kChainLds) --rows;
     return rows;
 }
 // Attention cuts each head into workgroups of 16 dimensions that all score all keys (one by one it takes fewer where there are many pairs of sequence and head): worth it
