@@ -433,21 +433,26 @@ size_t chain_bytes(int d, int HD, int F) {
 }
 
 static int chain_steps(int d, int HD, int F) { return std::max({d, HD, F + 31}) / 32; }
-// The fifth row: where QKV, gate|up and O still see all their inputs in one look (4 pairs a thread, 4096 values); each further look is a trip more.  5 rows, 66 positions, 4 layers, one
-// launch / one by one: d = 768, 12 heads of 64, ffn 2304 77 / 89 us (1 sequence) and 84 / 96 (5); d = 896, 14 heads, ffn 2048 103 / 85 and 106 / 92; d = 1024, 16 heads 105 / 86 and
-// 108 / 93; d = 768, 18 heads 91 / 85; d = 512, 24 heads 90 / 87.
 int chain_rows(int d, int HD, int F) {
-    int rows = !chain_shape_ok(d, HD, F) ? 0 : kGroupRows * std::max(d, HD) <= 8 * kChainThreads ? kGroupRows : kGroupRows - 1;
+    int rows = chain_shape_ok(d, HD, F) ? kGroupRows : 0;
     while (rows > 0 && chain_lds(chain_steps(d, HD, F), rows) > kChainLds) --rows;
     return rows;
 }
+// The fifth row: where QKV, gate|up and O still see all their inputs in one look (4 pairs a thread, 4096 values); each further look is a trip more.  5 rows, 66 positions, 4 layers, one
+// launch / one by one: d = 768, 12 heads of 64, ffn 2304 77 / 89 us (1 sequence) and 84 / 96 (5); d = 896, 14 heads, ffn 2048 103 / 85 and 106 / 92; d = 1024, 16 heads 105 / 86 and
+// 108 / 93; d = 768, 18 heads 91 / 85; d = 512, 24 heads 90 / 87.
 // Attention cuts each head into workgroups of 16 dimensions that all score all keys (one by one it takes fewer where there are many pairs of sequence and head): worth it
 // while they leave places free.  One launch / one by one, 4 layers, 66 and 640 positions: d = 512, ffn 2048, heads of 128: 16, 3 sequences (384 workgroups) 0.93 and 0.91, 4 (512) 1.02
 // and 1.11, 5 (640) 1.21 and 1.17; 24, 3 sequences (576) 1.12 and 1.06; d = 256, 24 heads of 64, ffn 1024: 4 sequences (384) 0.89 and 0.84, 5 (480) 1.03 and 0.94;
 // one workgroup per CU: 4-layer draft, 4 sequences (256) 0.92 and 0.89, d = 512, 24 heads of 128, 2 sequences of 2 rows (384) 0.99 and 0.95, at 300 positions 1.05.
-bool chain_pays(int d, int HD, int F, int n_seqs, int M) {
+// Over a long cache the runs of keys make up for the one and, with heads of 64, for some of the other: 1000 and 2000 positions, 5 rows of one sequence, d = 1024, 16 heads of 64 0.93 and
+// 0.82, d = 512, 16 heads of 128 0.87 and 0.75; 24 heads of 64, 5 sequences (480), d = 768 0.88 and 0.87; 16 heads of 128, 4 sequences (512) 1.07 and 1.10.
+bool chain_pays(int d, int HD, int F, int dh, int n_seqs, int M, int longest) {
     const int rows = n_seqs * M, groups = n_seqs * (HD / 16);
-    return rows <= chain_rows(d, HD, F) && groups <= (chain_lds(chain_steps(d, HD, F), rows) <= kChainLdsTwo ? 384 : 256);
+    const bool long_cache = longest >= 1000;
+    if (rows > chain_rows(d, HD, F) || (rows == kGroupRows && rows * std::max(d, HD) > 8 * kChainThreads && !long_cache)) return false;
+    if (long_cache && dh == 64) return groups <= 512;
+    return groups <= (chain_lds(chain_steps(d, HD, F), rows) <= kChainLdsTwo ? 384 : 256);
 }
 bool chain_supported(int d, int HD, int F, int dh) {
     for (const void *f : {dh == 128 ? (const void *)chain_kernel<128, false> : (const void *)chain_kernel<64, false>,

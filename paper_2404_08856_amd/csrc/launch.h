@@ -165,7 +165,7 @@ struct ChainArgs {
 };
 bool chain_shape_ok(int d, int HD, int F);
 int chain_rows(int d, int HD, int F);                   // rows of a launch at most; 0: none
-bool chain_pays(int d, int HD, int F, int n_seqs, int M);   // faster than the layers kernel by kernel
+bool chain_pays(int d, int HD, int F, int dh, int n_seqs, int M, int longest);   // faster than the layers kernel by kernel
 size_t chain_bytes(int d, int HD, int F);
 bool chain_supported(int d, int HD, int F, int dh);     // on this device; prepares the kernel
 // at: k_cache, v_cache of layer 0; qkv, xout, slices, partials, arrive: unused; longest: as for launch_attention

@@ -618,7 +618,7 @@ int32_t forward(spd_model *m, const int32_t *tokens, int token_stride, const flo
         at.d_error = (int32_t *)(m->ws + L.d_error);
     }
     const int d = c.d_model;
-    if (rows <= m->chain && chain_pays(d, c.n_heads * c.head_dim, c.d_ffn, n_seqs, M) && !m->prof_on) {      // (traced one by one: the launches of a layer)
+    if (rows <= m->chain && chain_pays(d, c.n_heads * c.head_dim, c.d_ffn, c.head_dim, n_seqs, M, longest) && !m->prof_on) {      // (traced one by one: the launches of a layer)
         int32_t rc = run_chain(m, at, seq0, n_seqs, M, longest, tokens, tokens ? token_stride : M, embeds, st);
         if (rc == SPD_OK && logits_out) rc = run_lm_head(m, rows, logits_out, st);
         if (rc) return rc;

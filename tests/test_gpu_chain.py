@@ -42,11 +42,13 @@ def forwards(m, shape, lens, M, one_by_one, calls=2):
     return torch.stack(out)
 
 
-def in_one_launch(shape, n_seqs, M):
-    """Whether calls of M rows for each of n_seqs sequences take the one launch: its input fragments, a fifth row in one look, places for attention."""
-    HD, rows = shape.n_heads * shape.head_dim, n_seqs * M
+def in_one_launch(shape, lens, M):
+    """Whether calls of M rows a sequence take the one launch: its input fragments, a fifth row in one look, places for attention, a long cache."""
+    HD, rows, long_cache = shape.n_heads * shape.head_dim, len(lens) * M, max(lens) >= 1000
     fragments = max(shape.d_model, HD, shape.d_ffn + 31) // 32 * rows * 192 + 16
-    return rows <= (5 if 5 * max(shape.d_model, HD) <= 4096 else 4) and fragments <= 72 * 1024 and n_seqs * HD // 16 <= (384 if fragments <= 52 * 1024 else 256)
+    if rows > 5 or fragments > 72 * 1024 or (rows == 5 and 5 * max(shape.d_model, HD) > 4096 and not long_cache):
+        return False
+    return len(lens) * HD // 16 <= (512 if long_cache and shape.head_dim == 64 else 384 if fragments <= 52 * 1024 else 256)
 
 
 def compare(m, shape, lens, M):
@@ -59,7 +61,7 @@ def compare(m, shape, lens, M):
     assert torch.isfinite(got).all()
     assert float((got - want).norm()) <= 1e-4 * float(want.norm()), float((got - want).norm() / want.norm())
     # the two add in other orders, and a call that takes the same kernels repeats its bits: so this says which kernels ran
-    assert torch.equal(got, want) != in_one_launch(shape, len(lens), M)
+    assert torch.equal(got, want) != in_one_launch(shape, lens, M)
 
 
 @pytest.mark.parametrize("d,heads,dh,ffn", [(128, 2, 64, 344), (256, 4, 64, 688), (384, 3, 128, 8), (768, 12, 64, 2048), (1024, 8, 128, 2816), (1024, 16, 64, 2048),
@@ -76,7 +78,8 @@ def test_shapes_and_rows(d, heads, dh, ffn, rows):
     (512, 24, 128, 2048, 2, 1), (512, 24, 128, 2048, 2, 2), (1024, 8, 128, 2816, 4, 1), (512, 8, 64, 3072, 2, 2), (512, 8, 64, 3072, 5, 1)])       # one workgroup per CU: 384, 256; too long
 def test_edges_of_the_rule(d, heads, dh, ffn, n_seqs, M):
     m, shape = model(d, heads, dh, ffn)
-    compare(m, shape, [50] * n_seqs, M)
+    for longest in (50, 990, 1000):
+        compare(m, shape, [longest] + [9] * (n_seqs - 1), M)
 
 
 @pytest.mark.parametrize("lens,M", [([0], 1), ([0], 5), ([1], 2), ([31], 2), ([32], 1), ([33], 4), ([511], 1), ([512], 1), ([1000], 5), ([383, 3], 2), ([384, 0], 2), ([700, 64, 1], 1),
