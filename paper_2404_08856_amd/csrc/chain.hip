@@ -415,10 +415,14 @@ __global__ __launch_bounds__(kChainThreads, 4) void chain_kernel(ChainKernelArgs
     }
 }
 
-// From how many cached positions of the longest sequence on its keys are cut into runs.  With places by blockIdx, step of the 12-layer draft, slices / runs: 1 sequence, 300
-// positions 176 / 182 us, 500 179 / 183, 1000 220 / 186; 2 sequences, 300 199 / 205, 1472 275 / 222; 5 sequences, 66 250 / 254, 300 275 / 260; the 4-layer draft: 1
-// sequence, 500 87.2 / 88.3, 1000 106 / 89; 3 sequences, 200 108 / 106.
-static int chain_runs_from(int n_seqs) { return 256 + 256 / n_seqs; }
+// From how many cached positions of the longest sequence on its keys are cut into runs.  Up to 256 every wave of a slice has one unit of keys at most.  A call's layers and
+// LM head, slices / runs: 12-layer draft, 1 sequence, 300 positions 181 / 184 us, 500 190 / 186, 1000 236 / 192; 2 sequences, 300 202 / 207, 500 209 / 208; 2 rows of one, 400 204 / 208,
+// 500 208 / 207; 3 rows of one, 300 235 / 238, 400 243 / 240; 4 sequences, 300 246 / 243; 5 rows, 200 245 / 240 (1 sequence) and 256 / 259 (5), 300 260 / 240 and 272 / 257.  Heads of
+// 128 gain earlier (4-layer draft): 1 sequence, 300 84.8 / 85.0, 2 98.0 / 96.4, 3 108.5 / 98.8, 4 118.2 / 111.2; 3 rows of one, 300 106.3 / 95.3 (kernel by kernel 104.2).
+static int chain_runs_from(int n_seqs, int rows, int dh) {
+    if (rows >= (dh == 128 ? 3 : 5)) return 257;
+    return 256 + 256 / (dh == 64 && rows == 2 ? n_seqs : rows);
+}
 // Fragments of the longest input in LDS.  Two workgroups fit a CU up to 52 KiB (kChainLdsTwo: next to 19 KiB of static LDS, heads of 64, or 27, heads of 128; 31 or 39
 // with runs of keys), one beyond.  One is enough for the 4-layer draft at 4 rows (66 KiB, 66 positions: 101 us a call against 111 one by one), not at 5 (82 KiB: 121 / 112).
 constexpr size_t kChainLds = 72 * 1024, kChainLdsTwo = 52 * 1024;
@@ -466,7 +470,7 @@ hipError_t launch_chain(const ChainArgs &c, const AttnArgs &given, int longest, 
     if (c.rows < 1 || c.rows > chain_rows(c.d, c.HD, c.F) || t.M < 1 || t.M * t.n_seqs != c.rows || t.m0 != 0 || t.Mq != t.M) return hipErrorInvalidValue;
     if ((t.dh != 64 && t.dh != 128) || t.H * t.dh != c.HD || (t.v_stride % 32) != 0 || t.v_stride < t.max_positions || t.M > t.max_positions) return hipErrorInvalidValue;
     if ((!tokens) == (!embeds) || token_stride < t.M || c.n_layers < 1 || c.d % 32 || c.HD % 32 || c.F % 8 || c.layer_stride % 256) return hipErrorInvalidValue;
-    const bool runs = longest >= chain_runs_from(t.n_seqs);
+    const bool runs = longest >= chain_runs_from(t.n_seqs, c.rows, t.dh);
     ChainKernelArgs k;
     k.c = c;
     k.KSd = c.d / 32; k.KShd = c.HD / 32; k.KSf = (c.F + 31) / 32;

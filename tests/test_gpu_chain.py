@@ -82,7 +82,7 @@ def test_edges_of_the_rule(d, heads, dh, ffn, n_seqs, M):
         compare(m, shape, [longest] + [9] * (n_seqs - 1), M)
 
 
-@pytest.mark.parametrize("lens,M", [([0], 1), ([0], 5), ([1], 2), ([31], 2), ([32], 1), ([33], 4), ([511], 1), ([512], 1), ([1000], 5), ([383, 3], 2), ([384, 0], 2), ([700, 64, 1], 1),
+@pytest.mark.parametrize("lens,M", [([0], 1), ([0], 5), ([1], 2), ([31], 2), ([32], 1), ([33], 4), ([511], 1), ([512], 1), ([1000], 5), ([383, 3], 2), ([384, 0], 2), ([256], 3), ([257], 3), ([256], 5), ([257], 5), ([341, 9], 2), ([319, 256, 257, 1], 1), ([700, 64, 1], 1),
                                     ([308, 307, 300, 33, 1], 1)])
 @pytest.mark.parametrize("heads,dh", [(4, 64), (2, 128)])
 def test_cache_lengths(lens, M, heads, dh):
