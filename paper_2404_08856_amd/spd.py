@@ -104,7 +104,8 @@ def _check(rc):
 
 # Pointers go to ctypes as plain integers, and the stream without a Python object around it: an accept call of one sequence was 12 us of this
 # and one launch, more than its kernel takes.
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+_current_device = torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)     # (no name that torch promises)
 
 
 def _stream():

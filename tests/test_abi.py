@@ -128,3 +128,16 @@ def test_null_handles_are_refused_by_every_entry_point():
         rc = fn(*args)
         assert rc == spd.SPD_ERR_INVALID_ARG, (name, rc)
         assert lib.spd_last_error(), name
+
+
+def test_binding_without_torch_s_private_stream_accessor():
+    """The raw stream comes from a name of torch's that is not public: without it, from the public one."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_2404_08856_amd import spd\n"
+            "class S: cuda_stream = 77\n"
+            "torch.cuda.current_stream = lambda device=None: S\n"
+            "assert spd._raw_stream(0) == 77\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
