@@ -84,3 +84,25 @@ def test_lengths_on_the_device_that_stay_short_do_not_take_the_runs():
     target.spd_kv_set_len([124] * n)
     target.spd_verify_forward(step, outs[1])
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.fixture
+def kernel_by_kernel(monkeypatch):
+    """Models whose calls of up to 5 rows run the separate kernels: by default these small ones take the launch of all layers, whose rule has its own line."""
+    from paper_2404_08856_amd import spd
+
+    class Separate(spd.Model):
+        def __init__(self, *args):
+            super().__init__(*args)
+            self.spd_model_set_tuning(separate_qkv_attention=1)
+
+    monkeypatch.setattr(spd, "Model", Separate)
+
+
+@pytest.mark.parametrize("lens,device_lens", [([607, 1, 600], False), ([608, 0, 33], True)])
+def test_one_query_on_both_sides_of_the_line(lens, device_lens, kernel_by_kernel):
+    test_runs_of_keys_against_oracle("dh128", lens, 1, device_lens)
+
+
+def test_short_lengths_on_the_device_kernel_by_kernel(kernel_by_kernel):
+    test_lengths_on_the_device_that_stay_short_do_not_take_the_runs()

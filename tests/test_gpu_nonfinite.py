@@ -17,11 +17,11 @@ pytestmark = pytest.mark.gpu
 KEY, QUERY, PLAIN = 0, 1, 2                     # tokens
 
 
-def steered(heads, a, key_b, query_b=0.0, layers=1):
-    """Queries of QUERY: 8 a on one dimension; keys of KEY and QUERY: 8 key_b and 8 query_b on it, all others 0."""
-    shape = synth.ModelShape(layers, 64, heads, 64, 64, 64, rope_theta=1e30)
+def steered(heads, a, key_b, query_b=0.0, layers=1, d=64):
+    """Queries of QUERY: 8 a on one dimension; keys of KEY and QUERY: 8 key_b and 8 query_b on it, all others 0 (d = 128: 11.3 for 8)."""
+    shape = synth.ModelShape(layers, d, heads, 64, 64, 64, rope_theta=1e30)
     w = synth.make_weights(shape, 3)
-    w["embed"] = torch.zeros(64, 64, dtype=torch.bfloat16)
+    w["embed"] = torch.zeros(64, d, dtype=torch.bfloat16)
     for t in range(64):
         w["embed"][t, min(t, 2)] = 1.0          # an RMS norm of 1 / 8: the normalised row is 8 on this dimension
     for lw in w["layers"]:
@@ -124,3 +124,59 @@ def test_last_row_of_a_prompt_that_sees_an_infinite_key(heads, n):
     model.spd_kv_export(0, 0, 0, k, v)
     assert torch.isinf(k[n // 3]).any() and torch.isfinite(v).all()
     assert torch.isnan(last).all()
+
+
+# d = 128: calls of up to 5 rows are one launch of all layers.  Slices of a head and runs of keys; one sequence among others
+@pytest.mark.parametrize("n_seqs,heads,context,M", [(1, 1, 40, 1), (1, 2, 40, 5), (3, 2, 40, 1), (1, 2, 900, 1), (1, 2, 900, 5), (3, 2, 900, 1)])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_overflowed_score_in_the_launch_of_all_layers(n_seqs, heads, context, M, sign):
+    from paper_2404_08856_amd import spd
+    print(f"overflowed score, one launch: {n_seqs} x {heads} heads, context {context}, M {M}, sign {sign}", flush=True)
+    shape, w = steered(heads, 1e19, sign * 1e19, layers=2, d=128)
+    model = spd.Model(spd.make_config(shape, n_seqs, context + M), to_device(w))
+    asks = n_seqs // 2                                       # the sequence whose queries ask for the key
+    for s in range(n_seqs):
+        model.spd_prefill_tokens(s, torch.from_numpy(prompt(context, context // 3)).cuda())
+    vt = torch.full((n_seqs, M), PLAIN, dtype=torch.int32, device="cuda")
+    vt[asks] = QUERY
+    outs = []
+    for one_by_one in (0, 1):
+        model.spd_model_set_tuning(separate_qkv_attention=one_by_one)
+        model.spd_kv_set_len([context] * n_seqs)
+        outs.append(torch.empty((n_seqs, M, shape.vocab), device="cuda"))
+        model.spd_verify_forward(vt, outs[-1])
+    model.spd_device_status()
+    others = [s for s in range(n_seqs) if s != asks]
+    for out in outs:
+        assert torch.isfinite(out[others]).all()
+        assert torch.isnan(out[asks]).all() if sign > 0 else torch.isfinite(out[asks]).all()
+    if sign < 0:                                             # keys and values flip a rounding now and then
+        assert float((outs[0] - outs[1]).norm()) <= 1e-4 * float(outs[1].norm())
+
+
+@pytest.mark.parametrize("context", [40, 900])
+@pytest.mark.parametrize("at", [0, 1, 4])
+def test_infinite_value_in_the_launch_of_all_layers(context, at):
+    """A new row whose first-layer V overflows bf16: finite and not finite where the separate kernels leave it so, and in every row from there on."""
+    from paper_2404_08856_amd import spd
+    print(f"infinite value, one launch: context {context}, row {at}", flush=True)
+    shape, w = steered(2, 0.0, 0.0, layers=2, d=128)
+    w["layers"][0]["wv"][5, KEY] = 2.0 ** 127
+    model = spd.Model(spd.make_config(shape, 1, context + 5), to_device(w))
+    model.spd_prefill_tokens(0, torch.full((context,), PLAIN, dtype=torch.int32, device="cuda"))
+    vt = torch.full((1, 5), PLAIN, dtype=torch.int32, device="cuda")
+    vt[0, at] = KEY
+    seen = []
+    for one_by_one in (0, 1):
+        model.spd_model_set_tuning(separate_qkv_attention=one_by_one)
+        model.spd_kv_set_len([context])
+        out = torch.empty((1, 5, shape.vocab), device="cuda")
+        model.spd_verify_forward(vt, out)
+        k, v = (torch.empty((5, shape.n_heads, shape.head_dim), device="cuda") for _ in range(2))
+        model.spd_kv_export(0, 0, context, k, v)
+        assert torch.isinf(v[at, 0, 5]) and torch.isinf(v).sum() == 1 and torch.isfinite(k).all()
+        model.spd_kv_export(1, 0, context, k, v)
+        assert not torch.isfinite(v[at:]).any() and not torch.isfinite(out[0, at:]).any()
+        seen.append(torch.cat([torch.isfinite(x).flatten() for x in (k, v, out)]))
+    assert torch.equal(*seen)
+    model.spd_device_status()
