@@ -115,7 +115,9 @@ int32_t spd_model_destroy(spd_model *model);
  * code never needs this call: spd_model_create picks the measured defaults).  Zero-initialise the
  * struct for "all defaults".  Takes effect from the next forward; host-side only.  All fields but wait_spin_limit choose
  * among the kernels of single projections: while one of them is set, the layers of a small model, by default one
- * launch for up to 5 rows, run kernel by kernel.
+ * launch for calls of up to 5 rows where that is faster, run kernel by kernel.  (That launch takes nearly the whole GPU until
+ * it ends: work on other streams that used to run beside a draft's short kernels waits for up to a whole step.  All of
+ * it together is done sooner; a program to which the other stream's latency matters more sets separate_qkv_attention.)
  * Projections are indexed qkv, o, gate_up, down, lm_head. */
 #define SPD_N_PROJECTIONS 5
 typedef struct {
@@ -293,7 +295,7 @@ int32_t spd_block_finish(spd_model *target, spd_model *draft, const float *targe
                          void *workspace, size_t workspace_bytes, void *stream);
 
 /* Waits for `stream` and reports conditions that kernels can only flag on the device:
- * SPD_ERR_HIP if a bounded wait between workgroups (fused QKV + attention kernel) ever ran
+ * SPD_ERR_HIP if a bounded wait between workgroups (fused QKV + attention kernel, launch of all layers of a small model) ever ran
  * into its spin limit -- never in a healthy run; results since then are
  * invalid --, SPD_ERR_CAPACITY if a forward in device-length mode found no room for its rows,
  * else SPD_OK. */
@@ -306,7 +308,7 @@ int32_t spd_device_status(spd_model *model, void *stream);
  * reports it), a group of several launches is bracketed by events recorded on the
  * caller's stream.  Where QKV projection and attention run as one kernel, kind 0
  * covers both and kind 5 stays empty.  The layers of a small model, otherwise one launch for up to 5 rows, run kernel by kernel
- * while tracing is enabled.  spd_trace_read WAITS for
+ * while tracing is enabled (other kernels than without, and sums in another order).  spd_trace_read WAITS for
  * the recorded events (the one call here that blocks the host), adds the elapsed
  * milliseconds and launch counts per kind into h_ms_sum[n_kinds] / h_count[n_kinds] and
  * forgets them.  Kinds: 0 QKV projection, 1 O projection, 2 gate|up projection + SwiGLU,

@@ -24,9 +24,13 @@
 //
 // Bound by the stages' latency, about 2.3 us each (12-layer draft, 66 positions, from the last word written to the last word written: QKV 1.9, attention
 // 2.6, O 2.0, gate|up 2.3, down 3.0), and by the count of starts at the beginning of a launch.  Whole draft step, one by one / in one launch, 12-layer draft:
-// 1 sequence, 66 cached positions 249 / 168 us, 640 281 / 194, 2000 375 / 221; 3 sequences, 200 289 / 233; 5 sequences, 66 289 / 260, 640 320 / 273, 2000
-// 373 / 308; 4-layer draft: 1 sequence, 66 112 / 84, 2000 178 / 112; 4 sequences, 66 122 / 110, 300 130 / 127, 1472 171 / 142.  (With the place by blockIdx, which is not
+// 1 sequence, 66 cached positions 240 / 171 us, 640 272 / 196, 2000 366 / 222; 3 sequences, 200 279 / 232; 5 sequences, 66 282 / 259, 300 294 / 267, 640 310 / 273, 2000
+// 362 / 309; 4-layer draft: 1 sequence, 66 108 / 85, 2000 172 / 112; 4 sequences, 66 120 / 111, 300 126 / 121, 1472 166 / 142.  (With the place by blockIdx, which is not
 // safe, 155 at 66 positions; with the count taken and not used 163: 8 us are the count, the rest is how a stage's workgroups spread over the CUs.)
+//
+// The workgroups that wait hold the registers and the LDS of nearly all CUs, so work on another stream gets its turn between two launches, where it ran beside the short kernels
+// before.  40 steps of the 12-layer draft on one stream, on another (kernel by kernel / in one launch): 10 verify calls of four 7B layers, done after 4.2 / 9.5 ms (alone 4.0),
+// the draft after 12.5 / 7.4; 40 accept steps 0.44 / 2.35 ms (alone 0.39), the draft 9.3 / 6.4; a second draft, both 11.2 / 7.6.
 #include <algorithm>
 
 #include "attention_core.h"

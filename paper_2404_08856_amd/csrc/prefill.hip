@@ -8,7 +8,7 @@
 //    is unused and no sum over term columns is needed.  Block (row tile rt of 16 rows, K-step s, term t) is the
 //    1 KiB at index (rt * KS + s) * 3 + t, lane l = r + 16 g holding X[16 rt + r][32 s + 8 g .. + 7].
 //  * prefill_gemm_kernel: tiled GEMM, both operands through LDS.  Bound by the matrix cores and the card's power: the 7B QKV projection of
-//    2047 rows runs at 1.35 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.43 to 1.68).
+//    2047 rows runs at 1.41 PFLOP/s counting all three terms (a large bf16 matrix product of the library: 1.43 to 1.68).
 //  * prefill_attention_kernel: attention of 64 queries per workgroup over the cached keys (which by then include
 //    the pass's own rows).
 // Measured against passes of 64 rows through the batched verify kernels, whose attention takes 8 queries a launch:
@@ -483,9 +483,10 @@ static hipError_t launch_pg(PrefillGemmKernelArgs &k, int epilogue, hipStream_t 
 
 // Workgroup shape of a projection: large = 256 features x 128 rows, one 8-wave workgroup per CU; small = 128 x 64, two
 // 4-wave workgroups per CU (a quarter of the work each, so a large workgroup stands for four small ones).  The large
-// shape moves less through LDS per product; the small one wastes less of the last round and of ragged edges.  Large
-// where its rounds cost no more than the small one's (7B, 2047 rows, gate|up: 6 large rounds against 11 small ones:
-// 921 us small, 946 large by the rate of whole rounds; 640 rows, O: 80 large workgroups leave two thirds of the CUs idle).
+// shape moves less through LDS per product; the small one wastes less of the last round and of ragged edges, and its sums are more exact (it has the
+// registers to keep the second and third terms apart: K and V of a 7B layer, 2047 rows, 1.4 roundings of 10000 flipped against 2.2).  Large only where its rounds
+// are at most half the small one's, though one of them costs 1.75 small ones: where the small shape is slower but more exact it stays (7B, small / large: gate|up, 896 rows 397 / 383 us,
+// 1280 544 / 517, 1664 711 / 650, 2047 867 / 804; QKV, 1664 364 / 344).  640 rows, O: 80 large workgroups leave two thirds of the CUs idle (75 / 118).
 static bool prefill_large(int n_tiles, int rows) {
     const int large = ((n_tiles + 15) / 16) * ((rows + 127) / 128), small = ((n_tiles + 7) / 8) * ((rows + 63) / 64);
     const int rounds_large = (large + 255) / 256, rounds_small = (small + 511) / 512;
@@ -612,7 +613,8 @@ __global__ __launch_bounds__(256) void prefill_append_kernel(PrefillAttnArgs a) 
 // Bound by the vector instructions of the softmax and the three-term split next to as many matrix-core cycles: no
 // branches per key, packed conversions and register swaps instead of LDS for the maximum took the 7B shape at 2047
 // rows from 133 to 114 us per layer, the 12-layer draft at 1472 rows from 58 to 34.  A second set of 4 waves on every other
-// unit of the same queries (merged at the end) was no faster where workgroups are few (31 us) and slower at 2047 rows (157).
+// unit of the same 64 queries (merged at the end) was no faster where workgroups are few (31 us) and slower at 2047 rows (157): as many workgroups, twice the waves.
+// (The form with two waves for the same queries has 32 queries and 4 waves: twice the workgroups, see prefill_split.)
 // Heads of 64 take two units per step: a wave is alone on its SIMD for most of a launch (12 heads x 23 blocks of queries), and one unit's
 // products run next to the other's softmax (1472 rows, 36.2 to 32.4 us).  Heads of 128 come with more workgroups: at 2047 rows three of them per CU
 // (one unit per step, at most 168 registers) take 113 us, two 125 with two units and 131 with one.

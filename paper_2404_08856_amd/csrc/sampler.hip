@@ -572,9 +572,9 @@ __global__ __launch_bounds__(kSampThreads, 4) void accept_decide_slices_kernel(A
 // An answer is the token (or kAccepted) under a mark, and its complement under another.  The marks hold the number of the call, so what calls that overlapped
 // on one workspace may have left (one can take half of the other's answers away) is nobody's answer later.  Only a captured call keeps its number from replay to replay.
 // Bound by one CU's vector instructions (about 64 cycles per entry and wave: 3 us) and its loads (256 KiB, 4 us).  32000 entries, draft
-// length 4, graph replays, one launch / statistics and slices: draft as probabilities, 1 sequence 10.1 / 14.9 us, 8 10.3 / 15.7, 32 12.3 / 16.9, 51
-// 16.5 / 19.9, 64 (a second round of workgroups) 21.8 / 21.9; draft as logits, 1 9.6 / 14.1, 51 19.3 / 24.6, 64 26.1 / 26.1; 1000 entries, 51 10.0 / 15.3,
-// 64 15.2 / 16.3.
+// length 4, graph replays, one launch / statistics and slices: draft as probabilities, 1 sequence 10.3 / 14.0 us, 32 12.8 / 15.9, 51 17.0 / 19.3; draft as logits, 51
+// 19.7 / 23.6; greedy, 51 22.2 / 25.2; 1000 entries as logits, 51 13.0 / 16.2.  With a second round of workgroups: 52 sequences (260 positions) probabilities 21.1 / 21.1, logits
+// 23.7 / 23.8, greedy 27.3 / 25.5, 1000 entries 19.7 / 16.3, greedy 22.9 / 18.2; 64 (320) 22.6 / 22.2, 28.0 / 26.8, 32.2 / 28.5, 20.6 / 18.0, 24.6 / 20.7.
 constexpr unsigned kAnswerMark = 0xffc5a11cu, kAnswerMark2 = 0x9e3779b9u, kAccepted = 0x80000000u;    // marks of call 0, which there is not
 template <bool ALIGNED>
 __global__ __launch_bounds__(kSampThreads) void accept_positions_kernel(AcceptArgs a, unsigned long long call) {
@@ -667,7 +667,7 @@ hipError_t launch_accept(const AcceptArgs &a, hipStream_t stream) {
     if (a.gamma < 1 || a.gamma > 63) return hipErrorInvalidValue;
     const RowKind kind = row_kind(a.target, a.draft, a.vocab);
     const bool need_stats = ((a.flags & 3u) != 3u);
-    // one round of workgroups, one per CU (a second one costs more than it saves: see above); answers are 8-byte words
+    // one round of workgroups, one per CU (a second one saves nothing and costs up to 6 us: see above); answers are 8-byte words
     if (kind != ROW_MEMORY && ((uintptr_t)a.stats & 7) == 0 && (long)a.n_seqs * (a.gamma + 1) <= 256) {
         static std::atomic<unsigned long long> calls{0};          // numbers calls of all threads and devices
         const unsigned long long call = calls.fetch_add(1, std::memory_order_relaxed) + 1;
