@@ -485,7 +485,7 @@ static hipError_t launch_pg(PrefillGemmKernelArgs &k, int epilogue, hipStream_t 
 // 4-wave workgroups per CU (a quarter of the work each, so a large workgroup stands for four small ones).  The large
 // shape moves less through LDS per product; the small one wastes less of the last round and of ragged edges, and its sums are more exact (it has the
 // registers to keep the second and third terms apart: K and V of a 7B layer, 2047 rows, 1.4 roundings of 10000 flipped against 2.2).  Large only where its rounds
-// are at most half the small one's, though one of them costs 1.75 small ones: where the small shape is slower but more exact it stays (7B, small / large: gate|up, 896 rows 397 / 383 us,
+// are at most half the small one's, though one of them costs 1.7 small ones: where the small shape is slower but more exact it stays (7B, small / large: gate|up, 896 rows 397 / 383 us,
 // 1280 544 / 517, 1664 711 / 650, 2047 867 / 804; QKV, 1664 364 / 344).  640 rows, O: 80 large workgroups leave two thirds of the CUs idle (75 / 118).
 static bool prefill_large(int n_tiles, int rows) {
     const int large = ((n_tiles + 15) / 16) * ((rows + 127) / 128), small = ((n_tiles + 7) / 8) * ((rows + 63) / 64);
